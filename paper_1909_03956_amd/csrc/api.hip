@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "api_internal.h"
+#include "phasor_table.h"
 #include "sphere.h"
 
 using namespace swv;
@@ -50,8 +51,10 @@ int ensure(swv_ctx ctx, DevBuf& b, size_t bytes) {
 void tune_defaults(swv_ctx ctx) {
     // (per_lane, block) per family, both size classes; see swv_tune_get.  The
     // fastest shapes measured on MI355X for a few thousand components, a
-    // thousand pixels and 10^6 - 10^7 rows.
-    const int pl[kFamilies][2] = {{2, 64}, {1, 256}, {1, 64}, {4, 128}, {4, 128}};
+    // thousand pixels and 10^6 - 10^7 rows.  FP64 direct sum: per_lane is the
+    // most rows a lane takes (small calls take fewer, direct_shape); its
+    // workgroups share a table and have a size of their own, whatever `block`.
+    const int pl[kFamilies][2] = {{4, 64}, {1, 256}, {1, 64}, {4, 128}, {4, 128}};
     for (int f = 0; f < kFamilies; ++f)
         for (int c = 0; c < 2; ++c) {
             ctx->per_lane[f][c] = pl[f][0];
@@ -147,23 +150,28 @@ int upload_tree(swv_ctx ctx, swv_tree t, const TRec** out) {
     return SWV_OK;
 }
 
-static std::vector<Comp> packed_leaves(swv_tree t) {
+// The leaves as the direct kernels read them: FP64 records, then (from a
+// 64-byte border) the FP32-compensated form's.
+static std::vector<CompCell> packed_leaves(swv_tree t) {
     const size_t n = t->leaf_pix.size();
-    std::vector<Comp> c(n);
-    for (size_t k = 0; k < n; ++k)
-        c[k] = Comp{t->leaf_l[k], t->leaf_m[k], t->leaf_nm1[k], t->leaf_flux[k]};
+    std::vector<CompCell> c(n + (n + 1) / 2);
+    for (size_t k = 0; k < n; ++k) {
+        const double l = t->leaf_l[k], m = t->leaf_m[k], nm1 = t->leaf_nm1[k], F = t->leaf_flux[k];
+        c[k] = comp_cell(l, m, nm1, F);
+        ((Comp*)(c.data() + n))[k] = Comp{l, m, nm1, F};
+    }
     return c;
 }
 
-static int upload_leaves(swv_ctx ctx, swv_tree t, const Comp** out) {
+static int upload_leaves(swv_ctx ctx, swv_tree t, const CompCell** out) {
     auto it = t->device_leaves.find(ctx->device);
     if (it != t->device_leaves.end()) {
-        *out = (const Comp*)it->second;
+        *out = (const CompCell*)it->second;
         return SWV_OK;
     }
-    const std::vector<Comp> c = packed_leaves(t);
+    const std::vector<CompCell> c = packed_leaves(t);
     void* p = nullptr;
-    const size_t bytes = c.size() * sizeof(Comp);
+    const size_t bytes = c.size() * sizeof(CompCell);
     hipError_t e = hipMalloc(&p, bytes < 32 ? 32 : bytes);
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -177,7 +185,7 @@ static int upload_leaves(swv_ctx ctx, swv_tree t, const Comp** out) {
         }
     }
     t->device_leaves[ctx->device] = p;
-    *out = (const Comp*)p;
+    *out = (const CompCell*)p;
     return SWV_OK;
 }
 
@@ -360,6 +368,22 @@ int swv_ctx_destroy(swv_ctx ctx) {
 }
 
 // ------------------------------------------------------- direct route ---
+// The table-phasor direct sum over packed components.
+static int run_direct_cell(swv_ctx ctx, int64_t n_vis, const double* u, const double* v,
+                           const double* w, const CompCell* comp, int64_t n_comp, int sign,
+                           void* vis_out) {
+    const DirectShape sh =
+        direct_shape(n_vis, n_comp, ctx->per_lane[kFamDirect64][size_class(n_vis)], ctx->n_cu);
+    const size_t bytes = direct_partial_bytes(sh, n_vis);
+    if (bytes) {
+        const int rc = ensure(ctx, ctx->partial, bytes);
+        if (rc) return rc;
+    }
+    HIPCALL(launch_direct_cell(ctx->stream, sh, n_vis, u, v, w, comp, n_comp, sign,
+                               (double2*)vis_out, (double2*)ctx->partial.p, ctx->d_status));
+    return SWV_OK;
+}
+
 int swv_predict_direct(swv_ctx ctx, int64_t n_vis, const double* u, const double* v,
                        const double* w, int64_t n_comp, const double* l, const double* m,
                        const double* flux, int sign, int prec, void* vis_out) {
@@ -373,14 +397,25 @@ int swv_predict_direct(swv_ctx ctx, int64_t n_vis, const double* u, const double
     if (n_vis == 0) return SWV_OK;
     TRY_BEGIN
     GUARD(ctx);
-    rc = ensure(ctx, ctx->comp, sizeof(Comp) * (size_t)(n_comp > 0 ? n_comp : 1));
+    if (prec == SWV_FP64 && n_comp < kTableMinComp) {
+        HIPCALL(launch_direct_few(ctx->stream, n_vis, u, v, w, (int)n_comp, l, m, flux, sign,
+                                  (double2*)vis_out, ctx->d_status));
+        return SWV_OK;
+    }
+    const size_t rec = prec == SWV_FP64 ? sizeof(CompCell) : sizeof(Comp);
+    rc = ensure(ctx, ctx->comp, rec * (size_t)(n_comp > 0 ? n_comp : 1));
     if (rc) return rc;
+    if (prec == SWV_FP64) {
+        CompCell* comp = (CompCell*)ctx->comp.p;
+        HIPCALL(launch_ingest(ctx->stream, n_comp, l, m, flux, comp, ctx->d_status));
+        return run_direct_cell(ctx, n_vis, u, v, w, comp, n_comp, sign, vis_out);
+    }
     Comp* comp = (Comp*)ctx->comp.p;
     HIPCALL(launch_ingest(ctx->stream, n_comp, l, m, flux, comp, ctx->d_status));
-    const int fam = prec == SWV_FP64 ? kFamDirect64 : kFamDirect32;
     const int sc = size_class(n_vis);
-    HIPCALL(launch_direct(ctx->stream, prec, ctx->per_lane[fam][sc], ctx->block[fam][sc], n_vis,
-                          u, v, w, comp, n_comp, sign, vis_out, ctx->d_status));
+    HIPCALL(launch_direct_f32c(ctx->stream, ctx->per_lane[kFamDirect32][sc],
+                               ctx->block[kFamDirect32][sc], n_vis, u, v, w, comp, n_comp, sign,
+                               vis_out, ctx->d_status));
     return SWV_OK;
     TRY_END
 }
@@ -499,10 +534,10 @@ int swv_tree_set_flux(swv_tree t, const double* leaf_flux) {
         if (e != hipSuccess) return hip_fail(e, "swv_tree_set_flux upload");
     }
     if (!t->device_leaves.empty()) {
-        const std::vector<Comp> c = packed_leaves(t);
+        const std::vector<CompCell> c = packed_leaves(t);
         for (auto& kv : t->device_leaves) {
             DeviceGuard g(kv.first);
-            hipError_t e = hipMemcpy(kv.second, c.data(), c.size() * sizeof(Comp),
+            hipError_t e = hipMemcpy(kv.second, c.data(), c.size() * sizeof(CompCell),
                                      hipMemcpyHostToDevice);
             if (e != hipSuccess) return hip_fail(e, "swv_tree_set_flux upload");
         }
@@ -555,14 +590,15 @@ int swv_predict_tree_leaves(swv_ctx ctx, swv_tree t, int64_t n_vis, const double
     if (n_vis == 0) return SWV_OK;
     TRY_BEGIN
     GUARD(ctx);
-    const Comp* comp = nullptr;
+    const CompCell* comp = nullptr;
     rc = upload_leaves(ctx, t, &comp);
     if (rc) return rc;
-    const int fam = prec == SWV_FP64 ? kFamDirect64 : kFamDirect32;
+    const int64_t n = (int64_t)t->leaf_pix.size();
+    if (prec == SWV_FP64) return run_direct_cell(ctx, n_vis, u, v, w, comp, n, sign, vis_out);
     const int sc = size_class(n_vis);
-    HIPCALL(launch_direct(ctx->stream, prec, ctx->per_lane[fam][sc], ctx->block[fam][sc], n_vis,
-                          u, v, w, comp, (int64_t)t->leaf_pix.size(), sign, vis_out,
-                          ctx->d_status));
+    HIPCALL(launch_direct_f32c(ctx->stream, ctx->per_lane[kFamDirect32][sc],
+                               ctx->block[kFamDirect32][sc], n_vis, u, v, w,
+                               (const Comp*)(comp + n), n, sign, vis_out, ctx->d_status));
     return SWV_OK;
     TRY_END
 }
@@ -782,8 +818,8 @@ int swv_grad_direct(swv_ctx ctx, int64_t n_vis, const double* u, const double* v
     const int64_t n_chunks = n_vis > 0 ? (n_vis + chunk - 1) / chunk : 0;
     rc = ensure(ctx, ctx->partial, 32 * (size_t)n_comp * (size_t)(n_chunks > 0 ? n_chunks : 1));
     if (rc) return rc;
-    HIPCALL(launch_grad(ctx->stream, cpl, chunk, n_vis, u, v, w, y, comp, n_comp, sign, alpha,
-                        (double*)ctx->partial.p, d_flux, d_l, d_m));
+    HIPCALL(launch_grad(ctx->stream, cpl, chunk, n_vis, u, v, w, y, (const double*)comp, 4, n_comp,
+                        sign, alpha, (double*)ctx->partial.p, d_flux, d_l, d_m));
     return SWV_OK;
     TRY_END
 }

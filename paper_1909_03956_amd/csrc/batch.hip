@@ -20,13 +20,15 @@ struct swv_plan_s {
     std::vector<swv_tree> trees;      // held (one reference each) while the plan lives
     BatchInst* d_direct = nullptr;
     BatchInst* d_tree = nullptr;
-    WorkItem* d_items_direct = nullptr;
+    WorkItem* d_items_direct = nullptr;   // FP64 direct instances
+    WorkItem* d_items_direct32 = nullptr; // F32C direct instances
     WorkItem* d_items_tree = nullptr;     // FP64 tree instances
     WorkItem* d_items_tree32 = nullptr;   // F32C tree instances
-    unsigned n_items_direct = 0, n_items_tree = 0, n_items_tree32 = 0;
-    Comp* d_pack = nullptr;
-    unsigned* d_counters = nullptr;  // [0] direct, [1] tree FP64, [2] tree F32C
-    int vpl = 2, block = 256, grid_direct = 0, grid_tree = 0, grid_tree32 = 0, max_comp = 0;
+    unsigned n_items_direct = 0, n_items_direct32 = 0, n_items_tree = 0, n_items_tree32 = 0;
+    CompCell* d_pack = nullptr;
+    // [0] direct FP64, [1] tree FP64, [2] tree F32C, [3] direct F32C
+    unsigned* d_counters = nullptr;
+    int vpl = 2, grid_direct = 0, grid_direct32 = 0, grid_tree = 0, grid_tree32 = 0, max_comp = 0;
     int jmax = 1, smax = 1;           // largest J and segment depth of the trees
     int tree_walker = 0, tree_depth = 1;
     bool pruned = false;              // some tree is thresholded (leaves above level J)
@@ -67,6 +69,7 @@ void plan_release(swv_plan p) {
         DeviceGuard g(ctx->device);
         (void)hipStreamSynchronize(ctx->stream);
         for (void* q : {(void*)p->d_direct, (void*)p->d_tree, (void*)p->d_items_direct,
+                    (void*)p->d_items_direct32,
                         (void*)p->d_items_tree,
                         (void*)p->d_items_tree32, (void*)p->d_pack, (void*)p->d_counters})
             if (q) (void)hipFree(q);
@@ -78,6 +81,7 @@ void plan_release(swv_plan p) {
 
 void free_plan_device(swv_plan p) {
     for (void* q : {(void*)p->d_direct, (void*)p->d_tree, (void*)p->d_items_direct,
+                    (void*)p->d_items_direct32,
                     (void*)p->d_items_tree,
                         (void*)p->d_items_tree32, (void*)p->d_pack, (void*)p->d_counters})
         if (q) (void)hipFree(q);
@@ -88,11 +92,13 @@ hipError_t enqueue_plan(swv_plan p, hipStream_t s) {
     hipError_t e = launch_batch_ingest(s, p->d_direct, (int)p->direct.size(), p->max_comp,
                                        p->d_pack, p->ctx->d_status);
     if (e != hipSuccess) return e;
-    e = launch_reset_counters(s, p->d_counters, 3);
+    e = launch_reset_counters(s, p->d_counters, 4);
     if (e != hipSuccess) return e;
-    e = launch_batch_direct(s, p->vpl, p->block, p->grid_direct, p->d_direct, p->d_pack,
-                            p->d_items_direct, p->n_items_direct, p->d_counters,
-                            p->ctx->d_status);
+    e = launch_batch_direct(s, p->vpl, p->grid_direct, p->d_direct, p->d_pack, p->d_items_direct,
+                            p->n_items_direct, p->d_counters, p->ctx->d_status);
+    if (e != hipSuccess) return e;
+    e = launch_batch_direct_f32c(s, p->grid_direct32, p->d_direct, p->d_pack, p->d_items_direct32,
+                                 p->n_items_direct32, p->d_counters + 3, p->ctx->d_status);
     if (e != hipSuccess) return e;
     e = launch_batch_tree(s, p->tree_walker, p->tree_depth, SWV_FP64, p->grid_tree, p->d_tree, p->d_items_tree, p->n_items_tree, p->d_counters + 1,
                           p->ctx->d_status, p->pruned);
@@ -150,9 +156,7 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
         p = new swv_plan_s();
         p->ctx = ctx;
         p->n_inst = n;
-        p->vpl = ctx->per_lane[kFamDirect64][1];
-        p->block = ctx->block[kFamDirect64][1];
-        int64_t off = 0, total_rows = 0;
+        int64_t off = 0, total_rows = 0, rows64 = 0;
         std::vector<int64_t> cost_per_row_direct, cost_per_row_tree;
         for (int k = 0; k < n; ++k) {
             const swv_instance& I = inst[k];
@@ -166,6 +170,7 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
             b.sgn = (double)I.sign;
             total_rows += I.n_vis;
             if (I.route == SWV_ROUTE_DIRECT) {
+                if (I.prec == SWV_FP64) rows64 += I.n_vis;
                 b.l = I.l;
                 b.m = I.m;
                 b.flux = I.flux;
@@ -217,15 +222,17 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
             p->tree_depth = kTreeMaxSeg;
         }
 
+        p->vpl = batch_direct_vpl(rows64, ctx->per_lane[kFamDirect64][1], ctx->n_cu);
         // persistent grids: as many blocks as stay resident
-        p->grid_direct = ctx->n_cu * batch_direct_blocks_per_cu(p->vpl, p->block);
+        p->grid_direct = ctx->n_cu * batch_direct_blocks_per_cu(p->vpl);
+        p->grid_direct32 = ctx->n_cu * batch_direct_f32c_blocks_per_cu();
         p->grid_tree = ctx->n_cu * (p->pruned ? batch_tree_pruned_blocks_per_cu(SWV_FP64)
                                               : batch_tree_blocks_per_cu(p->tree_walker,
                                                                          p->tree_depth, SWV_FP64));
         p->grid_tree32 = ctx->n_cu * (p->pruned ? batch_tree_pruned_blocks_per_cu(SWV_F32C)
                                                 : batch_tree_blocks_per_cu(p->tree_walker,
                                                                            p->tree_depth, SWV_F32C));
-        const int64_t waves = (int64_t)p->grid_direct * (p->block / 64);
+        const int64_t waves = (int64_t)p->grid_direct * (kTabBlock / 64);
         // about 16 items per resident wave, in whole wave tiles, at most 64 of them
         const int64_t unit = 64LL * p->vpl;
         int64_t tile = total_rows / std::max<int64_t>(1, 16 * waves);
@@ -252,29 +259,32 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
             for (const Item& it : items) w.push_back(it.w);
             return w;
         };
-        const std::vector<WorkItem> wd = make_items(p->direct, cost_per_row_direct, tile);
+        // items by precision (one launch each), keeping the cost order
+        std::vector<WorkItem> wd, wd32;
+        for (const WorkItem& it : make_items(p->direct, cost_per_row_direct, tile))
+            (p->direct[(size_t)it.inst].prec == SWV_F32C ? wd32 : wd).push_back(it);
         const int64_t tree_tile = std::max<int64_t>(64, tile / p->vpl / 64 * 64);
-        // tree items by precision (one launch each), keeping the cost order
         std::vector<WorkItem> wt, wt32;
         for (const WorkItem& it : make_items(p->tree, cost_per_row_tree, tree_tile))
             (p->tree[(size_t)it.inst].prec == SWV_F32C ? wt32 : wt).push_back(it);
-        if (wd.size() > 0xffffffffull || wt.size() > 0xffffffffull || wt32.size() > 0xffffffffull) {
+        if (wd.size() > 0xffffffffull || wd32.size() > 0xffffffffull || wt.size() > 0xffffffffull || wt32.size() > 0xffffffffull) {
             delete p;
             return fail(SWV_ENOTSUP, "swv_batch_plan: too many work items");
         }
         p->n_items_direct = (unsigned)wd.size();
+        p->n_items_direct32 = (unsigned)wd32.size();
         p->n_items_tree = (unsigned)wt.size();
         p->n_items_tree32 = (unsigned)wt32.size();
 
         int rc = dev_upload(p->direct, &p->d_direct);
         if (!rc) rc = dev_upload(p->tree, &p->d_tree);
         if (!rc) rc = dev_upload(wd, &p->d_items_direct);
+        if (!rc) rc = dev_upload(wd32, &p->d_items_direct32);
         if (!rc) rc = dev_upload(wt, &p->d_items_tree);
         if (!rc) rc = dev_upload(wt32, &p->d_items_tree32);
         if (!rc) {
-            std::vector<Comp> none;
-            none.resize((size_t)std::max<int64_t>(off, 1));
-            hipError_t e = hipMalloc((void**)&p->d_pack, none.size() * sizeof(Comp));
+            hipError_t e = hipMalloc((void**)&p->d_pack,
+                                     (size_t)std::max<int64_t>(off, 1) * sizeof(CompCell));
             if (e != hipSuccess) {
                 (void)hipGetLastError();
                 p->d_pack = nullptr;
@@ -282,7 +292,7 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
             }
         }
         if (!rc) {
-            hipError_t e = hipMalloc((void**)&p->d_counters, 3 * sizeof(unsigned));
+            hipError_t e = hipMalloc((void**)&p->d_counters, 4 * sizeof(unsigned));
             if (e != hipSuccess) {
                 (void)hipGetLastError();
                 p->d_counters = nullptr;
@@ -316,11 +326,12 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
 int swv_plan_stats(swv_plan p, swv_plan_stats_t* out) {
     if (!p || !out) return fail(SWV_EINVAL, "swv_plan_stats: null argument");
     out->n_instances = p->n_inst;
-    out->n_items = (int64_t)p->n_items_direct + p->n_items_tree + p->n_items_tree32;
+    out->n_items = (int64_t)p->n_items_direct + p->n_items_direct32 + p->n_items_tree +
+                   p->n_items_tree32;
     out->total_terms = p->total_terms;
     out->tile_rows = p->tile_rows;
     out->grid_blocks = p->grid_direct;
-    out->block_threads = p->block;
+    out->block_threads = kTabBlock;
     return SWV_OK;
 }
 
@@ -470,12 +481,15 @@ int swv_autotune(swv_ctx ctx, const char* cache_path, int flags) {
     uint64_t seed = 12345;
     for (const F& x : fills)
         k_fill<<<dim3((unsigned)((x.n + 255) / 256)), dim3(256), 0, s>>>(x.p, x.n, seed++, x.lo, x.hi);
-    Comp* comp = nullptr;
+    CompCell* comp = nullptr;
+    Comp* comp32 = nullptr;
     {
-        int rc = ensure(ctx, ctx->comp, sizeof(Comp) * n_comp);
+        int rc = ensure(ctx, ctx->comp, (sizeof(CompCell) + sizeof(Comp)) * n_comp);
         if (rc) return rc;
-        comp = (Comp*)ctx->comp.p;
+        comp = (CompCell*)ctx->comp.p;
+        comp32 = (Comp*)(comp + n_comp);
         hipError_t e = launch_ingest(s, n_comp, l, m, f, comp, ctx->d_status);
+        if (e == hipSuccess) e = launch_ingest(s, n_comp, l, m, f, comp32, ctx->d_status);
         if (e != hipSuccess) return hip_fail(e, "autotune ingest");
     }
     // a level-9 tree of 1,024 components in a 3 degree field
@@ -520,9 +534,14 @@ int swv_autotune(swv_ctx ctx, const char* cache_path, int flags) {
                     for (int r = 0; r <= reps; ++r) {
                         hipEventRecord(e0, s);
                         hipError_t e = hipSuccess;
-                        if (fam == kFamDirect64 || fam == kFamDirect32) {
-                            e = launch_direct(s, fam == kFamDirect64 ? SWV_FP64 : SWV_F32C, pl, bl,
-                                              rows, u, v, w, comp, n_comp, -1, out, ctx->d_status);
+                        if (fam == kFamDirect64) {
+                            // rows enough for whole rows per wave: no partial sums
+                            e = launch_direct_cell(s, DirectShape{pl, 1, 1}, rows, u, v, w, comp,
+                                                   n_comp, -1, (double2*)out, nullptr,
+                                                   ctx->d_status);
+                        } else if (fam == kFamDirect32) {
+                            e = launch_direct_f32c(s, pl, bl, rows, u, v, w, comp32, n_comp, -1,
+                                                   out, ctx->d_status);
                         } else if (fam == kFamTree) {
                             e = launch_tree(s, pl == 2 ? 1 : 0, bl, SWV_FP64, ta, rows, u, v, w,
                                             -1, out,
@@ -546,8 +565,8 @@ int swv_autotune(swv_ctx ctx, const char* cache_path, int flags) {
                             rc = ensure(ctx, ctx->partial, 32 * (size_t)n_comp * nch);
                             if (rc) { result = rc; break; }
                             part = (double*)ctx->partial.p;
-                            e = launch_grad(s, pl, chunk, rows, u, v, w, y, comp, n_comp, -1, 1.0,
-                                            part, g1, g2, g3);
+                            e = launch_grad(s, pl, chunk, rows, u, v, w, y, (const double*)comp, 8,
+                                            n_comp, -1, 1.0, part, g1, g2, g3);
                         }
                         hipEventRecord(e1, s);
                         if (e != hipSuccess) { result = hip_fail(e, "autotune launch"); break; }

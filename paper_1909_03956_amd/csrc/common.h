@@ -14,6 +14,12 @@ struct alignas(32) Comp {
     double l, m, nm1, I;
 };
 
+// One packed component of the FP64 direct kernels (64 bytes): the same, and the
+// coefficients of the phasor inside a table cell times the flux.
+struct alignas(64) CompCell {
+    double l, m, nm1, I, Ic0, Ic1, Is0, Is1;
+};
+
 // One record of the depth-first tree stream (32 bytes).
 //   root : a = A_1 * lambda_1 of the level-1 node that follows; meta = 0
 //   node : a, b, c = h^0, h^1, h^2 with h^m = s^m_{c0} gamma^m_j (sqrt(A_j)/4) 4^-(J-j-1),

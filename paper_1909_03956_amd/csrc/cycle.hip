@@ -36,7 +36,7 @@ struct swv_cycle_s {
     BatchInst* d_tree = nullptr;
     WorkItem* d_items_direct = nullptr;
     WorkItem* d_items_tree = nullptr;
-    Comp* d_pack = nullptr;
+    CompCell* d_pack = nullptr;
     TRec* d_rec = nullptr;
     unsigned* d_counters = nullptr;
     void* d_partial = nullptr;
@@ -47,7 +47,7 @@ struct swv_cycle_s {
     hipEvent_t up_event = nullptr;
     bool up_pending = false;
     bool dirty = true;
-    int vpl = 2, block = 64, grid_direct = 0, grid_tree = 0, walker = 0, depth = 1;
+    int vpl = 2, grid_direct = 0, grid_tree = 0, walker = 0, depth = 1;
     int max_comp_cap = 0;
     int64_t tile_rows = 64, tree_tile = 64;   // rows per work item, fixed at creation
     std::vector<AdjointShape> adj;          // per instance
@@ -168,7 +168,7 @@ hipError_t enqueue_cycle(swv_cycle cy, hipStream_t s) {
     if (e != hipSuccess) return e;
     e = launch_reset_counters(s, cy->d_counters, 2);
     if (e != hipSuccess) return e;
-    e = launch_batch_direct(s, cy->vpl, cy->block, cy->grid_direct, cy->d_direct, cy->d_pack,
+    e = launch_batch_direct(s, cy->vpl, cy->grid_direct, cy->d_direct, cy->d_pack,
                             cy->d_items_direct, (unsigned)cy->items_direct.size(),
                             cy->d_counters, ctx->d_status);
     if (e != hipSuccess) return e;
@@ -190,7 +190,8 @@ hipError_t enqueue_cycle(swv_cycle cy, hipStream_t s) {
         if (I.d_flux && I.comp_cap > 0) {
             const int d = cy->slot[k];
             e = launch_grad(s, cy->gcpl[k], cy->gchunk[k], I.n_vis, I.u, I.v, I.w, I.resid,
-                            cy->d_pack + cy->direct[d].comp_offset, I.comp_cap, I.sign,
+                            (const double*)(cy->d_pack + cy->direct[d].comp_offset), 8,
+                            I.comp_cap, I.sign,
                             -2.0 * I.inv_sigma2, (double*)cy->d_partial, I.d_flux, I.d_l, I.d_m,
                             &cy->d_direct[d].n_comp);
             if (e != hipSuccess) return e;
@@ -224,9 +225,7 @@ int swv_cycle_create(swv_ctx ctx, int n, const swv_cycle_instance* inst, swv_cyc
         cy->adj.resize(n);
         cy->gcpl.assign(n, 1);
         cy->gchunk.assign(n, 1);
-        cy->vpl = ctx->per_lane[kFamDirect64][1];
-        cy->block = ctx->block[kFamDirect64][1];
-        int64_t comp_off = 0, rec_off = 0, rows = 0;
+        int64_t comp_off = 0, rec_off = 0, rows = 0, rows64 = 0;
         int jcap = 1;
         for (int k = 0; k < n; ++k) {
             const swv_cycle_instance& I = inst[k];
@@ -240,6 +239,7 @@ int swv_cycle_create(swv_ctx ctx, int n, const swv_cycle_instance* inst, swv_cyc
             b.sgn = (double)I.sign;
             rows += I.n_vis;
             if (I.route == SWV_ROUTE_DIRECT) {
+                rows64 += I.n_vis;
                 b.comp_offset = comp_off;
                 b.n_comp = 0;              // no model until swv_cycle_set_components
                 comp_off += I.comp_cap;
@@ -273,9 +273,10 @@ int swv_cycle_create(swv_ctx ctx, int n, const swv_cycle_instance* inst, swv_cyc
         // largest J, else the branch walker at its deepest segment count
         cy->walker = jcap <= kBatchTreeMaxJ ? 0 : 1;
         cy->depth = cy->walker == 0 ? jcap : kTreeMaxSeg;
-        cy->grid_direct = ctx->n_cu * batch_direct_blocks_per_cu(cy->vpl, cy->block);
+        cy->vpl = batch_direct_vpl(rows64, ctx->per_lane[kFamDirect64][1], ctx->n_cu);
+        cy->grid_direct = ctx->n_cu * batch_direct_blocks_per_cu(cy->vpl);
         cy->grid_tree = ctx->n_cu * batch_tree_blocks_per_cu(cy->walker, cy->depth, SWV_FP64);
-        const int64_t waves = (int64_t)cy->grid_direct * (cy->block / 64);
+        const int64_t waves = (int64_t)cy->grid_direct * (kTabBlock / 64);
         const int64_t unit = 64LL * cy->vpl;
         int64_t tile = rows / std::max<int64_t>(1, 16 * waves);
         tile = std::max<int64_t>(unit, std::min<int64_t>(64 * unit, (tile + unit - 1) / unit * unit));

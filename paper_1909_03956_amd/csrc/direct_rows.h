@@ -6,12 +6,26 @@
 // component list, so a component record (l, m, n-1, I; 32 B) is one scalar
 // load into SGPRs that enters the FMAs as the scalar operand.  The sum over
 // components is a per-lane running sum in a fixed order: bit-reproducible,
-// no atomics.  Work per (row, component): phase 3 ops, reduction 2,
-// phasor 20, MAC 2.
+// no atomics.
+//
+// FP64 work per (row, component).  Fewer than kTableMinComp components: phase
+// 3 instructions, reduction 2, polynomial phasor 20, MAC 2.  From there on the
+// table phasor with the flux folded into the cell polynomials (four products
+// per component, at ingest): phase 3, cell 3 + 1, rest 5, and 4 FMAs that turn
+// the node straight into the two sums, 16 in all and two register copies per
+// component and wave.  2^21 rows x 2,000 components: 3.43 -> 2.22 ms.
+//
+// The component list is summed in a fixed two-level order that depends on its
+// length alone: 8 ranges of A = ceil(n / 8), each in sub-ranges of
+// B = max(32, ceil(A / 8)); every sub-range sums from zero, sub-ranges add up
+// in order to ranges, ranges to the result.  The kernels that share a row's
+// components between waves or workgroups split at those borders, so all of
+// them give the same bits, and partial sums stay short.
 #pragma once
 
 #include "device_math.h"
 #include "launch.h"
+#include "phasor_table.h"
 
 namespace swv {
 
@@ -28,12 +42,189 @@ __device__ __forceinline__ Comp pack_component(double L, double M, double I, int
     return Comp{L, M, -r2 / (1.0 + sqrt(1.0 - r2)), I};
 }
 
+__device__ __forceinline__ CompCell pack_component_cell(double L, double M, double I, int& bad) {
+    const Comp c = pack_component(L, M, I, bad);
+    return comp_cell(c.l, c.m, c.nm1, c.I);
+}
+
+using CompCellPtr = const __attribute__((address_space(4))) CompCell*;
+
+// Borders of the summation order.
+struct CompRanges {
+    int n, A, B;
+    __host__ __device__ explicit CompRanges(int n_comp)
+        : n(n_comp), A((int)(((int64_t)n_comp + 7) / 8)), B(0) {
+        B = (A + 7) / 8;
+        B = B < 32 ? 32 : B;
+    }
+    // components [begin, end) of range a, sub-range b
+    __host__ __device__ int begin(int a, int b) const {
+        const int64_t k = (int64_t)a * A + (int64_t)b * B, e = end_of(a);
+        return (int)(k < e ? k : e);
+    }
+    __host__ __device__ int end(int a, int b) const { return begin(a, b + 1); }
+    __host__ __device__ int64_t end_of(int a) const {
+        const int64_t e = (int64_t)(a + 1) * A;
+        return e < n ? e : n;
+    }
+};
+
+// Copy of a wave-uniform double into a vector register: an FP64 FMA can read
+// one scalar operand only, so one coefficient of each two-term polynomial has
+// to be a vector.
+__device__ __forceinline__ double vector_copy(double s) {
+    double v;
+    asm("v_mov_b64 %0, %1" : "=v"(v) : "s"(s));
+    return v;
+}
+
+// re + i im += sum of components [k0, k1).  NB components per step: their
+// scalar loads go out together and 4 table gathers or more are in flight
+// (scalar and LDS loads share one wait counter, so a load issued ahead would be
+// waited for with the next gather anyway).
+template <int VPL, bool WIDE, int NB>
+__device__ __forceinline__ void component_step(CellPtr T, CompCellPtr cp, int k,
+                                               const double (&U)[VPL], const double (&V)[VPL],
+                                               const double (&W)[VPL], double (&re)[VPL],
+                                               double (&im)[VPL]) {
+    CompCell c[NB];
+    double Ic1[NB], Is1[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+        c[b] = CompCell{cp[k + b].l,   cp[k + b].m,   cp[k + b].nm1, cp[k + b].I,
+                        cp[k + b].Ic0, cp[k + b].Ic1, cp[k + b].Is0, cp[k + b].Is1};
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        Ic1[b] = vector_copy(c[b].Ic1);
+        Is1[b] = vector_copy(c[b].Is1);
+    }
+    double d[NB][VPL];
+    Cell e[NB][VPL];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < VPL; ++i)
+            e[b][i] = find_cell<WIDE>(
+                T, fma(U[i], c[b].l, fma(V[i], c[b].m, W[i] * c[b].nm1)), d[b][i]);
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) {
+            const double q = d[b][i] * d[b][i];
+            const double cI = fma(q, fma(q, Ic1[b], c[b].Ic0), c[b].I);
+            const double sI = d[b][i] * fma(q, Is1[b], c[b].Is0);
+            re[i] = fma(e[b][i].x, cI, re[i]);
+            im[i] = fma(e[b][i].y, cI, im[i]);
+            re[i] = fma(-e[b][i].y, sI, re[i]);
+            im[i] = fma(e[b][i].x, sI, im[i]);
+        }
+}
+
+template <int VPL, bool WIDE>
+__device__ __forceinline__ void add_components(CellPtr T, CompCellPtr cp, int k0, int k1,
+                                               const double (&U)[VPL], const double (&V)[VPL],
+                                               const double (&W)[VPL], double (&re)[VPL],
+                                               double (&im)[VPL]) {
+    constexpr int NB = VPL >= 4 ? 1 : 4 / VPL;
+    int k = k0;
+#pragma unroll 1
+    for (; k + NB <= k1; k += NB) component_step<VPL, WIDE, NB>(T, cp, k, U, V, W, re, im);
+    if constexpr (NB > 1) {
+#pragma unroll 1
+        for (; k < k1; ++k) component_step<VPL, WIDE, 1>(T, cp, k, U, V, W, re, im);
+    }
+}
+
+// The sums of ranges [a0, a1), handed to put(a, re, im) as each is complete.
+template <int VPL, bool WIDE, class Put>
+__device__ __forceinline__ void range_sums(CellPtr T, CompCellPtr cp, const CompRanges& R, int a0,
+                                           int a1, const double (&U)[VPL], const double (&V)[VPL],
+                                           const double (&W)[VPL], Put&& put) {
+#pragma unroll 1
+    for (int a = a0; a < a1; ++a) {
+        double rr[VPL], ri[VPL];
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) rr[i] = ri[i] = 0.0;
+        const int last = (int)R.end_of(a);
+#pragma unroll 1
+        for (int k0 = a * R.A; k0 < last; k0 += R.B) {
+            double re[VPL], im[VPL];
+#pragma unroll
+            for (int i = 0; i < VPL; ++i) re[i] = im[i] = 0.0;
+            add_components<VPL, WIDE>(T, cp, k0, k0 + R.B < last ? k0 + R.B : last, U, V, W, re,
+                                      im);
+#pragma unroll
+            for (int i = 0; i < VPL; ++i) {
+                rr[i] += re[i];
+                ri[i] += im[i];
+            }
+        }
+        put(a, rr, ri);
+    }
+}
+
+// Rows j[0 .. VPL) of a lane, clamped to the last one.  Returns whether the
+// phases of some row of the wave need the WIDE form (or are not finite).
 template <int VPL>
+__device__ __forceinline__ bool load_rows(const int64_t (&j)[VPL], int64_t limit,
+                                          const double* __restrict__ u,
+                                          const double* __restrict__ v,
+                                          const double* __restrict__ w, double (&U)[VPL],
+                                          double (&V)[VPL], double (&W)[VPL]) {
+    bool small = true;
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) {
+        const int64_t jj = j[i] < limit ? j[i] : limit - 1;
+        U[i] = u[jj];
+        V[i] = v[jj];
+        W[i] = w[jj];
+        small = small && fabs(U[i]) + fabs(V[i]) + fabs(W[i]) < kTabMaxBaseline;
+    }
+    return __any(!small);
+}
+
+// All components by one wave.
+template <int VPL>
+__device__ __forceinline__ void direct_rows_cell(CellPtr T, const int64_t (&j)[VPL], int64_t limit,
+                                                 const double* __restrict__ u,
+                                                 const double* __restrict__ v,
+                                                 const double* __restrict__ w,
+                                                 const CompCell* __restrict__ comp, int n_comp,
+                                                 double sgn, double2* __restrict__ out,
+                                                 int* __restrict__ status) {
+    double U[VPL], V[VPL], W[VPL], sr[VPL], si[VPL];
+    const bool wide = load_rows<VPL>(j, limit, u, v, w, U, V, W);
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) sr[i] = si[i] = 0.0;
+    const CompRanges R(n_comp);
+    const CompCellPtr cp = uniform_ptr(comp);
+    const auto add = [&](int, const double(&rr)[VPL], const double(&ri)[VPL]) {
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) {
+            sr[i] += rr[i];
+            si[i] += ri[i];
+        }
+    };
+    if (__builtin_expect(wide, 0))
+        range_sums<VPL, true>(T, cp, R, 0, 8, U, V, W, add);
+    else
+        range_sums<VPL, false>(T, cp, R, 0, 8, U, V, W, add);
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) {
+        if (j[i] < limit) {
+            if (!isfinite(U[i] + V[i] + W[i])) atomicOr(status, kStatusNonFinite);
+            out[j[i]] = make_double2(sr[i], sgn * si[i]);
+        }
+    }
+}
+
+// Polynomial phasor, components in list order; comp: records in any address space.
+template <int VPL, class RecPtr>
 __device__ __forceinline__ void direct_rows_f64(const int64_t (&j)[VPL], int64_t limit,
                                                 const double* __restrict__ u,
                                                 const double* __restrict__ v,
                                                 const double* __restrict__ w,
-                                                const Comp* __restrict__ comp, int n_comp,
+                                                RecPtr comp, int n_comp,
                                                 double sgn, double2* __restrict__ out,
                                                 int* __restrict__ status) {
     double U[VPL], V[VPL], W[VPL], re[VPL], iq[VPL];
@@ -46,9 +237,8 @@ __device__ __forceinline__ void direct_rows_f64(const int64_t (&j)[VPL], int64_t
         re[i] = 0.0;
         iq[i] = 0.0;
     }
-    const auto* cp = uniform_ptr(comp);
     for (int k = 0; k < n_comp; ++k) {
-        const Comp cur{cp[k].l, cp[k].m, cp[k].nm1, cp[k].I};
+        const Comp cur{comp[k].l, comp[k].m, comp[k].nm1, comp[k].I};
 #pragma unroll
         for (int i = 0; i < VPL; ++i) {
             double c, q;

@@ -14,18 +14,22 @@
 namespace swv {
 
 // Packs the components of every direct instance: block row y is instance y.
-__global__ void k_batch_ingest(const BatchInst* __restrict__ inst, Comp* __restrict__ pack,
+__global__ void k_batch_ingest(const BatchInst* __restrict__ inst, CompCell* __restrict__ pack,
                                int* __restrict__ status) {
     const BatchInst I = inst[blockIdx.y];
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= I.n_comp) return;
     int bad;
-    pack[I.comp_offset + k] = pack_component(I.l[k], I.m[k], I.flux[k], bad);
+    CompCell* own = pack + I.comp_offset;
+    if (I.prec == SWV_FP64)
+        own[k] = pack_component_cell(I.l[k], I.m[k], I.flux[k], bad);
+    else
+        ((Comp*)own)[k] = pack_component(I.l[k], I.m[k], I.flux[k], bad);
     if (bad) atomicOr(status, bad);
 }
 
 hipError_t launch_batch_ingest(hipStream_t s, const BatchInst* inst, int n_inst, int max_comp,
-                               Comp* pack, int* status) {
+                               CompCell* pack, int* status) {
     if (n_inst <= 0 || max_comp <= 0) return hipSuccess;
     k_batch_ingest<<<dim3((unsigned)((max_comp + 255) / 256), (unsigned)n_inst), dim3(256), 0,
                      s>>>(inst, pack, status);
@@ -49,13 +53,16 @@ __device__ __forceinline__ unsigned next_item(unsigned* counter) {
     return __builtin_amdgcn_readfirstlane(it);
 }
 
-template <int VPL, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_batch_direct(const BatchInst* __restrict__ inst,
-                                                        const Comp* __restrict__ pack,
-                                                        const WorkItem* __restrict__ items,
-                                                        unsigned n_items,
-                                                        unsigned* __restrict__ counter,
-                                                        int* __restrict__ status) {
+// FP64 items: one workgroup fills the phasor table once, then its waves take
+// items on their own.  Lists too short for the table kernels go through the
+// polynomial phasor, as in the single-instance call, so the bits are the same.
+template <int VPL>
+__global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) void
+k_batch_direct(const BatchInst* __restrict__ inst, const CompCell* __restrict__ pack,
+               const WorkItem* __restrict__ items, unsigned n_items,
+               unsigned* __restrict__ counter, int* __restrict__ status) {
+    __shared__ Cell T[kTabCells];
+    fill_cells(T);
     const int lane = threadIdx.x & 63;
     const auto* IT = uniform_ptr(items);
     const auto* IN = uniform_ptr(inst);
@@ -70,20 +77,52 @@ __global__ __launch_bounds__(BLOCK) void k_batch_direct(const BatchInst* __restr
         const double* u = IN[ii].u;
         const double* v = IN[ii].v;
         const double* w = IN[ii].w;
-        void* out = IN[ii].out;
-        const Comp* comp = pack + IN[ii].comp_offset;
+        double2* out = (double2*)IN[ii].out;
+        const CompCell* comp = pack + IN[ii].comp_offset;
         const int n_comp = IN[ii].n_comp;
         const double sgn = IN[ii].sgn;
-        const bool f64 = IN[ii].prec == SWV_FP64;
         for (int sub = 0; sub < nrows; sub += 64 * VPL) {
             int64_t j[VPL];
 #pragma unroll
             for (int i = 0; i < VPL; ++i) j[i] = row0 + sub + i * 64 + lane;
-            if (f64)
-                direct_rows_f64<VPL>(j, limit, u, v, w, comp, n_comp, sgn, (double2*)out, status);
-            else
-                direct_rows_f32c<VPL>(j, limit, u, v, w, comp, n_comp, (float)sgn, (float2*)out,
+            if (n_comp >= kTableMinComp)
+                direct_rows_cell<VPL>((CellPtr)T, j, limit, u, v, w, comp, n_comp, sgn, out,
                                       status);
+            else
+                direct_rows_f64<VPL>(j, limit, u, v, w, uniform_ptr(comp), n_comp, sgn, out,
+                                     status);
+        }
+    }
+}
+
+// F32C items.
+__global__ __launch_bounds__(kBatchF32Block) void k_batch_direct_f32c(
+    const BatchInst* __restrict__ inst, const CompCell* __restrict__ pack,
+    const WorkItem* __restrict__ items, unsigned n_items, unsigned* __restrict__ counter,
+    int* __restrict__ status) {
+    const int lane = threadIdx.x & 63;
+    const auto* IT = uniform_ptr(items);
+    const auto* IN = uniform_ptr(inst);
+    for (;;) {
+        const unsigned it = next_item(counter);
+        if (it >= n_items) break;
+        const int64_t row0 = IT[it].row0;
+        const int nrows = IT[it].nrows;
+        const int ii = IT[it].inst;
+        const int64_t n_vis = IN[ii].n_vis;
+        const int64_t limit = row0 + nrows < n_vis ? row0 + nrows : n_vis;
+        const double* u = IN[ii].u;
+        const double* v = IN[ii].v;
+        const double* w = IN[ii].w;
+        float2* out = (float2*)IN[ii].out;
+        const Comp* comp = (const Comp*)(pack + IN[ii].comp_offset);
+        const int n_comp = IN[ii].n_comp;
+        const float sgn = (float)IN[ii].sgn;
+        for (int sub = 0; sub < nrows; sub += 64 * kBatchF32Vpl) {
+            int64_t j[kBatchF32Vpl];
+#pragma unroll
+            for (int i = 0; i < kBatchF32Vpl; ++i) j[i] = row0 + sub + i * 64 + lane;
+            direct_rows_f32c<kBatchF32Vpl>(j, limit, u, v, w, comp, n_comp, sgn, out, status);
         }
     }
 }
@@ -163,23 +202,31 @@ __attribute__((amdgpu_waves_per_eu(tree_waves_per_simd<JMAX, WALKER>()))) void k
     }
 }
 
-template <int VPL, int BLOCK>
-static int direct_occupancy() {
+template <class K>
+static int resident(K kernel, int block) {
     int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_batch_direct<VPL, BLOCK>, BLOCK, 0) !=
-        hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, block, 0) != hipSuccess) {
+        (void)hipGetLastError();
         return 1;
+    }
     return nb > 0 ? nb : 1;
 }
 
-int batch_direct_blocks_per_cu(int vpl, int block) {
-#define SWV_OCC(V, B) if (vpl == V && block == B) return direct_occupancy<V, B>();
-    SWV_OCC(1, 64) SWV_OCC(1, 128) SWV_OCC(1, 256)
-    SWV_OCC(2, 64) SWV_OCC(2, 128) SWV_OCC(2, 256)
-    SWV_OCC(4, 64) SWV_OCC(4, 128) SWV_OCC(4, 256)
-#undef SWV_OCC
-    return 1;
+int batch_direct_blocks_per_cu(int vpl) {
+    return vpl == 1   ? resident(k_batch_direct<1>, kTabBlock)
+           : vpl == 2 ? resident(k_batch_direct<2>, kTabBlock)
+                      : resident(k_batch_direct<4>, kTabBlock);
 }
+
+int batch_direct_vpl(int64_t rows, int vpl_max, int n_cu) {
+    int vpl = vpl_max;
+    while (vpl > 1 && rows < 4 * 64 * (int64_t)vpl * n_cu * batch_direct_blocks_per_cu(vpl) *
+                                 (kTabBlock / 64))
+        vpl /= 2;
+    return vpl;
+}
+
+int batch_direct_f32c_blocks_per_cu() { return resident(k_batch_direct_f32c, kBatchF32Block); }
 
 template <int JMAX, int WALKER, int PREC, bool PRUNED = false>
 static int tree_occupancy() {
@@ -210,21 +257,27 @@ int batch_tree_blocks_per_cu(int walker, int depth, int prec) {
     return 1;
 }
 
-hipError_t launch_batch_direct(hipStream_t s, int vpl, int block, int grid,
-                               const BatchInst* inst, const Comp* pack, const WorkItem* items,
-                               unsigned n_items, unsigned* counter, int* status) {
+hipError_t launch_batch_direct(hipStream_t s, int vpl, int grid, const BatchInst* inst,
+                               const CompCell* pack, const WorkItem* items, unsigned n_items,
+                               unsigned* counter, int* status) {
     if (n_items == 0) return hipSuccess;
-#define SWV_RUN(V, B)                                                                     \
-    if (vpl == V && block == B) {                                                         \
-        k_batch_direct<V, B><<<dim3(grid), dim3(B), 0, s>>>(inst, pack, items, n_items,    \
-                                                            counter, status);             \
-        return hipGetLastError();                                                         \
+    const dim3 g(grid), b(kTabBlock);
+    switch (vpl) {
+        case 1: k_batch_direct<1><<<g, b, 0, s>>>(inst, pack, items, n_items, counter, status); break;
+        case 2: k_batch_direct<2><<<g, b, 0, s>>>(inst, pack, items, n_items, counter, status); break;
+        case 4: k_batch_direct<4><<<g, b, 0, s>>>(inst, pack, items, n_items, counter, status); break;
+        default: return hipErrorInvalidValue;
     }
-    SWV_RUN(1, 64) SWV_RUN(1, 128) SWV_RUN(1, 256)
-    SWV_RUN(2, 64) SWV_RUN(2, 128) SWV_RUN(2, 256)
-    SWV_RUN(4, 64) SWV_RUN(4, 128) SWV_RUN(4, 256)
-#undef SWV_RUN
-    return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_direct_f32c(hipStream_t s, int grid, const BatchInst* inst,
+                                    const CompCell* pack, const WorkItem* items,
+                                    unsigned n_items, unsigned* counter, int* status) {
+    if (n_items == 0) return hipSuccess;
+    k_batch_direct_f32c<<<dim3(grid), dim3(kBatchF32Block), 0, s>>>(inst, pack, items, n_items,
+                                                                    counter, status);
+    return hipGetLastError();
 }
 
 hipError_t launch_batch_tree(hipStream_t s, int walker, int depth, int prec, int grid,

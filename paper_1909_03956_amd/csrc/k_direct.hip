@@ -1,6 +1,8 @@
 // Direct component sum (section 3.3, Eq. 12) on gfx950: the component
 // ingest and the single-instance kernels.  Rows of a block are strided by
 // the block size so each of a lane's VPL loads is coalesced.
+#include <cmath>
+
 #include "direct_rows.h"
 
 namespace swv {
@@ -15,6 +17,16 @@ __global__ void k_ingest(int64_t n, const double* __restrict__ l, const double* 
     if (bad) atomicOr(status, bad);
 }
 
+__global__ void k_ingest_cell(int64_t n, const double* __restrict__ l,
+                              const double* __restrict__ m, const double* __restrict__ flux,
+                              CompCell* __restrict__ out, int* __restrict__ status) {
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n) return;
+    int bad;
+    out[k] = pack_component_cell(l[k], m[k], flux[k], bad);
+    if (bad) atomicOr(status, bad);
+}
+
 hipError_t launch_ingest(hipStream_t s, int64_t n, const double* l, const double* m,
                          const double* flux, Comp* out, int* status) {
     if (n <= 0) return hipSuccess;
@@ -23,20 +35,254 @@ hipError_t launch_ingest(hipStream_t s, int64_t n, const double* l, const double
     return hipGetLastError();
 }
 
-template <int VPL, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_direct_f64(const double* __restrict__ u,
-                                                      const double* __restrict__ v,
-                                                      const double* __restrict__ w, int64_t n_vis,
-                                                      const Comp* __restrict__ comp, int n_comp,
-                                                      double sgn, double2* __restrict__ out,
-                                                      int* __restrict__ status) {
-    const int64_t base = (int64_t)blockIdx.x * (BLOCK * VPL) + threadIdx.x;
-    int64_t j[VPL];
-#pragma unroll
-    for (int i = 0; i < VPL; ++i) j[i] = base + (int64_t)i * BLOCK;
-    direct_rows_f64<VPL>(j, n_vis, u, v, w, comp, n_comp, sgn, out, status);
+hipError_t launch_ingest(hipStream_t s, int64_t n, const double* l, const double* m,
+                         const double* flux, CompCell* out, int* status) {
+    if (n <= 0) return hipSuccess;
+    const int b = 256;
+    k_ingest_cell<<<dim3((unsigned)((n + b - 1) / b)), dim3(b), 0, s>>>(n, l, m, flux, out,
+                                                                        status);
+    return hipGetLastError();
 }
 
+// ------------------------------------------------- FP64, few components ---
+// Each block packs the components itself (one launch instead of two and no
+// workspace: the call is latency-bound); lanes read them as LDS broadcasts.
+// Four rows per lane from 2^20 rows on: fewer packings, and more row loads in
+// flight where the call is bound by them.
+constexpr int kFewBlock = 256;
+
+template <int VPL>
+__global__ __launch_bounds__(kFewBlock) void k_direct_few(
+    const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
+    int64_t n_vis, const double* __restrict__ l, const double* __restrict__ m,
+    const double* __restrict__ flux, int n_comp, double sgn, double2* __restrict__ out,
+    int* __restrict__ status) {
+    __shared__ Comp comp[kTableMinComp];
+    if ((int)threadIdx.x < n_comp) {
+        int bad;
+        comp[threadIdx.x] = pack_component(l[threadIdx.x], m[threadIdx.x], flux[threadIdx.x], bad);
+        if (bad && blockIdx.x == 0) atomicOr(status, bad);
+    }
+    __syncthreads();
+    int64_t j[VPL];
+#pragma unroll
+    for (int i = 0; i < VPL; ++i)
+        j[i] = ((int64_t)blockIdx.x * VPL + i) * kFewBlock + threadIdx.x;
+    direct_rows_f64<VPL>(j, n_vis, u, v, w, (const Comp*)comp, n_comp, sgn, out, status);
+}
+
+hipError_t launch_direct_few(hipStream_t s, int64_t n_vis, const double* u, const double* v,
+                             const double* w, int n_comp, const double* l, const double* m,
+                             const double* flux, int sign, double2* out, int* status) {
+    if (n_vis <= 0) return hipSuccess;
+    if (n_comp >= kTableMinComp) return hipErrorInvalidValue;
+    const int vpl = n_vis < (int64_t(1) << 20) ? 1 : 4;
+    const dim3 grid((unsigned)((n_vis + kFewBlock * vpl - 1) / (kFewBlock * vpl))), blk(kFewBlock);
+    if (vpl == 1)
+        k_direct_few<1><<<grid, blk, 0, s>>>(u, v, w, n_vis, l, m, flux, n_comp, (double)sign, out,
+                                             status);
+    else
+        k_direct_few<4><<<grid, blk, 0, s>>>(u, v, w, n_vis, l, m, flux, n_comp, (double)sign, out,
+                                             status);
+    return hipGetLastError();
+}
+
+// -------------------------------------------------- FP64, table phasor ----
+template <int VPL>
+__global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_direct_cell(
+    const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
+    int64_t n_vis, const CompCell* __restrict__ comp, int n_comp, double sgn,
+    double2* __restrict__ out, int* __restrict__ status) {
+    __shared__ Cell T[kTabCells];
+    fill_cells(T);
+    const int64_t base = (int64_t)blockIdx.x * (kTabBlock * VPL) + threadIdx.x;
+    int64_t j[VPL];
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) j[i] = base + (int64_t)i * kTabBlock;
+    direct_rows_cell<VPL>((CellPtr)T, j, n_vis, u, v, w, comp, n_comp, sgn, out, status);
+}
+
+// Calls too small to fill the chip by rows alone: SPLIT waves of the workgroup
+// share a row's components, 8 / SPLIT ranges each.  Their range sums meet in
+// LDS (where the table was) and are added in range order.
+template <int VPL, int SPLIT>
+__global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) void
+k_direct_cell_split(const double* __restrict__ u, const double* __restrict__ v,
+                    const double* __restrict__ w, int64_t n_vis,
+                    const CompCell* __restrict__ comp, int n_comp, double sgn,
+                    double2* __restrict__ out, int* __restrict__ status) {
+    constexpr int kLanes = kTabBlock / SPLIT;   // lanes that own rows
+    constexpr int kRows = kLanes * VPL;         // rows per workgroup
+    __shared__ Cell T[kTabCells];
+    static_assert(8 * kRows <= kTabCells, "range sums fit where the table was");
+    fill_cells(T);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int part = wave % SPLIT, local = wave / SPLIT * 64 + lane;
+    const int64_t row0 = (int64_t)blockIdx.x * kRows;
+    int64_t j[VPL];
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) j[i] = row0 + i * kLanes + local;
+    double U[VPL], V[VPL], W[VPL];
+    const bool wide = load_rows<VPL>(j, n_vis, u, v, w, U, V, W);
+    const CompRanges R(n_comp);
+    constexpr int kOwn = 8 / SPLIT;   // ranges per wave
+    double pr[kOwn][VPL], pi[kOwn][VPL];
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+        const auto keep = [&](int, const double(&re)[VPL], const double(&im)[VPL]) {
+#pragma unroll
+            for (int i = 0; i < VPL; ++i) {
+                pr[q][i] = re[i];
+                pi[q][i] = im[i];
+            }
+        };
+        const int a = part * kOwn + q;
+        if (__builtin_expect(wide, 0))
+            range_sums<VPL, true>((CellPtr)T, uniform_ptr(comp), R, a, a + 1, U, V, W, keep);
+        else
+            range_sums<VPL, false>((CellPtr)T, uniform_ptr(comp), R, a, a + 1, U, V, W, keep);
+    }
+    __syncthreads();   // every wave is done with the table
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q)
+#pragma unroll
+        for (int i = 0; i < VPL; ++i)
+            T[(part * kOwn + q) * kRows + i * kLanes + local] = Cell{pr[q][i], pi[q][i]};
+    __syncthreads();
+    for (int r = threadIdx.x; r < kRows && row0 + r < n_vis; r += kTabBlock) {
+        double re = 0.0, im = 0.0;
+#pragma unroll
+        for (int a = 0; a < 8; ++a) {
+            const Cell p = T[a * kRows + r];
+            re += p.x;
+            im += p.y;
+        }
+        const int64_t jr = row0 + r;
+        if (!isfinite(u[jr] + v[jr] + w[jr])) atomicOr(status, kStatusNonFinite);
+        out[jr] = make_double2(re, sgn * im);
+    }
+}
+
+// The smallest row counts: workgroup (x, b) takes 64 rows and sub-range b of
+// all 8 ranges, one range per wave; partial[a][b][row].
+__global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) void
+k_direct_cell_part(const double* __restrict__ u, const double* __restrict__ v,
+                   const double* __restrict__ w, int64_t n_vis,
+                   const CompCell* __restrict__ comp, int n_comp, double2* __restrict__ partial,
+                   int* __restrict__ status) {
+    __shared__ Cell T[kTabCells];
+    fill_cells(T);
+    const int lane = threadIdx.x & 63, a = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b = blockIdx.y;
+    const int64_t j[1] = {(int64_t)blockIdx.x * 64 + lane};
+    double U[1], V[1], W[1], re[1] = {0.0}, im[1] = {0.0};
+    const bool wide = load_rows<1>(j, n_vis, u, v, w, U, V, W);
+    const CompRanges R(n_comp);
+    const int k0 = R.begin(a, b), k1 = R.end(a, b);
+    if (__builtin_expect(wide, 0))
+        add_components<1, true>((CellPtr)T, uniform_ptr(comp), k0, k1, U, V, W, re, im);
+    else
+        add_components<1, false>((CellPtr)T, uniform_ptr(comp), k0, k1, U, V, W, re, im);
+    if (j[0] < n_vis) {
+        if (a == 0 && b == 0 && !isfinite(U[0] + V[0] + W[0])) atomicOr(status, kStatusNonFinite);
+        partial[((int64_t)a * 8 + b) * n_vis + j[0]] = make_double2(re[0], im[0]);
+    }
+}
+
+__global__ __launch_bounds__(64) void k_direct_join(const double2* __restrict__ partial,
+                                                    int64_t n_vis, double sgn,
+                                                    double2* __restrict__ out) {
+    const int64_t j = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    if (j >= n_vis) return;
+    double re = 0.0, im = 0.0;
+#pragma unroll
+    for (int a = 0; a < 8; ++a) {
+        double rr = 0.0, ri = 0.0;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const double2 p = partial[((int64_t)a * 8 + b) * n_vis + j];
+            rr += p.x;
+            ri += p.y;
+        }
+        re += rr;
+        im += ri;
+    }
+    out[j] = make_double2(re, sgn * im);
+}
+
+// Layout with the least estimated time.  A workgroup's time, in units of one
+// wave's (64 rows, component) pass with the CU full (two workgroups): per_comp x
+// components of a wave (fewer rows per lane cost a little more each, for the
+// per-component copies and loads), plus about 14 for filling the table.
+// Workgroups run in rounds of two per CU; a call of one workgroup per CU or less
+// gets no credit for that, since nothing keeps two of them off the same CU
+// (261,120 rows x 1,000 components in 255 workgroups: 180 us at best, 336 us
+// behind the ingest kernel).
+DirectShape direct_shape(int64_t n_vis, int64_t n_comp, int vpl_max, int n_cu) {
+    const struct {
+        int vpl, split, parts;
+        double per_comp;
+    } all[] = {{4, 1, 1, 4.0}, {2, 1, 1, 2.04}, {1, 1, 1, 1.28}, {2, 2, 1, 2.04}, {2, 4, 1, 2.04},
+               {1, 2, 1, 1.28}, {1, 4, 1, 1.28}, {1, 8, 1, 1.28}, {1, 8, 8, 1.28}};
+    DirectShape best;
+    double best_t = HUGE_VAL;
+    for (const auto& c : all) {
+        if (c.vpl > vpl_max) continue;
+        const int64_t rows = (int64_t)kTabBlock / c.split * c.vpl;
+        const int64_t blocks = (n_vis + rows - 1) / rows * c.parts;
+        // the partial sums of a call cost a second launch and 2 x 1 KB a row
+        if (c.parts > 1 && (blocks > 4 * (int64_t)n_cu || n_comp < 256)) continue;
+        const int64_t rounds = (blocks + 2 * (int64_t)n_cu - 1) / (2 * (int64_t)n_cu);
+        double t = (double)rounds * (c.per_comp * (double)n_comp / (c.split * c.parts) + 14.0);
+        if (c.parts > 1) t += 45.0;   // the second launch
+        if (t < best_t) {
+            best_t = t;
+            best.vpl = c.vpl;
+            best.split = c.split;
+            best.parts = c.parts;
+        }
+    }
+    return best;
+}
+
+size_t direct_partial_bytes(const DirectShape& sh, int64_t n_vis) {
+    return sh.parts > 1 ? 64 * sizeof(double2) * (size_t)n_vis : 0;
+}
+
+hipError_t launch_direct_cell(hipStream_t s, const DirectShape& sh, int64_t n_vis, const double* u,
+                              const double* v, const double* w, const CompCell* comp,
+                              int64_t n_comp, int sign, double2* out, double2* partial,
+                              int* status) {
+    if (n_vis <= 0) return hipSuccess;
+    const double sg = (double)sign;
+    const int nc = (int)n_comp;
+    const dim3 blk(kTabBlock);
+    const int64_t rows = (int64_t)kTabBlock / sh.split * sh.vpl;
+    const unsigned nb = (unsigned)((n_vis + rows - 1) / rows);
+    if (sh.parts > 1) {
+        if (!partial || sh.split != 8 || sh.parts != 8) return hipErrorInvalidValue;
+        k_direct_cell_part<<<dim3(nb, 8), blk, 0, s>>>(u, v, w, n_vis, comp, nc, partial, status);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        k_direct_join<<<dim3(nb), dim3(64), 0, s>>>(partial, n_vis, sg, out);
+        return hipGetLastError();
+    }
+#define SWV_CELL(V, S) \
+    if (sh.vpl == V && sh.split == S)
+    SWV_CELL(4, 1) k_direct_cell<4><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(2, 1) k_direct_cell<2><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(1, 1) k_direct_cell<1><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(2, 2) k_direct_cell_split<2, 2><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(2, 4) k_direct_cell_split<2, 4><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(1, 2) k_direct_cell_split<1, 2><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(1, 4) k_direct_cell_split<1, 4><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(1, 8) k_direct_cell_split<1, 8><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else return hipErrorInvalidValue;
+#undef SWV_CELL
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------------ F32C ---
 template <int VPL, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_direct_f32c(const double* __restrict__ u,
                                                        const double* __restrict__ v,
@@ -53,41 +299,36 @@ __global__ __launch_bounds__(BLOCK) void k_direct_f32c(const double* __restrict_
 }
 
 template <int VPL, int BLOCK>
-static hipError_t run_direct(hipStream_t s, int prec, int64_t n_vis, const double* u,
-                             const double* v, const double* w, const Comp* comp, int64_t n_comp,
-                             int sign, void* out, int* status) {
+static hipError_t run_direct(hipStream_t s, int64_t n_vis, const double* u, const double* v,
+                             const double* w, const Comp* comp, int64_t n_comp, int sign,
+                             void* out, int* status) {
     const int64_t rows = (int64_t)BLOCK * VPL;
     const dim3 grid((unsigned)((n_vis + rows - 1) / rows)), blk(BLOCK);
-    if (prec == SWV_FP64)
-        k_direct_f64<VPL, BLOCK><<<grid, blk, 0, s>>>(u, v, w, n_vis, comp, (int)n_comp,
-                                                       (double)sign, (double2*)out, status);
-    else
-        k_direct_f32c<VPL, BLOCK><<<grid, blk, 0, s>>>(u, v, w, n_vis, comp, (int)n_comp,
-                                                        (float)sign, (float2*)out, status);
+    k_direct_f32c<VPL, BLOCK><<<grid, blk, 0, s>>>(u, v, w, n_vis, comp, (int)n_comp, (float)sign,
+                                                   (float2*)out, status);
     return hipGetLastError();
 }
 
 template <int VPL>
-static hipError_t run_direct_b(hipStream_t s, int prec, int block, int64_t n_vis,
-                               const double* u, const double* v, const double* w,
-                               const Comp* comp, int64_t n_comp, int sign, void* out,
-                               int* status) {
+static hipError_t run_direct_b(hipStream_t s, int block, int64_t n_vis, const double* u,
+                               const double* v, const double* w, const Comp* comp, int64_t n_comp,
+                               int sign, void* out, int* status) {
     switch (block) {
-        case 64: return run_direct<VPL, 64>(s, prec, n_vis, u, v, w, comp, n_comp, sign, out, status);
-        case 128: return run_direct<VPL, 128>(s, prec, n_vis, u, v, w, comp, n_comp, sign, out, status);
-        case 256: return run_direct<VPL, 256>(s, prec, n_vis, u, v, w, comp, n_comp, sign, out, status);
+        case 64: return run_direct<VPL, 64>(s, n_vis, u, v, w, comp, n_comp, sign, out, status);
+        case 128: return run_direct<VPL, 128>(s, n_vis, u, v, w, comp, n_comp, sign, out, status);
+        case 256: return run_direct<VPL, 256>(s, n_vis, u, v, w, comp, n_comp, sign, out, status);
         default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_direct(hipStream_t s, int prec, int vpl, int block, int64_t n_vis,
-                         const double* u, const double* v, const double* w, const Comp* comp,
-                         int64_t n_comp, int sign, void* out, int* status) {
+hipError_t launch_direct_f32c(hipStream_t s, int vpl, int block, int64_t n_vis, const double* u,
+                              const double* v, const double* w, const Comp* comp, int64_t n_comp,
+                              int sign, void* out, int* status) {
     if (n_vis <= 0) return hipSuccess;
     switch (vpl) {
-        case 1: return run_direct_b<1>(s, prec, block, n_vis, u, v, w, comp, n_comp, sign, out, status);
-        case 2: return run_direct_b<2>(s, prec, block, n_vis, u, v, w, comp, n_comp, sign, out, status);
-        case 4: return run_direct_b<4>(s, prec, block, n_vis, u, v, w, comp, n_comp, sign, out, status);
+        case 1: return run_direct_b<1>(s, block, n_vis, u, v, w, comp, n_comp, sign, out, status);
+        case 2: return run_direct_b<2>(s, block, n_vis, u, v, w, comp, n_comp, sign, out, status);
+        case 4: return run_direct_b<4>(s, block, n_vis, u, v, w, comp, n_comp, sign, out, status);
         default: return hipErrorInvalidValue;
     }
 }

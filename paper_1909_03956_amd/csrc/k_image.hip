@@ -331,8 +331,8 @@ constexpr int kGradRowTile = 256;
 template <int CPL, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_grad_partial(
     const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
-    const double2* __restrict__ y, int64_t n_vis, int64_t chunk, const Comp* __restrict__ comp,
-    int64_t n_comp, const int* __restrict__ n_comp_dev, double sgn, int64_t n_chunks,
+    const double2* __restrict__ y, int64_t n_vis, int64_t chunk, const double* __restrict__ comp,
+    int comp_stride, int64_t n_comp, const int* __restrict__ n_comp_dev, double sgn, int64_t n_chunks,
     int64_t tiles, int64_t bid0, double* __restrict__ partial) {
     // one row: u, v, w, yr, yi, 4 s yr, 4 s yi, (pad) -- 64 bytes
     __shared__ double2 rows[kGradRowTile][4];
@@ -348,9 +348,9 @@ __global__ __launch_bounds__(BLOCK) void k_grad_partial(
     for (int i = 0; i < CPL; ++i) {
         int64_t k = k0 + (int64_t)i * BLOCK;
         k = k < n_comp ? k : n_comp - 1;
-        L[i] = comp[k].l;
-        M[i] = comp[k].m;
-        N[i] = comp[k].nm1;
+        L[i] = comp[k * comp_stride];
+        M[i] = comp[k * comp_stride + 1];
+        N[i] = comp[k * comp_stride + 2];
         z0[i] = zu[i] = zv[i] = zw[i] = 0.0;
     }
     const int64_t j0 = chunk_id * chunk;
@@ -411,8 +411,8 @@ __global__ __launch_bounds__(BLOCK) void k_grad_partial(
 }
 
 __global__ __launch_bounds__(kSumCols * kSumQ) void k_grad_finish(
-    const double* __restrict__ partial, int64_t n_chunks, const Comp* __restrict__ comp,
-    int64_t n_comp, const int* __restrict__ n_comp_dev, double sgn, double alpha,
+    const double* __restrict__ partial, int64_t n_chunks, const double* __restrict__ comp,
+    int comp_stride, int64_t n_comp, const int* __restrict__ n_comp_dev, double sgn, double alpha,
     double* __restrict__ d_flux, double* __restrict__ d_l, double* __restrict__ d_m) {
     __shared__ double red[4][kSumQ][kSumCols];
     if (n_comp_dev) n_comp = *n_comp_dev;
@@ -434,11 +434,12 @@ __global__ __launch_bounds__(kSumCols * kSumQ) void k_grad_finish(
     if (q != 0 || k >= n_comp) return;
     const double z0 = red[0][0][tx], zu = red[1][0][tx], zv = red[2][0][tx],
                  zw = red[3][0][tx];
-    const double n = 1.0 + comp[k].nm1;
-    const double f = -alpha * comp[k].I * sgn * 2.0 * M_PI;
+    const double* c = comp + k * comp_stride;   // l, m, n - 1, I
+    const double n = 1.0 + c[2];
+    const double f = -alpha * c[3] * sgn * 2.0 * M_PI;
     d_flux[k] = alpha * z0;
-    d_l[k] = f * (zu - (comp[k].l / n) * zw);
-    d_m[k] = f * (zv - (comp[k].m / n) * zw);
+    d_l[k] = f * (zu - (c[0] / n) * zw);
+    d_m[k] = f * (zv - (c[1] / n) * zw);
 }
 
 template <int CPL, int BLOCK>
@@ -464,9 +465,9 @@ int grad_blocks_per_cu(int cpl, int block) {
 }
 
 hipError_t launch_grad(hipStream_t s, int cpl, int64_t chunk, int64_t n_vis, const double* u,
-                       const double* v, const double* w, const void* y, const Comp* comp,
-                       int64_t n_comp, int sign, double alpha, double* partial, double* d_flux,
-                       double* d_l, double* d_m, const int* n_comp_dev) {
+                       const double* v, const double* w, const void* y, const double* comp,
+                       int comp_stride, int64_t n_comp, int sign, double alpha, double* partial,
+                       double* d_flux, double* d_l, double* d_m, const int* n_comp_dev) {
     if (n_comp <= 0) return hipSuccess;
     if (cpl != 1 && cpl != 2 && cpl != 4) return hipErrorInvalidValue;
     const int64_t n_chunks = n_vis > 0 ? (n_vis + chunk - 1) / chunk : 0;
@@ -479,8 +480,8 @@ hipError_t launch_grad(hipStream_t s, int cpl, int64_t chunk, int64_t n_vis, con
         launch_slabs(xcd_padded(n_chunks) * tiles, [&](int64_t b0, unsigned nb) {
 #define SWV_RUN_G(C, B)                                                                      \
     if (cpl == C && block == B)                                                              \
-        k_grad_partial<C, B><<<dim3(nb), dim3(B), 0, s>>>(u, v, w, yy, n_vis, chunk, comp, n_comp, \
-                                                          n_comp_dev, sg, n_chunks, tiles, b0,  \
+        k_grad_partial<C, B><<<dim3(nb), dim3(B), 0, s>>>(u, v, w, yy, n_vis, chunk, comp,         \
+                                                          comp_stride, n_comp, n_comp_dev, sg, n_chunks, tiles, b0,  \
                                                           partial);
             SWV_RUN_G(1, 128) SWV_RUN_G(1, 256) SWV_RUN_G(1, 512) SWV_RUN_G(1, 1024)
             SWV_RUN_G(2, 128) SWV_RUN_G(2, 256) SWV_RUN_G(2, 512) SWV_RUN_G(2, 1024)
@@ -491,7 +492,7 @@ hipError_t launch_grad(hipStream_t s, int cpl, int64_t chunk, int64_t n_vis, con
         if (e != hipSuccess) return e;
     }
     k_grad_finish<<<dim3((unsigned)((n_comp + kSumCols - 1) / kSumCols)), dim3(kSumCols * kSumQ),
-                    0, s>>>(partial, n_chunks, comp, n_comp, n_comp_dev, (double)sign, alpha,
+                    0, s>>>(partial, n_chunks, comp, comp_stride, n_comp, n_comp_dev, (double)sign, alpha,
                             d_flux, d_l, d_m);
     return hipGetLastError();
 }

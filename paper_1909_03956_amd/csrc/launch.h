@@ -20,12 +20,46 @@ __device__ __forceinline__ const __attribute__((address_space(4))) T* uniform_pt
 constexpr int kPerLaneOptions[3] = {1, 2, 4};
 constexpr int kBlockOptions[3] = {64, 128, 256};
 
+// Threads of the workgroups that share a phasor table in LDS (phasor_table.h).
+constexpr int kTabBlock = 512;
+
 hipError_t launch_ingest(hipStream_t s, int64_t n, const double* l, const double* m,
                          const double* flux, Comp* out, int* status);
+hipError_t launch_ingest(hipStream_t s, int64_t n, const double* l, const double* m,
+                         const double* flux, CompCell* out, int* status);
 
-hipError_t launch_direct(hipStream_t s, int prec, int vpl, int block, int64_t n_vis,
-                         const double* u, const double* v, const double* w, const Comp* comp,
-                         int64_t n_comp, int sign, void* out, int* status);
+// FP32-compensated direct sum.
+hipError_t launch_direct_f32c(hipStream_t s, int vpl, int block, int64_t n_vis, const double* u,
+                              const double* v, const double* w, const Comp* comp, int64_t n_comp,
+                              int sign, void* out, int* status);
+
+// Shortest component list of the FP64 kernels with the table phasor.  Below
+// it the sum is bound by the rows' 40 bytes (at 8 components their transfer
+// and the polynomial phasors take about the same time), and filling the table
+// (64 KB per workgroup) would cost more than it saves.
+constexpr int kTableMinComp = 16;
+
+// FP64 direct sum of fewer than kTableMinComp components, packed in the kernel.
+hipError_t launch_direct_few(hipStream_t s, int64_t n_vis, const double* u, const double* v,
+                             const double* w, int n_comp, const double* l, const double* m,
+                             const double* flux, int sign, double2* out, int* status);
+
+// How the table kernels lay out one call: rows per lane, waves of a workgroup
+// that share a row's components (1, 2, 4, 8), and workgroups that share them
+// besides (1 or 8, through partial sums in memory).  Every layout gives the
+// same bits.
+struct DirectShape {
+    int vpl = 1, split = 1, parts = 1;
+};
+// vpl_max: most rows per lane (1, 2, 4).
+DirectShape direct_shape(int64_t n_vis, int64_t n_comp, int vpl_max, int n_cu);
+// Bytes of partial sums launch_direct_cell needs (0 if parts is 1).
+size_t direct_partial_bytes(const DirectShape& sh, int64_t n_vis);
+// FP64 direct sum of packed components (table phasor).
+hipError_t launch_direct_cell(hipStream_t s, const DirectShape& sh, int64_t n_vis, const double* u,
+                              const double* v, const double* w, const CompCell* comp,
+                              int64_t n_comp, int sign, double2* out, double2* partial,
+                              int* status);
 
 struct TreeArgs {
     const TRec* rec;
@@ -70,12 +104,14 @@ int adjoint_blocks_per_cu(int prec, int ppl, int block);
 void grad_tiling(int cpl, int64_t n_comp, int* block, int64_t* tiles);
 int grad_blocks_per_cu(int cpl, int block);
 
-// n_comp_dev (optional): the actual component count on the device, at most
+// comp: packed components, {l, m, n - 1, I} at the start of every comp_stride
+// doubles (4 for Comp, 8 for CompCell).  n_comp_dev (optional): the actual component count on the device, at most
 // n_comp, which then only sizes the grid (see k_grad_partial).
 hipError_t launch_grad(hipStream_t s, int cpl, int64_t chunk, int64_t n_vis, const double* u,
-                       const double* v, const double* w, const void* y, const Comp* comp,
-                       int64_t n_comp, int sign, double alpha, double* partial, double* d_flux,
-                       double* d_l, double* d_m, const int* n_comp_dev = nullptr);
+                       const double* v, const double* w, const void* y, const double* comp,
+                       int comp_stride, int64_t n_comp, int sign, double alpha, double* partial,
+                       double* d_flux, double* d_l, double* d_m,
+                       const int* n_comp_dev = nullptr);
 
 hipError_t launch_residual(hipStream_t s, int64_t n_vis, const void* obs, const void* model,
                            double inv_sigma2, void* resid, double* partial, double* chi2);
@@ -84,6 +120,8 @@ hipError_t launch_residual(hipStream_t s, int64_t n_vis, const void* obs, const 
 int residual_blocks(int64_t n_vis);
 
 // ------------------------------------------------------------ batched --
+// Packed components of all direct instances; an FP32-compensated instance
+// keeps its 32-byte records at the start of its stretch.
 // One prediction instance as the persistent kernels read it.
 struct BatchInst {
     const double* u;
@@ -111,16 +149,26 @@ struct WorkItem {
 };
 
 hipError_t launch_batch_ingest(hipStream_t s, const BatchInst* inst, int n_inst, int max_comp,
-                               Comp* pack, int* status);
+                               CompCell* pack, int* status);
 hipError_t launch_reset_counters(hipStream_t s, unsigned* counters, int n);
-// Blocks per CU that stay resident for the persistent kernels.
-int batch_direct_blocks_per_cu(int vpl, int block);
+// Blocks per CU that stay resident for the persistent kernels: FP64 (blocks of
+// kTabBlock threads) and F32C (blocks of kBatchF32Block).
+int batch_direct_blocks_per_cu(int vpl);
+// Rows per lane of a persistent FP64 launch over `rows` rows: fewer when the
+// widest would leave a resident wave less than four row tiles to balance with.
+int batch_direct_vpl(int64_t rows, int vpl_max, int n_cu);
+int batch_direct_f32c_blocks_per_cu();
+constexpr int kBatchF32Vpl = 2, kBatchF32Block = 64;
 // walker / depth as for launch_tree: depth is the largest J (walker 0) or
 // segment depth (walker 1) over the plan's trees.
 int batch_tree_blocks_per_cu(int walker, int depth, int prec);
-hipError_t launch_batch_direct(hipStream_t s, int vpl, int block, int grid,
-                               const BatchInst* inst, const Comp* pack, const WorkItem* items,
-                               unsigned n_items, unsigned* counter, int* status);
+// FP64 and F32C work items go through separate launches.
+hipError_t launch_batch_direct(hipStream_t s, int vpl, int grid, const BatchInst* inst,
+                               const CompCell* pack, const WorkItem* items, unsigned n_items,
+                               unsigned* counter, int* status);
+hipError_t launch_batch_direct_f32c(hipStream_t s, int grid, const BatchInst* inst,
+                                    const CompCell* pack, const WorkItem* items,
+                                    unsigned n_items, unsigned* counter, int* status);
 // prec: the precision of every instance the work items refer to.  pruned: some
 // tree holds leaves above level J; only the branch walker at depth kTreeMaxSeg
 // is compiled for that.
