@@ -9,38 +9,12 @@
 // into fixed chunks; each (chunk, tile) block writes its partial sums, and a
 // second kernel adds the chunks in index order -- deterministic and free of
 // atomics.
-//
-// Block order (1-D grid): workgroups are dealt to the 8 XCDs round-robin by
-// linear id, and blocks sharing a chunk read the same rows.  Ids therefore
-// walk groups of 8 chunks -- one per XCD -- and, inside a group, all tiles in
-// consecutive dispatch rounds: every tile of a chunk runs on the same XCD at
-// about the same time and the chunk's rows come from HBM into one L2 once.
+// Block order: chunking.h.
+#include "chunking.h"
 #include "device_math.h"
 #include "launch.h"
 
 namespace swv {
-
-// Chunk count rounded up to a whole number of XCD rounds.
-static int64_t xcd_padded(int64_t n_chunks) { return (n_chunks + 7) / 8 * 8; }
-
-// (chunk, tile) of linear block id `bid` in the order described above.
-__device__ __forceinline__ void chunk_tile(int64_t bid, int64_t tiles, int64_t& chunk,
-                                           int64_t& tile) {
-    const int64_t per_group = 8 * tiles;
-    const int64_t g = bid / per_group;
-    const int64_t r = bid - g * per_group;
-    tile = r >> 3;
-    chunk = g * 8 + (r & 7);
-}
-
-// Launches `total` blocks as 1-D grids of at most 2^30 blocks, passing the
-// first linear id of each.
-template <class F>
-static void launch_slabs(int64_t total, F&& launch) {
-    constexpr int64_t kSlab = int64_t(1) << 30;
-    for (int64_t b0 = 0; b0 < total; b0 += kSlab)
-        launch(b0, (unsigned)(total - b0 < kSlab ? total - b0 : kSlab));
-}
 
 // ---------------------------------------------------------------- adjoint --
 // img[p] = sum_j conj(e_jp) y_j, e = exp(s 2 pi i phi).  With e = c + i s S:

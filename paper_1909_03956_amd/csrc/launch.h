@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
+
 #include "common.h"
 
 namespace swv {
@@ -96,6 +98,45 @@ hipError_t launch_adjoint(hipStream_t s, int prec, int ppl, int block, int64_t c
                           int64_t n_vis, const double* u, const double* v, const double* w,
                           const void* y, int64_t n_pix, const double* l, const double* m,
                           const double* nm1, int sign, void* partial, void* out);
+
+// Dirty images on a regular grid by axis phasors (k_grid_image.hip): quads of
+// pixels (+-l, +-m), l = (kx0 + i) cell for i < Kx, m alike.
+struct GridGeom {
+    int kx0, Kx, ky0, Ky;
+    double cell;
+    __host__ __device__ double r2(int i, int k) const {
+        const double l = (double)(kx0 + i) * cell, m = (double)(ky0 + k) * cell;
+        return l * l + m * m;
+    }
+    __host__ __device__ bool on_disk(int i, int k) const { return r2(i, k) < 1.0; }
+    __host__ __device__ double nm1(int i, int k) const {
+        const double t = r2(i, k);
+        return t < 1.0 ? -t / (1.0 + sqrt(1.0 - t)) : 0.0;
+    }
+};
+// How waves cover the quads: region 0 with lanes along x (along y if swapped),
+// region 1, the rest of the lane axis, with the axes exchanged.
+struct GridPlan {
+    int lane0[2] = {0, 0}, lane_n[2] = {0, 0}, step0[2] = {0, 0}, step_n[2] = {0, 0};
+    int64_t jobs[2] = {0, 0};
+    int64_t tiles = 0;   // workgroups per chunk of rows
+    bool swapped = false;
+};
+// Geometry and cover of an image; whether this form takes fewer instructions
+// than the general adjoint on the image's pixels.
+bool grid_plan(int nx, int ny, int cx, int cy, double cell, GridGeom* g, GridPlan* p);
+size_t grid_row_bytes(const GridGeom& g);
+size_t grid_slab_bytes(const GridGeom& g, int64_t rows);
+size_t grid_partial_bytes(const GridGeom& g, int64_t n_chunks);
+int grid_blocks_per_cu();
+// Adds `rows` rows in chunks of `chunk` to the partial sums (resume) or starts
+// them.  y null: unit visibilities.
+hipError_t launch_grid_slab(hipStream_t s, const GridGeom& g, const GridPlan& p, int64_t rows,
+                            int64_t chunk, const double* u, const double* v, const double* w,
+                            const void* y, int sign, bool resume, void* slab, double* partial);
+hipError_t launch_grid_finish(hipStream_t s, const GridGeom& g, const double* partial,
+                              int64_t n_chunks, int nx, int ny, int cx, int cy, int64_t n_vis,
+                              double* img);
 
 // Resident blocks per compute unit of the adjoint and gradient kernels.
 int adjoint_blocks_per_cu(int prec, int ppl, int block);

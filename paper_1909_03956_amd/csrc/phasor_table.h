@@ -26,6 +26,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "device_math.h"
 #include "launch.h"
 #include "sincos_table.h"
 
@@ -74,6 +75,50 @@ __device__ __forceinline__ Cell find_cell(CellPtr T, double phase, double& d) {
     d = r - (t - kTabMagic);
     unsigned off;
     // 16-bit shift: (low word mod 4096) * 16, upper half zero
+    asm("v_lshlrev_b16_e32 %0, 4, %1" : "=v"(off) : "v"((unsigned)__double_as_longlong(t)));
+    return *(CellPtr)((const __attribute__((address_space(3))) char*)T + off);
+}
+
+// The cell polynomials' coefficients and the magic number as vector registers,
+// for kernels whose records do not carry them: an FP64 FMA reads one scalar
+// operand only, and the compiler would copy one of two constants for every use.
+struct CellCoefs {
+    double c0, c1, s0, s1, magic;
+};
+__device__ __forceinline__ double vector_const(double x) {
+    double v = x;
+    asm("" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ CellCoefs cell_coefs() {
+    return CellCoefs{vector_const(kCellC[0]), vector_const(kCellC[1]), vector_const(kCellS[0]),
+                     vector_const(kCellS[1]), vector_const(kTabMagic)};
+}
+
+// a b + c with a a scalar register (wave-uniform).
+__device__ __forceinline__ double fma_s(double a, double b, double c) {
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "s"(a), "v"(b), "v"(c));
+    return d;
+}
+
+// The same of the phase a b, which is never rounded at its own magnitude: one
+// rounding to the cell, one of the rest.  a is wave-uniform.
+template <bool WIDE>
+__device__ __forceinline__ Cell find_cell_product(CellPtr T, double a, double b, double magic,
+                                                  double& d) {
+    double t;
+    if constexpr (WIDE) {
+        const double p = a * b;
+        const double r = (p - rint(p)) + fma(a, b, -p);   // may exceed half a turn
+        const double r1 = r - rint(r);
+        t = r1 + magic;
+        d = r1 - (t - magic);
+    } else {
+        t = fma_s(a, b, magic);
+        d = fma(a, b, -(t - magic));
+    }
+    unsigned off;
     asm("v_lshlrev_b16_e32 %0, 4, %1" : "=v"(off) : "v"((unsigned)__double_as_longlong(t)));
     return *(CellPtr)((const __attribute__((address_space(3))) char*)T + off);
 }
