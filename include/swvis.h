@@ -298,7 +298,7 @@ int swv_adjoint(swv_ctx ctx, int64_t n_vis, const double* u, const double* v, co
  * allocates nothing (no hipMalloc, hipFree or allocating library routine).
  * SWV_ENOMEM, before any work is enqueued, if the partial sums,
  * 16 * n_pix * (row chunks of swv_adjoint) bytes, exceed 32 MiB (e.g. about
- * 2,000,000 pixel-chunks: 955 pixels over 8.36M rows need 15.6 MB).  All
+ * 2,000,000 pixel-chunks: 955 pixels over 8.36M rows need 31.3 MB).  All
  * calls on one device share the array and every call overwrites the part it
  * uses before reading it: calls that overlap on one device (other streams,
  * other contexts, other threads) race and must be ordered by the caller. */

@@ -240,8 +240,13 @@ AdjointShape adjoint_shape(swv_ctx ctx, int64_t n_vis, int64_t n_pix, int prec) 
     const int sc = size_class(n_vis);
     sh.ppl = ctx->per_lane[kFamAdjoint][sc];
     sh.block = ctx->block[kFamAdjoint][sc];
-    const int64_t tiles = (n_pix + (int64_t)sh.ppl * sh.block - 1) / ((int64_t)sh.ppl * sh.block);
-    sh.chunk = choose_chunk(n_vis, tiles, ctx->n_cu, adjoint_blocks_per_cu(prec, sh.ppl, sh.block));
+    if (prec == SWV_FP64) {
+        sh.chunk = adjoint_cell_chunk(n_vis, n_pix, sh.ppl, ctx->n_cu);
+    } else {
+        const int64_t tile = (int64_t)sh.ppl * sh.block;
+        sh.chunk = choose_chunk(n_vis, (n_pix + tile - 1) / tile, ctx->n_cu,
+                                adjoint_f32c_blocks_per_cu(sh.ppl, sh.block));
+    }
     sh.n_chunks = n_vis > 0 ? (n_vis + sh.chunk - 1) / sh.chunk : 0;
     return sh;
 }

@@ -547,13 +547,15 @@ int swv_autotune(swv_ctx ctx, const char* cache_path, int flags) {
                                             -1, out,
                                             ctx->d_status);
                         } else if (fam == kFamAdjoint) {
+                            // in the FP32-compensated form: `block` is its alone
                             const int64_t tiles = (n_pix + (int64_t)pl * bl - 1) / ((int64_t)pl * bl);
-                            const int64_t chunk = choose_chunk(rows, tiles, ctx->n_cu, adjoint_blocks_per_cu(SWV_FP64, pl, bl));
+                            const int64_t chunk = choose_chunk(rows, tiles, ctx->n_cu,
+                                                               adjoint_f32c_blocks_per_cu(pl, bl));
                             const int64_t nch = (rows + chunk - 1) / chunk;
                             rc = ensure(ctx, ctx->partial, 16 * (size_t)n_pix * nch);
                             if (rc) { result = rc; break; }
                             part = (double*)ctx->partial.p;
-                            e = launch_adjoint(s, SWV_FP64, pl, bl, chunk, rows, u, v, w, y, n_pix,
+                            e = launch_adjoint(s, SWV_F32C, pl, bl, chunk, rows, u, v, w, y, n_pix,
                                                l, m, nm, -1, part, out);
                         } else {
                             int gblock = 128;

@@ -97,9 +97,8 @@ __device__ __forceinline__ void add_row(CellPtr T, const CellCoefs& K, double w,
     for (int i = 0; i < G; ++i) e[i] = find_cell_product<WIDE>(T, w, nm1[i], K.magic, d[i]);
 #pragma unroll
     for (int i = 0; i < G; ++i) {
-        const double q = d[i] * d[i];
-        const double cr = fma(q, fma_v(q, K.c1, K.c0), 1.0);
-        const double sr = d[i] * fma_v(q, K.s1, K.s0);
+        double cr, sr;
+        cell_rest(K, d[i], cr, sr);
         double tr = cr, ti = sr;
         if constexpr (!UNIT) {
             tr = fma(cr, yr, -(sr * yi));

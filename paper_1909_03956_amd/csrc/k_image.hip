@@ -10,24 +10,168 @@
 // second kernel adds the chunks in index order -- deterministic and free of
 // atomics.
 // Block order: chunking.h.
+#include <type_traits>
+
 #include "chunking.h"
 #include "device_math.h"
 #include "launch.h"
+#include "phasor_table.h"
 
 namespace swv {
 
 // ---------------------------------------------------------------- adjoint --
-// img[p] = sum_j conj(e_jp) y_j, e = exp(s 2 pi i phi).  With e = c + i s S:
-// conj(e) y = (c yr + s S yi) + i (c yi - s S yr), S = 4 q.
-// One lane's G pixels q0, q0 + 64, ... over the rows of chunk chunk_id.
-template <int G, int PREC>
-__device__ __forceinline__ void adjoint_lane(
+// img[p] = sum_j conj(e_jp) y_j, e = exp(s 2 pi i phi).
+//
+// FP64: one wave per (chunk of rows, column of up to four groups of 64 pixels).
+// With the pixels' directions times -s, conj(e) = exp(2 pi i phi) = node x rest,
+// and y is turned by the rest, then by the node straight into the sums: 20 FP64
+// instructions per row and pixel (phase 3, cell 4, rest 5, 4 + 4), against 29
+// with the polynomial phasor; bound by their issue.  8,355,840 rows x 955
+// pixels: 7.48 -> 5.52 ms (77 % of the issue rate at 2.4 GHz).
+//
+// Jobs are numbered chunk-major and dealt to the waves of 512-thread workgroups
+// (two share a CU, a 64 KB table each) in runs, one run of workgroups per XCD
+// (workgroup ids go to the XCDs round-robin), so a chunk's rows come into one
+// L2 and no workgroup is partly idle but the last.
+constexpr int kAdjWaves = kTabBlock / 64;
+// rows per step: 1, 2 and 4 take 0.708, 0.485 and 0.394 ms on 5,000,000 rows x 40
+// pixels, where the rows' loads show, and 5.57, 5.53 and 5.52 ms on 955 pixels
+constexpr int kAdjRows = 4;
+constexpr int64_t kAdjMinRows = 32;
+
+// Group range of column c: the groups spread evenly over the columns.
+__device__ __forceinline__ int64_t column_group(int64_t c, int64_t cols, int64_t groups) {
+    return c * groups / cols;
+}
+
+template <int G, bool WIDE>
+__device__ __forceinline__ void adjoint_rows(
+    CellPtr T, const double* u, const double* v, const double* w, const double2* y, int nrow,
+    const double (&L)[G], const double (&M)[G], const double (&N)[G], double (&ar)[G],
+    double (&ai)[G]) {
+    const auto* U = uniform_ptr(u);
+    const auto* V = uniform_ptr(v);
+    const auto* W = uniform_ptr(w);
+    const auto* Y = uniform_ptr(y);
+    const CellCoefs K = cell_coefs();
+    // R rows per step: their scalar loads go out together
+    const auto step = [&](auto rows, int j) {
+        constexpr int R = decltype(rows)::value;
+        double uj[R], vj[R], wj[R], yr[R], yi[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            uj[r] = U[j + r];
+            vj[r] = V[j + r];
+            wj[r] = W[j + r];
+            yr[r] = Y[j + r].x;
+            yi[r] = Y[j + r].y;
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            Cell e[G];
+            double d[G];
+#pragma unroll
+            for (int i = 0; i < G; ++i)
+                e[i] = find_cell<WIDE>(T, fma(uj[r], L[i], fma(vj[r], M[i], wj[r] * N[i])), d[i],
+                                       K.magic);
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                double cr, sr;
+                cell_rest(K, d[i], cr, sr);
+                const double tr = fma(cr, yr[r], -(sr * yi[r]));
+                const double ti = fma(cr, yi[r], sr * yr[r]);
+                ar[i] = fma(e[i].x, tr, ar[i]);
+                ai[i] = fma(e[i].x, ti, ai[i]);
+                ar[i] = fma(-e[i].y, ti, ar[i]);
+                ai[i] = fma(e[i].y, tr, ai[i]);
+            }
+        }
+    };
+    int j = 0;
+#pragma unroll 1
+    for (; j + kAdjRows <= nrow; j += kAdjRows) step(std::integral_constant<int, kAdjRows>(), j);
+#pragma unroll 1
+    for (; j < nrow; ++j) step(std::integral_constant<int, 1>(), j);
+}
+
+template <int G>
+__device__ __forceinline__ void adjoint_wave(
+    CellPtr T, const double* __restrict__ u, const double* __restrict__ v,
+    const double* __restrict__ w, const double2* __restrict__ y, int nrow, bool wide,
+    const double* __restrict__ pl, const double* __restrict__ pm, const double* __restrict__ pn,
+    int64_t q0, int64_t n_pix, double sgn, double2* __restrict__ partial) {
+    double L[G], M[G], N[G], ar[G], ai[G];
+    bool far = false;
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+        int64_t p = q0 + (int64_t)i * 64;
+        p = p < n_pix ? p : n_pix - 1;
+        L[i] = -sgn * pl[p];
+        M[i] = -sgn * pm[p];
+        N[i] = -sgn * pn[p];
+        far = far || !(fabs(L[i]) <= 2.0 && fabs(M[i]) <= 2.0 && fabs(N[i]) <= 2.0);
+        ar[i] = ai[i] = 0.0;
+    }
+    if (__builtin_expect(wide || __any(far), 0))
+        adjoint_rows<G, true>(T, u, v, w, y, nrow, L, M, N, ar, ai);
+    else
+        adjoint_rows<G, false>(T, u, v, w, y, nrow, L, M, N, ar, ai);
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+        const int64_t p = q0 + (int64_t)i * 64;
+        if (p < n_pix) partial[p] = make_double2(ar[i], ai[i]);
+    }
+}
+
+__global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_adjoint_cell(
+    const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
+    const double2* __restrict__ y, int64_t n_vis, int64_t chunk, const double* __restrict__ pl,
+    const double* __restrict__ pm, const double* __restrict__ pn, int64_t n_pix, double sgn,
+    int64_t groups, int64_t cols, int64_t jobs, int64_t run, double2* __restrict__ partial) {
+    __shared__ Cell T[kTabCells];
+    const int64_t bid = blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t job = ((bid & 7) * run + (bid >> 3)) * kAdjWaves + wave;
+    const bool active = job < jobs;
+    const int64_t chunk_id = active ? job / cols : 0;
+    const int64_t j0 = chunk_id * chunk;
+    const int nrow = __builtin_amdgcn_readfirstlane((int)(j0 + chunk < n_vis ? chunk : n_vis - j0));
+    // rows whose phases need the WIDE form (or are not finite) put the whole
+    // chunk through it
+    bool big = false;
+    if (active)
+        for (int j = lane; j < nrow; j += 64)
+            big = big || !(fabs(u[j0 + j]) + fabs(v[j0 + j]) + fabs(w[j0 + j]) < kTabMaxBaseline);
+    const bool wide = __any(big);
+    fill_cells(T);
+    if (!active) return;
+    const int64_t c = job - chunk_id * cols;
+    const int64_t g0 = column_group(c, cols, groups);
+    const int G = __builtin_amdgcn_readfirstlane((int)(column_group(c + 1, cols, groups) - g0));
+    const int64_t q0 = g0 * 64 + lane;
+    double2* part = partial + chunk_id * n_pix;
+    const CellPtr TP = (CellPtr)T;
+#define SWV_WAVE(N)                                                                               \
+    adjoint_wave<N>(TP, u + j0, v + j0, w + j0, y + j0, nrow, wide, pl, pm, pn, q0, n_pix, sgn, part)
+    switch (G) {
+        case 1: SWV_WAVE(1); break;
+        case 2: SWV_WAVE(2); break;
+        case 3: SWV_WAVE(3); break;
+        default: SWV_WAVE(4); break;
+    }
+#undef SWV_WAVE
+}
+
+// FP32-compensated: FP64 phase reduced exactly; FP32 phasor, products and Kahan
+// sums.  One lane's G pixels q0, q0 + 64, ... over the rows of chunk chunk_id.
+// With e = c + i s S: conj(e) y = (c yr + s S yi) + i (c yi - s S yr).
+template <int G>
+__device__ __forceinline__ void adjoint_lane_f32c(
     const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
     const double2* __restrict__ y, int64_t n_vis, int64_t chunk, const double* __restrict__ pl,
     const double* __restrict__ pm, const double* __restrict__ pn, int64_t n_pix, double sgn,
     int64_t chunk_id, int64_t q0, double2* __restrict__ partial) {
     double L[G], M[G], N[G];
-    double ar[G], ai[G];
     float sr[G], cr[G], si[G], ci[G];
 #pragma unroll
     for (int i = 0; i < G; ++i) {
@@ -36,7 +180,6 @@ __device__ __forceinline__ void adjoint_lane(
         L[i] = pl[p];
         M[i] = pm[p];
         N[i] = pn[p];
-        ar[i] = ai[i] = 0.0;
         sr[i] = cr[i] = si[i] = ci[i] = 0.0f;
     }
     const int64_t j0 = chunk_id * chunk;
@@ -47,78 +190,55 @@ __device__ __forceinline__ void adjoint_lane(
     const auto* V = uniform_ptr(v + j0);
     const auto* W = uniform_ptr(w + j0);
     const auto* Y = uniform_ptr(y + j0);
-    if constexpr (PREC == SWV_FP64) {
-#pragma unroll 4
-        for (int j = 0; j < nrow; ++j) {
-            const double uj = U[j], vj = V[j], wj = W[j];
-            const double yr = Y[j].x, yi = Y[j].y;
-            const double y4r = 4.0 * sgn * yr, y4i = 4.0 * sgn * yi;
-#pragma unroll
-            for (int i = 0; i < G; ++i) {
-                double c, q;
-                cis2pi_q(reduced_phase(uj, vj, wj, L[i], M[i], N[i]), c, q);
-                ar[i] = fma(c, yr, ar[i]);
-                ar[i] = fma(q, y4i, ar[i]);
-                ai[i] = fma(c, yi, ai[i]);
-                ai[i] = fma(-q, y4r, ai[i]);
-            }
-        }
-    } else {
-        // rows in pairs: the pair's four products and the running compensation
-        // meet in one chain of FMAs, then one Kahan step, so a row costs half a
-        // step (the chain's roundings stay within a few 2^-24 of the pair's
-        // terms); an odd last row enters alone
-        // sgn is +-1, so fsg * (float)y is (float)(sgn * y) bit for bit
-        const float fsg = (float)sgn;
-        const auto cis = [&](double uj, double vj, double wj, int i, float& c, float& s) {
-            cis2pi_f32((float)fract_phase(uj, vj, wj, L[i], M[i], N[i]), c, s);
-        };
-        const int npair = nrow & ~1;
+    // rows in pairs: the pair's four products and the running compensation
+    // meet in one chain of FMAs, then one Kahan step, so a row costs half a
+    // step (the chain's roundings stay within a few 2^-24 of the pair's
+    // terms); an odd last row enters alone
+    // sgn is +-1, so fsg * (float)y is (float)(sgn * y) bit for bit
+    const float fsg = (float)sgn;
+    const auto cis = [&](double uj, double vj, double wj, int i, float& c, float& s) {
+        cis2pi_f32((float)fract_phase(uj, vj, wj, L[i], M[i], N[i]), c, s);
+    };
+    const int npair = nrow & ~1;
 #pragma unroll 2
-        for (int j = 0; j < npair; j += 2) {
-            const double u0 = U[j], v0 = V[j], w0 = W[j], yr0 = Y[j].x, yi0 = Y[j].y;
-            const double u1 = U[j + 1], v1 = V[j + 1], w1 = W[j + 1];
-            const double yr1 = Y[j + 1].x, yi1 = Y[j + 1].y;
-            const float fyr0 = (float)yr0, fyi0 = (float)yi0;
-            const float fsyr0 = fsg * fyr0, fsyi0 = fsg * fyi0;
-            const float fyr1 = (float)yr1, fyi1 = (float)yi1;
-            const float fsyr1 = fsg * fyr1, fsyi1 = fsg * fyi1;
+    for (int j = 0; j < npair; j += 2) {
+        const double u0 = U[j], v0 = V[j], w0 = W[j], yr0 = Y[j].x, yi0 = Y[j].y;
+        const double u1 = U[j + 1], v1 = V[j + 1], w1 = W[j + 1];
+        const double yr1 = Y[j + 1].x, yi1 = Y[j + 1].y;
+        const float fyr0 = (float)yr0, fyi0 = (float)yi0;
+        const float fsyr0 = fsg * fyr0, fsyi0 = fsg * fyi0;
+        const float fyr1 = (float)yr1, fyi1 = (float)yi1;
+        const float fsyr1 = fsg * fyr1, fsyi1 = fsg * fyi1;
 #pragma unroll
-            for (int i = 0; i < G; ++i) {
-                float c0, s0, c1, s1;
-                cis(u0, v0, w0, i, c0, s0);
-                cis(u1, v1, w1, i, c1, s1);
-                kahan_step(fmaf(c0, fyr0, fmaf(s0, fsyi0, fmaf(c1, fyr1, fmaf(s1, fsyi1, -cr[i])))),
-                           sr[i], cr[i]);
-                kahan_step(fmaf(c0, fyi0, fmaf(-s0, fsyr0, fmaf(c1, fyi1, fmaf(-s1, fsyr1, -ci[i])))),
-                           si[i], ci[i]);
-            }
+        for (int i = 0; i < G; ++i) {
+            float c0, s0, c1, s1;
+            cis(u0, v0, w0, i, c0, s0);
+            cis(u1, v1, w1, i, c1, s1);
+            kahan_step(fmaf(c0, fyr0, fmaf(s0, fsyi0, fmaf(c1, fyr1, fmaf(s1, fsyi1, -cr[i])))),
+                       sr[i], cr[i]);
+            kahan_step(fmaf(c0, fyi0, fmaf(-s0, fsyr0, fmaf(c1, fyi1, fmaf(-s1, fsyr1, -ci[i])))),
+                       si[i], ci[i]);
         }
-        if (npair < nrow) {
-            const int j = npair;
-            const double yr = Y[j].x, yi = Y[j].y;
-            const float fyr = (float)yr, fyi = (float)yi;
-            const float fsyr = fsg * fyr, fsyi = fsg * fyi;
+    }
+    if (npair < nrow) {
+        const int j = npair;
+        const double yr = Y[j].x, yi = Y[j].y;
+        const float fyr = (float)yr, fyi = (float)yi;
+        const float fsyr = fsg * fyr, fsyi = fsg * fyi;
 #pragma unroll
-            for (int i = 0; i < G; ++i) {
-                float c, s;
-                cis(U[j], V[j], W[j], i, c, s);
-                kahan_step(fmaf(c, fyr, fmaf(s, fsyi, -cr[i])), sr[i], cr[i]);
-                kahan_step(fmaf(c, fyi, fmaf(-s, fsyr, -ci[i])), si[i], ci[i]);
-            }
+        for (int i = 0; i < G; ++i) {
+            float c, s;
+            cis(U[j], V[j], W[j], i, c, s);
+            kahan_step(fmaf(c, fyr, fmaf(s, fsyi, -cr[i])), sr[i], cr[i]);
+            kahan_step(fmaf(c, fyi, fmaf(-s, fsyr, -ci[i])), si[i], ci[i]);
         }
     }
 #pragma unroll
     for (int i = 0; i < G; ++i) {
         const int64_t p = q0 + (int64_t)i * 64;
-        if (p < n_pix) {
-            double2 o;
-            if constexpr (PREC == SWV_FP64)
-                o = make_double2(ar[i], ai[i]);
-            else
-                o = make_double2((double)sr[i] - (double)cr[i], (double)si[i] - (double)ci[i]);
-            partial[chunk_id * n_pix + p] = o;
-        }
+        if (p < n_pix)
+            partial[chunk_id * n_pix + p] =
+                make_double2((double)sr[i] - (double)cr[i], (double)si[i] - (double)ci[i]);
     }
 }
 
@@ -127,8 +247,8 @@ __device__ __forceinline__ void adjoint_lane(
 // in whole groups at the end of the last tile, which are not computed (the
 // 955-pixel image of the major cycle in one 1,024-pixel tile: 64 of its 69
 // idle slots).  A pixel's sum is the same whichever lane takes it.
-template <int PPL, int BLOCK, int PREC>
-__global__ __launch_bounds__(BLOCK) void k_adjoint(
+template <int PPL, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_adjoint_f32c(
     const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
     const double2* __restrict__ y, int64_t n_vis, int64_t chunk, const double* __restrict__ pl,
     const double* __restrict__ pm, const double* __restrict__ pn, int64_t n_pix, double sgn,
@@ -144,18 +264,18 @@ __global__ __launch_bounds__(BLOCK) void k_adjoint(
         left <= 0 ? 0 : (left >= 64 * PPL ? PPL : (int)((left + 63) / 64)));
     const int64_t q0 = g0 + lane;
     if (groups >= PPL) {
-        adjoint_lane<PPL, PREC>(u, v, w, y, n_vis, chunk, pl, pm, pn, n_pix, sgn, chunk_id, q0,
+        adjoint_lane_f32c<PPL>(u, v, w, y, n_vis, chunk, pl, pm, pn, n_pix, sgn, chunk_id, q0,
                                 partial);
     } else if constexpr (PPL >= 2) {
         if (groups == 1)
-            adjoint_lane<1, PREC>(u, v, w, y, n_vis, chunk, pl, pm, pn, n_pix, sgn, chunk_id, q0,
+            adjoint_lane_f32c<1>(u, v, w, y, n_vis, chunk, pl, pm, pn, n_pix, sgn, chunk_id, q0,
                                   partial);
         if constexpr (PPL >= 4) {
             if (groups == 2)
-                adjoint_lane<2, PREC>(u, v, w, y, n_vis, chunk, pl, pm, pn, n_pix, sgn, chunk_id,
+                adjoint_lane_f32c<2>(u, v, w, y, n_vis, chunk, pl, pm, pn, n_pix, sgn, chunk_id,
                                       q0, partial);
             if (groups == 3)
-                adjoint_lane<3, PREC>(u, v, w, y, n_vis, chunk, pl, pm, pn, n_pix, sgn, chunk_id,
+                adjoint_lane_f32c<3>(u, v, w, y, n_vis, chunk, pl, pm, pn, n_pix, sgn, chunk_id,
                                       q0, partial);
         }
     }
@@ -176,7 +296,21 @@ __global__ __launch_bounds__(kSumCols * kSumQ) void k_sum_chunks_c128(
     const int64_t p = (int64_t)blockIdx.x * kSumCols + tx;
     double re = 0.0, im = 0.0;
     if (p < n) {
-        for (int64_t c = q; c < n_chunks; c += kSumQ) {
+        // eight loads in flight: the chain of 16 threads' chunks is what
+        // bounds this kernel
+        constexpr int kAhead = 8;
+        int64_t c = q;
+        for (; c + (kAhead - 1) * kSumQ < n_chunks; c += kAhead * kSumQ) {
+            double2 x[kAhead];
+#pragma unroll
+            for (int t = 0; t < kAhead; ++t) x[t] = partial[(c + t * kSumQ) * n + p];
+#pragma unroll
+            for (int t = 0; t < kAhead; ++t) {
+                re += x[t].x;
+                im += x[t].y;
+            }
+        }
+        for (; c < n_chunks; c += kSumQ) {
             const double2 x = partial[c * n + p];
             re += x.x;
             im += x.y;
@@ -195,31 +329,17 @@ __global__ __launch_bounds__(kSumCols * kSumQ) void k_sum_chunks_c128(
     if (q == 0 && p < n) out[p] = make_double2(red_r[0][tx], red_i[0][tx]);
 }
 
-template <int PPL, int BLOCK, int PREC>
-static void run_adjoint(hipStream_t s, int64_t tiles, int64_t chunk, int64_t n_vis,
-                        const double* u, const double* v, const double* w, const void* y,
-                        int64_t n_pix, const double* l, const double* m, const double* nm1,
-                        int sign, void* partial) {
+template <int PPL, int BLOCK>
+static void run_adjoint_f32c(hipStream_t s, int64_t tiles, int64_t chunk, int64_t n_vis,
+                             const double* u, const double* v, const double* w, const void* y,
+                             int64_t n_pix, const double* l, const double* m, const double* nm1,
+                             int sign, void* partial) {
     const int64_t n_chunks = (n_vis + chunk - 1) / chunk;
     launch_slabs(xcd_padded(n_chunks) * tiles, [&](int64_t b0, unsigned nb) {
-        k_adjoint<PPL, BLOCK, PREC><<<dim3(nb), dim3(BLOCK), 0, s>>>(
+        k_adjoint_f32c<PPL, BLOCK><<<dim3(nb), dim3(BLOCK), 0, s>>>(
             u, v, w, (const double2*)y, n_vis, chunk, l, m, nm1, n_pix, (double)sign, n_chunks,
             tiles, b0, (double2*)partial);
     });
-}
-
-template <int PPL, int PREC>
-static hipError_t run_adjoint_b(hipStream_t s, int block, int64_t grid, int64_t chunk,
-                                int64_t n_vis, const double* u, const double* v, const double* w,
-                                const void* y, int64_t n_pix, const double* l, const double* m,
-                                const double* nm1, int sign, void* partial) {
-    switch (block) {
-        case 64: run_adjoint<PPL, 64, PREC>(s, grid, chunk, n_vis, u, v, w, y, n_pix, l, m, nm1, sign, partial); break;
-        case 128: run_adjoint<PPL, 128, PREC>(s, grid, chunk, n_vis, u, v, w, y, n_pix, l, m, nm1, sign, partial); break;
-        case 256: run_adjoint<PPL, 256, PREC>(s, grid, chunk, n_vis, u, v, w, y, n_pix, l, m, nm1, sign, partial); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
 }
 
 // Blocks of one kernel shape that fit on a compute unit at once (registers,
@@ -234,16 +354,15 @@ static int resident_blocks(K kernel, int block) {
     return nb > 0 ? nb : 1;
 }
 
-template <int PPL, int BLOCK, int PREC>
-static int adjoint_occ() {
-    static const int v = resident_blocks(k_adjoint<PPL, BLOCK, PREC>, BLOCK);
+template <int PPL, int BLOCK>
+static int adjoint_f32c_occ() {
+    static const int v = resident_blocks(k_adjoint_f32c<PPL, BLOCK>, BLOCK);
     return v;
 }
 
-int adjoint_blocks_per_cu(int prec, int ppl, int block) {
-#define SWV_OCC_A(P, B)                                                                   \
-    if (ppl == P && block == B)                                                           \
-        return prec == SWV_FP64 ? adjoint_occ<P, B, SWV_FP64>() : adjoint_occ<P, B, SWV_F32C>();
+int adjoint_f32c_blocks_per_cu(int ppl, int block) {
+#define SWV_OCC_A(P, B) \
+    if (ppl == P && block == B) return adjoint_f32c_occ<P, B>();
     SWV_OCC_A(1, 64) SWV_OCC_A(1, 128) SWV_OCC_A(1, 256)
     SWV_OCC_A(2, 64) SWV_OCC_A(2, 128) SWV_OCC_A(2, 256)
     SWV_OCC_A(4, 64) SWV_OCC_A(4, 128) SWV_OCC_A(4, 256)
@@ -251,31 +370,67 @@ int adjoint_blocks_per_cu(int prec, int ppl, int block) {
     return 1;
 }
 
+// Rows per chunk of the FP64 adjoint.  Workgroups of kAdjWaves jobs run in
+// rounds of two per CU; four rounds rather than one, since the dies' clocks
+// differ, but fewer while the partial sums (one set per chunk) exceed 32 MiB,
+// and whole rounds: the chunk count is the most that fits r of them.  At least
+// kAdjMinRows rows, so that filling the table stays small beside them, and at
+// least 8 chunks from 512 rows on.
+int64_t adjoint_cell_chunk(int64_t n_vis, int64_t n_pix, int ppl, int n_cu) {
+    if (n_vis <= 0) return 1;
+    const int64_t groups = (n_pix + 63) / 64, cols = (groups + ppl - 1) / ppl;
+    const int64_t round = (int64_t)n_cu * 2 * kAdjWaves;
+    const int64_t cap = (int64_t(32) << 20) / (16 * (n_pix > 0 ? n_pix : 1));
+    int64_t chunks = 0;
+    for (int64_t r = 4; r >= 1; --r) {
+        chunks = r * round / (cols > 0 ? cols : 1);
+        if (chunks <= cap) break;
+    }
+    if (chunks > cap) chunks = cap;
+    if (chunks < 8) chunks = 8;
+    const int64_t least = n_vis < 512 ? 64 : kAdjMinRows;
+    int64_t chunk = (n_vis + chunks - 1) / chunks;
+    if (chunk < least) chunk = least;
+    return chunk < (int64_t(1) << 30) ? chunk : int64_t(1) << 30;   // rows per chunk fit an int
+}
+
+static hipError_t run_adjoint_cell(hipStream_t s, int ppl, int64_t chunk, int64_t n_vis,
+                                   const double* u, const double* v, const double* w,
+                                   const void* y, int64_t n_pix, const double* l, const double* m,
+                                   const double* nm1, int sign, void* partial) {
+    const int64_t groups = (n_pix + 63) / 64, cols = (groups + ppl - 1) / ppl;
+    const int64_t jobs = (n_vis + chunk - 1) / chunk * cols;
+    const int64_t run = ((jobs + kAdjWaves - 1) / kAdjWaves + 7) / 8;   // workgroups per XCD
+    if (run > (int64_t(1) << 27)) return hipErrorInvalidConfiguration;
+    k_adjoint_cell<<<dim3((unsigned)(8 * run)), dim3(kTabBlock), 0, s>>>(
+        u, v, w, (const double2*)y, n_vis, chunk, l, m, nm1, n_pix, (double)sign, groups, cols,
+        jobs, run, (double2*)partial);
+    return hipGetLastError();
+}
+
 hipError_t launch_adjoint(hipStream_t s, int prec, int ppl, int block, int64_t chunk,
                           int64_t n_vis, const double* u, const double* v, const double* w,
                           const void* y, int64_t n_pix, const double* l, const double* m,
                           const double* nm1, int sign, void* partial, void* out) {
     if (n_pix <= 0) return hipSuccess;
+    if (ppl != 1 && ppl != 2 && ppl != 4) return hipErrorInvalidValue;
     const int64_t n_chunks = n_vis > 0 ? (n_vis + chunk - 1) / chunk : 0;
-    if (n_chunks > 0) {
+    if (n_chunks > 0 && prec == SWV_FP64) {
+        const hipError_t e = run_adjoint_cell(s, ppl, chunk, n_vis, u, v, w, y, n_pix, l, m, nm1,
+                                              sign, partial);
+        if (e != hipSuccess) return e;
+    } else if (n_chunks > 0) {
         const int64_t per_block = (int64_t)block * ppl;
-        const int64_t grid = (n_pix + per_block - 1) / per_block;   // pixel tiles
-        hipError_t e;
-        if (prec == SWV_FP64) {
-            switch (ppl) {
-                case 1: e = run_adjoint_b<1, SWV_FP64>(s, block, grid, chunk, n_vis, u, v, w, y, n_pix, l, m, nm1, sign, partial); break;
-                case 2: e = run_adjoint_b<2, SWV_FP64>(s, block, grid, chunk, n_vis, u, v, w, y, n_pix, l, m, nm1, sign, partial); break;
-                case 4: e = run_adjoint_b<4, SWV_FP64>(s, block, grid, chunk, n_vis, u, v, w, y, n_pix, l, m, nm1, sign, partial); break;
-                default: return hipErrorInvalidValue;
-            }
-        } else {
-            switch (ppl) {
-                case 1: e = run_adjoint_b<1, SWV_F32C>(s, block, grid, chunk, n_vis, u, v, w, y, n_pix, l, m, nm1, sign, partial); break;
-                case 2: e = run_adjoint_b<2, SWV_F32C>(s, block, grid, chunk, n_vis, u, v, w, y, n_pix, l, m, nm1, sign, partial); break;
-                case 4: e = run_adjoint_b<4, SWV_F32C>(s, block, grid, chunk, n_vis, u, v, w, y, n_pix, l, m, nm1, sign, partial); break;
-                default: return hipErrorInvalidValue;
-            }
-        }
+        const int64_t tiles = (n_pix + per_block - 1) / per_block;
+#define SWV_RUN_A(P, B)           \
+    if (ppl == P && block == B)   \
+        run_adjoint_f32c<P, B>(s, tiles, chunk, n_vis, u, v, w, y, n_pix, l, m, nm1, sign, partial);
+        SWV_RUN_A(1, 64) SWV_RUN_A(1, 128) SWV_RUN_A(1, 256)
+        SWV_RUN_A(2, 64) SWV_RUN_A(2, 128) SWV_RUN_A(2, 256)
+        SWV_RUN_A(4, 64) SWV_RUN_A(4, 128) SWV_RUN_A(4, 256)
+#undef SWV_RUN_A
+        if (block != 64 && block != 128 && block != 256) return hipErrorInvalidValue;
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     k_sum_chunks_c128<<<dim3((unsigned)((n_pix + kSumCols - 1) / kSumCols)),

@@ -94,6 +94,9 @@ hipError_t launch_tree(hipStream_t s, int walker, int block, int prec, const Tre
                        int64_t n_vis, const double* u, const double* v, const double* w,
                        int sign, void* out, int* status);
 
+// ppl: FP64 the most 64-pixel groups per wave, F32C pixels per lane; block: F32C
+// threads per workgroup (the FP64 form's workgroups share a phasor table and
+// have a size of their own).
 hipError_t launch_adjoint(hipStream_t s, int prec, int ppl, int block, int64_t chunk,
                           int64_t n_vis, const double* u, const double* v, const double* w,
                           const void* y, int64_t n_pix, const double* l, const double* m,
@@ -138,8 +141,10 @@ hipError_t launch_grid_finish(hipStream_t s, const GridGeom& g, const double* pa
                               int64_t n_chunks, int nx, int ny, int cx, int cy, int64_t n_vis,
                               double* img);
 
-// Resident blocks per compute unit of the adjoint and gradient kernels.
-int adjoint_blocks_per_cu(int prec, int ppl, int block);
+// Rows per chunk of the FP64 adjoint.
+int64_t adjoint_cell_chunk(int64_t n_vis, int64_t n_pix, int ppl, int n_cu);
+// Resident blocks per compute unit of the F32C adjoint and gradient kernels.
+int adjoint_f32c_blocks_per_cu(int ppl, int block);
 // Gradient kernel block (128 .. 1024 threads, the smallest that holds every
 // component at cpl per lane, else 1024) and the component tiles it leaves.
 void grad_tiling(int cpl, int64_t n_comp, int* block, int64_t* tiles);

@@ -63,22 +63,6 @@ __device__ __forceinline__ void fill_cells(Cell* T) {
     __syncthreads();
 }
 
-// Cell of a phase in turns and the rest d (turns, |d| <= 1/8192).  The phase
-// minus the node is exact.  WIDE takes whole turns off first, exactly, which
-// leaves the same cell and the same d wherever both forms apply (a whole turn
-// is an even number of cells, so ties round alike); non-finite phases give
-// NaN and some cell of the table.
-template <bool WIDE>
-__device__ __forceinline__ Cell find_cell(CellPtr T, double phase, double& d) {
-    const double r = WIDE ? phase - rint(phase) : phase;
-    const double t = r + kTabMagic;
-    d = r - (t - kTabMagic);
-    unsigned off;
-    // 16-bit shift: (low word mod 4096) * 16, upper half zero
-    asm("v_lshlrev_b16_e32 %0, 4, %1" : "=v"(off) : "v"((unsigned)__double_as_longlong(t)));
-    return *(CellPtr)((const __attribute__((address_space(3))) char*)T + off);
-}
-
 // The cell polynomials' coefficients and the magic number as vector registers,
 // for kernels whose records do not carry them: an FP64 FMA reads one scalar
 // operand only, and the compiler would copy one of two constants for every use.
@@ -93,6 +77,30 @@ __device__ __forceinline__ double vector_const(double x) {
 __device__ __forceinline__ CellCoefs cell_coefs() {
     return CellCoefs{vector_const(kCellC[0]), vector_const(kCellC[1]), vector_const(kCellS[0]),
                      vector_const(kCellS[1]), vector_const(kTabMagic)};
+}
+
+// Cell of a phase in turns and the rest d (turns, |d| <= 1/8192).  The phase
+// minus the node is exact.  WIDE takes whole turns off first, exactly, which
+// leaves the same cell and the same d wherever both forms apply (a whole turn
+// is an even number of cells, so ties round alike); non-finite phases give
+// NaN and some cell of the table.
+template <bool WIDE>
+__device__ __forceinline__ Cell find_cell(CellPtr T, double phase, double& d,
+                                          double magic = kTabMagic) {
+    const double r = WIDE ? phase - rint(phase) : phase;
+    const double t = r + magic;
+    d = r - (t - magic);
+    unsigned off;
+    // 16-bit shift: (low word mod 4096) * 16, upper half zero
+    asm("v_lshlrev_b16_e32 %0, 4, %1" : "=v"(off) : "v"((unsigned)__double_as_longlong(t)));
+    return *(CellPtr)((const __attribute__((address_space(3))) char*)T + off);
+}
+
+// (cos, sin)(2 pi d) of the rest.
+__device__ __forceinline__ void cell_rest(const CellCoefs& K, double d, double& c, double& s) {
+    const double q = d * d;
+    c = fma(q, fma_v(q, K.c1, K.c0), 1.0);
+    s = d * fma_v(q, K.s1, K.s0);
 }
 
 // a b + c with a a scalar register (wave-uniform).
