@@ -1075,7 +1075,7 @@ def main():
     kernel_of = {"direct_fp64": ("k_direct.hip", "k_direct_f64"),
                  "adjoint": ("k_image.hip", "k_adjoint"), "grad": ("k_image.hip", "k_grad_partial")}
     for J in TREE_LEVELS:
-        kernel_of[f"tree_J{J}"] = ("k_tree.hip", f"k_tree_J{J}")
+        kernel_of[f"tree_J{J}"] = ("k_direct.hip", f"k_tree_J{J}")
     dom = max(flops, key=lambda s: med[s])
     achieved = flops[dom] / (med[dom] * 1e-3) / 1e12
     src, kname = kernel_of[dom]

@@ -167,27 +167,20 @@ int swv_tree_level(swv_tree tree, int j, int64_t* pix, int32_t* child_mask, doub
  * the tree predict the new model.  Waits for the devices holding copies. */
 int swv_tree_set_flux(swv_tree tree, const double* leaf_flux);
 
-/* Model visibilities by the wavelet route (section 3.3, Eqs. 14-17; the
- * per-visibility work of section 3.6.1): for every row, the plane wave
- * eta_{J,k} = exp(s 2 pi i B . (s_k - P)) at the leaf centres, then per
- * existing node eta_j = 1/4 sum_c eta_{j+1} and
- * sigma^m_j = sqrt(A_j)/4 sum_c s^m_c eta_{j+1} (Eqs. 9, 10 applied to the
- * plane wave), and
+/* Model visibilities by the wavelet route (section 3.3, Eqs. 14-17):
  *     vis_out = A_1 sum_k lambda_1 eta_1 + sum_{j<J} sum_k sum_m gamma^m sigma^m
- * (Eq. 17 with lambda_J a flux density; equal to the direct sum over the
- * pixel-snapped leaves, Eq. 16).  u, v, w [n_vis] DEVICE; vis_out DEVICE
- * complex128 (SWV_FP64) or complex64 (SWV_F32C: the leaf phase in FP64,
- * reduced exactly, then the FP32 hardware sine and cosine; the node
- * arithmetic stays FP64).  The tree is copied to the device on first use with
- * this context's device.
- * Two traversals compute the same operations in the same order (bitwise equal
- * results): one keeps a state set per level (J <= 16), the other one per open
- * node with two or more children (any J, up to 15 such nodes on one
- * root-to-leaf path, see swv_tree_stats_t.max_branching).  By default the
- * first serves J <= 10, and J <= 16 unless more than three in four internal
- * nodes have a single child; the tuning table can force either (swv_tune_set).
- * SWV_ENOTSUP if neither fits, or if the tree's record stream (32 bytes per
- * record) exceeds 4 GiB - 32. */
+ * (Eq. 17 with lambda_J a flux density), where eta_{J,k} =
+ * exp(s 2 pi i B . (s_k - P)) is the plane wave at the leaf centres and
+ * eta_j = 1/4 sum_c eta_{j+1}, sigma^m_j = sqrt(A_j)/4 sum_c s^m_c eta_{j+1}
+ * (Eqs. 9, 10 applied to the plane wave).  All of it is linear in the leaves'
+ * plane waves, so the tree's coefficients are run down to one weight per leaf,
+ * once per tree on the host, and a row costs one term per leaf.
+ * u, v, w [n_vis] DEVICE; vis_out DEVICE complex128 (SWV_FP64) or complex64
+ * (SWV_F32C; the arithmetic is FP64 for either).  The weights are copied to the
+ * device on first use with this context's device (64 bytes per leaf).
+ * SWV_ENOTSUP for a tree deeper than J = 16 with more than 15 nodes of two or
+ * more children on one root-to-leaf path (swv_tree_stats_t.max_branching), or
+ * whose record stream (32 bytes per record) exceeds 4 GiB - 32. */
 int swv_predict_tree(swv_ctx ctx, swv_tree tree, int64_t n_vis, const double* u,
                      const double* v, const double* w, int sign, int prec, void* vis_out);
 
@@ -195,10 +188,10 @@ int swv_predict_tree(swv_ctx ctx, swv_tree tree, int64_t n_vis, const double* u,
  * tree's merged leaves at their pixel centres,
  *     vis_out[j] = sum_k F_k exp(s 2 pi i B_j . (s_k - P)),
  * which Eq. 17 equals exactly (the wavelet terms of every level collapse onto
- * the leaves they were built from).  One term per leaf instead of one per
- * node; SWV_FP64 or SWV_F32C as in swv_predict_direct.  The leaves are copied
- * to the device on first use with this context's device (32 bytes each) and
- * refreshed by swv_tree_set_flux.  Arguments as swv_predict_tree. */
+ * the leaves they were built from), with the leaves' own fluxes as weights and
+ * SWV_FP64 or SWV_F32C as in swv_predict_direct.  The leaves are copied to the
+ * device on first use with this context's device and refreshed by
+ * swv_tree_set_flux.  Arguments as swv_predict_tree. */
 int swv_predict_tree_leaves(swv_ctx ctx, swv_tree tree, int64_t n_vis, const double* u,
                             const double* v, const double* w, int sign, int prec,
                             void* vis_out);
@@ -217,9 +210,8 @@ int swv_predict_tree_leaves(swv_ctx ctx, swv_tree tree, int64_t n_vis, const dou
  *    leaves, and nothing below it is visited.
  * swv_predict_tree then evaluates Eq. 17 over the thresholded tree (FP64 or
  * F32C); fraction 1 gives the exact tree route.  The thresholded tree works
- * with swv_predict_tree (64-thread blocks), swv_tree_stats (n_leaves counts the
- * leaves of every level, n_internal the remaining internal nodes) and batched
- * plans (which then walk every tree with the traversal per branching node);
+ * with swv_predict_tree, swv_tree_stats (n_leaves counts the leaves of every
+ * level, n_internal the remaining internal nodes) and batched plans;
  * swv_tree_leaves, swv_tree_level, swv_tree_set_flux, swv_predict_tree_leaves
  * and swv_cycle_set_tree return SWV_ENOTSUP for it.  0 <= fraction <= 1. */
 int swv_tree_threshold(swv_tree tree, double fraction, swv_tree* out);
@@ -599,20 +591,20 @@ typedef struct {
 
 /* A major cycle over many instances (section 2.2 steps 1-3, with the chi^2
  * gradients beside them), runnable eagerly or as one captured HIP graph:
- *   1. the model visibilities of every instance in one persistent launch per
- *      route (as swv_batch_plan: direct sums and wavelet trees, FP64);
+ *   1. the model visibilities of every instance in one persistent launch (as
+ *      swv_batch_plan: direct sums and wavelet trees, FP64);
  *   2. per instance the subtract step with chi^2 (swv_residual_chi2), the
  *      residual image on its pixel set (swv_adjoint of the residuals) and,
  *      for a direct instance with gradient outputs, the chi^2 gradients of its
  *      components (swv_grad_direct of the residuals with alpha = -2 inv_sigma2).
  * The model of each instance may change between cycles within the stated
- * capacities: its size, pointers and tree records are read on the device, so
+ * capacities: its size, pointers and leaf sum are read on the device, so
  * a captured graph replays the new model without a new capture.  Grids and
  * tilings follow the capacities: results are bitwise the same eager and
  * replayed, and agree with the single calls to their tolerances (the
- * gradients' summation order follows comp_cap).  The cycle holds a tree
- * record buffer of 32 (comp_cap J_cap + 12) bytes per tree instance (at most
- * 4 GiB - 32 each, else SWV_ENOTSUP) and workspaces for the largest image and
+ * gradients' summation order follows comp_cap).  The cycle holds a leaf buffer
+ * of about 51 (comp_cap J_cap + 12) bytes per tree instance (SWV_ENOTSUP if 32
+ * times that many records exceed 4 GiB - 32) and workspaces for the largest image and
  * gradient step.  The buffers named by `inst` must outlive the cycle.  Until a
  * model is set an instance predicts zero. */
 int swv_cycle_create(swv_ctx ctx, int n, const swv_cycle_instance* inst, swv_cycle* out);
@@ -623,11 +615,11 @@ int swv_cycle_create(swv_ctx ctx, int n, const swv_cycle_instance* inst, swv_cyc
 int swv_cycle_set_components(swv_cycle cycle, int k, int64_t n_comp, const double* l,
                              const double* m, const double* flux);
 
-/* Sets the tree of tree instance k for the following cycles: its records are
+/* Sets the tree of tree instance k for the following cycles: its leaf sum is
  * copied into the instance's buffer (after the work already on the context's
  * stream, which this call waits for), so the tree may be destroyed afterwards.
  * SWV_EINVAL if J exceeds tree_level_cap or the records the capacity;
- * SWV_ENOTSUP if the cycle's traversal cannot walk the tree. */
+ * SWV_ENOTSUP for a tree that swv_predict_tree does not take. */
 int swv_cycle_set_tree(swv_cycle cycle, int k, swv_tree tree);
 
 /* Enqueues one cycle on the context's stream (uploading changed models first). */
@@ -664,7 +656,7 @@ int swv_measure_peaks(swv_ctx ctx, swv_peaks_t* out);
 /* ------------------------------------------------------------- tuning --- */
 
 /* Times every compiled tile shape of each kernel family (direct FP64,
- * direct F32C, tree, adjoint, gradients) on synthetic inputs of the two size
+ * direct F32C, adjoint, gradients) on synthetic inputs of the two size
  * classes (2^18 and 2^22 rows), keeps
  * the fastest per (family, size class) in the context's tuning table and, if
  * `cache_path` is not NULL, writes the table there as JSON.  flags: 0 =
@@ -677,10 +669,11 @@ int swv_tune_load(swv_ctx ctx, const char* cache_path);
 /* Tile shape the context uses per kernel family and size class.  Families:
  * 0 direct FP64, 1 direct F32C, 2 tree, 3 adjoint, 4 gradients.  Size class
  * 0 is fewer than 2^20 visibility rows, 1 the rest.  per_lane is rows per lane
- * (direct), pixels per lane (adjoint) or components per lane (gradients), in
- * {1, 2, 4}; for the tree it selects the traversal (1: by depth and shape as
- * swv_predict_tree describes; 2: per branching node where it fits; 4: per
- * level where J <= 16).  block is threads per block in {64, 128, 256}; the
+ * (direct; FP64: at most), pixels per lane (adjoint; FP64: at most) or
+ * components per lane (gradients), in {1, 2, 4}.  block is threads per block in
+ * {64, 128, 256} (the FP64 direct sum and adjoint have their own).  The tree's
+ * entries are kept and checked but decide nothing: it runs the FP64 direct sum's
+ * kernels with their shapes.  The
  * gradients' entries hold 128 (swv_tune_set rejects any other value for them):
  * their launches take the narrowest block of 128 .. 1024 threads that holds
  * every component at per_lane (else 1024).  Results do not depend on the

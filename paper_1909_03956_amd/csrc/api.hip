@@ -108,9 +108,6 @@ bool tune_valid(int family, int per_lane, int block) {
     if (family < 0 || family >= kFamilies) return false;
     const bool pl_ok = per_lane == 1 || per_lane == 2 || per_lane == 4;
     const bool bl_ok = block == 64 || block == 128 || block == 256;
-    // tree: per_lane selects the traversal (1 by depth and shape, 2 branch
-    // walker, 4 level walker where it fits)
-    if (family == kFamTree) return (per_lane == 1 || per_lane == 2 || per_lane == 4) && bl_ok;
     if (family == kFamGrad) return pl_ok && block == 128;
     return pl_ok && bl_ok;
 }
@@ -122,32 +119,45 @@ int check_sign_prec(int sign, int prec, bool allow_f32) {
     return SWV_OK;
 }
 
-int upload_tree(swv_ctx ctx, swv_tree t, const TRec** out) {
-    auto it = t->device_records.find(ctx->device);
-    if (it != t->device_records.end()) {
-        *out = (const TRec*)it->second;
-        return SWV_OK;
-    }
+// A device copy of `c` under the context's device in `copies`, made once.
+static int upload_cells(swv_ctx ctx, std::map<int, void*>& copies, const std::vector<CompCell>& c,
+                        CompCell** out) {
     void* p = nullptr;
-    const size_t bytes = t->records.size() * sizeof(TRec);
-    if (bytes > kMaxRecordBytes)
-        return fail(SWV_ENOTSUP, "tree upload: a record stream of %zu bytes exceeds the traversal's "
-                    "%zu-byte limit", bytes, (size_t)kMaxRecordBytes);
+    const size_t bytes = c.size() * sizeof(CompCell);
     hipError_t e = hipMalloc(&p, bytes < 32 ? 32 : bytes);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(SWV_ENOMEM, "tree upload: %s", hipGetErrorString(e));
     }
     if (bytes) {
-        e = hipMemcpy(p, t->records.data(), bytes, hipMemcpyHostToDevice);
+        e = hipMemcpy(p, c.data(), bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             (void)hipFree(p);
             return hip_fail(e, "tree upload");
         }
     }
-    t->device_records[ctx->device] = p;
-    *out = (const TRec*)p;
+    copies[ctx->device] = p;
+    *out = (CompCell*)p;
     return SWV_OK;
+}
+
+std::vector<CompCell> packed_sum(const swv_tree_s& t) {
+    std::vector<CompCell> c;
+    for (const Comp& k : collapse_tree(t)) c.push_back(comp_cell(k.l, k.m, k.nm1, k.I));
+    return c;
+}
+
+int upload_tree(swv_ctx ctx, swv_tree t, CompCell** out) {
+    auto it = t->device_sum.find(ctx->device);
+    if (it != t->device_sum.end()) {
+        *out = (CompCell*)it->second;
+        return SWV_OK;
+    }
+    const size_t bytes = t->records.size() * sizeof(TRec);
+    if (bytes > kMaxRecordBytes)
+        return fail(SWV_ENOTSUP, "tree upload: a record stream of %zu bytes exceeds the "
+                    "%zu-byte limit", bytes, (size_t)kMaxRecordBytes);
+    return upload_cells(ctx, t->device_sum, packed_sum(*t), out);
 }
 
 // The leaves as the direct kernels read them: FP64 records, then (from a
@@ -163,60 +173,17 @@ static std::vector<CompCell> packed_leaves(swv_tree t) {
     return c;
 }
 
-static int upload_leaves(swv_ctx ctx, swv_tree t, const CompCell** out) {
+static int upload_leaves(swv_ctx ctx, swv_tree t, CompCell** out) {
     auto it = t->device_leaves.find(ctx->device);
     if (it != t->device_leaves.end()) {
-        *out = (const CompCell*)it->second;
+        *out = (CompCell*)it->second;
         return SWV_OK;
     }
-    const std::vector<CompCell> c = packed_leaves(t);
-    void* p = nullptr;
-    const size_t bytes = c.size() * sizeof(CompCell);
-    hipError_t e = hipMalloc(&p, bytes < 32 ? 32 : bytes);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(SWV_ENOMEM, "tree leaves upload: %s", hipGetErrorString(e));
-    }
-    if (bytes) {
-        e = hipMemcpy(p, c.data(), bytes, hipMemcpyHostToDevice);
-        if (e != hipSuccess) {
-            (void)hipFree(p);
-            return hip_fail(e, "tree leaves upload");
-        }
-    }
-    t->device_leaves[ctx->device] = p;
-    *out = (const CompCell*)p;
-    return SWV_OK;
+    return upload_cells(ctx, t->device_leaves, packed_leaves(t), out);
 }
 
-int tree_walker(swv_tree t, int preferred) {
-    const bool level_ok = t->J <= kTreeMaxJ;
-    const bool branch_ok = t->max_branching + 1 <= kTreeMaxSeg;
-    if (preferred == 2 && branch_ok) return 1;
-    if (!level_ok) return branch_ok ? 1 : -1;
-    if (preferred == 4 || t->J <= kTreeLevelAlwaysJ || !branch_ok) return 0;
-    // a thresholded tree (leaves at many levels) keeps the branch walker: by
-    // levels, the sweep track's J = 16 tree at 0.5 % retained took 0.48 ms,
-    // 2.4 times its time at 1 %
-    if (t->thresholded) return 1;
-    // deeper trees: runs of one-child nodes cost the branch walker less (cfg2's
-    // 2,000 components at J = 11, 12, 53-62 % of the internal nodes with one
-    // child: 10.8 and 18.1 ms by levels against 14.9 and 23.3 ms by branchings;
-    // 140 sparse components at J = 12-16, 89-94 %: 0.75-0.98 ms by branchings
-    // against 1.49-1.99 ms by levels)
-    int64_t internal = 0;
-    for (int j = 1; j < t->J; ++j) internal += (int64_t)t->levels[j - 1].pix.size();
-    return 4 * t->n_one_child > 3 * internal ? 1 : 0;
-}
-
-TreeArgs tree_args(swv_tree t, const TRec* d_rec) {
-    TreeArgs a;
-    a.rec = d_rec;
-    a.n_roots = (int)t->n_roots;
-    a.J = t->J;
-    a.seg_depth = t->max_branching + 1;
-    a.pruned = t->thresholded ? 1 : 0;
-    return a;
+bool tree_supported(swv_tree t) {
+    return t->J <= kTreeMaxJ || t->max_branching + 1 <= kTreeMaxSeg;
 }
 
 int check_adjoint_args(const char* who, swv_ctx ctx, int64_t n_vis, const double* u,
@@ -373,10 +340,10 @@ int swv_ctx_destroy(swv_ctx ctx) {
 }
 
 // ------------------------------------------------------- direct route ---
-// The table-phasor direct sum over packed components.
+// The FP64 direct sum over packed components; prec of the output alone.
 static int run_direct_cell(swv_ctx ctx, int64_t n_vis, const double* u, const double* v,
                            const double* w, const CompCell* comp, int64_t n_comp, int sign,
-                           void* vis_out) {
+                           int prec, void* vis_out) {
     const DirectShape sh =
         direct_shape(n_vis, n_comp, ctx->per_lane[kFamDirect64][size_class(n_vis)], ctx->n_cu);
     const size_t bytes = direct_partial_bytes(sh, n_vis);
@@ -384,8 +351,8 @@ static int run_direct_cell(swv_ctx ctx, int64_t n_vis, const double* u, const do
         const int rc = ensure(ctx, ctx->partial, bytes);
         if (rc) return rc;
     }
-    HIPCALL(launch_direct_cell(ctx->stream, sh, n_vis, u, v, w, comp, n_comp, sign,
-                               (double2*)vis_out, (double2*)ctx->partial.p, ctx->d_status));
+    HIPCALL(launch_direct_cell(ctx->stream, sh, n_vis, u, v, w, comp, n_comp, sign, prec, vis_out,
+                               (double2*)ctx->partial.p, ctx->d_status));
     return SWV_OK;
 }
 
@@ -413,7 +380,7 @@ int swv_predict_direct(swv_ctx ctx, int64_t n_vis, const double* u, const double
     if (prec == SWV_FP64) {
         CompCell* comp = (CompCell*)ctx->comp.p;
         HIPCALL(launch_ingest(ctx->stream, n_comp, l, m, flux, comp, ctx->d_status));
-        return run_direct_cell(ctx, n_vis, u, v, w, comp, n_comp, sign, vis_out);
+        return run_direct_cell(ctx, n_vis, u, v, w, comp, n_comp, sign, SWV_FP64, vis_out);
     }
     Comp* comp = (Comp*)ctx->comp.p;
     HIPCALL(launch_ingest(ctx->stream, n_comp, l, m, flux, comp, ctx->d_status));
@@ -522,7 +489,7 @@ int swv_tree_set_flux(swv_tree t, const double* leaf_flux) {
         if (!std::isfinite(leaf_flux[k]))
             return fail(SWV_EDOMAIN, "swv_tree_set_flux: flux %zu is not finite", k);
     TRY_BEGIN
-    for (auto* copies : {&t->device_records, &t->device_leaves})
+    for (auto* copies : {&t->device_sum, &t->device_leaves})
         for (auto& kv : *copies) {   // device copies may still be read
             DeviceGuard g(kv.first);
             hipError_t e = hipDeviceSynchronize();
@@ -532,15 +499,12 @@ int swv_tree_set_flux(swv_tree t, const double* leaf_flux) {
     std::copy(leaf_flux, leaf_flux + n, t->leaf_flux.begin());
     build_coefficients(t);
     if (t->records.size() != n_rec) return fail(SWV_EINVAL, "swv_tree_set_flux: internal error");
-    for (auto& kv : t->device_records) {   // same structure: refresh in place
-        DeviceGuard g(kv.first);
-        hipError_t e = hipMemcpy(kv.second, t->records.data(), n_rec * sizeof(TRec),
-                                 hipMemcpyHostToDevice);
-        if (e != hipSuccess) return hip_fail(e, "swv_tree_set_flux upload");
-    }
-    if (!t->device_leaves.empty()) {
-        const std::vector<CompCell> c = packed_leaves(t);
-        for (auto& kv : t->device_leaves) {
+    // same structure: refresh the device copies in place
+    for (auto* copies : {&t->device_sum, &t->device_leaves}) {
+        if (copies->empty()) continue;
+        const std::vector<CompCell> c =
+            copies == &t->device_sum ? packed_sum(*t) : packed_leaves(t);
+        for (auto& kv : *copies) {
             DeviceGuard g(kv.first);
             hipError_t e = hipMemcpy(kv.second, c.data(), c.size() * sizeof(CompCell),
                                      hipMemcpyHostToDevice);
@@ -559,23 +523,19 @@ int swv_predict_tree(swv_ctx ctx, swv_tree t, int64_t n_vis, const double* u, co
     NEED(u, n_vis); NEED(v, n_vis); NEED(w, n_vis); NEED(vis_out, n_vis);
     int rc = check_sign_prec(sign, prec, true);
     if (rc) return rc;
-    const int sc = size_class(n_vis);
-    const int walker = tree_walker(t, ctx->per_lane[kFamTree][sc]);
-    if (walker < 0)
+    if (!tree_supported(t))
         return fail(SWV_ENOTSUP,
                     "swv_predict_tree: J = %d with %d nested branchings on one path: above the "
-                    "compiled maxima (J %d, or %d branchings)",
+                    "maxima (J %d, or %d branchings)",
                     t->J, t->max_branching, kTreeMaxJ, kTreeMaxSeg - 1);
     if (n_vis == 0) return SWV_OK;
     TRY_BEGIN
     GUARD(ctx);
-    const TRec* rec = nullptr;
-    rc = upload_tree(ctx, t, &rec);
+    CompCell* comp = nullptr;
+    rc = upload_tree(ctx, t, &comp);
     if (rc) return rc;
-    const TreeArgs a = tree_args(t, rec);
-    HIPCALL(launch_tree(ctx->stream, walker, ctx->block[kFamTree][sc], prec, a, n_vis, u, v, w,
-                        sign, vis_out, ctx->d_status));
-    return SWV_OK;
+    return run_direct_cell(ctx, n_vis, u, v, w, comp, (int64_t)t->leaf_pix.size(), sign, prec,
+                           vis_out);
     TRY_END
 }
 
@@ -595,11 +555,12 @@ int swv_predict_tree_leaves(swv_ctx ctx, swv_tree t, int64_t n_vis, const double
     if (n_vis == 0) return SWV_OK;
     TRY_BEGIN
     GUARD(ctx);
-    const CompCell* comp = nullptr;
+    CompCell* comp = nullptr;
     rc = upload_leaves(ctx, t, &comp);
     if (rc) return rc;
     const int64_t n = (int64_t)t->leaf_pix.size();
-    if (prec == SWV_FP64) return run_direct_cell(ctx, n_vis, u, v, w, comp, n, sign, vis_out);
+    if (prec == SWV_FP64)
+        return run_direct_cell(ctx, n_vis, u, v, w, comp, n, sign, SWV_FP64, vis_out);
     const int sc = size_class(n_vis);
     HIPCALL(launch_direct_f32c(ctx->stream, ctx->per_lane[kFamDirect32][sc],
                                ctx->block[kFamDirect32][sc], n_vis, u, v, w,
@@ -611,7 +572,7 @@ int swv_predict_tree_leaves(swv_ctx ctx, swv_tree t, int64_t n_vis, const double
 int swv_tree_destroy(swv_tree t) {
     if (!t) return SWV_OK;
     if (--t->refs > 0) return SWV_OK;   // a plan still reads its device records
-    for (auto* copies : {&t->device_records, &t->device_leaves})
+    for (auto* copies : {&t->device_sum, &t->device_leaves})
         for (auto& kv : *copies) {
             DeviceGuard g(kv.first);
             (void)hipDeviceSynchronize();

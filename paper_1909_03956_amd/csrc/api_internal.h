@@ -64,11 +64,12 @@ int size_class(int64_t rows);
 int64_t choose_chunk(int64_t n_rows, int64_t tiles, int n_cu, int blocks_per_cu);
 int check_sign_prec(int sign, int prec, bool allow_f32);
 bool tune_valid(int family, int per_lane, int block);
-int upload_tree(swv_ctx ctx, swv_tree t, const TRec** out);
-TreeArgs tree_args(swv_tree t, const TRec* d_rec);
-// Traversal for tree t given the tuned choice (1 level walker, 2 branch
-// walker): 0 level walker, 1 branch walker, -1 if no compiled one fits.
-int tree_walker(swv_tree t, int preferred);
+// Device copy of the tree's leaf sum (t->leaf_pix.size() components), made at the
+// first use on a device.
+int upload_tree(swv_ctx ctx, swv_tree t, CompCell** out);
+std::vector<CompCell> packed_sum(const swv_tree_s& t);
+// Whether the entry points predict this tree (kTreeMaxJ, kTreeMaxSeg).
+bool tree_supported(swv_tree t);
 // Releases a plan made by the degridding predictor (no-op on NULL).
 void destroy_fft_plan(void* plan);
 

@@ -16,22 +16,15 @@ using namespace swv;
 struct swv_plan_s {
     swv_ctx ctx = nullptr;
     int64_t n_inst = 0;
-    std::vector<BatchInst> direct, tree;
+    std::vector<BatchInst> inst;
     std::vector<swv_tree> trees;      // held (one reference each) while the plan lives
-    BatchInst* d_direct = nullptr;
-    BatchInst* d_tree = nullptr;
-    WorkItem* d_items_direct = nullptr;   // FP64 direct instances
-    WorkItem* d_items_direct32 = nullptr; // F32C direct instances
-    WorkItem* d_items_tree = nullptr;     // FP64 tree instances
-    WorkItem* d_items_tree32 = nullptr;   // F32C tree instances
-    unsigned n_items_direct = 0, n_items_direct32 = 0, n_items_tree = 0, n_items_tree32 = 0;
-    CompCell* d_pack = nullptr;
-    // [0] direct FP64, [1] tree FP64, [2] tree F32C, [3] direct F32C
-    unsigned* d_counters = nullptr;
-    int vpl = 2, grid_direct = 0, grid_direct32 = 0, grid_tree = 0, grid_tree32 = 0, max_comp = 0;
-    int jmax = 1, smax = 1;           // largest J and segment depth of the trees
-    int tree_walker = 0, tree_depth = 1;
-    bool pruned = false;              // some tree is thresholded (leaves above level J)
+    BatchInst* d_inst = nullptr;
+    WorkItem* d_items = nullptr;      // FP64 direct instances and trees
+    WorkItem* d_items32 = nullptr;    // F32C direct instances
+    unsigned n_items = 0, n_items32 = 0;
+    CompCell* d_pack = nullptr;       // components of the direct instances
+    unsigned* d_counters = nullptr;   // next item of each launch
+    int vpl = 2, grid = 0, grid32 = 0, max_comp = 0;
     int tile_rows = 0;
     int64_t total_terms = 0;
     int refs = 1;  // graphs captured from this plan hold a reference
@@ -62,50 +55,37 @@ int dev_upload(const std::vector<T>& h, T** out) {
     return SWV_OK;
 }
 
+void free_plan_device(swv_plan p) {
+    for (void* q : {(void*)p->d_inst, (void*)p->d_items, (void*)p->d_items32, (void*)p->d_pack,
+                    (void*)p->d_counters})
+        if (q) (void)hipFree(q);
+}
+
 void plan_release(swv_plan p) {
     if (--p->refs > 0) return;
     swv_ctx ctx = p->ctx;
     {
         DeviceGuard g(ctx->device);
         (void)hipStreamSynchronize(ctx->stream);
-        for (void* q : {(void*)p->d_direct, (void*)p->d_tree, (void*)p->d_items_direct,
-                    (void*)p->d_items_direct32,
-                        (void*)p->d_items_tree,
-                        (void*)p->d_items_tree32, (void*)p->d_pack, (void*)p->d_counters})
-            if (q) (void)hipFree(q);
+        free_plan_device(p);
     }
     for (swv_tree t : p->trees) (void)swv_tree_destroy(t);   // drops the plan's reference
     delete p;
     ctx_release(ctx);
 }
 
-void free_plan_device(swv_plan p) {
-    for (void* q : {(void*)p->d_direct, (void*)p->d_tree, (void*)p->d_items_direct,
-                    (void*)p->d_items_direct32,
-                    (void*)p->d_items_tree,
-                        (void*)p->d_items_tree32, (void*)p->d_pack, (void*)p->d_counters})
-        if (q) (void)hipFree(q);
-}
-
 // Enqueues the planned prediction on stream s.
 hipError_t enqueue_plan(swv_plan p, hipStream_t s) {
-    hipError_t e = launch_batch_ingest(s, p->d_direct, (int)p->direct.size(), p->max_comp,
-                                       p->d_pack, p->ctx->d_status);
-    if (e != hipSuccess) return e;
-    e = launch_reset_counters(s, p->d_counters, 4);
-    if (e != hipSuccess) return e;
-    e = launch_batch_direct(s, p->vpl, p->grid_direct, p->d_direct, p->d_pack, p->d_items_direct,
-                            p->n_items_direct, p->d_counters, p->ctx->d_status);
-    if (e != hipSuccess) return e;
-    e = launch_batch_direct_f32c(s, p->grid_direct32, p->d_direct, p->d_pack, p->d_items_direct32,
-                                 p->n_items_direct32, p->d_counters + 3, p->ctx->d_status);
-    if (e != hipSuccess) return e;
-    e = launch_batch_tree(s, p->tree_walker, p->tree_depth, SWV_FP64, p->grid_tree, p->d_tree, p->d_items_tree, p->n_items_tree, p->d_counters + 1,
-                          p->ctx->d_status, p->pruned);
-    if (e != hipSuccess) return e;
-    return launch_batch_tree(s, p->tree_walker, p->tree_depth, SWV_F32C, p->grid_tree32,
-                             p->d_tree, p->d_items_tree32, p->n_items_tree32,
-                             p->d_counters + 2, p->ctx->d_status, p->pruned);
+    int* status = p->ctx->d_status;
+    hipError_t e = launch_batch_ingest(s, p->d_inst, (int)p->inst.size(), p->max_comp, status);
+    if (e == hipSuccess) e = launch_reset_counters(s, p->d_counters, 2);
+    if (e == hipSuccess)
+        e = launch_batch_direct(s, p->vpl, p->grid, p->d_inst, p->d_items, p->n_items,
+                                p->d_counters, status);
+    if (e == hipSuccess)
+        e = launch_batch_direct_f32c(s, p->grid32, p->d_inst, p->d_items32, p->n_items32,
+                                     p->d_counters + 1, status);
+    return e;
 }
 
 int check_instance(const swv_instance& I, int k) {
@@ -127,9 +107,9 @@ int check_instance(const swv_instance& I, int k) {
         if (!I.tree) return fail(SWV_EINVAL, "instance %d: null tree", k);
         if (I.prec != SWV_FP64 && I.prec != SWV_F32C)
             return fail(SWV_EINVAL, "instance %d: bad precision %d", k, I.prec);
-        if (tree_walker(I.tree, 1) < 0)
+        if (!tree_supported(I.tree))
             return fail(SWV_ENOTSUP,
-                        "instance %d: J = %d with %d nested branchings: above the compiled "
+                        "instance %d: J = %d with %d nested branchings: above the "
                         "maxima (J %d, or %d branchings)",
                         k, I.tree->J, I.tree->max_branching, kTreeMaxJ, kTreeMaxSeg - 1);
     }
@@ -157,7 +137,7 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
         p->ctx = ctx;
         p->n_inst = n;
         int64_t off = 0, total_rows = 0, rows64 = 0;
-        std::vector<int64_t> cost_per_row_direct, cost_per_row_tree;
+        std::vector<int64_t> offset(n, 0);
         for (int k = 0; k < n; ++k) {
             const swv_instance& I = inst[k];
             BatchInst b{};
@@ -168,71 +148,36 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
             b.n_vis = I.n_vis;
             b.prec = I.prec;
             b.sgn = (double)I.sign;
+            b.is_tree = I.route == SWV_ROUTE_TREE;
             total_rows += I.n_vis;
-            if (I.route == SWV_ROUTE_DIRECT) {
+            if (!b.is_tree) {
                 if (I.prec == SWV_FP64) rows64 += I.n_vis;
                 b.l = I.l;
                 b.m = I.m;
                 b.flux = I.flux;
-                b.comp_offset = off;
                 b.n_comp = (int)I.n_comp;
+                offset[k] = off;
                 off += I.n_comp;
                 p->max_comp = std::max(p->max_comp, (int)I.n_comp);
-                p->direct.push_back(b);
-                cost_per_row_direct.push_back(std::max<int64_t>(I.n_comp, 1));
                 p->total_terms += I.n_vis * I.n_comp;
             } else {
-                const TRec* rec = nullptr;
-                int rc = upload_tree(ctx, I.tree, &rec);
+                rows64 += I.n_vis;
+                const int rc = upload_tree(ctx, I.tree, &b.comp);
                 if (rc) {
                     delete p;
                     return rc;
                 }
-                b.rec = rec;
-                b.n_roots = (int)I.tree->n_roots;
-                b.J = I.tree->J;
-                p->jmax = std::max(p->jmax, b.J);
-                p->smax = std::max(p->smax, I.tree->max_branching + 1);
-                p->pruned = p->pruned || I.tree->thresholded;
-                p->tree.push_back(b);
-                cost_per_row_tree.push_back((int64_t)I.tree->records.size() + 1);
+                b.n_comp = (int)I.tree->leaf_pix.size();
                 p->total_terms += I.n_vis * I.tree->n_comp;
             }
-        }
-        // one traversal for all trees of the plan: the tuned one where it fits
-        const bool level_ok = p->jmax <= kBatchTreeMaxJ, branch_ok = p->smax <= kTreeMaxSeg;
-        const bool want_branch = ctx->per_lane[kFamTree][1] == 2;
-        if (!p->tree.empty() && !level_ok && !branch_ok) {
-            delete p;
-            return fail(SWV_ENOTSUP,
-                        "swv_batch_plan: no compiled traversal fits every tree (largest J %d, "
-                        "segment depth %d)",
-                        p->jmax, p->smax);
-        }
-        p->tree_walker = (branch_ok && (want_branch || !level_ok)) ? 1 : 0;
-        p->tree_depth = p->tree_walker ? p->smax : p->jmax;
-        if (p->pruned) {
-            // thresholded trees: the branch walker compiled for leaves above level J
-            if (!branch_ok) {
-                delete p;
-                return fail(SWV_ENOTSUP, "swv_batch_plan: a thresholded tree's branching is "
-                                         "above the compiled maximum");
-            }
-            p->tree_walker = 1;
-            p->tree_depth = kTreeMaxSeg;
+            p->inst.push_back(b);
         }
 
         p->vpl = batch_direct_vpl(rows64, ctx->per_lane[kFamDirect64][1], ctx->n_cu);
         // persistent grids: as many blocks as stay resident
-        p->grid_direct = ctx->n_cu * batch_direct_blocks_per_cu(p->vpl);
-        p->grid_direct32 = ctx->n_cu * batch_direct_f32c_blocks_per_cu();
-        p->grid_tree = ctx->n_cu * (p->pruned ? batch_tree_pruned_blocks_per_cu(SWV_FP64)
-                                              : batch_tree_blocks_per_cu(p->tree_walker,
-                                                                         p->tree_depth, SWV_FP64));
-        p->grid_tree32 = ctx->n_cu * (p->pruned ? batch_tree_pruned_blocks_per_cu(SWV_F32C)
-                                                : batch_tree_blocks_per_cu(p->tree_walker,
-                                                                           p->tree_depth, SWV_F32C));
-        const int64_t waves = (int64_t)p->grid_direct * (kTabBlock / 64);
+        p->grid = ctx->n_cu * batch_direct_blocks_per_cu(p->vpl);
+        p->grid32 = ctx->n_cu * batch_direct_f32c_blocks_per_cu();
+        const int64_t waves = (int64_t)p->grid * (kTabBlock / 64);
         // about 16 items per resident wave, in whole wave tiles, at most 64 of them
         const int64_t unit = 64LL * p->vpl;
         int64_t tile = total_rows / std::max<int64_t>(1, 16 * waves);
@@ -243,56 +188,44 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
             WorkItem w;
             int64_t cost;
         };
-        auto make_items = [&](const std::vector<BatchInst>& list,
-                              const std::vector<int64_t>& cpr, int64_t tile_rows) {
-            std::vector<Item> items;
-            for (size_t k = 0; k < list.size(); ++k)
-                for (int64_t r = 0; r < list[k].n_vis; r += tile_rows) {
-                    const int nr = (int)std::min<int64_t>(tile_rows, list[k].n_vis - r);
-                    items.push_back(Item{WorkItem{r, (int)k, nr}, (int64_t)nr * cpr[k]});
-                }
-            // longest processing time first
-            std::stable_sort(items.begin(), items.end(),
-                             [](const Item& a, const Item& b) { return a.cost > b.cost; });
-            std::vector<WorkItem> w;
-            w.reserve(items.size());
-            for (const Item& it : items) w.push_back(it.w);
-            return w;
-        };
-        // items by precision (one launch each), keeping the cost order
-        std::vector<WorkItem> wd, wd32;
-        for (const WorkItem& it : make_items(p->direct, cost_per_row_direct, tile))
-            (p->direct[(size_t)it.inst].prec == SWV_F32C ? wd32 : wd).push_back(it);
-        const int64_t tree_tile = std::max<int64_t>(64, tile / p->vpl / 64 * 64);
-        std::vector<WorkItem> wt, wt32;
-        for (const WorkItem& it : make_items(p->tree, cost_per_row_tree, tree_tile))
-            (p->tree[(size_t)it.inst].prec == SWV_F32C ? wt32 : wt).push_back(it);
-        if (wd.size() > 0xffffffffull || wd32.size() > 0xffffffffull || wt.size() > 0xffffffffull || wt32.size() > 0xffffffffull) {
+        std::vector<Item> items;
+        for (size_t k = 0; k < p->inst.size(); ++k)
+            for (int64_t r = 0; r < p->inst[k].n_vis; r += tile) {
+                const int nr = (int)std::min<int64_t>(tile, p->inst[k].n_vis - r);
+                items.push_back(Item{WorkItem{r, (int)k, nr},
+                                     (int64_t)nr * std::max(p->inst[k].n_comp, 1)});
+            }
+        // longest processing time first
+        std::stable_sort(items.begin(), items.end(),
+                         [](const Item& a, const Item& b) { return a.cost > b.cost; });
+        // items by launch, keeping the cost order
+        std::vector<WorkItem> w64, w32;
+        for (const Item& it : items) {
+            const BatchInst& b = p->inst[(size_t)it.w.inst];
+            (b.prec == SWV_F32C && !b.is_tree ? w32 : w64).push_back(it.w);
+        }
+        if (w64.size() > 0xffffffffull || w32.size() > 0xffffffffull) {
             delete p;
             return fail(SWV_ENOTSUP, "swv_batch_plan: too many work items");
         }
-        p->n_items_direct = (unsigned)wd.size();
-        p->n_items_direct32 = (unsigned)wd32.size();
-        p->n_items_tree = (unsigned)wt.size();
-        p->n_items_tree32 = (unsigned)wt32.size();
+        p->n_items = (unsigned)w64.size();
+        p->n_items32 = (unsigned)w32.size();
 
-        int rc = dev_upload(p->direct, &p->d_direct);
-        if (!rc) rc = dev_upload(p->tree, &p->d_tree);
-        if (!rc) rc = dev_upload(wd, &p->d_items_direct);
-        if (!rc) rc = dev_upload(wd32, &p->d_items_direct32);
-        if (!rc) rc = dev_upload(wt, &p->d_items_tree);
-        if (!rc) rc = dev_upload(wt32, &p->d_items_tree32);
-        if (!rc) {
-            hipError_t e = hipMalloc((void**)&p->d_pack,
-                                     (size_t)std::max<int64_t>(off, 1) * sizeof(CompCell));
-            if (e != hipSuccess) {
-                (void)hipGetLastError();
-                p->d_pack = nullptr;
-                rc = fail(SWV_ENOMEM, "swv_batch_plan: component buffer");
-            }
+        int rc = SWV_OK;
+        hipError_t e = hipMalloc((void**)&p->d_pack,
+                                 (size_t)std::max<int64_t>(off, 1) * sizeof(CompCell));
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            p->d_pack = nullptr;
+            rc = fail(SWV_ENOMEM, "swv_batch_plan: component buffer");
         }
+        for (int k = 0; k < n && !rc; ++k)
+            if (!p->inst[k].is_tree) p->inst[k].comp = p->d_pack + offset[k];
+        if (!rc) rc = dev_upload(p->inst, &p->d_inst);
+        if (!rc) rc = dev_upload(w64, &p->d_items);
+        if (!rc) rc = dev_upload(w32, &p->d_items32);
         if (!rc) {
-            hipError_t e = hipMalloc((void**)&p->d_counters, 4 * sizeof(unsigned));
+            e = hipMalloc((void**)&p->d_counters, 2 * sizeof(unsigned));
             if (e != hipSuccess) {
                 (void)hipGetLastError();
                 p->d_counters = nullptr;
@@ -312,7 +245,7 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
         return fail(SWV_ENOMEM, "swv_batch_plan: host allocation failed");
     }
     ++ctx->refs;  // the plan keeps its context alive
-    // and every tree whose device records it reads
+    // and every tree whose device copy it reads
     for (int k = 0; k < n; ++k)
         if (inst[k].route == SWV_ROUTE_TREE) {
             ++inst[k].tree->refs;
@@ -326,11 +259,10 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
 int swv_plan_stats(swv_plan p, swv_plan_stats_t* out) {
     if (!p || !out) return fail(SWV_EINVAL, "swv_plan_stats: null argument");
     out->n_instances = p->n_inst;
-    out->n_items = (int64_t)p->n_items_direct + p->n_items_direct32 + p->n_items_tree +
-                   p->n_items_tree32;
+    out->n_items = (int64_t)p->n_items + p->n_items32;
     out->total_terms = p->total_terms;
     out->tile_rows = p->tile_rows;
-    out->grid_blocks = p->grid_direct;
+    out->grid_blocks = p->grid;
     out->block_threads = kTabBlock;
     return SWV_OK;
 }
@@ -492,37 +424,13 @@ int swv_autotune(swv_ctx ctx, const char* cache_path, int flags) {
         if (e == hipSuccess) e = launch_ingest(s, n_comp, l, m, f, comp32, ctx->d_status);
         if (e != hipSuccess) return hip_fail(e, "autotune ingest");
     }
-    // a level-9 tree of 1,024 components in a 3 degree field
-    std::vector<double> hl(1024), hm(1024), hf(1024);
-    uint64_t st = 777;
-    auto rnd = [&st]() {
-        st = st * 6364136223846793005ull + 1442695040888963407ull;
-        return (double)(st >> 11) * (1.0 / 9007199254740992.0);
-    };
-    for (int i = 0; i < 1024; ++i) {
-        hl[i] = (rnd() - 0.5) * 0.05;
-        hm[i] = (rnd() - 0.5) * 0.05;
-        hf[i] = 0.01 + rnd();
-    }
-    swv_tree tree = nullptr;
-    int rc = swv_tree_build(9, 3.0, 0.5, 1024, hl.data(), hm.data(), hf.data(), &tree);
-    if (rc) return rc;
-    const TRec* rec = nullptr;
-    rc = upload_tree(ctx, tree, &rec);
-    if (rc) {
-        swv_tree_destroy(tree);
-        return rc;
-    }
-    const TreeArgs ta = tree_args(tree, rec);
-
     hipEvent_t e0, e1;
-    if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
-        swv_tree_destroy(tree);
+    if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
         return fail(SWV_EHIP, "swv_autotune: event creation failed");
-    }
     std::string report;
     int result = SWV_OK;
     for (int fam = 0; fam < kFamilies && result == SWV_OK; ++fam) {
+        if (fam == kFamTree) continue;   // runs the FP64 direct sum's kernels
         for (int cls = 0; cls < 2 && result == SWV_OK; ++cls) {
             const int64_t rows = rows_of[cls];
             float best = 1e30f;
@@ -537,22 +445,18 @@ int swv_autotune(swv_ctx ctx, const char* cache_path, int flags) {
                         if (fam == kFamDirect64) {
                             // rows enough for whole rows per wave: no partial sums
                             e = launch_direct_cell(s, DirectShape{pl, 1, 1}, rows, u, v, w, comp,
-                                                   n_comp, -1, (double2*)out, nullptr,
+                                                   n_comp, -1, SWV_FP64, out, nullptr,
                                                    ctx->d_status);
                         } else if (fam == kFamDirect32) {
                             e = launch_direct_f32c(s, pl, bl, rows, u, v, w, comp32, n_comp, -1,
                                                    out, ctx->d_status);
-                        } else if (fam == kFamTree) {
-                            e = launch_tree(s, pl == 2 ? 1 : 0, bl, SWV_FP64, ta, rows, u, v, w,
-                                            -1, out,
-                                            ctx->d_status);
                         } else if (fam == kFamAdjoint) {
                             // in the FP32-compensated form: `block` is its alone
                             const int64_t tiles = (n_pix + (int64_t)pl * bl - 1) / ((int64_t)pl * bl);
                             const int64_t chunk = choose_chunk(rows, tiles, ctx->n_cu,
                                                                adjoint_f32c_blocks_per_cu(pl, bl));
                             const int64_t nch = (rows + chunk - 1) / chunk;
-                            rc = ensure(ctx, ctx->partial, 16 * (size_t)n_pix * nch);
+                            const int rc = ensure(ctx, ctx->partial, 16 * (size_t)n_pix * nch);
                             if (rc) { result = rc; break; }
                             part = (double*)ctx->partial.p;
                             e = launch_adjoint(s, SWV_F32C, pl, bl, chunk, rows, u, v, w, y, n_pix,
@@ -564,7 +468,7 @@ int swv_autotune(swv_ctx ctx, const char* cache_path, int flags) {
                             const int64_t chunk =
                                 choose_chunk(rows, tiles, ctx->n_cu, grad_blocks_per_cu(pl, gblock));
                             const int64_t nch = (rows + chunk - 1) / chunk;
-                            rc = ensure(ctx, ctx->partial, 32 * (size_t)n_comp * nch);
+                            const int rc = ensure(ctx, ctx->partial, 32 * (size_t)n_comp * nch);
                             if (rc) { result = rc; break; }
                             part = (double*)ctx->partial.p;
                             e = launch_grad(s, pl, chunk, rows, u, v, w, y, (const double*)comp, 8,
@@ -601,7 +505,6 @@ int swv_autotune(swv_ctx ctx, const char* cache_path, int flags) {
     }
     hipEventDestroy(e0);
     hipEventDestroy(e1);
-    swv_tree_destroy(tree);
     if (result != SWV_OK) return result;
     if (cache_path) {
         FILE* fh = fopen(cache_path, "w");

@@ -20,7 +20,7 @@ struct alignas(64) CompCell {
     double l, m, nm1, I, Ic0, Ic1, Is0, Is1;
 };
 
-// One record of the depth-first tree stream (32 bytes).
+// One record of the depth-first tree stream (32 bytes, host).
 //   root : a = A_1 * lambda_1 of the level-1 node that follows; meta = 0
 //   node : a, b, c = h^0, h^1, h^2 with h^m = s^m_{c0} gamma^m_j (sqrt(A_j)/4) 4^-(J-j-1),
 //          c0 the node's first child, s the Eq. 10 signs (a thresholded tree:

@@ -2,15 +2,14 @@
 // chi^2 gradients beside them).  An instance is one channel x pointing with
 // its observed visibilities; every cycle runs, in one capture:
 //   1. the batched persistent prediction of every instance (direct sums and
-//      wavelet trees, one launch per route, FP64);
+//      wavelet trees in one launch, FP64);
 //   2. per instance: the subtract step with chi^2, the residual image on the
 //      instance's pixel set (the exact adjoint) and, for a direct instance,
 //      the chi^2 gradients of its components.
 // The model of an instance changes from cycle to cycle.  Everything that
-// depends on it is read on the device: component counts and pointers, the
-// tree's root count and level from the instance descriptors, the tree records
-// from a buffer sized for the largest model the instance accepts, the order
-// of the work items from their list.  Grids and tilings are fixed by those
+// depends on it is read on the device: component counts and pointers from the
+// instance descriptors, a tree's leaf sum from a buffer sized for the largest
+// model the instance accepts, the order of the work items from their list.  Grids and tilings are fixed by those
 // capacities.  A new model is therefore an upload before the next replay,
 // never a new capture.
 #include <algorithm>
@@ -26,18 +25,14 @@ using namespace swv;
 struct swv_cycle_s {
     swv_ctx ctx = nullptr;
     std::vector<swv_cycle_instance> spec;
-    std::vector<int> slot;                  // index of instance k in `direct` or `tree`
     std::vector<int64_t> cost;              // per-row cost of instance k's current model
-    std::vector<BatchInst> direct, tree;    // host copies of the device descriptors
-    std::vector<int> direct_inst, tree_inst;   // instance of each descriptor
-    std::vector<WorkItem> items_direct, items_tree;
-    std::vector<int64_t> rec_cap;           // per tree descriptor: record capacity
-    BatchInst* d_direct = nullptr;
-    BatchInst* d_tree = nullptr;
-    WorkItem* d_items_direct = nullptr;
-    WorkItem* d_items_tree = nullptr;
-    CompCell* d_pack = nullptr;
-    TRec* d_rec = nullptr;
+    std::vector<BatchInst> inst;            // host copy of the device descriptors
+    std::vector<WorkItem> items;
+    std::vector<int64_t> rec_cap;           // per instance: a tree's record capacity
+    BatchInst* d_inst = nullptr;
+    WorkItem* d_items = nullptr;
+    CompCell* d_pack = nullptr;             // direct instances' components
+    CompCell* d_sum = nullptr;              // tree instances' leaf sums
     unsigned* d_counters = nullptr;
     void* d_partial = nullptr;
     double* d_chi2_part = nullptr;
@@ -47,9 +42,9 @@ struct swv_cycle_s {
     hipEvent_t up_event = nullptr;
     bool up_pending = false;
     bool dirty = true;
-    int vpl = 2, grid_direct = 0, grid_tree = 0, walker = 0, depth = 1;
+    int vpl = 2, grid = 0;
     int max_comp_cap = 0;
-    int64_t tile_rows = 64, tree_tile = 64;   // rows per work item, fixed at creation
+    int64_t tile_rows = 64;                 // rows per work item, fixed at creation
     std::vector<AdjointShape> adj;          // per instance
     std::vector<int> gcpl;                  // per instance: gradient components per lane
     std::vector<int64_t> gchunk;            // per instance: gradient row chunk
@@ -74,8 +69,7 @@ int dev_alloc(T** p, size_t count) {
 void free_cycle(swv_cycle cy) {
     if (cy->exec) (void)hipGraphExecDestroy(cy->exec);
     if (cy->graph) (void)hipGraphDestroy(cy->graph);
-    for (void* q : {(void*)cy->d_direct, (void*)cy->d_tree, (void*)cy->d_items_direct,
-                    (void*)cy->d_items_tree, (void*)cy->d_pack, (void*)cy->d_rec,
+    for (void* q : {(void*)cy->d_inst, (void*)cy->d_items, (void*)cy->d_pack, (void*)cy->d_sum,
                     (void*)cy->d_counters, cy->d_partial, (void*)cy->d_chi2_part})
         if (q) (void)hipFree(q);
     if (cy->h_mirror) (void)hipHostFree(cy->h_mirror);
@@ -107,27 +101,24 @@ int check_spec(const swv_cycle_instance& I, int k) {
     return SWV_OK;
 }
 
-// Work items of the instances of one route: row tiles, longest processing
-// time first for the current models.
-void order_items(swv_cycle cy, const std::vector<int>& insts, int64_t tile_rows,
-                 std::vector<WorkItem>& items) {
+// Work items: row tiles, longest processing time first for the current models.
+void order_items(swv_cycle cy) {
     struct Item {
         WorkItem w;
         int64_t cost;
     };
     std::vector<Item> all;
-    for (size_t d = 0; d < insts.size(); ++d) {
-        const int k = insts[d];
+    for (size_t k = 0; k < cy->spec.size(); ++k) {
         const int64_t n = cy->spec[k].n_vis;
-        for (int64_t r = 0; r < n; r += tile_rows) {
-            const int nr = (int)std::min<int64_t>(tile_rows, n - r);
-            all.push_back(Item{WorkItem{r, (int)d, nr}, (int64_t)nr * cy->cost[k]});
+        for (int64_t r = 0; r < n; r += cy->tile_rows) {
+            const int nr = (int)std::min<int64_t>(cy->tile_rows, n - r);
+            all.push_back(Item{WorkItem{r, (int)k, nr}, (int64_t)nr * cy->cost[k]});
         }
     }
     std::stable_sort(all.begin(), all.end(),
                      [](const Item& a, const Item& b) { return a.cost > b.cost; });
-    items.clear();
-    for (const Item& it : all) items.push_back(it.w);
+    cy->items.clear();
+    for (const Item& it : all) cy->items.push_back(it.w);
 }
 
 // Uploads changed descriptors and the new work order on the context's stream.
@@ -140,20 +131,12 @@ int upload(swv_cycle cy) {
         cy->up_pending = false;
     }
     char* m = (char*)cy->h_mirror;
-    const size_t bd = cy->direct.size() * sizeof(BatchInst), bt = cy->tree.size() * sizeof(BatchInst);
-    const size_t bid = cy->items_direct.size() * sizeof(WorkItem),
-                 bit = cy->items_tree.size() * sizeof(WorkItem);
-    if (bd) std::memcpy(m, cy->direct.data(), bd);
-    if (bt) std::memcpy(m + bd, cy->tree.data(), bt);
-    if (bid) std::memcpy(m + bd + bt, cy->items_direct.data(), bid);
-    if (bit) std::memcpy(m + bd + bt + bid, cy->items_tree.data(), bit);
+    const size_t bi = cy->inst.size() * sizeof(BatchInst), bw = cy->items.size() * sizeof(WorkItem);
+    if (bi) std::memcpy(m, cy->inst.data(), bi);
+    if (bw) std::memcpy(m + bi, cy->items.data(), bw);
     const hipStream_t s = cy->ctx->stream;
-    if (bd) e = hipMemcpyAsync(cy->d_direct, m, bd, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && bt) e = hipMemcpyAsync(cy->d_tree, m + bd, bt, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && bid)
-        e = hipMemcpyAsync(cy->d_items_direct, m + bd + bt, bid, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && bit)
-        e = hipMemcpyAsync(cy->d_items_tree, m + bd + bt + bid, bit, hipMemcpyHostToDevice, s);
+    if (bi) e = hipMemcpyAsync(cy->d_inst, m, bi, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess && bw) e = hipMemcpyAsync(cy->d_items, m + bi, bw, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipEventRecord(cy->up_event, s);
     if (e != hipSuccess) return hip_fail(e, "swv_cycle: descriptor upload");
     cy->up_pending = true;
@@ -163,17 +146,13 @@ int upload(swv_cycle cy) {
 
 hipError_t enqueue_cycle(swv_cycle cy, hipStream_t s) {
     swv_ctx ctx = cy->ctx;
-    hipError_t e = launch_batch_ingest(s, cy->d_direct, (int)cy->direct.size(), cy->max_comp_cap,
-                                       cy->d_pack, ctx->d_status);
+    hipError_t e = launch_batch_ingest(s, cy->d_inst, (int)cy->inst.size(), cy->max_comp_cap,
+                                       ctx->d_status);
     if (e != hipSuccess) return e;
-    e = launch_reset_counters(s, cy->d_counters, 2);
+    e = launch_reset_counters(s, cy->d_counters, 1);
     if (e != hipSuccess) return e;
-    e = launch_batch_direct(s, cy->vpl, cy->grid_direct, cy->d_direct, cy->d_pack,
-                            cy->d_items_direct, (unsigned)cy->items_direct.size(),
-                            cy->d_counters, ctx->d_status);
-    if (e != hipSuccess) return e;
-    e = launch_batch_tree(s, cy->walker, cy->depth, SWV_FP64, cy->grid_tree, cy->d_tree, cy->d_items_tree, (unsigned)cy->items_tree.size(),
-                          cy->d_counters + 1, ctx->d_status);
+    e = launch_batch_direct(s, cy->vpl, cy->grid, cy->d_inst, cy->d_items,
+                            (unsigned)cy->items.size(), cy->d_counters, ctx->d_status);
     if (e != hipSuccess) return e;
     for (size_t k = 0; k < cy->spec.size(); ++k) {
         const swv_cycle_instance& I = cy->spec[k];
@@ -188,12 +167,10 @@ hipError_t enqueue_cycle(swv_cycle cy, hipStream_t s) {
             if (e != hipSuccess) return e;
         }
         if (I.d_flux && I.comp_cap > 0) {
-            const int d = cy->slot[k];
             e = launch_grad(s, cy->gcpl[k], cy->gchunk[k], I.n_vis, I.u, I.v, I.w, I.resid,
-                            (const double*)(cy->d_pack + cy->direct[d].comp_offset), 8,
-                            I.comp_cap, I.sign,
+                            (const double*)cy->inst[k].comp, 8, I.comp_cap, I.sign,
                             -2.0 * I.inv_sigma2, (double*)cy->d_partial, I.d_flux, I.d_l, I.d_m,
-                            &cy->d_direct[d].n_comp);
+                            &cy->d_inst[k].n_comp);
             if (e != hipSuccess) return e;
         }
     }
@@ -220,16 +197,16 @@ int swv_cycle_create(swv_ctx ctx, int n, const swv_cycle_instance* inst, swv_cyc
         cy = new swv_cycle_s();
         cy->ctx = ctx;
         cy->spec.assign(inst, inst + n);
-        cy->slot.assign(n, -1);
+        cy->rec_cap.assign(n, 0);
         cy->cost.assign(n, 1);
         cy->adj.resize(n);
         cy->gcpl.assign(n, 1);
         cy->gchunk.assign(n, 1);
-        int64_t comp_off = 0, rec_off = 0, rows = 0, rows64 = 0;
-        int jcap = 1;
+        int64_t comp_off = 0, sum_off = 0, rows = 0;
+        std::vector<int64_t> offset(n, 0);   // into the component or leaf-sum buffer
         for (int k = 0; k < n; ++k) {
             const swv_cycle_instance& I = inst[k];
-            BatchInst b{};
+            BatchInst b{};                   // no model until set_components / set_tree
             b.u = I.u;
             b.v = I.v;
             b.w = I.w;
@@ -237,16 +214,12 @@ int swv_cycle_create(swv_ctx ctx, int n, const swv_cycle_instance* inst, swv_cyc
             b.n_vis = I.n_vis;
             b.prec = SWV_FP64;
             b.sgn = (double)I.sign;
+            b.is_tree = I.route == SWV_ROUTE_TREE;
             rows += I.n_vis;
-            if (I.route == SWV_ROUTE_DIRECT) {
-                rows64 += I.n_vis;
-                b.comp_offset = comp_off;
-                b.n_comp = 0;              // no model until swv_cycle_set_components
+            if (!b.is_tree) {
+                offset[k] = comp_off;
                 comp_off += I.comp_cap;
                 cy->max_comp_cap = std::max(cy->max_comp_cap, (int)I.comp_cap);
-                cy->slot[k] = (int)cy->direct.size();
-                cy->direct.push_back(b);
-                cy->direct_inst.push_back(k);
             } else {
                 // a level-j node exists only above a leaf: at most J records per leaf, plus
                 // the roots
@@ -254,37 +227,25 @@ int swv_cycle_create(swv_ctx ctx, int n, const swv_cycle_instance* inst, swv_cyc
                 if ((uint64_t)cap * sizeof(TRec) > kMaxRecordBytes) {
                     delete cy;
                     return fail(SWV_ENOTSUP, "swv_cycle_create: instance %d: %lld records exceed the "
-                                "traversal's %zu-byte stream limit", k, (long long)cap,
+                                "%zu-byte stream limit", k, (long long)cap,
                                 (size_t)kMaxRecordBytes);
                 }
-                b.rec = nullptr;           // set below, once the record buffer exists
-                b.comp_offset = rec_off;   // offset into the record buffer
-                b.n_roots = 0;             // no model until swv_cycle_set_tree
-                b.J = 1;
-                rec_off += cap;
-                jcap = std::max(jcap, I.tree_level_cap);
-                cy->rec_cap.push_back(cap);
-                cy->slot[k] = (int)cy->tree.size();
-                cy->tree.push_back(b);
-                cy->tree_inst.push_back(k);
+                cy->rec_cap[k] = cap;
+                offset[k] = sum_off;
+                // four in five records of a tree at most are leaves: every four have a parent
+                sum_off += (4 * cap + 4) / 5;
             }
+            cy->inst.push_back(b);
         }
-        // one traversal for every tree of the cycle: the level walker up to its
-        // largest J, else the branch walker at its deepest segment count
-        cy->walker = jcap <= kBatchTreeMaxJ ? 0 : 1;
-        cy->depth = cy->walker == 0 ? jcap : kTreeMaxSeg;
-        cy->vpl = batch_direct_vpl(rows64, ctx->per_lane[kFamDirect64][1], ctx->n_cu);
-        cy->grid_direct = ctx->n_cu * batch_direct_blocks_per_cu(cy->vpl);
-        cy->grid_tree = ctx->n_cu * batch_tree_blocks_per_cu(cy->walker, cy->depth, SWV_FP64);
-        const int64_t waves = (int64_t)cy->grid_direct * (kTabBlock / 64);
+        cy->vpl = batch_direct_vpl(rows, ctx->per_lane[kFamDirect64][1], ctx->n_cu);
+        cy->grid = ctx->n_cu * batch_direct_blocks_per_cu(cy->vpl);
+        const int64_t waves = (int64_t)cy->grid * (kTabBlock / 64);
         const int64_t unit = 64LL * cy->vpl;
         int64_t tile = rows / std::max<int64_t>(1, 16 * waves);
         tile = std::max<int64_t>(unit, std::min<int64_t>(64 * unit, (tile + unit - 1) / unit * unit));
         cy->tile_rows = tile;
-        cy->tree_tile = std::max<int64_t>(64, tile / cy->vpl / 64 * 64);
-        order_items(cy, cy->direct_inst, cy->tile_rows, cy->items_direct);
-        order_items(cy, cy->tree_inst, cy->tree_tile, cy->items_tree);
-        if (cy->items_direct.size() > 0xffffffffull || cy->items_tree.size() > 0xffffffffull) {
+        order_items(cy);
+        if (cy->items.size() > 0xffffffffull) {
             delete cy;
             return fail(SWV_ENOTSUP, "swv_cycle_create: too many work items");
         }
@@ -311,19 +272,16 @@ int swv_cycle_create(swv_ctx ctx, int n, const swv_cycle_instance* inst, swv_cyc
                 partial = std::max(partial, 32 * (size_t)I.comp_cap * (size_t)nch);
             }
         }
-        int rc = dev_alloc(&cy->d_direct, cy->direct.size());
-        if (!rc) rc = dev_alloc(&cy->d_tree, cy->tree.size());
-        if (!rc) rc = dev_alloc(&cy->d_items_direct, cy->items_direct.size());
-        if (!rc) rc = dev_alloc(&cy->d_items_tree, cy->items_tree.size());
+        int rc = dev_alloc(&cy->d_inst, cy->inst.size());
+        if (!rc) rc = dev_alloc(&cy->d_items, cy->items.size());
         if (!rc) rc = dev_alloc(&cy->d_pack, (size_t)std::max<int64_t>(comp_off, 1));
-        if (!rc) rc = dev_alloc(&cy->d_rec, (size_t)std::max<int64_t>(rec_off, 1));
-        if (!rc) rc = dev_alloc(&cy->d_counters, 2);
+        if (!rc) rc = dev_alloc(&cy->d_sum, (size_t)std::max<int64_t>(sum_off, 1));
+        if (!rc) rc = dev_alloc(&cy->d_counters, 1);
         if (!rc) rc = dev_alloc((char**)&cy->d_partial, partial);
         if (!rc) rc = dev_alloc(&cy->d_chi2_part, (size_t)res_blocks);
         if (!rc) {
-            cy->mirror_bytes = (cy->direct.size() + cy->tree.size()) * sizeof(BatchInst) +
-                               (cy->items_direct.size() + cy->items_tree.size()) * sizeof(WorkItem) +
-                               64;
+            cy->mirror_bytes = cy->inst.size() * sizeof(BatchInst) +
+                               cy->items.size() * sizeof(WorkItem) + 64;
             if (hipHostMalloc(&cy->h_mirror, cy->mirror_bytes, hipHostMallocDefault) != hipSuccess) {
                 (void)hipGetLastError();
                 cy->h_mirror = nullptr;
@@ -340,7 +298,8 @@ int swv_cycle_create(swv_ctx ctx, int n, const swv_cycle_instance* inst, swv_cyc
             delete cy;
             return rc;
         }
-        for (size_t d = 0; d < cy->tree.size(); ++d) cy->tree[d].rec = cy->d_rec + cy->tree[d].comp_offset;
+        for (int k = 0; k < n; ++k)
+            cy->inst[k].comp = (cy->inst[k].is_tree ? cy->d_sum : cy->d_pack) + offset[k];
     } catch (const std::bad_alloc&) {
         if (cy) {
             free_cycle(cy);
@@ -364,13 +323,13 @@ int swv_cycle_set_components(swv_cycle cy, int k, int64_t n_comp, const double* 
                     (long long)n_comp, (long long)cy->spec[k].comp_cap);
     if (n_comp > 0 && (!l || !m || !flux))
         return fail(SWV_EINVAL, "swv_cycle_set_components: null component pointer");
-    BatchInst& b = cy->direct[(size_t)cy->slot[k]];
+    BatchInst& b = cy->inst[(size_t)k];
     b.l = l;
     b.m = m;
     b.flux = flux;
     b.n_comp = (int)n_comp;
     cy->cost[k] = std::max<int64_t>(n_comp, 1);
-    order_items(cy, cy->direct_inst, cy->tile_rows, cy->items_direct);
+    order_items(cy);
     cy->dirty = true;
     return SWV_OK;
 }
@@ -382,35 +341,37 @@ int swv_cycle_set_tree(swv_cycle cy, int k, swv_tree t) {
     if (!t) return fail(SWV_EINVAL, "swv_cycle_set_tree: null tree");
     if (t->thresholded)
         return fail(SWV_ENOTSUP, "swv_cycle_set_tree: thresholded trees are not supported in a "
-                                 "captured cycle (its traversal is fixed at capture)");
-    const int d = cy->slot[k];
+                                 "captured cycle");
     if (t->J > cy->spec[k].tree_level_cap)
         return fail(SWV_EINVAL, "swv_cycle_set_tree: J = %d above the instance's cap %d", t->J,
                     cy->spec[k].tree_level_cap);
-    if ((int64_t)t->records.size() > cy->rec_cap[(size_t)d])
+    if ((int64_t)t->records.size() > cy->rec_cap[(size_t)k])
         return fail(SWV_EINVAL, "swv_cycle_set_tree: %zu records above the capacity %lld",
-                    t->records.size(), (long long)cy->rec_cap[(size_t)d]);
-    if (cy->walker == 1 && t->max_branching + 1 > cy->depth)
+                    t->records.size(), (long long)cy->rec_cap[(size_t)k]);
+    if (!tree_supported(t))
         return fail(SWV_ENOTSUP, "swv_cycle_set_tree: %d nested branchings, above %d",
-                    t->max_branching, cy->depth - 1);
+                    t->max_branching, kTreeMaxSeg - 1);
     DeviceGuard g(cy->ctx->device);
     if (!g.ok) return fail(SWV_EHIP, "swv_cycle_set_tree: cannot select device");
-    BatchInst& b = cy->tree[(size_t)d];
-    if (!t->records.empty()) {
-        // ordered after the work already on the stream, which may still read
-        // the previous model's records; the wait keeps the copy's source valid
-        hipError_t e = hipMemcpyAsync((void*)b.rec, t->records.data(),
-                                      t->records.size() * sizeof(TRec), hipMemcpyHostToDevice,
-                                      cy->ctx->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(cy->ctx->stream);
-        if (e != hipSuccess) return hip_fail(e, "swv_cycle_set_tree: record upload");
+    try {
+        BatchInst& b = cy->inst[(size_t)k];
+        const std::vector<CompCell> sum = packed_sum(*t);
+        if (!sum.empty()) {
+            // ordered after the work already on the stream, which may still read
+            // the previous model's sum; the wait keeps the copy's source valid
+            hipError_t e = hipMemcpyAsync(b.comp, sum.data(), sum.size() * sizeof(CompCell),
+                                          hipMemcpyHostToDevice, cy->ctx->stream);
+            if (e == hipSuccess) e = hipStreamSynchronize(cy->ctx->stream);
+            if (e != hipSuccess) return hip_fail(e, "swv_cycle_set_tree: upload");
+        }
+        b.n_comp = (int)sum.size();
+        cy->cost[k] = std::max<int64_t>((int64_t)sum.size(), 1);
+        order_items(cy);
+        cy->dirty = true;
+        return SWV_OK;
+    } catch (const std::bad_alloc&) {
+        return fail(SWV_ENOMEM, "swv_cycle_set_tree: host allocation failed");
     }
-    b.n_roots = (int)t->n_roots;
-    b.J = t->J;
-    cy->cost[k] = (int64_t)t->records.size() + 1;
-    order_items(cy, cy->tree_inst, cy->tree_tile, cy->items_tree);
-    cy->dirty = true;
-    return SWV_OK;
 }
 
 int swv_cycle_run(swv_cycle cy) {

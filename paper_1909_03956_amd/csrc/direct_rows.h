@@ -183,14 +183,22 @@ __device__ __forceinline__ bool load_rows(const int64_t (&j)[VPL], int64_t limit
     return __any(!small);
 }
 
-// All components by one wave.
-template <int VPL>
+// A visibility in the output's type (the sums are FP64 for either).
+__device__ __forceinline__ void store_vis(double2* out, int64_t j, double re, double im) {
+    out[j] = make_double2(re, im);
+}
+__device__ __forceinline__ void store_vis(float2* out, int64_t j, double re, double im) {
+    out[j] = make_float2((float)re, (float)im);
+}
+
+// All components by one wave; put(j, re, im) stores a row.
+template <int VPL, class Put>
 __device__ __forceinline__ void direct_rows_cell(CellPtr T, const int64_t (&j)[VPL], int64_t limit,
                                                  const double* __restrict__ u,
                                                  const double* __restrict__ v,
                                                  const double* __restrict__ w,
                                                  const CompCell* __restrict__ comp, int n_comp,
-                                                 double sgn, double2* __restrict__ out,
+                                                 double sgn, Put&& put,
                                                  int* __restrict__ status) {
     double U[VPL], V[VPL], W[VPL], sr[VPL], si[VPL];
     const bool wide = load_rows<VPL>(j, limit, u, v, w, U, V, W);
@@ -213,20 +221,19 @@ __device__ __forceinline__ void direct_rows_cell(CellPtr T, const int64_t (&j)[V
     for (int i = 0; i < VPL; ++i) {
         if (j[i] < limit) {
             if (!isfinite(U[i] + V[i] + W[i])) atomicOr(status, kStatusNonFinite);
-            out[j[i]] = make_double2(sr[i], sgn * si[i]);
+            put(j[i], sr[i], sgn * si[i]);
         }
     }
 }
 
 // Polynomial phasor, components in list order; comp: records in any address space.
-template <int VPL, class RecPtr>
+template <int VPL, class RecPtr, class Put>
 __device__ __forceinline__ void direct_rows_f64(const int64_t (&j)[VPL], int64_t limit,
                                                 const double* __restrict__ u,
                                                 const double* __restrict__ v,
                                                 const double* __restrict__ w,
                                                 RecPtr comp, int n_comp,
-                                                double sgn, double2* __restrict__ out,
-                                                int* __restrict__ status) {
+                                                double sgn, Put&& put, int* __restrict__ status) {
     double U[VPL], V[VPL], W[VPL], re[VPL], iq[VPL];
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
@@ -252,7 +259,7 @@ __device__ __forceinline__ void direct_rows_f64(const int64_t (&j)[VPL], int64_t
     for (int i = 0; i < VPL; ++i) {
         if (j[i] < limit) {
             if (!isfinite(U[i] + V[i] + W[i])) atomicOr(status, kStatusNonFinite);
-            out[j[i]] = make_double2(re[i], s4 * iq[i]);
+            put(j[i], re[i], s4 * iq[i]);
         }
     }
 }

@@ -68,7 +68,28 @@ __global__ __launch_bounds__(kFewBlock) void k_direct_few(
 #pragma unroll
     for (int i = 0; i < VPL; ++i)
         j[i] = ((int64_t)blockIdx.x * VPL + i) * kFewBlock + threadIdx.x;
-    direct_rows_f64<VPL>(j, n_vis, u, v, w, (const Comp*)comp, n_comp, sgn, out, status);
+    const auto put = [out](int64_t row, double re, double im) { store_vis(out, row, re, im); };
+    direct_rows_f64<VPL>(j, n_vis, u, v, w, (const Comp*)comp, n_comp, sgn, put, status);
+}
+
+// The same of packed components (a tree's leaf sum): scalar loads.
+template <int VPL, class OUT>
+__global__ __launch_bounds__(kFewBlock) void k_direct_few_packed(
+    const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
+    int64_t n_vis, const CompCell* __restrict__ comp, int n_comp, double sgn,
+    OUT* __restrict__ out, int* __restrict__ status) {
+    int64_t j[VPL];
+#pragma unroll
+    for (int i = 0; i < VPL; ++i)
+        j[i] = ((int64_t)blockIdx.x * VPL + i) * kFewBlock + threadIdx.x;
+    const auto put = [out](int64_t row, double re, double im) { store_vis(out, row, re, im); };
+    direct_rows_f64<VPL>(j, n_vis, u, v, w, uniform_ptr(comp), n_comp, sgn, put, status);
+}
+
+static int few_vpl(int64_t n_vis) { return n_vis < (int64_t(1) << 20) ? 1 : 4; }
+static dim3 few_grid(int64_t n_vis) {
+    const int64_t rows = kFewBlock * few_vpl(n_vis);
+    return dim3((unsigned)((n_vis + rows - 1) / rows));
 }
 
 hipError_t launch_direct_few(hipStream_t s, int64_t n_vis, const double* u, const double* v,
@@ -76,9 +97,8 @@ hipError_t launch_direct_few(hipStream_t s, int64_t n_vis, const double* u, cons
                              const double* flux, int sign, double2* out, int* status) {
     if (n_vis <= 0) return hipSuccess;
     if (n_comp >= kTableMinComp) return hipErrorInvalidValue;
-    const int vpl = n_vis < (int64_t(1) << 20) ? 1 : 4;
-    const dim3 grid((unsigned)((n_vis + kFewBlock * vpl - 1) / (kFewBlock * vpl))), blk(kFewBlock);
-    if (vpl == 1)
+    const dim3 grid = few_grid(n_vis), blk(kFewBlock);
+    if (few_vpl(n_vis) == 1)
         k_direct_few<1><<<grid, blk, 0, s>>>(u, v, w, n_vis, l, m, flux, n_comp, (double)sign, out,
                                              status);
     else
@@ -88,29 +108,30 @@ hipError_t launch_direct_few(hipStream_t s, int64_t n_vis, const double* u, cons
 }
 
 // -------------------------------------------------- FP64, table phasor ----
-template <int VPL>
+template <int VPL, class OUT>
 __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_direct_cell(
     const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
     int64_t n_vis, const CompCell* __restrict__ comp, int n_comp, double sgn,
-    double2* __restrict__ out, int* __restrict__ status) {
+    OUT* __restrict__ out, int* __restrict__ status) {
     __shared__ Cell T[kTabCells];
     fill_cells(T);
     const int64_t base = (int64_t)blockIdx.x * (kTabBlock * VPL) + threadIdx.x;
     int64_t j[VPL];
 #pragma unroll
     for (int i = 0; i < VPL; ++i) j[i] = base + (int64_t)i * kTabBlock;
-    direct_rows_cell<VPL>((CellPtr)T, j, n_vis, u, v, w, comp, n_comp, sgn, out, status);
+    const auto put = [out](int64_t row, double re, double im) { store_vis(out, row, re, im); };
+    direct_rows_cell<VPL>((CellPtr)T, j, n_vis, u, v, w, comp, n_comp, sgn, put, status);
 }
 
 // Calls too small to fill the chip by rows alone: SPLIT waves of the workgroup
 // share a row's components, 8 / SPLIT ranges each.  Their range sums meet in
 // LDS (where the table was) and are added in range order.
-template <int VPL, int SPLIT>
+template <int VPL, int SPLIT, class OUT>
 __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) void
 k_direct_cell_split(const double* __restrict__ u, const double* __restrict__ v,
                     const double* __restrict__ w, int64_t n_vis,
                     const CompCell* __restrict__ comp, int n_comp, double sgn,
-                    double2* __restrict__ out, int* __restrict__ status) {
+                    OUT* __restrict__ out, int* __restrict__ status) {
     constexpr int kLanes = kTabBlock / SPLIT;   // lanes that own rows
     constexpr int kRows = kLanes * VPL;         // rows per workgroup
     __shared__ Cell T[kTabCells];
@@ -159,7 +180,7 @@ k_direct_cell_split(const double* __restrict__ u, const double* __restrict__ v,
         }
         const int64_t jr = row0 + r;
         if (!isfinite(u[jr] + v[jr] + w[jr])) atomicOr(status, kStatusNonFinite);
-        out[jr] = make_double2(re, sgn * im);
+        store_vis(out, jr, re, sgn * im);
     }
 }
 
@@ -189,9 +210,10 @@ k_direct_cell_part(const double* __restrict__ u, const double* __restrict__ v,
     }
 }
 
+template <class OUT>
 __global__ __launch_bounds__(64) void k_direct_join(const double2* __restrict__ partial,
                                                     int64_t n_vis, double sgn,
-                                                    double2* __restrict__ out) {
+                                                    OUT* __restrict__ out) {
     const int64_t j = (int64_t)blockIdx.x * 64 + threadIdx.x;
     if (j >= n_vis) return;
     double re = 0.0, im = 0.0;
@@ -207,7 +229,7 @@ __global__ __launch_bounds__(64) void k_direct_join(const double2* __restrict__ 
         re += rr;
         im += ri;
     }
-    out[j] = make_double2(re, sgn * im);
+    store_vis(out, j, re, sgn * im);
 }
 
 // Layout with the least estimated time.  A workgroup's time, in units of one
@@ -249,13 +271,23 @@ size_t direct_partial_bytes(const DirectShape& sh, int64_t n_vis) {
     return sh.parts > 1 ? 64 * sizeof(double2) * (size_t)n_vis : 0;
 }
 
-hipError_t launch_direct_cell(hipStream_t s, const DirectShape& sh, int64_t n_vis, const double* u,
-                              const double* v, const double* w, const CompCell* comp,
-                              int64_t n_comp, int sign, double2* out, double2* partial,
-                              int* status) {
+template <class OUT>
+static hipError_t run_direct_cell(hipStream_t s, const DirectShape& sh, int64_t n_vis,
+                                  const double* u, const double* v, const double* w,
+                                  const CompCell* comp, int64_t n_comp, int sign, OUT* out,
+                                  double2* partial, int* status) {
     if (n_vis <= 0) return hipSuccess;
     const double sg = (double)sign;
     const int nc = (int)n_comp;
+    if (n_comp < kTableMinComp) {
+        if (few_vpl(n_vis) == 1)
+            k_direct_few_packed<1, OUT><<<few_grid(n_vis), dim3(kFewBlock), 0, s>>>(
+                u, v, w, n_vis, comp, nc, sg, out, status);
+        else
+            k_direct_few_packed<4, OUT><<<few_grid(n_vis), dim3(kFewBlock), 0, s>>>(
+                u, v, w, n_vis, comp, nc, sg, out, status);
+        return hipGetLastError();
+    }
     const dim3 blk(kTabBlock);
     const int64_t rows = (int64_t)kTabBlock / sh.split * sh.vpl;
     const unsigned nb = (unsigned)((n_vis + rows - 1) / rows);
@@ -264,22 +296,33 @@ hipError_t launch_direct_cell(hipStream_t s, const DirectShape& sh, int64_t n_vi
         k_direct_cell_part<<<dim3(nb, 8), blk, 0, s>>>(u, v, w, n_vis, comp, nc, partial, status);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        k_direct_join<<<dim3(nb), dim3(64), 0, s>>>(partial, n_vis, sg, out);
+        k_direct_join<OUT><<<dim3(nb), dim3(64), 0, s>>>(partial, n_vis, sg, out);
         return hipGetLastError();
     }
 #define SWV_CELL(V, S) \
     if (sh.vpl == V && sh.split == S)
-    SWV_CELL(4, 1) k_direct_cell<4><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
-    else SWV_CELL(2, 1) k_direct_cell<2><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
-    else SWV_CELL(1, 1) k_direct_cell<1><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
-    else SWV_CELL(2, 2) k_direct_cell_split<2, 2><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
-    else SWV_CELL(2, 4) k_direct_cell_split<2, 4><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
-    else SWV_CELL(1, 2) k_direct_cell_split<1, 2><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
-    else SWV_CELL(1, 4) k_direct_cell_split<1, 4><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
-    else SWV_CELL(1, 8) k_direct_cell_split<1, 8><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    SWV_CELL(4, 1) k_direct_cell<4, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(2, 1) k_direct_cell<2, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(1, 1) k_direct_cell<1, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(2, 2) k_direct_cell_split<2, 2, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(2, 4) k_direct_cell_split<2, 4, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(1, 2) k_direct_cell_split<1, 2, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(1, 4) k_direct_cell_split<1, 4, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(1, 8) k_direct_cell_split<1, 8, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
     else return hipErrorInvalidValue;
 #undef SWV_CELL
     return hipGetLastError();
+}
+
+hipError_t launch_direct_cell(hipStream_t s, const DirectShape& sh, int64_t n_vis, const double* u,
+                              const double* v, const double* w, const CompCell* comp,
+                              int64_t n_comp, int sign, int prec, void* out, double2* partial,
+                              int* status) {
+    if (prec == SWV_FP64)
+        return run_direct_cell(s, sh, n_vis, u, v, w, comp, n_comp, sign, (double2*)out, partial,
+                               status);
+    return run_direct_cell(s, sh, n_vis, u, v, w, comp, n_comp, sign, (float2*)out, partial,
+                           status);
 }
 
 // ------------------------------------------------------------------ F32C ---

@@ -57,42 +57,20 @@ struct DirectShape {
 DirectShape direct_shape(int64_t n_vis, int64_t n_comp, int vpl_max, int n_cu);
 // Bytes of partial sums launch_direct_cell needs (0 if parts is 1).
 size_t direct_partial_bytes(const DirectShape& sh, int64_t n_vis);
-// FP64 direct sum of packed components (table phasor).
+// FP64 direct sum of packed components (fewer than kTableMinComp: polynomial
+// phasor, whatever the layout); prec is that of the output alone (SWV_F32C:
+// complex64).
 hipError_t launch_direct_cell(hipStream_t s, const DirectShape& sh, int64_t n_vis, const double* u,
                               const double* v, const double* w, const CompCell* comp,
-                              int64_t n_comp, int sign, double2* out, double2* partial,
+                              int64_t n_comp, int sign, int prec, void* out, double2* partial,
                               int* status);
 
-struct TreeArgs {
-    const TRec* rec;
-    int n_roots;
-    int J;
-    int seg_depth;                    // 1 + most branching nodes on a root-to-leaf path
-    int pruned;                       // leaves above level J (coefficient thresholding)
-};
-
-// Largest J of the level walker (one state set per level) in the single-tree
-// kernel, and in the batched and cycle kernels; beyond them the branch walker,
-// whose state follows the branching depth.
+// Limits of the trees the entry points predict: levels up to kTreeMaxJ, or at
+// any level fewer than kTreeMaxSeg branching nodes on a root-to-leaf path; a
+// record stream that 32-bit byte offsets address.
 constexpr int kTreeMaxJ = 16;
-constexpr int kBatchTreeMaxJ = 10;
-// Depth up to which the single-tree kernel takes the level walker for every
-// tree; above it (up to kTreeMaxJ) only for trees in which at most three in
-// four internal nodes have a single child.
-constexpr int kTreeLevelAlwaysJ = 10;
-// Largest segment depth of the branch walker (one register set per branching
-// node); it serves every J.
 constexpr int kTreeMaxSeg = 16;
-// The traversals address a record stream by 32-bit byte offsets.
 constexpr size_t kMaxRecordBytes = 0xFFFFFFE0u;
-
-// walker 0: level walker (t.J <= kTreeMaxJ); 1: branch walker
-// (t.seg_depth <= kTreeMaxSeg).  prec SWV_FP64 (complex128 out) or SWV_F32C
-// (FP32 leaf phasors, complex64 out).  A thresholded tree (t.pruned) runs the
-// traversals compiled for leaves above level J, at 64-thread blocks.
-hipError_t launch_tree(hipStream_t s, int walker, int block, int prec, const TreeArgs& t,
-                       int64_t n_vis, const double* u, const double* v, const double* w,
-                       int sign, void* out, int* status);
 
 // ppl: FP64 the most 64-pixel groups per wave, F32C pixels per lane; block: F32C
 // threads per workgroup (the FP64 form's workgroups share a phasor table and
@@ -166,24 +144,20 @@ hipError_t launch_residual(hipStream_t s, int64_t n_vis, const void* obs, const 
 int residual_blocks(int64_t n_vis);
 
 // ------------------------------------------------------------ batched --
-// Packed components of all direct instances; an FP32-compensated instance
-// keeps its 32-byte records at the start of its stretch.
 // One prediction instance as the persistent kernels read it.
 struct BatchInst {
     const double* u;
     const double* v;
     const double* w;
     void* out;
-    const double* l;      // direct: caller's components, packed by the batched ingest
-    const double* m;
+    const double* l;      // direct: caller's components, packed into comp by the batched ingest
+    const double* m;      // (an FP32-compensated instance: Comp records at its start)
     const double* flux;
-    const TRec* rec;      // tree: record stream on the device
+    CompCell* comp;       // packed components; tree: its leaf sum (l null)
     int64_t n_vis;
-    int64_t comp_offset;  // direct: first packed component of this instance
     int n_comp;
-    int n_roots;
-    int J;
     int prec;
+    int is_tree;
     double sgn;
 };
 
@@ -195,7 +169,7 @@ struct WorkItem {
 };
 
 hipError_t launch_batch_ingest(hipStream_t s, const BatchInst* inst, int n_inst, int max_comp,
-                               CompCell* pack, int* status);
+                               int* status);
 hipError_t launch_reset_counters(hipStream_t s, unsigned* counters, int n);
 // Blocks per CU that stay resident for the persistent kernels: FP64 (blocks of
 // kTabBlock threads) and F32C (blocks of kBatchF32Block).
@@ -205,24 +179,13 @@ int batch_direct_blocks_per_cu(int vpl);
 int batch_direct_vpl(int64_t rows, int vpl_max, int n_cu);
 int batch_direct_f32c_blocks_per_cu();
 constexpr int kBatchF32Vpl = 2, kBatchF32Block = 64;
-// walker / depth as for launch_tree: depth is the largest J (walker 0) or
-// segment depth (walker 1) over the plan's trees.
-int batch_tree_blocks_per_cu(int walker, int depth, int prec);
-// FP64 and F32C work items go through separate launches.
+// Items of FP64 direct instances and of trees of either precision go through the
+// first launch, those of F32C direct instances through the second.
 hipError_t launch_batch_direct(hipStream_t s, int vpl, int grid, const BatchInst* inst,
-                               const CompCell* pack, const WorkItem* items, unsigned n_items,
-                               unsigned* counter, int* status);
+                               const WorkItem* items, unsigned n_items, unsigned* counter,
+                               int* status);
 hipError_t launch_batch_direct_f32c(hipStream_t s, int grid, const BatchInst* inst,
-                                    const CompCell* pack, const WorkItem* items,
-                                    unsigned n_items, unsigned* counter, int* status);
-// prec: the precision of every instance the work items refer to.  pruned: some
-// tree holds leaves above level J; only the branch walker at depth kTreeMaxSeg
-// is compiled for that.
-hipError_t launch_batch_tree(hipStream_t s, int walker, int depth, int prec, int grid,
-                             const BatchInst* inst, const WorkItem* items,
-                             unsigned n_items, unsigned* counter, int* status,
-                             bool pruned = false);
-int batch_tree_pruned_blocks_per_cu(int prec);
-constexpr int kBatchTreeBlock = 64;
+                                    const WorkItem* items, unsigned n_items, unsigned* counter,
+                                    int* status);
 
 }  // namespace swv

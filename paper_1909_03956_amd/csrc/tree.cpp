@@ -9,13 +9,11 @@
 //     lambda_j = 1/4 sum_c lambda_{j+1,4k+c}            (Eq. 9)
 //     gamma^m_j = sqrt(A_j)/4 sum_c s^m_c lambda_{j+1}  (Eq. 10)
 //     with ancestors k_j = k_J >> 2(J - j) (section 3.5).
-// The levels are kept as sorted, level-ordered arrays.  For the per-visibility
-// traversal the tree is also written as one depth-first (pre-order) record
-// stream: a root record per level-1 node, then node records, each followed by
-// its children's subtrees in child order, with leaf records at level J.
-// Runs of one-child nodes are marked in the stream, and the largest number of
-// branching nodes on a path is recorded, for a traversal that keeps state
-// only for branching ancestors.
+// The levels are kept as sorted, level-ordered arrays.  The tree is also written
+// as one depth-first (pre-order) record stream: a root record per level-1 node,
+// then node records, each followed by its children's subtrees in child order,
+// with leaf records at level J.  collapse_tree runs down that stream once and
+// leaves what a visibility needs: one weight per leaf.
 #include "tree.h"
 
 #include <algorithm>
@@ -30,12 +28,11 @@ namespace swv {
 // Eq. 10 sign pattern s^m_c (row m, column c).
 static const double kSign[3][4] = {{+1, -1, +1, -1}, {+1, +1, -1, -1}, {+1, -1, -1, +1}};
 
-// The factor a node record's coefficients carry for the traversal:
-// gamma^m_j sigma^m_j = gamma^m_j (sqrt(A_j)/4) sum_c s^m_c eta_{j+1,c}, and the
-// traversal hands up T_{j+1} = 4^(J-j-1) eta_{j+1} and forms the sums relative
-// to the node's first child c0 (times s^m_{c0}), so the record holds
-// h^m = s^m_{c0} gamma^m_j (sqrt(A_j)/4) 4^-(J-j-1) and the row's work for the
-// node's part of Eq. 17 is one product per coefficient.
+// The factor a node record's coefficients carry: gamma^m_j sigma^m_j =
+// gamma^m_j (sqrt(A_j)/4) sum_c s^m_c eta_{j+1,c}, and with T_{j+1} =
+// 4^(J-j-1) eta_{j+1} (the plain sum of the plane waves of the leaves below) and
+// the signs relative to the node's first child c0, the record holds
+// h^m = s^m_{c0} gamma^m_j (sqrt(A_j)/4) 4^-(J-j-1).
 static double record_factor(int j, int J) { return std::ldexp(level_scale(j), -2 * (J - j - 1)); }
 
 static void record_coefficients(double a, unsigned mask, const double* gamma, const bool* keep,
@@ -134,6 +131,54 @@ void build_coefficients(swv_tree_s* t) {
         t->records.push_back(TRec{A1 * L1.lambda[r], 0.0, 0.0, 0ull});
         emit(*t, 1, r, t->records);
     }
+}
+
+// ------------------------------------------------------------- leaf sum --
+// Eq. 17 is linear in the leaves' plane waves e_k: going up the tree, eta and
+// sigma are signed sums of them (Eqs. 9, 10), so
+//     V = sum_roots A_1 lambda_1 4^-(J-1) T_1 + sum_nodes sum_m h^m D^m = sum_k W_k e_k,
+// where W_k is the root's factor plus, at every ancestor, sum_m h^m s^m_c of the
+// child c on the way to the leaf (s relative to the first child, as in the
+// records): the traversal's transpose, run on the coefficients once per tree
+// instead of on the plane waves once per visibility.  For an unthresholded tree
+// W_k is the leaf's flux up to rounding (the wavelet transform's inverse); a
+// leaf above level J stands for 4^(J-j) plane waves.
+namespace {
+
+struct Collapser {
+    const std::vector<TRec>& rec;
+    const int J;
+    std::vector<Comp> out;
+    size_t pos = 0;
+
+    void walk(double value) {
+        const TRec& r = rec[pos++];
+        const unsigned mask = meta_mask(r.meta);
+        if (mask == 0) {
+            out.push_back(Comp{r.a, r.b, r.c, std::ldexp(value, 2 * (J - meta_level(r.meta)))});
+            return;
+        }
+        const int c0 = __builtin_ctz(mask);
+        const double h[3] = {r.a, r.b, r.c};
+        for (int c = c0; c < 4; ++c) {
+            if (!(mask & (1u << c))) continue;
+            double d = 0.0;
+            for (int m = 0; m < 3; ++m) d += kSign[m][c ^ c0] * h[m];
+            walk(value + d);
+        }
+    }
+};
+
+}  // namespace
+
+std::vector<Comp> collapse_tree(const swv_tree_s& t) {
+    Collapser c{t.records, t.J, {}};
+    c.out.reserve(t.leaf_pix.size());
+    for (int64_t r = 0; r < t.n_roots; ++r) {
+        const double root = t.records[c.pos++].a;
+        c.walk(std::ldexp(root, -2 * (t.J - 1)));
+    }
+    return std::move(c.out);
 }
 
 // ------------------------------------------------------------ thresholding --

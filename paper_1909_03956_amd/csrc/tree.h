@@ -29,18 +29,19 @@ struct swv_tree_s {
     std::vector<int64_t> leaf_pix;
     std::vector<double> leaf_l, leaf_m, leaf_nm1, leaf_flux;
     std::vector<swv::TreeLevel> levels;  // levels[j - 1] is level j
-    // depth-first record stream consumed by the device traversal
+    // depth-first record stream
     std::vector<swv::TRec> records;
     int64_t n_roots = 0;
     // most nodes with two or more children on one root-to-leaf path
     int max_branching = 0;
     double build_seconds = 0;
-    // device copies of `records`, one per HIP device id
-    std::map<int, void*> device_records;
+    // device copies of the leaf sum (collapse_tree, packed as components of the
+    // direct kernels), one per HIP device id
+    std::map<int, void*> device_sum;
     // device copies of the leaves packed as direct-sum components (l, m, n - 1,
     // flux), one per HIP device id (swv_predict_tree_leaves)
     std::map<int, void*> device_leaves;
-    // the caller's handle plus one per plan that reads the device records; the
+    // the caller's handle plus one per plan that reads the device copies; the
     // tree is freed when the last of them is released
     int refs = 1;
     // coefficient thresholding (swv_tree_threshold / swv_tree_prune): the tree
@@ -66,6 +67,10 @@ int build_tree(int J, double ra_p, double dec_p, int64_t n, const double* l, con
 // The same from the components' level-J pixel ids (the cross-referenced form).
 int build_tree_pixels(int J, double ra_p, double dec_p, int64_t n, const int64_t* kJ,
                       const double* flux, swv_tree_s* out);
+
+// The tree's visibility (Eq. 17) as a sum over its leaves in stream order:
+// {l, m, n - 1, weight}.
+std::vector<Comp> collapse_tree(const swv_tree_s& t);
 
 // Flat index of gamma^m_{j,k}: 3 x (nodes at levels < j) + 3 k + m.  The
 // retained coefficients of a proportion `fraction`: the round(fraction N)
