@@ -38,26 +38,18 @@ HBM_GBS = 8000.0
 TREE_LEVELS = (8, 9, 10)
 CPU_SHARE = 16                 # host cores of one GPU's share of the host
 
-# Algorithmic flops per unit (FMA = 2, other arithmetic = 1; a rint counts 1):
-#   phase u l + v m + w (n-1): 1 mul + 2 FMA = 5; reduction rint + sub = 2;
-#   phasor: r^2 1, sine polynomial 6 FMA + 1 mul = 13, cosine 6 FMA = 12,
-#   4x identities 8 -> 34.  Per-term work after the phasor:
+# Flops per unit of the FP64 kernels (FMA = 2, other arithmetic = 1):
+#   phase u l + v m + w (n-1): 1 mul + 2 FMA = 5; table cell and rest 3
+#   additions; rest's polynomials: square 1, cosine 2 FMA = 4, sine 1 FMA +
+#   1 mul = 3 -> 8.  Per-term work after them:
 FLOPS = {
-    "direct_fp64": 5 + 2 + 34 + 4,            # MAC: 2 FMA                      -> 45
-    "adjoint": 5 + 2 + 34 + 8,                # complex MAC: 4 FMA               -> 49
-    "grad": 5 + 2 + 34 + 6 + 1 + 6,           # z = conj(y) e; Re z; 3 FMA on Im z -> 54
-    # Haar analysis of the plane wave and Eq. 17 (section 2.4): a node with k
-    # children forms S and D^0..2 from k-1 complex additions each (the signs
-    # +-1 are not arithmetic), then eta = S/4 (2), sigma^m = (sqrt(A_j)/4) D^m
-    # (6) and gamma^m sigma^m into V (3 complex x real MACs, 12)
-    "tree_leaf": 5 + 2 + 34,                  # eta_J at the leaf
-    "tree_node": 2 + 6 + 12,                  # eta, sigma, gamma sigma
-    "tree_child": 2 + 6,                      # every child after a node's first: S, D^0..2
-    "tree_root": 4,                           # A_1 lambda_1 eta_1 into V
+    "direct_fp64": 5 + 3 + 8 + 8,             # node into the two sums: 4 FMA      -> 24
+    "adjoint": 5 + 3 + 8 + 6 + 8,             # y turned by the rest, node into sums -> 30
+    "grad": 5 + 3 + 8 + 6 + 4 + 3 + 6,        # the same; Re z, Im z, 3 FMA on Im z -> 35
 }
-# Of those, the FP64 phasor polynomial (one implementation choice of a
-# complex exponential; a hardware FP64 sincos would need none of them).
-PHASOR_FLOPS = 34
+# Of those, what a complex exponential costs as implemented (a hardware FP64
+# sincos would need none of them).
+PHASOR_FLOPS = 3 + 8
 
 # Algorithmic operations per term of the FP32-compensated forms, by the unit
 # that executes them: the FP64 phase and its exact reduction to [0, 1) (1 mul,
@@ -74,13 +66,9 @@ F32C_OPS = {
 
 
 def tree_flops_per_row(st: dict) -> int:
-    """Algorithmic flops per visibility row of the tree route over a tree with
-    the given stats: every node but the level-1 ones is some node's child, and
-    each internal node has one first child, so the sum over nodes of (k - 1)
-    is leaves - roots."""
-    roots = st["nodes_per_level"][0]
-    return (st["n_leaves"] * FLOPS["tree_leaf"] + st["n_internal"] * FLOPS["tree_node"] +
-            (st["n_leaves"] - roots) * FLOPS["tree_child"] + roots * FLOPS["tree_root"])
+    """Flops per visibility row of the wavelet route over a tree with the given
+    stats: one term of the direct sum per leaf."""
+    return st["n_leaves"] * FLOPS["direct_fp64"]
 
 
 def precision_errors(low, ref, scale: float) -> dict:
@@ -790,7 +778,7 @@ def run_batched(swv, torch, np, dev, configs, peaks=None):
         out[name] = {"ms": round(ms, 2), "Gvis_terms_per_s": round(terms / (ms * 1e-3) / 1e9, 1),
                      "Grows_per_s": round(rows / (ms * 1e-3) / 1e9, 3), "plan": plan.stats(),
                      "roofline": {"bound": "alu",
-                                  "kernel": "k_batch_direct" if name == "direct" else "k_batch_tree",
+                                  "kernel": "k_batch_direct",
                                   "achieved": round(ach, 2), "peak": PEAK_FP64_TFLOPS,
                                   "unit": "TFLOP/s", "frac": round(ach / PEAK_FP64_TFLOPS, 4),
                                   "flops_per_launch": fl, "avg_launch_ms": round(ms, 3),
@@ -1090,7 +1078,7 @@ def main():
     for s in flops:
         routes[s]["TFLOP_per_s"] = round(flops[s] / (med[s] * 1e-3) / 1e12, 2)
         routes[s]["fp64_alu_frac"] = round(flops[s] / (med[s] * 1e-3) / 1e12 / PEAK_FP64_TFLOPS, 4)
-    # the same fractions without the phasor polynomial's flops (34 per phasor)
+    # the same fractions without the phasor's own flops
     phasors = {"direct_fp64": n_vis * n_comp, "adjoint": n_vis * n_pix,
                "grad": n_vis * n_comp}
     for J in TREE_LEVELS:

@@ -777,10 +777,7 @@ int swv_grad_direct(swv_ctx ctx, int64_t n_vis, const double* u, const double* v
     Comp* comp = (Comp*)ctx->comp.p;
     HIPCALL(launch_ingest(ctx->stream, n_comp, l, m, flux, comp, ctx->d_status));
     const int cpl = ctx->per_lane[kFamGrad][size_class(n_vis)];
-    int gblock = 128;
-    int64_t tiles = 1;
-    grad_tiling(cpl, n_comp, &gblock, &tiles);
-    const int64_t chunk = choose_chunk(n_vis, tiles, ctx->n_cu, grad_blocks_per_cu(cpl, gblock));
+    const int64_t chunk = grad_chunk(n_vis, n_comp, cpl, ctx->n_cu);
     const int64_t n_chunks = n_vis > 0 ? (n_vis + chunk - 1) / chunk : 0;
     rc = ensure(ctx, ctx->partial, 32 * (size_t)n_comp * (size_t)(n_chunks > 0 ? n_chunks : 1));
     if (rc) return rc;

@@ -462,11 +462,7 @@ int swv_autotune(swv_ctx ctx, const char* cache_path, int flags) {
                             e = launch_adjoint(s, SWV_F32C, pl, bl, chunk, rows, u, v, w, y, n_pix,
                                                l, m, nm, -1, part, out);
                         } else {
-                            int gblock = 128;
-                            int64_t tiles = 1;
-                            grad_tiling(pl, n_comp, &gblock, &tiles);
-                            const int64_t chunk =
-                                choose_chunk(rows, tiles, ctx->n_cu, grad_blocks_per_cu(pl, gblock));
+                            const int64_t chunk = grad_chunk(rows, n_comp, pl, ctx->n_cu);
                             const int64_t nch = (rows + chunk - 1) / chunk;
                             const int rc = ensure(ctx, ctx->partial, 32 * (size_t)n_comp * nch);
                             if (rc) { result = rc; break; }

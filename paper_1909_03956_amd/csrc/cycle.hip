@@ -261,11 +261,7 @@ int swv_cycle_create(swv_ctx ctx, int n, const swv_cycle_instance* inst, swv_cyc
             }
             if (I.d_flux && I.comp_cap > 0) {
                 const int cpl = ctx->per_lane[kFamGrad][size_class(I.n_vis)];
-                int gblock = 128;
-                int64_t tiles = 1;
-                grad_tiling(cpl, I.comp_cap, &gblock, &tiles);
-                const int64_t chunk =
-                    choose_chunk(I.n_vis, tiles, ctx->n_cu, grad_blocks_per_cu(cpl, gblock));
+                const int64_t chunk = grad_chunk(I.n_vis, I.comp_cap, cpl, ctx->n_cu);
                 const int64_t nch = I.n_vis > 0 ? (I.n_vis + chunk - 1) / chunk : 1;
                 cy->gcpl[k] = cpl;
                 cy->gchunk[k] = chunk;

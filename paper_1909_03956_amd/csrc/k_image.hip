@@ -4,12 +4,10 @@
 //
 // Adjoint and gradients swap the roles of the direct kernel: lanes own the
 // outputs (pixels or components) and every lane of the wave walks the same
-// visibility rows (the adjoint reads them with scalar loads, the gradients
-// stage them through LDS).  The visibility axis is split
-// into fixed chunks; each (chunk, tile) block writes its partial sums, and a
-// second kernel adds the chunks in index order -- deterministic and free of
-// atomics.
-// Block order: chunking.h.
+// visibility rows, read with scalar loads.  The visibility axis is split into
+// fixed chunks whose partial sums a second kernel adds in a fixed order --
+// deterministic and free of atomics.
+#include <algorithm>
 #include <type_traits>
 
 #include "chunking.h"
@@ -39,9 +37,41 @@ constexpr int kAdjWaves = kTabBlock / 64;
 constexpr int kAdjRows = 4;
 constexpr int64_t kAdjMinRows = 32;
 
-// Group range of column c: the groups spread evenly over the columns.
-__device__ __forceinline__ int64_t column_group(int64_t c, int64_t cols, int64_t groups) {
-    return c * groups / cols;
+// What a wave does: rows j0 .. j0 + nrow of chunk `chunk`, the G groups of 64
+// outputs from group g0 (the groups spread evenly over the columns).  active is
+// false past the last job.
+struct WaveJob {
+    int64_t chunk, j0, g0;
+    int nrow, G;
+    bool active;
+};
+__device__ __forceinline__ WaveJob wave_job(int64_t n_vis, int64_t chunk, int64_t groups,
+                                            int64_t cols, int64_t jobs, int64_t run) {
+    const int64_t bid = blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t job = ((bid & 7) * run + (bid >> 3)) * kAdjWaves + wave;
+    WaveJob w;
+    w.active = job < jobs;
+    w.chunk = w.active ? job / cols : 0;
+    const int64_t c = w.active ? job - w.chunk * cols : 0;
+    w.j0 = w.chunk * chunk;
+    w.nrow = __builtin_amdgcn_readfirstlane((int)(w.j0 + chunk < n_vis ? chunk : n_vis - w.j0));
+    w.g0 = c * groups / cols;
+    w.G = __builtin_amdgcn_readfirstlane((int)((c + 1) * groups / cols - w.g0));
+    return w;
+}
+
+// Whether a row of the wave's chunk has phases that need the WIDE form (or are
+// not finite): the whole chunk then goes through it.
+__device__ __forceinline__ bool chunk_is_wide(const WaveJob& job, const double* __restrict__ u,
+                                              const double* __restrict__ v,
+                                              const double* __restrict__ w) {
+    bool big = false;
+    if (job.active)
+        for (int j = threadIdx.x & 63; j < job.nrow; j += 64)
+            big = big || !(fabs(u[job.j0 + j]) + fabs(v[job.j0 + j]) + fabs(w[job.j0 + j]) <
+                           kTabMaxBaseline);
+    return __any(big);
 }
 
 template <int G, bool WIDE>
@@ -129,31 +159,17 @@ __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) 
     const double* __restrict__ pm, const double* __restrict__ pn, int64_t n_pix, double sgn,
     int64_t groups, int64_t cols, int64_t jobs, int64_t run, double2* __restrict__ partial) {
     __shared__ Cell T[kTabCells];
-    const int64_t bid = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t job = ((bid & 7) * run + (bid >> 3)) * kAdjWaves + wave;
-    const bool active = job < jobs;
-    const int64_t chunk_id = active ? job / cols : 0;
-    const int64_t j0 = chunk_id * chunk;
-    const int nrow = __builtin_amdgcn_readfirstlane((int)(j0 + chunk < n_vis ? chunk : n_vis - j0));
-    // rows whose phases need the WIDE form (or are not finite) put the whole
-    // chunk through it
-    bool big = false;
-    if (active)
-        for (int j = lane; j < nrow; j += 64)
-            big = big || !(fabs(u[j0 + j]) + fabs(v[j0 + j]) + fabs(w[j0 + j]) < kTabMaxBaseline);
-    const bool wide = __any(big);
+    const WaveJob job = wave_job(n_vis, chunk, groups, cols, jobs, run);
+    const bool wide = chunk_is_wide(job, u, v, w);
     fill_cells(T);
-    if (!active) return;
-    const int64_t c = job - chunk_id * cols;
-    const int64_t g0 = column_group(c, cols, groups);
-    const int G = __builtin_amdgcn_readfirstlane((int)(column_group(c + 1, cols, groups) - g0));
-    const int64_t q0 = g0 * 64 + lane;
-    double2* part = partial + chunk_id * n_pix;
+    if (!job.active) return;
+    const int64_t j0 = job.j0, q0 = job.g0 * 64 + (threadIdx.x & 63);
+    const int nrow = job.nrow;
+    double2* part = partial + job.chunk * n_pix;
     const CellPtr TP = (CellPtr)T;
 #define SWV_WAVE(N)                                                                               \
     adjoint_wave<N>(TP, u + j0, v + j0, w + j0, y + j0, nrow, wide, pl, pm, pn, q0, n_pix, sgn, part)
-    switch (G) {
+    switch (job.G) {
         case 1: SWV_WAVE(1); break;
         case 2: SWV_WAVE(2); break;
         case 3: SWV_WAVE(3); break;
@@ -284,10 +300,15 @@ __global__ __launch_bounds__(BLOCK) void k_adjoint_f32c(
 // out[p] = sum over chunks c of partial[c][p].
 // Chunk reductions: a block owns kSumCols consecutive outputs (coalesced along
 // x); its kSumQ rows of threads each add the chunks q, q + kSumQ, ... in order,
-// and the kSumQ subtotals are then added by a fixed binary tree in LDS.  The
-// order depends only on the chunk count, so results are run-to-run identical.
-constexpr int kSumCols = 64;
-constexpr int kSumQ = 16;
+// kAhead loads in flight, and the kSumQ subtotals are then added by a fixed
+// binary tree in LDS.  The order depends only on the chunk count, so results are
+// run-to-run identical.  Bound by the latency of a thread's chain and by the few
+// blocks: 16 columns and 64 rows rather than 64 and 16 quarter the chain and
+// quadruple the blocks (300,000 rows x 300 pixels in
+// the F32C form: 120 -> 67 us the whole call).
+constexpr int kSumCols = 16;
+constexpr int kSumQ = 64;
+constexpr int kAhead = 8;
 
 __global__ __launch_bounds__(kSumCols * kSumQ) void k_sum_chunks_c128(
     const double2* __restrict__ partial, int64_t n_chunks, int64_t n, double2* __restrict__ out) {
@@ -296,9 +317,6 @@ __global__ __launch_bounds__(kSumCols * kSumQ) void k_sum_chunks_c128(
     const int64_t p = (int64_t)blockIdx.x * kSumCols + tx;
     double re = 0.0, im = 0.0;
     if (p < n) {
-        // eight loads in flight: the chain of 16 threads' chunks is what
-        // bounds this kernel
-        constexpr int kAhead = 8;
         int64_t c = q;
         for (; c + (kAhead - 1) * kSumQ < n_chunks; c += kAhead * kSumQ) {
             double2 x[kAhead];
@@ -370,35 +388,44 @@ int adjoint_f32c_blocks_per_cu(int ppl, int block) {
     return 1;
 }
 
-// Rows per chunk of the FP64 adjoint.  Workgroups of kAdjWaves jobs run in
-// rounds of two per CU; four rounds rather than one, since the dies' clocks
-// differ, but fewer while the partial sums (one set per chunk) exceed 32 MiB,
-// and whole rounds: the chunk count is the most that fits r of them.  At least
-// kAdjMinRows rows, so that filling the table stays small beside them, and at
-// least 8 chunks from 512 rows on.
-int64_t adjoint_cell_chunk(int64_t n_vis, int64_t n_pix, int ppl, int n_cu) {
+// Rows per chunk of the FP64 adjoint and gradients.  Workgroups of kAdjWaves
+// jobs run in rounds of two per CU; up to four rounds rather than one, since the
+// dies' clocks differ, but fewer while the partial sums (one set of `bytes` per
+// chunk) exceed 32 MiB, and whole rounds: the chunk count is the most that fits
+// r of them.  At least kAdjMinRows rows, so that filling the table stays small
+// beside them, and at least 8 chunks from 512 rows on.
+static int64_t cell_chunk(int64_t n_vis, int64_t cols, int64_t bytes, int n_cu) {
     if (n_vis <= 0) return 1;
-    const int64_t groups = (n_pix + 63) / 64, cols = (groups + ppl - 1) / ppl;
     const int64_t round = (int64_t)n_cu * 2 * kAdjWaves;
-    const int64_t cap = (int64_t(32) << 20) / (16 * (n_pix > 0 ? n_pix : 1));
+    const int64_t cap = (int64_t(32) << 20) / std::max<int64_t>(bytes, 1);
     int64_t chunks = 0;
     for (int64_t r = 4; r >= 1; --r) {
-        chunks = r * round / (cols > 0 ? cols : 1);
+        chunks = r * round / std::max<int64_t>(cols, 1);
         if (chunks <= cap) break;
     }
-    if (chunks > cap) chunks = cap;
-    if (chunks < 8) chunks = 8;
+    chunks = std::max<int64_t>(8, std::min(chunks, cap));
     const int64_t least = n_vis < 512 ? 64 : kAdjMinRows;
-    int64_t chunk = (n_vis + chunks - 1) / chunks;
-    if (chunk < least) chunk = least;
-    return chunk < (int64_t(1) << 30) ? chunk : int64_t(1) << 30;   // rows per chunk fit an int
+    const int64_t chunk = std::max(least, (n_vis + chunks - 1) / chunks);
+    return std::min<int64_t>(chunk, int64_t(1) << 30);   // rows per chunk fit an int
+}
+
+static int64_t columns(int64_t n, int per_lane) {
+    return ((n + 63) / 64 + per_lane - 1) / per_lane;
+}
+
+int64_t adjoint_cell_chunk(int64_t n_vis, int64_t n_pix, int ppl, int n_cu) {
+    return cell_chunk(n_vis, columns(n_pix, ppl), 16 * n_pix, n_cu);
+}
+
+int64_t grad_chunk(int64_t n_vis, int64_t n_comp, int cpl, int n_cu) {
+    return cell_chunk(n_vis, columns(n_comp, cpl), 32 * n_comp, n_cu);
 }
 
 static hipError_t run_adjoint_cell(hipStream_t s, int ppl, int64_t chunk, int64_t n_vis,
                                    const double* u, const double* v, const double* w,
                                    const void* y, int64_t n_pix, const double* l, const double* m,
                                    const double* nm1, int sign, void* partial) {
-    const int64_t groups = (n_pix + 63) / 64, cols = (groups + ppl - 1) / ppl;
+    const int64_t groups = (n_pix + 63) / 64, cols = columns(n_pix, ppl);
     const int64_t jobs = (n_vis + chunk - 1) / chunk * cols;
     const int64_t run = ((jobs + kAdjWaves - 1) / kAdjWaves + 7) / 8;   // workgroups per XCD
     if (run > (int64_t(1) << 27)) return hipErrorInvalidConfiguration;
@@ -440,157 +467,172 @@ hipError_t launch_adjoint(hipStream_t s, int prec, int ppl, int block, int64_t c
 }
 
 // -------------------------------------------------------------- gradients --
-// The gradients need four real sums per component k (CPL per lane) and chunk
-// of rows, with z = conj(y) e:
+// The gradients need four real sums per component k and chunk of rows, with
+// z = conj(y) e:
 //   Z0 = Re sum z                    (flux:      dchi2/dI ~ Re A^H r)
 //   Zu, Zv, Zw = Im sum {u, v, w} z  (positions: d phi/dl = u - w l / n, ...)
-// conj(y) e = (yr - i yi)(c + i s S) = (yr c + yi s S) + i (yr s S - yi c),
-// S = 4 q; the products 4 s y are formed once per row for all CPL components.
-//
-// Rows are staged through LDS in tiles of kGradRowTile: the block loads each
-// tile once with coalesced vector loads and forms 4 s y there, once per row;
-// every wave then reads the rows as LDS broadcasts.  The block is as wide as
-// the component list needs (up to 1024 threads), so that one block covers
-// every component of a chunk and each row is fetched from memory once.
-constexpr int kGradRowTile = 256;
-
-// n_comp_dev, if not null, holds the number of components on the device (a
-// captured major cycle whose model changes between replays): the grid is then
-// sized for n_comp, the capacity, and blocks past the actual count leave.
-template <int CPL, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_grad_partial(
-    const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
-    const double2* __restrict__ y, int64_t n_vis, int64_t chunk, const double* __restrict__ comp,
-    int comp_stride, int64_t n_comp, const int* __restrict__ n_comp_dev, double sgn, int64_t n_chunks,
-    int64_t tiles, int64_t bid0, double* __restrict__ partial) {
-    // one row: u, v, w, yr, yi, 4 s yr, 4 s yi, (pad) -- 64 bytes
-    __shared__ double2 rows[kGradRowTile][4];
-    int64_t chunk_id, tile;
-    chunk_tile(bid0 + blockIdx.x, tiles, chunk_id, tile);
-    if (chunk_id >= n_chunks) return;   // padding of the last XCD group (whole block)
-    if (n_comp_dev) n_comp = *n_comp_dev;
-    if (tile * (BLOCK * CPL) >= n_comp) return;   // no component in this tile (whole block)
-    const int64_t k0 = tile * (BLOCK * CPL) + threadIdx.x;
-    double L[CPL], M[CPL], N[CPL];
-    double z0[CPL], zu[CPL], zv[CPL], zw[CPL];
+// The kernel is the FP64 adjoint's with components for pixels: directions times
+// s, conj(y) turned by the rest of the angle, then by the node; Re z goes
+// straight into its sum, Im z is formed for the three others.  23 FP64
+// instructions per row and component (phase 3, cell 4, rest 5, 4 + 2 + 2 + 3)
+// against 32 with the polynomial phasor, bound by their issue.  Rows come by
+// scalar loads: staged in LDS as broadcasts they would take as long there as the
+// arithmetic does, beside the table's gathers.  261,120 rows x 1,000 components:
+// 0.23 ms (67 % of the issue rate at 2.4 GHz); with its prediction 0.53 -> 0.37 ms.
+template <int G, bool WIDE>
+__device__ __forceinline__ void grad_rows(CellPtr T, const double* u, const double* v,
+                                          const double* w, const double2* y, int nrow,
+                                          const double (&L)[G], const double (&M)[G],
+                                          const double (&N)[G], double (&z)[4][G]) {
+    const auto* U = uniform_ptr(u);
+    const auto* V = uniform_ptr(v);
+    const auto* W = uniform_ptr(w);
+    const auto* Y = uniform_ptr(y);
+    const CellCoefs K = cell_coefs();
+    const auto step = [&](auto rows, int j) {
+        constexpr int R = decltype(rows)::value;
+        double uj[R], vj[R], wj[R], yr[R], yi[R];
 #pragma unroll
-    for (int i = 0; i < CPL; ++i) {
-        int64_t k = k0 + (int64_t)i * BLOCK;
-        k = k < n_comp ? k : n_comp - 1;
-        L[i] = comp[k * comp_stride];
-        M[i] = comp[k * comp_stride + 1];
-        N[i] = comp[k * comp_stride + 2];
-        z0[i] = zu[i] = zv[i] = zw[i] = 0.0;
-    }
-    const int64_t j0 = chunk_id * chunk;
-    const int64_t j1 = j0 + chunk < n_vis ? j0 + chunk : n_vis;
-    const double s4 = 4.0 * sgn;
-    for (int64_t t0 = j0; t0 < j1; t0 += kGradRowTile) {
-        const int nt = (int)(j1 - t0 < kGradRowTile ? j1 - t0 : kGradRowTile);
-        __syncthreads();   // the previous tile has been read by every wave
-        for (int r = threadIdx.x; r < nt; r += BLOCK) {
-            const int64_t j = t0 + r;
-            const double2 yj = y[j];
-            rows[r][0] = make_double2(u[j], v[j]);
-            rows[r][1] = make_double2(w[j], yj.x);
-            rows[r][2] = make_double2(yj.y, s4 * yj.x);
-            rows[r][3] = make_double2(s4 * yj.y, 0.0);
+        for (int r = 0; r < R; ++r) {
+            uj[r] = U[j + r];
+            vj[r] = V[j + r];
+            wj[r] = W[j + r];
+            yr[r] = Y[j + r].x;
+            yi[r] = Y[j + r].y;
         }
-        __syncthreads();
-        // wave-uniform trip count, kept in scalar registers
-        const int nrow = __builtin_amdgcn_readfirstlane(nt);
-        // the next row's LDS reads are issued before this row's arithmetic,
-        // so their latency is hidden behind it (the last row reads itself
-        // again, in bounds)
-        double2 na = rows[0][0], nb = rows[0][1], nc = rows[0][2], nd = rows[0][3];
-#pragma unroll 1
-        for (int r = 0; r < nrow; ++r) {
-            const double2 a = na, b = nb, c2 = nc, d = nd;
-            const int rn = r + 1 < nrow ? r + 1 : r;
-            na = rows[rn][0];
-            nb = rows[rn][1];
-            nc = rows[rn][2];
-            nd = rows[rn][3];
-            const double uj = a.x, vj = a.y, wj = b.x;
-            const double yr = b.y, yi = c2.x, y4r = c2.y, y4i = d.x;
 #pragma unroll
-            for (int i = 0; i < CPL; ++i) {
-                double c, q;
-                cis2pi_q(reduced_phase(uj, vj, wj, L[i], M[i], N[i]), c, q);
-                // Re z goes straight into its sum: two FMAs, no product of its own
-                z0[i] = fma(c, yr, fma(q, y4i, z0[i]));
-                const double zi = fma(q, y4r, -(yi * c));
-                zu[i] = fma(uj, zi, zu[i]);
-                zv[i] = fma(vj, zi, zv[i]);
-                zw[i] = fma(wj, zi, zw[i]);
+        for (int r = 0; r < R; ++r) {
+            Cell e[G];
+            double d[G];
+#pragma unroll
+            for (int i = 0; i < G; ++i)
+                e[i] = find_cell<WIDE>(T, fma(uj[r], L[i], fma(vj[r], M[i], wj[r] * N[i])), d[i],
+                                       K.magic);
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                double cr, sr;
+                cell_rest(K, d[i], cr, sr);
+                const double tr = fma(cr, yr[r], sr * yi[r]);
+                const double ti = fma(sr, yr[r], -(cr * yi[r]));
+                z[0][i] = fma(e[i].x, tr, z[0][i]);
+                z[0][i] = fma(-e[i].y, ti, z[0][i]);
+                const double zi = fma(e[i].x, ti, e[i].y * tr);
+                z[1][i] = fma(uj[r], zi, z[1][i]);
+                z[2][i] = fma(vj[r], zi, z[2][i]);
+                z[3][i] = fma(wj[r], zi, z[3][i]);
             }
         }
-    }
+    };
+    int j = 0;
+#pragma unroll 1
+    for (; j + kAdjRows <= nrow; j += kAdjRows) step(std::integral_constant<int, kAdjRows>(), j);
+#pragma unroll 1
+    for (; j < nrow; ++j) step(std::integral_constant<int, 1>(), j);
+}
+
+template <int G>
+__device__ __forceinline__ void grad_wave(CellPtr T, const double* __restrict__ u,
+                                          const double* __restrict__ v,
+                                          const double* __restrict__ w,
+                                          const double2* __restrict__ y, int nrow, bool wide,
+                                          const double* __restrict__ comp, int comp_stride,
+                                          int64_t k0, int64_t n_comp, double sgn,
+                                          double* __restrict__ partial) {
+    double L[G], M[G], N[G], z[4][G];
 #pragma unroll
-    for (int i = 0; i < CPL; ++i) {
-        const int64_t k = k0 + (int64_t)i * BLOCK;
-        if (k < n_comp) {
-            double* o = partial + (chunk_id * 4) * n_comp + k;
-            o[0 * n_comp] = z0[i];
-            o[1 * n_comp] = zu[i];
-            o[2 * n_comp] = zv[i];
-            o[3 * n_comp] = zw[i];
-        }
+    for (int i = 0; i < G; ++i) {
+        int64_t k = k0 + (int64_t)i * 64;
+        k = k < n_comp ? k : n_comp - 1;
+        L[i] = sgn * comp[k * comp_stride];
+        M[i] = sgn * comp[k * comp_stride + 1];
+        N[i] = sgn * comp[k * comp_stride + 2];
+        z[0][i] = z[1][i] = z[2][i] = z[3][i] = 0.0;
+    }
+    if (__builtin_expect(wide, 0))
+        grad_rows<G, true>(T, u, v, w, y, nrow, L, M, N, z);
+    else
+        grad_rows<G, false>(T, u, v, w, y, nrow, L, M, N, z);
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+        const int64_t k = k0 + (int64_t)i * 64;
+        if (k < n_comp)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) partial[t * n_comp + k] = z[t][i];
     }
 }
 
-__global__ __launch_bounds__(kSumCols * kSumQ) void k_grad_finish(
+// n_comp_dev, if not null, holds the number of components on the device (a
+// captured major cycle whose model changes between replays): the jobs are then
+// those of n_comp, the capacity, and waves past the actual count leave.
+__global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_grad_cell(
+    const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
+    const double2* __restrict__ y, int64_t n_vis, int64_t chunk, const double* __restrict__ comp,
+    int comp_stride, int64_t n_comp, const int* __restrict__ n_comp_dev, double sgn,
+    int64_t groups, int64_t cols, int64_t jobs, int64_t run, double* __restrict__ partial) {
+    __shared__ Cell T[kTabCells];
+    if (n_comp_dev) n_comp = *n_comp_dev;
+    WaveJob job = wave_job(n_vis, chunk, groups, cols, jobs, run);
+    job.active = job.active && job.g0 * 64 < n_comp;
+    const bool wide = chunk_is_wide(job, u, v, w);
+    fill_cells(T);
+    if (!job.active) return;
+    const int64_t j0 = job.j0, k0 = job.g0 * 64 + (threadIdx.x & 63);
+    double* part = partial + job.chunk * 4 * n_comp;
+    const CellPtr TP = (CellPtr)T;
+#define SWV_WAVE(N)                                                                              \
+    grad_wave<N>(TP, u + j0, v + j0, w + j0, y + j0, job.nrow, wide, comp, comp_stride, k0, n_comp, \
+                 sgn, part)
+    switch (job.G) {
+        case 1: SWV_WAVE(1); break;
+        case 2: SWV_WAVE(2); break;
+        case 3: SWV_WAVE(3); break;
+        default: SWV_WAVE(4); break;
+    }
+#undef SWV_WAVE
+}
+
+// A block owns kGradCols components; thread (q, t, x) adds sum t of component x
+// over the chunks q, q + kGradQ, ... in order, then as in the chunk reduction.
+constexpr int kGradCols = 16;
+constexpr int kGradQ = 16;
+
+__global__ __launch_bounds__(4 * kGradCols * kGradQ) void k_grad_finish(
     const double* __restrict__ partial, int64_t n_chunks, const double* __restrict__ comp,
     int comp_stride, int64_t n_comp, const int* __restrict__ n_comp_dev, double sgn, double alpha,
     double* __restrict__ d_flux, double* __restrict__ d_l, double* __restrict__ d_m) {
-    __shared__ double red[4][kSumQ][kSumCols];
+    __shared__ double red[kGradQ][4][kGradCols];
     if (n_comp_dev) n_comp = *n_comp_dev;
-    if ((int64_t)blockIdx.x * kSumCols >= n_comp) return;   // whole block past the count
-    const int tx = threadIdx.x % kSumCols, q = threadIdx.x / kSumCols;
-    const int64_t k = (int64_t)blockIdx.x * kSumCols + tx;
-    double z[4] = {0, 0, 0, 0};
+    if ((int64_t)blockIdx.x * kGradCols >= n_comp) return;   // whole block past the count
+    const int tx = threadIdx.x % kGradCols, t = threadIdx.x / kGradCols % 4,
+              q = threadIdx.x / (4 * kGradCols);
+    const int64_t k = (int64_t)blockIdx.x * kGradCols + tx;
+    double z = 0.0;
     if (k < n_comp) {
-        for (int64_t c = q; c < n_chunks; c += kSumQ)
-            for (int t = 0; t < 4; ++t) z[t] += partial[(c * 4 + t) * n_comp + k];
+        const double* p = partial + t * n_comp + k;
+        int64_t c = q;
+        for (; c + (kAhead - 1) * kGradQ < n_chunks; c += kAhead * kGradQ) {
+            double x[kAhead];
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) x[i] = p[(c + i * kGradQ) * 4 * n_comp];
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) z += x[i];
+        }
+        for (; c < n_chunks; c += kGradQ) z += p[c * 4 * n_comp];
     }
-    for (int t = 0; t < 4; ++t) red[t][q][tx] = z[t];
+    red[q][t][tx] = z;
     __syncthreads();
-    for (int h = kSumQ / 2; h > 0; h >>= 1) {
-        if (q < h)
-            for (int t = 0; t < 4; ++t) red[t][q][tx] += red[t][q + h][tx];
+    for (int h = kGradQ / 2; h > 0; h >>= 1) {
+        if (q < h) red[q][t][tx] += red[q + h][t][tx];
         __syncthreads();
     }
-    if (q != 0 || k >= n_comp) return;
-    const double z0 = red[0][0][tx], zu = red[1][0][tx], zv = red[2][0][tx],
-                 zw = red[3][0][tx];
+    if (q != 0 || t != 0 || k >= n_comp) return;
+    const double z0 = red[0][0][tx], zu = red[0][1][tx], zv = red[0][2][tx], zw = red[0][3][tx];
     const double* c = comp + k * comp_stride;   // l, m, n - 1, I
     const double n = 1.0 + c[2];
     const double f = -alpha * c[3] * sgn * 2.0 * M_PI;
     d_flux[k] = alpha * z0;
     d_l[k] = f * (zu - (c[0] / n) * zw);
     d_m[k] = f * (zv - (c[1] / n) * zw);
-}
-
-template <int CPL, int BLOCK>
-static int grad_occ() {
-    static const int v = resident_blocks(k_grad_partial<CPL, BLOCK>, BLOCK);
-    return v;
-}
-
-void grad_tiling(int cpl, int64_t n_comp, int* block, int64_t* tiles) {
-    int b = 128;
-    while (b < 1024 && (int64_t)b * cpl < n_comp) b *= 2;
-    *block = b;
-    *tiles = n_comp > 0 ? (n_comp + (int64_t)b * cpl - 1) / ((int64_t)b * cpl) : 1;
-}
-
-int grad_blocks_per_cu(int cpl, int block) {
-#define SWV_OCC_G(C, B) if (cpl == C && block == B) return grad_occ<C, B>();
-    SWV_OCC_G(1, 128) SWV_OCC_G(1, 256) SWV_OCC_G(1, 512) SWV_OCC_G(1, 1024)
-    SWV_OCC_G(2, 128) SWV_OCC_G(2, 256) SWV_OCC_G(2, 512) SWV_OCC_G(2, 1024)
-    SWV_OCC_G(4, 128) SWV_OCC_G(4, 256) SWV_OCC_G(4, 512) SWV_OCC_G(4, 1024)
-#undef SWV_OCC_G
-    return 1;
 }
 
 hipError_t launch_grad(hipStream_t s, int cpl, int64_t chunk, int64_t n_vis, const double* u,
@@ -601,28 +643,20 @@ hipError_t launch_grad(hipStream_t s, int cpl, int64_t chunk, int64_t n_vis, con
     if (cpl != 1 && cpl != 2 && cpl != 4) return hipErrorInvalidValue;
     const int64_t n_chunks = n_vis > 0 ? (n_vis + chunk - 1) / chunk : 0;
     if (n_chunks > 0) {
-        int block = 128;
-        int64_t tiles = 1;
-        grad_tiling(cpl, n_comp, &block, &tiles);
-        const double sg = (double)sign;
-        const double2* yy = (const double2*)y;
-        launch_slabs(xcd_padded(n_chunks) * tiles, [&](int64_t b0, unsigned nb) {
-#define SWV_RUN_G(C, B)                                                                      \
-    if (cpl == C && block == B)                                                              \
-        k_grad_partial<C, B><<<dim3(nb), dim3(B), 0, s>>>(u, v, w, yy, n_vis, chunk, comp,         \
-                                                          comp_stride, n_comp, n_comp_dev, sg, n_chunks, tiles, b0,  \
-                                                          partial);
-            SWV_RUN_G(1, 128) SWV_RUN_G(1, 256) SWV_RUN_G(1, 512) SWV_RUN_G(1, 1024)
-            SWV_RUN_G(2, 128) SWV_RUN_G(2, 256) SWV_RUN_G(2, 512) SWV_RUN_G(2, 1024)
-            SWV_RUN_G(4, 128) SWV_RUN_G(4, 256) SWV_RUN_G(4, 512) SWV_RUN_G(4, 1024)
-#undef SWV_RUN_G
-        });
+        const int64_t groups = (n_comp + 63) / 64, cols = columns(n_comp, cpl);
+        const int64_t jobs = n_chunks * cols;
+        const int64_t run = ((jobs + kAdjWaves - 1) / kAdjWaves + 7) / 8;   // workgroups per XCD
+        if (run > (int64_t(1) << 27)) return hipErrorInvalidConfiguration;
+        k_grad_cell<<<dim3((unsigned)(8 * run)), dim3(kTabBlock), 0, s>>>(
+            u, v, w, (const double2*)y, n_vis, chunk, comp, comp_stride, n_comp, n_comp_dev,
+            (double)sign, groups, cols, jobs, run, partial);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    k_grad_finish<<<dim3((unsigned)((n_comp + kSumCols - 1) / kSumCols)), dim3(kSumCols * kSumQ),
-                    0, s>>>(partial, n_chunks, comp, comp_stride, n_comp, n_comp_dev, (double)sign, alpha,
-                            d_flux, d_l, d_m);
+    k_grad_finish<<<dim3((unsigned)((n_comp + kGradCols - 1) / kGradCols)),
+                    dim3(4 * kGradCols * kGradQ), 0, s>>>(partial, n_chunks, comp, comp_stride,
+                                                          n_comp, n_comp_dev, (double)sign, alpha,
+                                                          d_flux, d_l, d_m);
     return hipGetLastError();
 }
 

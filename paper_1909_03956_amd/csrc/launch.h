@@ -119,18 +119,16 @@ hipError_t launch_grid_finish(hipStream_t s, const GridGeom& g, const double* pa
                               int64_t n_chunks, int nx, int ny, int cx, int cy, int64_t n_vis,
                               double* img);
 
-// Rows per chunk of the FP64 adjoint.
+// Rows per chunk of the FP64 adjoint and of the gradients (ppl, cpl: groups of 64
+// outputs per wave at most).
 int64_t adjoint_cell_chunk(int64_t n_vis, int64_t n_pix, int ppl, int n_cu);
-// Resident blocks per compute unit of the F32C adjoint and gradient kernels.
+int64_t grad_chunk(int64_t n_vis, int64_t n_comp, int cpl, int n_cu);
+// Resident blocks per compute unit of the F32C adjoint.
 int adjoint_f32c_blocks_per_cu(int ppl, int block);
-// Gradient kernel block (128 .. 1024 threads, the smallest that holds every
-// component at cpl per lane, else 1024) and the component tiles it leaves.
-void grad_tiling(int cpl, int64_t n_comp, int* block, int64_t* tiles);
-int grad_blocks_per_cu(int cpl, int block);
 
 // comp: packed components, {l, m, n - 1, I} at the start of every comp_stride
 // doubles (4 for Comp, 8 for CompCell).  n_comp_dev (optional): the actual component count on the device, at most
-// n_comp, which then only sizes the grid (see k_grad_partial).
+// n_comp, which then only sizes the grid (see k_grad_cell).
 hipError_t launch_grad(hipStream_t s, int cpl, int64_t chunk, int64_t n_vis, const double* u,
                        const double* v, const double* w, const void* y, const double* comp,
                        int comp_stride, int64_t n_comp, int sign, double alpha, double* partial,
