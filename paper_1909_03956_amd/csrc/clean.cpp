@@ -12,19 +12,39 @@
 
 namespace swv {
 
-int cross_reference(int J, double ra_p, double dec_p, int nx, int ny, double cell, int64_t* pix) {
-    const Frame F = make_frame(ra_p, dec_p);
+int check_on_disk(int nx, int ny, double cell) {
     const int cx = nx / 2, cy = ny / 2;
+    // l^2 + m^2 grows with |l| and |m|, rounding included: the corner farthest
+    // from the centre decides
+    const double lc = (double)cx * cell, mc = (double)cy * cell;
+    if (lc * lc + mc * mc < 1.0) return SWV_OK;
     for (int iy = 0; iy < ny; ++iy)
         for (int ix = 0; ix < nx; ++ix) {
             const double l = (double)(ix - cx) * cell, m = (double)(iy - cy) * cell;
             if (!(l * l + m * m < 1.0))
                 return fail(SWV_EDOMAIN, "cross reference: pixel (%d, %d) is off the unit disk",
                             ix, iy);
-            ld xyz[3];
-            lm_to_xyz(F, l, m, xyz);
-            pix[(int64_t)iy * nx + ix] = ang2pix(J, xyz);
         }
+    return SWV_OK;
+}
+
+void cross_reference_pixels(int J, double ra_p, double dec_p, int nx, int ny, double cell,
+                            int64_t n, const int64_t* image_pix, int64_t* pix) {
+    const Frame F = make_frame(ra_p, dec_p);
+    const int cx = nx / 2, cy = ny / 2;
+    for (int64_t i = 0; i < n; ++i) {
+        const int64_t p = image_pix ? image_pix[i] : i;
+        const int iy = (int)(p / nx), ix = (int)(p - (int64_t)iy * nx);
+        ld xyz[3];
+        lm_to_xyz(F, (double)(ix - cx) * cell, (double)(iy - cy) * cell, xyz);
+        pix[i] = ang2pix(J, xyz);
+    }
+}
+
+int cross_reference(int J, double ra_p, double dec_p, int nx, int ny, double cell, int64_t* pix) {
+    const int rc = check_on_disk(nx, ny, cell);
+    if (rc) return rc;
+    cross_reference_pixels(J, ra_p, dec_p, nx, ny, cell, (int64_t)nx * ny, nullptr, pix);
     return SWV_OK;
 }
 
