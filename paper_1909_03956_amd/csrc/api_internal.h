@@ -37,7 +37,7 @@ struct swv_ctx_s {
     swv::DevBuf hog;        // per-workgroup peaks of the grid-wide Hogbom cycle
     void* fft_plan = nullptr;   // batched 2-D FFT plan of the degridding predictor
     void* scratch = nullptr;    // device address of the allocation-free entry points' array
-    int fft_shape[3] = {0, 0, 0};
+    int fft_shape[2] = {0, 0};
     int* d_status = nullptr;  // deferred-error bits raised by kernels
     int n_cu = 256;
     int per_lane[swv::kFamilies][2];

@@ -19,7 +19,6 @@
 #include <chrono>
 #include <climits>
 #include <cmath>
-#include <vector>
 
 #include "api_internal.h"
 #include "device_math.h"
@@ -32,7 +31,6 @@ constexpr int kDgBlock = 256;
 constexpr int kQuad = 100;           // Gauss-Legendre nodes of the kernel transform
 constexpr int kMaxSupport = 16;
 constexpr double kBetaPerW = 2.3;
-constexpr double kTwoPi = 6.283185307179586476925286766559;
 
 // Gauss-Legendre nodes and weights on [-1, 1]: Newton's method on P_n, with
 // P_n from the three-term recurrence k P_k = (2k - 1) z P_{k-1} - (k - 1) P_{k-2}
@@ -72,33 +70,50 @@ __host__ __device__ __forceinline__ double es_phi(double z, double beta) {
 
 // phi_hat(f) = sum_k coef_k cos(2 pi f x_k): Gauss-Legendre in theta with
 // x = (W / 2) sin(theta), coef_k = exp(beta (cos theta_k - 1)) cos theta_k w_k (pi / 2) (W / 2)
-__device__ double es_hat(double f, const double* __restrict__ xk,
-                         const double* __restrict__ coef) {
+struct Quadrature {
+    double x[kQuad], coef[kQuad];
+};
+
+__device__ __forceinline__ double cos_turns(double t) {
+    double c, q4;
+    cis2pi_q(t - rint(t), c, q4);
+    return c;
+}
+
+__device__ double es_hat(double f, const Quadrature& q) {
     double s = 0.0;
-    for (int k = 0; k < kQuad; ++k) s += coef[k] * cos(kTwoPi * f * xk[k]);
+    for (int k = 0; k < kQuad; ++k) s = fma(q.coef[k], cos_turns(f * q.x[k]), s);
     return s;
 }
 
-__global__ __launch_bounds__(kDgBlock) void k_hat_1d(int n, const double* __restrict__ f,
-                                                     const double* __restrict__ xk,
-                                                     const double* __restrict__ coef,
-                                                     double* __restrict__ out) {
-    const int i = blockIdx.x * kDgBlock + threadIdx.x;
-    if (i < n) out[i] = es_hat(f[i], xk, coef);
+// Kernel transforms of both image axes: h[i] at offset (i - nx / 2) / Nx for i <
+// nx, then those of y.  A wave per value: the few hundred of them are bound by
+// the length of a thread's chain.
+__global__ __launch_bounds__(kDgBlock) void k_hat_1d(int nx, int ny, int Nx, int Ny, Quadrature q,
+                                                     double* __restrict__ h) {
+    const int i = (int)(blockIdx.x * (kDgBlock / 64) + (threadIdx.x >> 6));
+    if (i >= nx + ny) return;
+    const double f = i < nx ? (double)(i - nx / 2) / Nx : (double)(i - nx - ny / 2) / Ny;
+    double s = 0.0;
+    for (int k = threadIdx.x & 63; k < kQuad; k += 64)
+        s = fma(q.coef[k], cos_turns(f * q.x[k]), s);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((threadIdx.x & 63) == 0) h[i] = s;
 }
 
 // base[p] = I[p] / (hy hx hw), sn[p] = n_p - 1 - c
 __global__ __launch_bounds__(kDgBlock) void k_degrid_prep(
     int nx, int ny, double cell, double c, double dw, const double* __restrict__ image,
-    const double* __restrict__ hx, const double* __restrict__ hy, const double* __restrict__ xk,
-    const double* __restrict__ coef, double* __restrict__ base, double* __restrict__ sn) {
+    const double* __restrict__ hx, const double* __restrict__ hy, Quadrature quad,
+    double* __restrict__ base, double* __restrict__ sn) {
     const int64_t p = (int64_t)blockIdx.x * kDgBlock + threadIdx.x;
     if (p >= (int64_t)nx * ny) return;
     const int iy = (int)(p / nx), ix = (int)(p - (int64_t)iy * nx);
     const double l = (double)(ix - nx / 2) * cell, m = (double)(iy - ny / 2) * cell;
     const double r2 = l * l + m * m;
     const double s = -r2 / (1.0 + sqrt(1.0 - r2)) - c;
-    const double hw = es_hat(dw * s, xk, coef);
+    const double hw = es_hat(dw * s, quad);
     base[p] = image[p] / (hy[iy] * hx[ix] * hw);
     sn[p] = s;
 }
@@ -130,77 +145,125 @@ __global__ __launch_bounds__(kDgBlock) void k_fill_planes(
     G[i] = out;
 }
 
-// One visibility per thread.  T = W + 1 cells per direction starting at
-// ceil(x - W/2): the last one lies outside the support unless x - W/2 is an
-// integer, and then takes weight phi(+-1) like the first; outside it the
-// weight is exactly 0.
+// A group of LV lanes per visibility (4, 8 or 16, the least that holds W): lane a
+// takes cell ceil(x - W/2) + a of every grid row, so a row of the stencil is one
+// contiguous read of the group, and the 3 W kernel weights are one exponential
+// per lane and direction.  With a visibility per lane every 16-byte cell was a
+// cache line of its own, and each lane computed all 3 W weights.  707,616 rows,
+// W = 10: 3.5 -> 0.9 ms, 12 TB/s of cells; half of the lines come from L1, the
+// rest at about 20 TB/s from L2, which bounds it.  Handing each XCD a contiguous
+// run of rows took 1.16 ms.
+//
+// Cell W of a direction lies outside the support unless x - W/2 is an integer,
+// and then takes weight phi(+-1) like the first; it is a rare extra step.
+__device__ __forceinline__ int wrap_index(int64_t k, int n) {
+    int r;
+    if (k == (int64_t)(int)k)
+        r = (int)k % n;
+    else
+        r = (int)(k % n);
+    return r < 0 ? r + n : r;
+}
+
 template <int W>
 __global__ __launch_bounds__(kDgBlock) void k_degrid(
     int64_t n_vis, const double* __restrict__ u, const double* __restrict__ v,
     const double* __restrict__ w, int Nx, int Ny, int64_t n_planes, double cell, double w0,
     double dw, double c, double beta, int sign, const double2* __restrict__ G,
     double2* __restrict__ out) {
-    constexpr int T = W + 1;
-    const int64_t j = (int64_t)blockIdx.x * kDgBlock + threadIdx.x;
-    if (j >= n_vis) return;
+    constexpr int LV = W <= 4 ? 4 : (W <= 8 ? 8 : 16);
+    const int a = threadIdx.x & (LV - 1);
+    const int64_t j = (int64_t)blockIdx.x * (kDgBlock / LV) + threadIdx.x / LV;
+    if (j >= n_vis) return;   // whole groups
     const double h = 0.5 * W;
     const double xi = u[j] * Nx * cell, zeta = v[j] * Ny * cell, eta = (w[j] - w0) / dw;
     // non-finite or absurd coordinates give NaN, never an index
     if (!(fabs(xi) < 0x1p50 && fabs(zeta) < 0x1p50 && eta >= 0.0 && eta <= (double)n_planes)) {
-        out[j] = make_double2(NAN, NAN);
+        if (a == 0) out[j] = make_double2(NAN, NAN);
         return;
     }
     const int64_t x0 = (int64_t)ceil(xi - h), y0 = (int64_t)ceil(zeta - h);
     const int64_t q0 = (int64_t)ceil(eta - h);
-    double fx[T], fy[T];
-    int cxk[T];
+    // the lane's weights, and those of cell W
+    const double fx = a < W ? es_phi((xi - (double)(x0 + a)) / h, beta) : 0.0;
+    const double fya = a < W ? es_phi((zeta - (double)(y0 + a)) / h, beta) : 0.0;
+    double fqa = 0.0;
+    if (a < W && q0 + a >= 0 && q0 + a < n_planes) fqa = es_phi((eta - (double)(q0 + a)) / h, beta);
+    const double fxe = es_phi((xi - (double)(x0 + W)) / h, beta);
+    const double fye = es_phi((zeta - (double)(y0 + W)) / h, beta);
+    const double fqe = q0 + W < n_planes ? es_phi((eta - (double)(q0 + W)) / h, beta) : 0.0;
+    double fy[W];
+    int row[W + 1];
+    int ky = wrap_index(y0, Ny);
 #pragma unroll
-    for (int a = 0; a < T; ++a) {
-        fx[a] = es_phi((xi - (double)(x0 + a)) / h, beta);
-        fy[a] = es_phi((zeta - (double)(y0 + a)) / h, beta);
-        int64_t k = (x0 + a) % Nx;
-        cxk[a] = (int)(k < 0 ? k + Nx : k);
+    for (int b = 0; b <= W; ++b) {
+        if (b < W) fy[b] = __shfl(fya, b, LV);
+        row[b] = ky * Nx;   // below 2^30
+        if (++ky == Ny) ky = 0;
     }
-    double vr = 0.0, vi = 0.0;
+    // sum over planes and rows of one column of cells
+    const auto column = [&](int kx, double& sr, double& si) {
+        sr = si = 0.0;
 #pragma unroll 1
-    for (int b3 = 0; b3 < T; ++b3) {
-        const int64_t q = q0 + b3;
-        if (q < 0 || q >= n_planes) continue;
-        const double fq = es_phi((eta - (double)q) / h, beta);
-        if (fq == 0.0) continue;
-        const double2* Gq = G + q * (int64_t)Nx * Ny;
-        double pr = 0.0, pi = 0.0;
-#pragma unroll 1
-        for (int b = 0; b < T; ++b) {
-            int64_t ky = (y0 + b) % Ny;
-            ky = ky < 0 ? ky + Ny : ky;
-            const double2* row = Gq + ky * Nx;
-            double rr = 0.0, ri = 0.0;
+        for (int t = 0; t <= W; ++t) {
+            const double fq = t < W ? __shfl(fqa, t, LV) : fqe;
+            if (fq == 0.0) continue;
+            const double2* P = G + (q0 + t) * ((int64_t)Nx * Ny) + kx;
+            double pr = 0.0, pi = 0.0;
 #pragma unroll
-            for (int a = 0; a < T; ++a) {
-                const double2 g = row[cxk[a]];
-                rr = fma(fx[a], g.x, rr);
-                ri = fma(fx[a], g.y, ri);
+            for (int b = 0; b < W; ++b) {
+                const double2 g = P[row[b]];
+                pr = fma(fy[b], g.x, pr);
+                pi = fma(fy[b], g.y, pi);
             }
-            pr = fma(fy[b], rr, pr);
-            pi = fma(fy[b], ri, pi);
+            if (__builtin_expect(fye != 0.0, 0)) {
+                const double2 g = P[row[W]];
+                pr = fma(fye, g.x, pr);
+                pi = fma(fye, g.y, pi);
+            }
+            sr = fma(fq, pr, sr);
+            si = fma(fq, pi, si);
         }
-        vr = fma(fq, pr, vr);
-        vi = fma(fq, pi, vi);
+    };
+    const int k0 = wrap_index(x0, Nx);
+    double vr = 0.0, vi = 0.0;
+    if (a < W) {
+        column((k0 + a) % Nx, vr, vi);
+        vr *= fx;
+        vi *= fx;
+    }
+    if (__builtin_expect(fxe != 0.0, 0)) {   // the same for the whole group
+        double er, ei;
+        column((k0 + W) % Nx, er, ei);
+        if (a == 0) {
+            vr = fma(fxe, er, vr);
+            vi = fma(fxe, ei, vi);
+        }
+    }
+#pragma unroll
+    for (int o = LV / 2; o > 0; o >>= 1) {
+        vr += __shfl_xor(vr, o, LV);
+        vi += __shfl_xor(vi, o, LV);
     }
     const double t = w[j] * c;
     double cs, q4;
     cis2pi_q(t - rint(t), cs, q4);
     const double sn = sign * 4.0 * q4;
-    out[j] = make_double2(vr * cs - vi * sn, vr * sn + vi * cs);
+    if (a == 0) out[j] = make_double2(vr * cs - vi * sn, vr * sn + vi * cs);
 }
 
 template <int W>
 void launch_degrid_w(hipStream_t s, int64_t n_vis, const double* u, const double* v,
                      const double* w, int Nx, int Ny, int64_t nq, double cell, double w0,
                      double dw, double c, double beta, int sign, const double2* G, double2* out) {
-    k_degrid<W><<<(unsigned)((n_vis + kDgBlock - 1) / kDgBlock), kDgBlock, 0, s>>>(
-        n_vis, u, v, w, Nx, Ny, nq, cell, w0, dw, c, beta, sign, G, out);
+    constexpr int LV = W <= 4 ? 4 : (W <= 8 ? 8 : 16);
+    // rows in slabs that stay within a launch's grid
+    constexpr int64_t kSlab = int64_t(1) << 28;
+    for (int64_t j = 0; j < n_vis; j += kSlab) {
+        const int64_t n = std::min<int64_t>(kSlab, n_vis - j);
+        k_degrid<W><<<(unsigned)((n * LV + kDgBlock - 1) / kDgBlock), kDgBlock, 0, s>>>(
+            n, u + j, v + j, w + j, Nx, Ny, nq, cell, w0, dw, c, beta, sign, G, out + j);
+    }
 }
 
 using DegridFn = void (*)(hipStream_t, int64_t, const double*, const double*, const double*, int,
@@ -264,6 +327,23 @@ __global__ __launch_bounds__(kDgBlock) void k_minmax_final(int n_part,
     }
 }
 
+// Nodes and coefficients of es_hat (the Gauss-Legendre rule is made once).
+Quadrature quadrature(int support, double beta) {
+    static const struct Rule {
+        double z[kQuad], wt[kQuad];
+        Rule() { gauss_legendre(kQuad, z, wt); }
+    } rule;
+    Quadrature q;
+    for (int k = 0; k < kQuad; ++k) {
+        // x = (W / 2) sin(theta), theta = (pi / 2) z: a smooth integrand
+        const double th = 0.5 * M_PI * rule.z[k];
+        q.x[k] = 0.5 * support * std::sin(th);
+        q.coef[k] = std::exp(beta * (std::cos(th) - 1.0)) * std::cos(th) * rule.wt[k] *
+                    (0.5 * M_PI) * (0.5 * support);
+    }
+    return q;
+}
+
 unsigned blocks_of(int64_t n) { return (unsigned)((n + kDgBlock - 1) / kDgBlock); }
 
 }  // namespace
@@ -320,6 +400,7 @@ extern "C" int swv_predict_degrid(swv_ctx ctx, int nx, int ny, double cell, cons
     const int nb = (int)std::min<int64_t>(kMinmaxBlocks, (n_vis + kDgBlock - 1) / kDgBlock);
     k_minmax_partial<<<nb, kDgBlock, 0, s>>>(n_vis, w, d_mm + 2);
     k_minmax_final<<<1, kDgBlock, 0, s>>>(nb, d_mm + 2, d_mm);
+    const Quadrature quad = quadrature(support, beta);   // while the GPU finds the range
     double mm[2];
     hipError_t e = hipMemcpyAsync(mm, d_mm, 16, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -334,67 +415,51 @@ extern "C" int swv_predict_degrid(swv_ctx ctx, int nx, int ny, double cell, cons
                     "swv_predict_degrid: %.0f w planes of %d x %d cells exceed 64 GiB "
                     "(field too wide for the w range)", nq_f, Nx, Ny);
     const int64_t nq = (int64_t)nq_f;
-    // scratch: planes, then base, sn, hx, hy, quadrature
+    // planes go through the FFT a few at a time: a plan for each plane count (it
+    // follows the rows' w range) took 8 ms whenever the count changed.  As many
+    // planes as keep a transform busy; the last batch may run over the end.
+    const int64_t batch = cells >= (1 << 21) ? 1 : cells >= (1 << 20) ? 2 : cells >= (1 << 19) ? 4 : 8;
+    const int64_t nq_pad = (nq + batch - 1) / batch * batch;
+    // scratch: planes, then base, sn, hx, hy
     const int64_t n_pix = (int64_t)nx * ny;
     const size_t plane_bytes = 16 * (size_t)(nq * cells);
-    const size_t extra = 8 * (size_t)(2 * n_pix + 2 * (nx + ny) + 2 * kQuad) + 256;
-    rc = ensure(ctx, ctx->degrid, plane_bytes + extra);
+    const size_t padded = 16 * (size_t)(nq_pad * cells);
+    const size_t extra = 8 * (size_t)(2 * n_pix + nx + ny) + 256;
+    rc = ensure(ctx, ctx->degrid, padded + extra);
     if (rc) return rc;
     double2* G = (double2*)ctx->degrid.p;
-    double* base = (double*)((char*)ctx->degrid.p + plane_bytes);
+    double* base = (double*)((char*)ctx->degrid.p + padded);
     double* sn = base + n_pix;
     double* hx = sn + n_pix;
     double* hy = hx + nx;
-    double* fxy = hy + ny;              // nx + ny transform arguments
-    double* xk = fxy + nx + ny;
-    double* coef = xk + kQuad;
-    {
-        std::vector<double> z(kQuad), wt(kQuad), hx_k(kQuad), hc(kQuad), f((size_t)(nx + ny));
-        gauss_legendre(kQuad, z.data(), wt.data());
-        // x = (W / 2) sin(theta), theta = (pi / 2) z: a smooth integrand
-        for (int k = 0; k < kQuad; ++k) {
-            const double th = 0.5 * M_PI * z[k];
-            hx_k[k] = 0.5 * support * std::sin(th);
-            hc[k] = std::exp(beta * (std::cos(th) - 1.0)) * std::cos(th) * wt[k] * (0.5 * M_PI) *
-                    (0.5 * support);
-        }
-        for (int i = 0; i < nx; ++i) f[i] = (double)(i - cx) / Nx;
-        for (int i = 0; i < ny; ++i) f[nx + i] = (double)(i - cy) / Ny;
-        e = hipMemcpyAsync(xk, hx_k.data(), 8 * kQuad, hipMemcpyHostToDevice, s);
-        if (e == hipSuccess) e = hipMemcpyAsync(coef, hc.data(), 8 * kQuad, hipMemcpyHostToDevice, s);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(fxy, f.data(), 8 * (size_t)(nx + ny), hipMemcpyHostToDevice, s);
-        // the host vectors must outlive the copies
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return hip_fail(e, "swv_predict_degrid: upload");
-    }
-    k_hat_1d<<<blocks_of(nx + ny), kDgBlock, 0, s>>>(nx + ny, fxy, xk, coef, hx);
-    k_degrid_prep<<<blocks_of(n_pix), kDgBlock, 0, s>>>(nx, ny, cell, c, dw, image, hx, hy, xk,
-                                                        coef, base, sn);
+    k_hat_1d<<<(unsigned)((nx + ny + kDgBlock / 64 - 1) / (kDgBlock / 64)), kDgBlock, 0, s>>>(
+        nx, ny, Nx, Ny, quad, hx);
+    k_degrid_prep<<<blocks_of(n_pix), kDgBlock, 0, s>>>(nx, ny, cell, c, dw, image, hx, hy, quad,
+                                                        base, sn);
     k_fill_planes<<<blocks_of(nq * cells), kDgBlock, 0, s>>>(nx, ny, Nx, Ny, nq, w0, dw, sign,
                                                              base, sn, G);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "swv_predict_degrid: plane fill");
-    // batched 2-D transform of every plane (plan cached per context and shape)
-    if (!ctx->fft_plan || ctx->fft_shape[0] != Nx || ctx->fft_shape[1] != Ny ||
-        ctx->fft_shape[2] != nq) {
+    // batched 2-D transforms of the planes (plan cached per context and shape)
+    if (!ctx->fft_plan || ctx->fft_shape[0] != Nx || ctx->fft_shape[1] != Ny) {
         destroy_fft_plan(ctx->fft_plan);
         ctx->fft_plan = nullptr;
         hipfftHandle plan = nullptr;
         int n2[2] = {Ny, Nx};
         if (hipfftPlanMany(&plan, 2, n2, nullptr, 1, (int)cells, nullptr, 1, (int)cells,
-                           HIPFFT_Z2Z, (int)nq) != HIPFFT_SUCCESS)
+                           HIPFFT_Z2Z, (int)batch) != HIPFFT_SUCCESS)
             return fail(SWV_EHIP, "swv_predict_degrid: hipfftPlanMany failed");
         ctx->fft_plan = (void*)plan;
         ctx->fft_shape[0] = Nx;
         ctx->fft_shape[1] = Ny;
-        ctx->fft_shape[2] = (int)nq;
     }
     hipfftHandle plan = (hipfftHandle)ctx->fft_plan;
-    if (hipfftSetStream(plan, s) != HIPFFT_SUCCESS ||
-        hipfftExecZ2Z(plan, (hipfftDoubleComplex*)G, (hipfftDoubleComplex*)G,
-                      sign < 0 ? HIPFFT_FORWARD : HIPFFT_BACKWARD) != HIPFFT_SUCCESS)
-        return fail(SWV_EHIP, "swv_predict_degrid: hipfftExecZ2Z failed");
+    bool ok = hipfftSetStream(plan, s) == HIPFFT_SUCCESS;
+    for (int64_t q = 0; q < nq && ok; q += batch) {
+        hipfftDoubleComplex* p = (hipfftDoubleComplex*)(G + q * cells);
+        ok = hipfftExecZ2Z(plan, p, p, sign < 0 ? HIPFFT_FORWARD : HIPFFT_BACKWARD) == HIPFFT_SUCCESS;
+    }
+    if (!ok) return fail(SWV_EHIP, "swv_predict_degrid: hipfftExecZ2Z failed");
     kDegrid[support](s, n_vis, u, v, w, Nx, Ny, nq, cell, w0, dw, c, beta, sign, G,
                      (double2*)vis_out);
     e = hipGetLastError();
