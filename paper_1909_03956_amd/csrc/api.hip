@@ -65,10 +65,6 @@ void tune_defaults(swv_ctx ctx) {
     // block: the same time as 128 threads, with 1.0x the rows' bytes fetched
     // from memory instead of 1.4x
     ctx->block[kFamAdjoint][1] = 256;
-    // FP32-compensated direct sum under 2^20 rows: two rows per lane share
-    // each component's scalar loads (0.230 against 0.264 ms for 1 per lane in
-    // the autotuner's small case, 2^18 rows; the two tie on its 2^22 rows)
-    ctx->per_lane[kFamDirect32][0] = 2;
 }
 
 int size_class(int64_t rows) { return rows < (int64_t(1) << 20) ? 0 : 1; }
@@ -168,7 +164,7 @@ static std::vector<CompCell> packed_leaves(swv_tree t) {
     for (size_t k = 0; k < n; ++k) {
         const double l = t->leaf_l[k], m = t->leaf_m[k], nm1 = t->leaf_nm1[k], F = t->leaf_flux[k];
         c[k] = comp_cell(l, m, nm1, F);
-        ((Comp*)(c.data() + n))[k] = Comp{l, m, nm1, F};
+        ((CompF*)(c.data() + n))[k] = CompF{l, m, nm1, (float)F, 0.0f};
     }
     return c;
 }
@@ -356,6 +352,23 @@ static int run_direct_cell(swv_ctx ctx, int64_t n_vis, const double* u, const do
     return SWV_OK;
 }
 
+// The FP32-compensated direct sum over packed components.
+static int run_direct_f32c(swv_ctx ctx, int64_t n_vis, const double* u, const double* v,
+                           const double* w, const CompF* comp, int64_t n_comp, int sign,
+                           void* vis_out) {
+    const DirectShape sh = direct_shape_f32c(n_vis, n_comp, ctx->n_cu);
+    const size_t bytes = direct_partial_bytes(sh, n_vis);
+    if (bytes) {
+        const int rc = ensure(ctx, ctx->partial, bytes);
+        if (rc) return rc;
+    }
+    const int sc = size_class(n_vis);
+    HIPCALL(launch_direct_f32c(ctx->stream, sh, ctx->per_lane[kFamDirect32][sc],
+                               ctx->block[kFamDirect32][sc], n_vis, u, v, w, comp, n_comp, sign,
+                               vis_out, (double2*)ctx->partial.p, ctx->d_status));
+    return SWV_OK;
+}
+
 int swv_predict_direct(swv_ctx ctx, int64_t n_vis, const double* u, const double* v,
                        const double* w, int64_t n_comp, const double* l, const double* m,
                        const double* flux, int sign, int prec, void* vis_out) {
@@ -374,7 +387,7 @@ int swv_predict_direct(swv_ctx ctx, int64_t n_vis, const double* u, const double
                                   (double2*)vis_out, ctx->d_status));
         return SWV_OK;
     }
-    const size_t rec = prec == SWV_FP64 ? sizeof(CompCell) : sizeof(Comp);
+    const size_t rec = prec == SWV_FP64 ? sizeof(CompCell) : sizeof(CompF);
     rc = ensure(ctx, ctx->comp, rec * (size_t)(n_comp > 0 ? n_comp : 1));
     if (rc) return rc;
     if (prec == SWV_FP64) {
@@ -382,13 +395,9 @@ int swv_predict_direct(swv_ctx ctx, int64_t n_vis, const double* u, const double
         HIPCALL(launch_ingest(ctx->stream, n_comp, l, m, flux, comp, ctx->d_status));
         return run_direct_cell(ctx, n_vis, u, v, w, comp, n_comp, sign, SWV_FP64, vis_out);
     }
-    Comp* comp = (Comp*)ctx->comp.p;
+    CompF* comp = (CompF*)ctx->comp.p;
     HIPCALL(launch_ingest(ctx->stream, n_comp, l, m, flux, comp, ctx->d_status));
-    const int sc = size_class(n_vis);
-    HIPCALL(launch_direct_f32c(ctx->stream, ctx->per_lane[kFamDirect32][sc],
-                               ctx->block[kFamDirect32][sc], n_vis, u, v, w, comp, n_comp, sign,
-                               vis_out, ctx->d_status));
-    return SWV_OK;
+    return run_direct_f32c(ctx, n_vis, u, v, w, comp, n_comp, sign, vis_out);
     TRY_END
 }
 
@@ -561,11 +570,7 @@ int swv_predict_tree_leaves(swv_ctx ctx, swv_tree t, int64_t n_vis, const double
     const int64_t n = (int64_t)t->leaf_pix.size();
     if (prec == SWV_FP64)
         return run_direct_cell(ctx, n_vis, u, v, w, comp, n, sign, SWV_FP64, vis_out);
-    const int sc = size_class(n_vis);
-    HIPCALL(launch_direct_f32c(ctx->stream, ctx->per_lane[kFamDirect32][sc],
-                               ctx->block[kFamDirect32][sc], n_vis, u, v, w,
-                               (const Comp*)(comp + n), n, sign, vis_out, ctx->d_status));
-    return SWV_OK;
+    return run_direct_f32c(ctx, n_vis, u, v, w, (const CompF*)(comp + n), n, sign, vis_out);
     TRY_END
 }
 

@@ -414,12 +414,12 @@ int swv_autotune(swv_ctx ctx, const char* cache_path, int flags) {
     for (const F& x : fills)
         k_fill<<<dim3((unsigned)((x.n + 255) / 256)), dim3(256), 0, s>>>(x.p, x.n, seed++, x.lo, x.hi);
     CompCell* comp = nullptr;
-    Comp* comp32 = nullptr;
+    CompF* comp32 = nullptr;
     {
-        int rc = ensure(ctx, ctx->comp, (sizeof(CompCell) + sizeof(Comp)) * n_comp);
+        int rc = ensure(ctx, ctx->comp, (sizeof(CompCell) + sizeof(CompF)) * n_comp);
         if (rc) return rc;
         comp = (CompCell*)ctx->comp.p;
-        comp32 = (Comp*)(comp + n_comp);
+        comp32 = (CompF*)(comp + n_comp);
         hipError_t e = launch_ingest(s, n_comp, l, m, f, comp, ctx->d_status);
         if (e == hipSuccess) e = launch_ingest(s, n_comp, l, m, f, comp32, ctx->d_status);
         if (e != hipSuccess) return hip_fail(e, "autotune ingest");
@@ -448,8 +448,8 @@ int swv_autotune(swv_ctx ctx, const char* cache_path, int flags) {
                                                    n_comp, -1, SWV_FP64, out, nullptr,
                                                    ctx->d_status);
                         } else if (fam == kFamDirect32) {
-                            e = launch_direct_f32c(s, pl, bl, rows, u, v, w, comp32, n_comp, -1,
-                                                   out, ctx->d_status);
+                            e = launch_direct_f32c(s, DirectShape(), pl, bl, rows, u, v, w, comp32,
+                                                   n_comp, -1, out, nullptr, ctx->d_status);
                         } else if (fam == kFamAdjoint) {
                             // in the FP32-compensated form: `block` is its alone
                             const int64_t tiles = (n_pix + (int64_t)pl * bl - 1) / ((int64_t)pl * bl);

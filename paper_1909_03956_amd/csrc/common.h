@@ -14,6 +14,12 @@ struct alignas(32) Comp {
     double l, m, nm1, I;
 };
 
+// The same for the FP32-compensated direct kernels: their products take I in FP32.
+struct alignas(32) CompF {
+    double l, m, nm1;
+    float I, unused;
+};
+
 // One packed component of the FP64 direct kernels (64 bytes): the same, and the
 // coefficients of the phasor inside a table cell times the flux.
 struct alignas(64) CompCell {

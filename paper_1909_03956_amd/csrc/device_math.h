@@ -39,6 +39,30 @@ __device__ __forceinline__ double fract_phase(double u, double v, double w, doub
     return __builtin_amdgcn_fract(fma(u, l, fma(v, m, w * nm1)));
 }
 
+// 1.5 2^20: a phase added to it rounds to 2^-32 turns, and its fraction modulo 1
+// is the sum's low 32 bits, as a signed number in [-1/2, 1/2) turns.
+constexpr double kTurnMagic = 1.5 * 0x1p20;
+// Rows whose |u| + |v| + |w| stays below this have |phase| < 2^19 for every
+// direction with |l|, |m| <= 1 and |n - 1| <= 2, as the magic number asks.
+constexpr double kTurnMaxBaseline = 0x1p18;
+
+// The phase reduced to [-1/2, 1/2) turns in FP32.  FAST: the three products enter
+// a sum that starts at the magic number, so the reduction costs nothing, and the
+// conversion to FP32 is that of an integer: 3 FP64 and 2 FP32 instructions,
+// against 4 FP64 ones and a conversion from FP64.  Its roundings (three of at
+// most 2^-33 turns) are far below the FP32 rounding of the result, at most 2^-26
+// turns; fract's [0, 1) rounds by up to 2^-25.
+template <bool FAST>
+__device__ __forceinline__ float turns_f32(double u, double v, double w, double l, double m,
+                                           double nm1, double magic) {
+    if constexpr (FAST) {
+        const double t = fma(u, l, fma(v, m, fma(w, nm1, magic)));
+        return (float)(int)__double_as_longlong(t) * 0x1p-32f;
+    } else {
+        return (float)fract_phase(u, v, w, l, m, nm1);
+    }
+}
+
 // Fused multiply-add as one 3-operand v_fma_f64 on VGPRs: the same rounding
 // as fma(), but never the two-address form (a copy of the addend into the
 // destination, then v_fmac_f64) that the compiler picks when the addend is a
@@ -48,6 +72,13 @@ __device__ __forceinline__ double fma_v(double a, double b, double c) {
     double d;
     asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
     return d;
+}
+
+// A constant held in a vector register.
+__device__ __forceinline__ double vector_const(double x) {
+    double v = x;
+    asm("" : "+v"(v));
+    return v;
 }
 
 template <bool VOP3>
@@ -92,7 +123,7 @@ __host__ __device__ __forceinline__ void cis2pi_q_vop3(double r, double& c, doub
     cis2pi_q_impl<true>(r, c, q);
 }
 
-// FP32 phasor of a reduced phase r in cycles (the callers pass r in [0, 1)):
+// FP32 phasor of a reduced phase r in cycles (the callers pass |r| <= 1):
 // cos(2 pi r), sin(2 pi r) from the hardware transcendental unit (v_cos_f32 /
 // v_sin_f32 take the angle in revolutions and are valid on [-256, 256]).
 __device__ __forceinline__ void cis2pi_f32(float r, float& c, float& s) {

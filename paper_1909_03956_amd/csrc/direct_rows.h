@@ -23,6 +23,8 @@
 // them give the same bits, and partial sums stay short.
 #pragma once
 
+#include <type_traits>
+
 #include "device_math.h"
 #include "launch.h"
 #include "phasor_table.h"
@@ -42,6 +44,11 @@ __device__ __forceinline__ Comp pack_component(double L, double M, double I, int
     return Comp{L, M, -r2 / (1.0 + sqrt(1.0 - r2)), I};
 }
 
+__device__ __forceinline__ CompF pack_component_f32c(double L, double M, double I, int& bad) {
+    const Comp c = pack_component(L, M, I, bad);
+    return CompF{c.l, c.m, c.nm1, (float)c.I, 0.0f};
+}
+
 __device__ __forceinline__ CompCell pack_component_cell(double L, double M, double I, int& bad) {
     const Comp c = pack_component(L, M, I, bad);
     return comp_cell(c.l, c.m, c.nm1, c.I);
@@ -52,10 +59,10 @@ using CompCellPtr = const __attribute__((address_space(4))) CompCell*;
 // Borders of the summation order.
 struct CompRanges {
     int n, A, B;
-    __host__ __device__ explicit CompRanges(int n_comp)
+    __host__ __device__ explicit CompRanges(int n_comp, int least = 32)
         : n(n_comp), A((int)(((int64_t)n_comp + 7) / 8)), B(0) {
         B = (A + 7) / 8;
-        B = B < 32 ? 32 : B;
+        B = B < least ? least : B;
     }
     // components [begin, end) of range a, sub-range b
     __host__ __device__ int begin(int a, int b) const {
@@ -163,14 +170,14 @@ __device__ __forceinline__ void range_sums(CellPtr T, CompCellPtr cp, const Comp
     }
 }
 
-// Rows j[0 .. VPL) of a lane, clamped to the last one.  Returns whether the
-// phases of some row of the wave need the WIDE form (or are not finite).
+// Rows j[0 .. VPL) of a lane, clamped to the last one.  Returns whether some row
+// of the wave has |u| + |v| + |w| of `most` or more (or is not finite).
 template <int VPL>
 __device__ __forceinline__ bool load_rows(const int64_t (&j)[VPL], int64_t limit,
                                           const double* __restrict__ u,
                                           const double* __restrict__ v,
-                                          const double* __restrict__ w, double (&U)[VPL],
-                                          double (&V)[VPL], double (&W)[VPL]) {
+                                          const double* __restrict__ w, double most,
+                                          double (&U)[VPL], double (&V)[VPL], double (&W)[VPL]) {
     bool small = true;
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
@@ -178,7 +185,7 @@ __device__ __forceinline__ bool load_rows(const int64_t (&j)[VPL], int64_t limit
         U[i] = u[jj];
         V[i] = v[jj];
         W[i] = w[jj];
-        small = small && fabs(U[i]) + fabs(V[i]) + fabs(W[i]) < kTabMaxBaseline;
+        small = small && fabs(U[i]) + fabs(V[i]) + fabs(W[i]) < most;
     }
     return __any(!small);
 }
@@ -201,7 +208,7 @@ __device__ __forceinline__ void direct_rows_cell(CellPtr T, const int64_t (&j)[V
                                                  double sgn, Put&& put,
                                                  int* __restrict__ status) {
     double U[VPL], V[VPL], W[VPL], sr[VPL], si[VPL];
-    const bool wide = load_rows<VPL>(j, limit, u, v, w, U, V, W);
+    const bool wide = load_rows<VPL>(j, limit, u, v, w, kTabMaxBaseline, U, V, W);
 #pragma unroll
     for (int i = 0; i < VPL; ++i) sr[i] = si[i] = 0.0;
     const CompRanges R(n_comp);
@@ -264,63 +271,113 @@ __device__ __forceinline__ void direct_rows_f64(const int64_t (&j)[VPL], int64_t
     }
 }
 
-// FP64 phase and reduction; FP32 phasor, products and Kahan-compensated sums.
+// FP32-compensated form: FP64 phase; FP32 phasor, products and Kahan sums.
+// Components come in fours: their products and the running compensation meet in a
+// chain of FMAs, then one Kahan step, so a component costs a quarter of a step
+// (the chain's roundings stay within a few 2^-24 of the four terms); then a pair
+// and a single one.  Per row and component 3 FP64 instructions, 2 FP32 for the
+// phase, the hardware sine and cosine, 3.5 FP32 for the sums.  1,263,601 rows x
+// 1,999 components: 0.92 -> 0.79 ms (from 4 FP64, a conversion from FP64 and 5
+// FP32, in pairs).
+//
+// The list is summed in the FP64 kernels' two-level order with sub-ranges of at
+// least kF32cSub components; their compensated sums enter the ranges' and the
+// total in FP64.
+constexpr int kF32cSub = 128;
+
+template <int VPL, bool FAST, class CompPtr>
+__device__ __forceinline__ void add_components_f32c(CompPtr cp, double magic, int k0, int k1,
+                                                    const double (&U)[VPL], const double (&V)[VPL],
+                                                    const double (&W)[VPL], double (&re)[VPL],
+                                                    double (&im)[VPL]) {
+    float sr[VPL], si[VPL], cr[VPL], ci[VPL];
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) sr[i] = cr[i] = si[i] = ci[i] = 0.0f;
+    const auto step = [&](auto count, int k) {
+        constexpr int N = decltype(count)::value;
+        CompF c[N];
+#pragma unroll
+        for (int b = 0; b < N; ++b)
+            c[b] = CompF{cp[k + b].l, cp[k + b].m, cp[k + b].nm1, cp[k + b].I, 0.0f};
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) {
+            float yr = -cr[i], yi = -ci[i];
+#pragma unroll
+            for (int b = N - 1; b >= 0; --b) {
+                float co, sn;
+                cis2pi_f32(turns_f32<FAST>(U[i], V[i], W[i], c[b].l, c[b].m, c[b].nm1, magic), co,
+                           sn);
+                yr = fmaf(c[b].I, co, yr);
+                yi = fmaf(c[b].I, sn, yi);
+            }
+            kahan_step(yr, sr[i], cr[i]);
+            kahan_step(yi, si[i], ci[i]);
+        }
+    };
+    int k = k0;
+#pragma unroll 1
+    for (; k + 4 <= k1; k += 4) step(std::integral_constant<int, 4>(), k);
+    if (k + 2 <= k1) {
+        step(std::integral_constant<int, 2>(), k);
+        k += 2;
+    }
+    if (k < k1) step(std::integral_constant<int, 1>(), k);
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) {
+        re[i] += (double)sr[i] - (double)cr[i];
+        im[i] += (double)si[i] - (double)ci[i];
+    }
+}
+
+// The sums of ranges [a0, a1), handed to put(a, re, im) as each is complete.
+template <int VPL, bool FAST, class CompPtr, class Put>
+__device__ __forceinline__ void range_sums_f32c(CompPtr cp, const CompRanges& R, int a0, int a1,
+                                                const double (&U)[VPL], const double (&V)[VPL],
+                                                const double (&W)[VPL], Put&& put) {
+    const double magic = vector_const(kTurnMagic);
+#pragma unroll 1
+    for (int a = a0; a < a1; ++a) {
+        double rr[VPL], ri[VPL];
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) rr[i] = ri[i] = 0.0;
+        const int last = (int)R.end_of(a);
+#pragma unroll 1
+        for (int k0 = a * R.A; k0 < last; k0 += R.B)
+            add_components_f32c<VPL, FAST>(cp, magic, k0, k0 + R.B < last ? k0 + R.B : last, U, V,
+                                           W, rr, ri);
+        put(a, rr, ri);
+    }
+}
+
 template <int VPL>
 __device__ __forceinline__ void direct_rows_f32c(const int64_t (&j)[VPL], int64_t limit,
                                                  const double* __restrict__ u,
                                                  const double* __restrict__ v,
                                                  const double* __restrict__ w,
-                                                 const Comp* __restrict__ comp, int n_comp,
-                                                 float sgn, float2* __restrict__ out,
+                                                 const CompF* __restrict__ comp, int n_comp,
+                                                 double sgn, float2* __restrict__ out,
                                                  int* __restrict__ status) {
-    double U[VPL], V[VPL], W[VPL];
-    float sr[VPL], cr[VPL], si[VPL], ci[VPL];
+    double U[VPL], V[VPL], W[VPL], sr[VPL], si[VPL];
+    const bool far = load_rows<VPL>(j, limit, u, v, w, kTurnMaxBaseline, U, V, W);
 #pragma unroll
-    for (int i = 0; i < VPL; ++i) {
-        const int64_t jj = j[i] < limit ? j[i] : limit - 1;
-        U[i] = u[jj];
-        V[i] = v[jj];
-        W[i] = w[jj];
-        sr[i] = cr[i] = si[i] = ci[i] = 0.0f;
-    }
-    const auto* cp = uniform_ptr(comp);
-    // components in pairs: the pair's two products and the running
-    // compensation meet in two FMAs, then one Kahan step, so a component costs
-    // half a step (the pair's roundings stay within 2 x 2^-24 of its terms);
-    // an odd last component enters alone
-    const int npair = n_comp & ~1;
-    for (int k = 0; k < npair; k += 2) {
-        const Comp a{cp[k].l, cp[k].m, cp[k].nm1, cp[k].I};
-        const Comp b{cp[k + 1].l, cp[k + 1].m, cp[k + 1].nm1, cp[k + 1].I};
-        const float aI = (float)a.I, bI = (float)b.I;
+    for (int i = 0; i < VPL; ++i) sr[i] = si[i] = 0.0;
+    const CompRanges R(n_comp, kF32cSub);
+    const auto add = [&](int, const double(&rr)[VPL], const double(&ri)[VPL]) {
 #pragma unroll
         for (int i = 0; i < VPL; ++i) {
-            const float ra = (float)fract_phase(U[i], V[i], W[i], a.l, a.m, a.nm1);
-            const float rb = (float)fract_phase(U[i], V[i], W[i], b.l, b.m, b.nm1);
-            float ca, sa, cb, sb;
-            cis2pi_f32(ra, ca, sa);
-            cis2pi_f32(rb, cb, sb);
-            kahan_step(fmaf(aI, ca, fmaf(bI, cb, -cr[i])), sr[i], cr[i]);
-            kahan_step(fmaf(aI, sa, fmaf(bI, sb, -ci[i])), si[i], ci[i]);
+            sr[i] += rr[i];
+            si[i] += ri[i];
         }
-    }
-    if (npair < n_comp) {
-        const Comp cur{cp[npair].l, cp[npair].m, cp[npair].nm1, cp[npair].I};
-        const float cI = (float)cur.I;
-#pragma unroll
-        for (int i = 0; i < VPL; ++i) {
-            const float r = (float)fract_phase(U[i], V[i], W[i], cur.l, cur.m, cur.nm1);
-            float c, s;
-            cis2pi_f32(r, c, s);
-            kahan_add_prod(cI, c, sr[i], cr[i]);
-            kahan_add_prod(cI, s, si[i], ci[i]);
-        }
-    }
+    };
+    if (__builtin_expect(far, 0))
+        range_sums_f32c<VPL, false>(uniform_ptr(comp), R, 0, 8, U, V, W, add);
+    else
+        range_sums_f32c<VPL, true>(uniform_ptr(comp), R, 0, 8, U, V, W, add);
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
         if (j[i] < limit) {
             if (!isfinite(U[i] + V[i] + W[i])) atomicOr(status, kStatusNonFinite);
-            out[j[i]] = make_float2(sr[i], sgn * si[i]);
+            store_vis(out, j[i], sr[i], sgn * si[i]);
         }
     }
 }

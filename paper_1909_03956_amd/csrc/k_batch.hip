@@ -22,7 +22,7 @@ __global__ void k_batch_ingest(const BatchInst* __restrict__ inst, int* __restri
     if (I.prec == SWV_FP64)
         own[k] = pack_component_cell(I.l[k], I.m[k], I.flux[k], bad);
     else
-        ((Comp*)own)[k] = pack_component(I.l[k], I.m[k], I.flux[k], bad);
+        ((CompF*)own)[k] = pack_component_f32c(I.l[k], I.m[k], I.flux[k], bad);
     if (bad) atomicOr(status, bad);
 }
 
@@ -118,9 +118,9 @@ __global__ __launch_bounds__(kBatchF32Block) void k_batch_direct_f32c(
         const double* v = IN[ii].v;
         const double* w = IN[ii].w;
         float2* out = (float2*)IN[ii].out;
-        const Comp* comp = (const Comp*)IN[ii].comp;
+        const CompF* comp = (const CompF*)IN[ii].comp;
         const int n_comp = IN[ii].n_comp;
-        const float sgn = (float)IN[ii].sgn;
+        const double sgn = IN[ii].sgn;
         for (int sub = 0; sub < nrows; sub += 64 * kBatchF32Vpl) {
             int64_t j[kBatchF32Vpl];
 #pragma unroll

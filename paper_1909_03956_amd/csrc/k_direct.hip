@@ -35,6 +35,25 @@ hipError_t launch_ingest(hipStream_t s, int64_t n, const double* l, const double
     return hipGetLastError();
 }
 
+__global__ void k_ingest_f32c(int64_t n, const double* __restrict__ l,
+                              const double* __restrict__ m, const double* __restrict__ flux,
+                              CompF* __restrict__ out, int* __restrict__ status) {
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n) return;
+    int bad;
+    out[k] = pack_component_f32c(l[k], m[k], flux[k], bad);
+    if (bad) atomicOr(status, bad);
+}
+
+hipError_t launch_ingest(hipStream_t s, int64_t n, const double* l, const double* m,
+                         const double* flux, CompF* out, int* status) {
+    if (n <= 0) return hipSuccess;
+    const int b = 256;
+    k_ingest_f32c<<<dim3((unsigned)((n + b - 1) / b)), dim3(b), 0, s>>>(n, l, m, flux, out,
+                                                                        status);
+    return hipGetLastError();
+}
+
 hipError_t launch_ingest(hipStream_t s, int64_t n, const double* l, const double* m,
                          const double* flux, CompCell* out, int* status) {
     if (n <= 0) return hipSuccess;
@@ -144,7 +163,7 @@ k_direct_cell_split(const double* __restrict__ u, const double* __restrict__ v,
 #pragma unroll
     for (int i = 0; i < VPL; ++i) j[i] = row0 + i * kLanes + local;
     double U[VPL], V[VPL], W[VPL];
-    const bool wide = load_rows<VPL>(j, n_vis, u, v, w, U, V, W);
+    const bool wide = load_rows<VPL>(j, n_vis, u, v, w, kTabMaxBaseline, U, V, W);
     const CompRanges R(n_comp);
     constexpr int kOwn = 8 / SPLIT;   // ranges per wave
     double pr[kOwn][VPL], pi[kOwn][VPL];
@@ -197,7 +216,7 @@ k_direct_cell_part(const double* __restrict__ u, const double* __restrict__ v,
     const int b = blockIdx.y;
     const int64_t j[1] = {(int64_t)blockIdx.x * 64 + lane};
     double U[1], V[1], W[1], re[1] = {0.0}, im[1] = {0.0};
-    const bool wide = load_rows<1>(j, n_vis, u, v, w, U, V, W);
+    const bool wide = load_rows<1>(j, n_vis, u, v, w, kTabMaxBaseline, U, V, W);
     const CompRanges R(n_comp);
     const int k0 = R.begin(a, b), k1 = R.end(a, b);
     if (__builtin_expect(wide, 0))
@@ -331,8 +350,8 @@ __global__ __launch_bounds__(BLOCK) void k_direct_f32c(const double* __restrict_
                                                        const double* __restrict__ v,
                                                        const double* __restrict__ w,
                                                        int64_t n_vis,
-                                                       const Comp* __restrict__ comp, int n_comp,
-                                                       float sgn, float2* __restrict__ out,
+                                                       const CompF* __restrict__ comp, int n_comp,
+                                                       double sgn, float2* __restrict__ out,
                                                        int* __restrict__ status) {
     const int64_t base = (int64_t)blockIdx.x * (BLOCK * VPL) + threadIdx.x;
     int64_t j[VPL];
@@ -341,20 +360,94 @@ __global__ __launch_bounds__(BLOCK) void k_direct_f32c(const double* __restrict_
     direct_rows_f32c<VPL>(j, n_vis, u, v, w, comp, n_comp, sgn, out, status);
 }
 
+// Calls too small to fill the chip by rows alone: SPLIT waves of the workgroup
+// share a row's components, 8 / SPLIT ranges each; the range sums meet in LDS.
+constexpr int kF32cBlock = 512;
+
+template <int SPLIT>
+__global__ __launch_bounds__(kF32cBlock) void k_direct_f32c_split(
+    const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
+    int64_t n_vis, const CompF* __restrict__ comp, int n_comp, double sgn,
+    float2* __restrict__ out, int* __restrict__ status) {
+    constexpr int kRows = kF32cBlock / SPLIT, kOwn = 8 / SPLIT;
+    __shared__ double2 part[8][kRows];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int own = wave % SPLIT, local = wave / SPLIT * 64 + lane;
+    const int64_t row0 = (int64_t)blockIdx.x * kRows;
+    const int64_t j[1] = {row0 + local};
+    double U[1], V[1], W[1];
+    const bool far = load_rows<1>(j, n_vis, u, v, w, kTurnMaxBaseline, U, V, W);
+    const CompRanges R(n_comp, kF32cSub);
+    const auto keep = [&](int a, const double(&re)[1], const double(&im)[1]) {
+        part[a][local] = make_double2(re[0], im[0]);
+    };
+    if (__builtin_expect(far, 0))
+        range_sums_f32c<1, false>(uniform_ptr(comp), R, own * kOwn, (own + 1) * kOwn, U, V, W, keep);
+    else
+        range_sums_f32c<1, true>(uniform_ptr(comp), R, own * kOwn, (own + 1) * kOwn, U, V, W, keep);
+    __syncthreads();
+    for (int r = threadIdx.x; r < kRows && row0 + r < n_vis; r += kF32cBlock) {
+        double re = 0.0, im = 0.0;
+#pragma unroll
+        for (int a = 0; a < 8; ++a) {
+            re += part[a][r].x;
+            im += part[a][r].y;
+        }
+        const int64_t jr = row0 + r;
+        if (!isfinite(u[jr] + v[jr] + w[jr])) atomicOr(status, kStatusNonFinite);
+        store_vis(out, jr, re, sgn * im);
+    }
+}
+
+// The smallest row counts: workgroup (x, b) takes 64 rows and sub-range b of all
+// 8 ranges, one range per wave; partial[a][b][row], joined as in FP64.
+__global__ __launch_bounds__(kF32cBlock) void k_direct_f32c_part(
+    const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
+    int64_t n_vis, const CompF* __restrict__ comp, int n_comp, double2* __restrict__ partial,
+    int* __restrict__ status) {
+    const int lane = threadIdx.x & 63, a = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b = blockIdx.y;
+    const int64_t j[1] = {(int64_t)blockIdx.x * 64 + lane};
+    double U[1], V[1], W[1], re[1] = {0.0}, im[1] = {0.0};
+    const bool far = load_rows<1>(j, n_vis, u, v, w, kTurnMaxBaseline, U, V, W);
+    const CompRanges R(n_comp, kF32cSub);
+    const int k0 = R.begin(a, b), k1 = R.end(a, b);
+    const double magic = vector_const(kTurnMagic);
+    if (__builtin_expect(far, 0))
+        add_components_f32c<1, false>(uniform_ptr(comp), magic, k0, k1, U, V, W, re, im);
+    else
+        add_components_f32c<1, true>(uniform_ptr(comp), magic, k0, k1, U, V, W, re, im);
+    if (j[0] < n_vis) {
+        if (a == 0 && b == 0 && !isfinite(U[0] + V[0] + W[0])) atomicOr(status, kStatusNonFinite);
+        partial[((int64_t)a * 8 + b) * n_vis + j[0]] = make_double2(re[0], im[0]);
+    }
+}
+
+// A wave alone on its SIMD runs at its latencies: components are shared until
+// there are 4 waves for each of them, by the workgroups too where the ranges have
+// sub-ranges enough to pay for the second launch.
+DirectShape direct_shape_f32c(int64_t n_vis, int64_t n_comp, int n_cu) {
+    const int64_t waves = (n_vis + 63) / 64, want = 16 * (int64_t)n_cu;
+    DirectShape sh;
+    while (sh.split < 8 && waves * sh.split < want && n_comp >= 16 * sh.split) sh.split *= 2;
+    if (sh.split == 8 && waves * 8 * 2 <= want && n_comp >= 32 * kF32cSub) sh.parts = 8;
+    return sh;
+}
+
 template <int VPL, int BLOCK>
 static hipError_t run_direct(hipStream_t s, int64_t n_vis, const double* u, const double* v,
-                             const double* w, const Comp* comp, int64_t n_comp, int sign,
+                             const double* w, const CompF* comp, int64_t n_comp, int sign,
                              void* out, int* status) {
     const int64_t rows = (int64_t)BLOCK * VPL;
     const dim3 grid((unsigned)((n_vis + rows - 1) / rows)), blk(BLOCK);
-    k_direct_f32c<VPL, BLOCK><<<grid, blk, 0, s>>>(u, v, w, n_vis, comp, (int)n_comp, (float)sign,
+    k_direct_f32c<VPL, BLOCK><<<grid, blk, 0, s>>>(u, v, w, n_vis, comp, (int)n_comp, (double)sign,
                                                    (float2*)out, status);
     return hipGetLastError();
 }
 
 template <int VPL>
 static hipError_t run_direct_b(hipStream_t s, int block, int64_t n_vis, const double* u,
-                               const double* v, const double* w, const Comp* comp, int64_t n_comp,
+                               const double* v, const double* w, const CompF* comp, int64_t n_comp,
                                int sign, void* out, int* status) {
     switch (block) {
         case 64: return run_direct<VPL, 64>(s, n_vis, u, v, w, comp, n_comp, sign, out, status);
@@ -364,10 +457,34 @@ static hipError_t run_direct_b(hipStream_t s, int block, int64_t n_vis, const do
     }
 }
 
-hipError_t launch_direct_f32c(hipStream_t s, int vpl, int block, int64_t n_vis, const double* u,
-                              const double* v, const double* w, const Comp* comp, int64_t n_comp,
-                              int sign, void* out, int* status) {
+hipError_t launch_direct_f32c(hipStream_t s, const DirectShape& sh, int vpl, int block,
+                              int64_t n_vis, const double* u, const double* v, const double* w,
+                              const CompF* comp, int64_t n_comp, int sign, void* out,
+                              double2* partial, int* status) {
     if (n_vis <= 0) return hipSuccess;
+    const int nc = (int)n_comp;
+    const double sg = (double)sign;
+    if (sh.parts > 1) {
+        if (!partial || sh.split != 8 || sh.parts != 8) return hipErrorInvalidValue;
+        const unsigned nb = (unsigned)((n_vis + 63) / 64);
+        k_direct_f32c_part<<<dim3(nb, 8), dim3(kF32cBlock), 0, s>>>(u, v, w, n_vis, comp, nc,
+                                                                    partial, status);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        k_direct_join<float2><<<dim3(nb), dim3(64), 0, s>>>(partial, n_vis, sg, (float2*)out);
+        return hipGetLastError();
+    }
+    if (sh.split > 1) {
+        const int64_t rows = kF32cBlock / sh.split;
+        const dim3 grid((unsigned)((n_vis + rows - 1) / rows)), blk(kF32cBlock);
+        switch (sh.split) {
+            case 2: k_direct_f32c_split<2><<<grid, blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, (float2*)out, status); break;
+            case 4: k_direct_f32c_split<4><<<grid, blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, (float2*)out, status); break;
+            case 8: k_direct_f32c_split<8><<<grid, blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, (float2*)out, status); break;
+            default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
     switch (vpl) {
         case 1: return run_direct_b<1>(s, block, n_vis, u, v, w, comp, n_comp, sign, out, status);
         case 2: return run_direct_b<2>(s, block, n_vis, u, v, w, comp, n_comp, sign, out, status);

@@ -28,12 +28,9 @@ constexpr int kTabBlock = 512;
 hipError_t launch_ingest(hipStream_t s, int64_t n, const double* l, const double* m,
                          const double* flux, Comp* out, int* status);
 hipError_t launch_ingest(hipStream_t s, int64_t n, const double* l, const double* m,
+                         const double* flux, CompF* out, int* status);
+hipError_t launch_ingest(hipStream_t s, int64_t n, const double* l, const double* m,
                          const double* flux, CompCell* out, int* status);
-
-// FP32-compensated direct sum.
-hipError_t launch_direct_f32c(hipStream_t s, int vpl, int block, int64_t n_vis, const double* u,
-                              const double* v, const double* w, const Comp* comp, int64_t n_comp,
-                              int sign, void* out, int* status);
 
 // Shortest component list of the FP64 kernels with the table phasor.  Below
 // it the sum is bound by the rows' 40 bytes (at 8 components their transfer
@@ -53,9 +50,16 @@ hipError_t launch_direct_few(hipStream_t s, int64_t n_vis, const double* u, cons
 struct DirectShape {
     int vpl = 1, split = 1, parts = 1;
 };
+// FP32-compensated direct sum; (vpl, block) where no components are shared.
+DirectShape direct_shape_f32c(int64_t n_vis, int64_t n_comp, int n_cu);
+hipError_t launch_direct_f32c(hipStream_t s, const DirectShape& sh, int vpl, int block,
+                              int64_t n_vis, const double* u, const double* v, const double* w,
+                              const CompF* comp, int64_t n_comp, int sign, void* out,
+                              double2* partial, int* status);
+
 // vpl_max: most rows per lane (1, 2, 4).
 DirectShape direct_shape(int64_t n_vis, int64_t n_comp, int vpl_max, int n_cu);
-// Bytes of partial sums launch_direct_cell needs (0 if parts is 1).
+// Bytes of partial sums a launch needs (0 if parts is 1).
 size_t direct_partial_bytes(const DirectShape& sh, int64_t n_vis);
 // FP64 direct sum of packed components (fewer than kTableMinComp: polynomial
 // phasor, whatever the layout); prec is that of the output alone (SWV_F32C:
@@ -149,7 +153,7 @@ struct BatchInst {
     const double* w;
     void* out;
     const double* l;      // direct: caller's components, packed into comp by the batched ingest
-    const double* m;      // (an FP32-compensated instance: Comp records at its start)
+    const double* m;      // (an FP32-compensated instance: CompF records at its start)
     const double* flux;
     CompCell* comp;       // packed components; tree: its leaf sum (l null)
     int64_t n_vis;

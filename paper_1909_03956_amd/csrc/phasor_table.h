@@ -69,11 +69,6 @@ __device__ __forceinline__ void fill_cells(Cell* T) {
 struct CellCoefs {
     double c0, c1, s0, s1, magic;
 };
-__device__ __forceinline__ double vector_const(double x) {
-    double v = x;
-    asm("" : "+v"(v));
-    return v;
-}
 __device__ __forceinline__ CellCoefs cell_coefs() {
     return CellCoefs{vector_const(kCellC[0]), vector_const(kCellC[1]), vector_const(kCellS[0]),
                      vector_const(kCellS[1]), vector_const(kTabMagic)};
