@@ -142,8 +142,9 @@ __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) 
     direct_rows_cell<VPL>((CellPtr)T, j, n_vis, u, v, w, comp, n_comp, sgn, put, status);
 }
 
-// Calls too small to fill the chip by rows alone: SPLIT waves of the workgroup
-// share a row's components, 8 / SPLIT ranges each.  Their range sums meet in
+// SPLIT waves of the workgroup share a row's components, 8 / SPLIT ranges each:
+// calls too small to fill the chip by rows alone, and long component lists
+// (direct_shape).  Their range sums meet in
 // LDS (where the table was) and are added in range order.
 template <int VPL, int SPLIT, class OUT>
 __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) void
@@ -254,7 +255,11 @@ __global__ __launch_bounds__(64) void k_direct_join(const double2* __restrict__ 
 // Layout with the least estimated time.  A workgroup's time, in units of one
 // wave's (64 rows, component) pass with the CU full (two workgroups): per_comp x
 // components of a wave (fewer rows per lane cost a little more each, for the
-// per-component copies and loads), plus about 14 for filling the table.
+// per-component copies and loads), plus about 14 for filling the table.  Shared by
+// waves, a row's components make more and shorter workgroups, which even out over
+// the dies' different clocks: 4 rows a lane over 1, 4 and 8 waves take 8.63, 8.30
+// and 8.17 ms (8,355,840 rows x 2,000 components), 1.28, 1.22 and 1.25 ms
+// (8,000,000 x 300) and 0.143, 0.159 and 0.180 ms (4,000,000 x 60).
 // Workgroups run in rounds of two per CU; a call of one workgroup per CU or less
 // gets no credit for that, since nothing keeps two of them off the same CU
 // (261,120 rows x 1,000 components in 255 workgroups: 180 us at best, 336 us
@@ -263,7 +268,7 @@ DirectShape direct_shape(int64_t n_vis, int64_t n_comp, int vpl_max, int n_cu) {
     const struct {
         int vpl, split, parts;
         double per_comp;
-    } all[] = {{4, 1, 1, 4.0}, {2, 1, 1, 2.04}, {1, 1, 1, 1.28}, {2, 2, 1, 2.04}, {2, 4, 1, 2.04},
+    } all[] = {{4, 1, 1, 4.0}, {4, 4, 1, 3.85}, {4, 8, 1, 3.75}, {2, 1, 1, 2.04}, {1, 1, 1, 1.28}, {2, 2, 1, 2.04}, {2, 4, 1, 2.04},
                {1, 2, 1, 1.28}, {1, 4, 1, 1.28}, {1, 8, 1, 1.28}, {1, 8, 8, 1.28}};
     DirectShape best;
     double best_t = HUGE_VAL;
@@ -325,6 +330,8 @@ static hipError_t run_direct_cell(hipStream_t s, const DirectShape& sh, int64_t 
     else SWV_CELL(1, 1) k_direct_cell<1, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
     else SWV_CELL(2, 2) k_direct_cell_split<2, 2, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
     else SWV_CELL(2, 4) k_direct_cell_split<2, 4, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(4, 4) k_direct_cell_split<4, 4, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
+    else SWV_CELL(4, 8) k_direct_cell_split<4, 8, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
     else SWV_CELL(1, 2) k_direct_cell_split<1, 2, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
     else SWV_CELL(1, 4) k_direct_cell_split<1, 4, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
     else SWV_CELL(1, 8) k_direct_cell_split<1, 8, OUT><<<dim3(nb), blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status);
