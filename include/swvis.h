@@ -525,18 +525,16 @@ typedef struct {
     int64_t n_instances;
     int64_t n_items;          /* (instance, visibility tile) work items */
     int64_t total_terms;      /* sum over instances of n_vis * terms */
-    int tile_rows;            /* visibilities per work item */
-    int grid_blocks;          /* persistent blocks launched */
+    int tile_rows;            /* most visibilities per work item */
+    int grid_blocks;          /* blocks launched for the FP64 instances */
     int block_threads;
 } swv_plan_stats_t;
 
-/* Plans one persistent launch per route (and, for trees, per precision) over
- * many instances: packs every
- * instance's components (direct) and uploads every tree, splits each
- * instance into visibility tiles and orders the (instance, tile) work items
- * by decreasing cost (longest-processing-time first).  Workgroups take items
- * from a device counter, so uneven instances balance across the chip.  The
- * tile shape comes from the context's tuning table.  `inst` [n] HOST; the
+/* Plans one launch for the FP64 direct instances and all trees, and one for the
+ * FP32-compensated direct instances: packs every instance's components (direct)
+ * and uploads every tree, splits each instance into visibility tiles and orders
+ * the (instance, tile) work items by decreasing cost (longest-processing-time
+ * first), so uneven instances balance across the chip.  `inst` [n] HOST; the
  * device buffers they name must outlive the plan. */
 int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out);
 
@@ -545,8 +543,7 @@ int swv_plan_stats(swv_plan plan, swv_plan_stats_t* out);
 /* Enqueues the planned prediction on the context's stream. */
 int swv_batch_run(swv_plan plan);
 
-/* Captures the planned prediction (counter reset by a kernel, then the
- * persistent launches) into a HIP graph on the context's stream. */
+/* Captures the planned prediction into a HIP graph on the context's stream. */
 int swv_graph_capture(swv_plan plan, swv_graph* out);
 
 /* Replays a captured graph on the context's stream. */
@@ -591,7 +588,7 @@ typedef struct {
 
 /* A major cycle over many instances (section 2.2 steps 1-3, with the chi^2
  * gradients beside them), runnable eagerly or as one captured HIP graph:
- *   1. the model visibilities of every instance in one persistent launch (as
+ *   1. the model visibilities of every instance in one launch (as
  *      swv_batch_plan: direct sums and wavelet trees, FP64);
  *   2. per instance the subtract step with chi^2 (swv_residual_chi2), the
  *      residual image on its pixel set (swv_adjoint of the residuals) and,

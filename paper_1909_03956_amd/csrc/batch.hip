@@ -23,8 +23,8 @@ struct swv_plan_s {
     WorkItem* d_items32 = nullptr;    // F32C direct instances
     unsigned n_items = 0, n_items32 = 0;
     CompCell* d_pack = nullptr;       // components of the direct instances
-    unsigned* d_counters = nullptr;   // next item of each launch
-    int vpl = 2, grid = 0, grid32 = 0, max_comp = 0;
+    unsigned* d_counters = nullptr;   // next item of the F32C launch
+    int grid32 = 0, max_comp = 0;
     int tile_rows = 0;
     int64_t total_terms = 0;
     int refs = 1;  // graphs captured from this plan hold a reference
@@ -78,13 +78,11 @@ void plan_release(swv_plan p) {
 hipError_t enqueue_plan(swv_plan p, hipStream_t s) {
     int* status = p->ctx->d_status;
     hipError_t e = launch_batch_ingest(s, p->d_inst, (int)p->inst.size(), p->max_comp, status);
-    if (e == hipSuccess) e = launch_reset_counters(s, p->d_counters, 2);
-    if (e == hipSuccess)
-        e = launch_batch_direct(s, p->vpl, p->grid, p->d_inst, p->d_items, p->n_items,
-                                p->d_counters, status);
+    if (e == hipSuccess) e = launch_batch_direct(s, p->d_inst, p->d_items, p->n_items, status);
+    if (e == hipSuccess && p->n_items32 > 0) e = launch_reset_counters(s, p->d_counters, 1);
     if (e == hipSuccess)
         e = launch_batch_direct_f32c(s, p->grid32, p->d_inst, p->d_items32, p->n_items32,
-                                     p->d_counters + 1, status);
+                                     p->d_counters, status);
     return e;
 }
 
@@ -136,7 +134,7 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
         p = new swv_plan_s();
         p->ctx = ctx;
         p->n_inst = n;
-        int64_t off = 0, total_rows = 0, rows64 = 0;
+        int64_t off = 0, rows64 = 0, rows32 = 0;
         std::vector<int64_t> offset(n, 0);
         for (int k = 0; k < n; ++k) {
             const swv_instance& I = inst[k];
@@ -149,9 +147,8 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
             b.prec = I.prec;
             b.sgn = (double)I.sign;
             b.is_tree = I.route == SWV_ROUTE_TREE;
-            total_rows += I.n_vis;
             if (!b.is_tree) {
-                if (I.prec == SWV_FP64) rows64 += I.n_vis;
+                (I.prec == SWV_FP64 ? rows64 : rows32) += I.n_vis;
                 b.l = I.l;
                 b.m = I.m;
                 b.flux = I.flux;
@@ -173,28 +170,29 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
             p->inst.push_back(b);
         }
 
-        p->vpl = batch_direct_vpl(rows64, ctx->per_lane[kFamDirect64][1], ctx->n_cu);
-        // persistent grids: as many blocks as stay resident
-        p->grid = ctx->n_cu * batch_direct_blocks_per_cu(p->vpl);
+        // persistent grid: as many blocks as stay resident, about 16 items for each
         p->grid32 = ctx->n_cu * batch_direct_f32c_blocks_per_cu();
-        const int64_t waves = (int64_t)p->grid * (kTabBlock / 64);
-        // about 16 items per resident wave, in whole wave tiles, at most 64 of them
-        const int64_t unit = 64LL * p->vpl;
-        int64_t tile = total_rows / std::max<int64_t>(1, 16 * waves);
-        tile = std::max<int64_t>(unit, std::min<int64_t>(64 * unit, (tile + unit - 1) / unit * unit));
-        p->tile_rows = (int)tile;
+        const int64_t unit = 64LL * kBatchF32Vpl;
+        int64_t tile32 = rows32 / std::max<int64_t>(1, 16 * (int64_t)p->grid32);
+        tile32 = std::max<int64_t>(
+            unit, std::min<int64_t>(64 * unit, (tile32 + unit - 1) / unit * unit));
 
         struct Item {
             WorkItem w;
             int64_t cost;
         };
         std::vector<Item> items;
-        for (size_t k = 0; k < p->inst.size(); ++k)
-            for (int64_t r = 0; r < p->inst[k].n_vis; r += tile) {
-                const int nr = (int)std::min<int64_t>(tile, p->inst[k].n_vis - r);
-                items.push_back(Item{WorkItem{r, (int)k, nr},
-                                     (int64_t)nr * std::max(p->inst[k].n_comp, 1)});
+        for (size_t k = 0; k < p->inst.size(); ++k) {
+            const BatchInst& b = p->inst[k];
+            const bool f32 = b.prec == SWV_F32C && !b.is_tree;
+            const int64_t tile = f32 ? tile32 : batch_item_rows(rows64, b.n_comp, ctx->n_cu);
+            p->tile_rows = std::max(p->tile_rows, (int)tile);
+            for (int64_t r = 0; r < b.n_vis; r += tile) {
+                const int nr = (int)std::min<int64_t>(tile, b.n_vis - r);
+                items.push_back(Item{WorkItem{r, (int)k, nr, batch_split(rows64, b.n_comp, ctx->n_cu), 0},
+                                     (int64_t)nr * std::max(b.n_comp, 1)});
             }
+        }
         // longest processing time first
         std::stable_sort(items.begin(), items.end(),
                          [](const Item& a, const Item& b) { return a.cost > b.cost; });
@@ -204,7 +202,7 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
             const BatchInst& b = p->inst[(size_t)it.w.inst];
             (b.prec == SWV_F32C && !b.is_tree ? w32 : w64).push_back(it.w);
         }
-        if (w64.size() > 0xffffffffull || w32.size() > 0xffffffffull) {
+        if (w64.size() > 0x7fffffffull || w32.size() > 0xffffffffull) {
             delete p;
             return fail(SWV_ENOTSUP, "swv_batch_plan: too many work items");
         }
@@ -225,7 +223,7 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
         if (!rc) rc = dev_upload(w64, &p->d_items);
         if (!rc) rc = dev_upload(w32, &p->d_items32);
         if (!rc) {
-            e = hipMalloc((void**)&p->d_counters, 2 * sizeof(unsigned));
+            e = hipMalloc((void**)&p->d_counters, sizeof(unsigned));
             if (e != hipSuccess) {
                 (void)hipGetLastError();
                 p->d_counters = nullptr;
@@ -262,7 +260,7 @@ int swv_plan_stats(swv_plan p, swv_plan_stats_t* out) {
     out->n_items = (int64_t)p->n_items + p->n_items32;
     out->total_terms = p->total_terms;
     out->tile_rows = p->tile_rows;
-    out->grid_blocks = p->grid;
+    out->grid_blocks = p->n_items;
     out->block_threads = kTabBlock;
     return SWV_OK;
 }

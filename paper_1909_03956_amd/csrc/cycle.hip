@@ -1,7 +1,7 @@
 // Major cycles as one HIP graph (section 2.2: predict, subtract, image; the
 // chi^2 gradients beside them).  An instance is one channel x pointing with
 // its observed visibilities; every cycle runs, in one capture:
-//   1. the batched persistent prediction of every instance (direct sums and
+//   1. the batched prediction of every instance (direct sums and
 //      wavelet trees in one launch, FP64);
 //   2. per instance: the subtract step with chi^2, the residual image on the
 //      instance's pixel set (the exact adjoint) and, for a direct instance,
@@ -33,7 +33,6 @@ struct swv_cycle_s {
     WorkItem* d_items = nullptr;
     CompCell* d_pack = nullptr;             // direct instances' components
     CompCell* d_sum = nullptr;              // tree instances' leaf sums
-    unsigned* d_counters = nullptr;
     void* d_partial = nullptr;
     double* d_chi2_part = nullptr;
     // pinned host mirrors of the descriptors and work items, for async uploads
@@ -42,9 +41,8 @@ struct swv_cycle_s {
     hipEvent_t up_event = nullptr;
     bool up_pending = false;
     bool dirty = true;
-    int vpl = 2, grid = 0;
     int max_comp_cap = 0;
-    int64_t tile_rows = 64;                 // rows per work item, fixed at creation
+    std::vector<int> tile_rows, split;      // of instance k's work items, fixed at creation
     std::vector<AdjointShape> adj;          // per instance
     std::vector<int> gcpl;                  // per instance: gradient components per lane
     std::vector<int64_t> gchunk;            // per instance: gradient row chunk
@@ -70,7 +68,7 @@ void free_cycle(swv_cycle cy) {
     if (cy->exec) (void)hipGraphExecDestroy(cy->exec);
     if (cy->graph) (void)hipGraphDestroy(cy->graph);
     for (void* q : {(void*)cy->d_inst, (void*)cy->d_items, (void*)cy->d_pack, (void*)cy->d_sum,
-                    (void*)cy->d_counters, cy->d_partial, (void*)cy->d_chi2_part})
+                    cy->d_partial, (void*)cy->d_chi2_part})
         if (q) (void)hipFree(q);
     if (cy->h_mirror) (void)hipHostFree(cy->h_mirror);
     if (cy->up_event) (void)hipEventDestroy(cy->up_event);
@@ -110,9 +108,9 @@ void order_items(swv_cycle cy) {
     std::vector<Item> all;
     for (size_t k = 0; k < cy->spec.size(); ++k) {
         const int64_t n = cy->spec[k].n_vis;
-        for (int64_t r = 0; r < n; r += cy->tile_rows) {
-            const int nr = (int)std::min<int64_t>(cy->tile_rows, n - r);
-            all.push_back(Item{WorkItem{r, (int)k, nr}, (int64_t)nr * cy->cost[k]});
+        for (int64_t r = 0; r < n; r += cy->tile_rows[k]) {
+            const int nr = (int)std::min<int64_t>(cy->tile_rows[k], n - r);
+            all.push_back(Item{WorkItem{r, (int)k, nr, cy->split[k], 0}, (int64_t)nr * cy->cost[k]});
         }
     }
     std::stable_sort(all.begin(), all.end(),
@@ -149,10 +147,7 @@ hipError_t enqueue_cycle(swv_cycle cy, hipStream_t s) {
     hipError_t e = launch_batch_ingest(s, cy->d_inst, (int)cy->inst.size(), cy->max_comp_cap,
                                        ctx->d_status);
     if (e != hipSuccess) return e;
-    e = launch_reset_counters(s, cy->d_counters, 1);
-    if (e != hipSuccess) return e;
-    e = launch_batch_direct(s, cy->vpl, cy->grid, cy->d_inst, cy->d_items,
-                            (unsigned)cy->items.size(), cy->d_counters, ctx->d_status);
+    e = launch_batch_direct(s, cy->d_inst, cy->d_items, (unsigned)cy->items.size(), ctx->d_status);
     if (e != hipSuccess) return e;
     for (size_t k = 0; k < cy->spec.size(); ++k) {
         const swv_cycle_instance& I = cy->spec[k];
@@ -237,15 +232,14 @@ int swv_cycle_create(swv_ctx ctx, int n, const swv_cycle_instance* inst, swv_cyc
             }
             cy->inst.push_back(b);
         }
-        cy->vpl = batch_direct_vpl(rows, ctx->per_lane[kFamDirect64][1], ctx->n_cu);
-        cy->grid = ctx->n_cu * batch_direct_blocks_per_cu(cy->vpl);
-        const int64_t waves = (int64_t)cy->grid * (kTabBlock / 64);
-        const int64_t unit = 64LL * cy->vpl;
-        int64_t tile = rows / std::max<int64_t>(1, 16 * waves);
-        tile = std::max<int64_t>(unit, std::min<int64_t>(64 * unit, (tile + unit - 1) / unit * unit));
-        cy->tile_rows = tile;
+        for (int k = 0; k < n; ++k) {
+            const int64_t cap = std::min<int64_t>(
+                inst[k].route == SWV_ROUTE_TREE ? cy->rec_cap[k] : inst[k].comp_cap, INT32_MAX);
+            cy->split.push_back(batch_split(rows, cap, ctx->n_cu));
+            cy->tile_rows.push_back(batch_item_rows(rows, cap, ctx->n_cu));
+        }
         order_items(cy);
-        if (cy->items.size() > 0xffffffffull) {
+        if (cy->items.size() > 0x7fffffffull) {
             delete cy;
             return fail(SWV_ENOTSUP, "swv_cycle_create: too many work items");
         }
@@ -272,7 +266,6 @@ int swv_cycle_create(swv_ctx ctx, int n, const swv_cycle_instance* inst, swv_cyc
         if (!rc) rc = dev_alloc(&cy->d_items, cy->items.size());
         if (!rc) rc = dev_alloc(&cy->d_pack, (size_t)std::max<int64_t>(comp_off, 1));
         if (!rc) rc = dev_alloc(&cy->d_sum, (size_t)std::max<int64_t>(sum_off, 1));
-        if (!rc) rc = dev_alloc(&cy->d_counters, 1);
         if (!rc) rc = dev_alloc((char**)&cy->d_partial, partial);
         if (!rc) rc = dev_alloc(&cy->d_chi2_part, (size_t)res_blocks);
         if (!rc) {

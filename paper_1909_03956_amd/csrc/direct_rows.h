@@ -171,13 +171,13 @@ __device__ __forceinline__ void range_sums(CellPtr T, CompCellPtr cp, const Comp
 }
 
 // Rows j[0 .. VPL) of a lane, clamped to the last one.  Returns whether some row
-// of the wave has |u| + |v| + |w| of `most` or more (or is not finite).
+// of the wave is beyond the cells' direct reach (or not finite).
 template <int VPL>
 __device__ __forceinline__ bool load_rows(const int64_t (&j)[VPL], int64_t limit,
                                           const double* __restrict__ u,
                                           const double* __restrict__ v,
-                                          const double* __restrict__ w, double most,
-                                          double (&U)[VPL], double (&V)[VPL], double (&W)[VPL]) {
+                                          const double* __restrict__ w, double (&U)[VPL],
+                                          double (&V)[VPL], double (&W)[VPL]) {
     bool small = true;
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
@@ -185,7 +185,7 @@ __device__ __forceinline__ bool load_rows(const int64_t (&j)[VPL], int64_t limit
         U[i] = u[jj];
         V[i] = v[jj];
         W[i] = w[jj];
-        small = small && fabs(U[i]) + fabs(V[i]) + fabs(W[i]) < most;
+        small = small && cells_reach(U[i], V[i], W[i]);
     }
     return __any(!small);
 }
@@ -208,7 +208,7 @@ __device__ __forceinline__ void direct_rows_cell(CellPtr T, const int64_t (&j)[V
                                                  double sgn, Put&& put,
                                                  int* __restrict__ status) {
     double U[VPL], V[VPL], W[VPL], sr[VPL], si[VPL];
-    const bool wide = load_rows<VPL>(j, limit, u, v, w, kTabMaxBaseline, U, V, W);
+    const bool wide = load_rows<VPL>(j, limit, u, v, w, U, V, W);
 #pragma unroll
     for (int i = 0; i < VPL; ++i) sr[i] = si[i] = 0.0;
     const CompRanges R(n_comp);
@@ -230,6 +230,66 @@ __device__ __forceinline__ void direct_rows_cell(CellPtr T, const int64_t (&j)[V
             if (!isfinite(U[i] + V[i] + W[i])) atomicOr(status, kStatusNonFinite);
             put(j[i], sr[i], sgn * si[i]);
         }
+    }
+}
+
+// Rows row0 .. row0 + kTabBlock / SPLIT * VPL of a workgroup, SPLIT waves sharing
+// a row's components, 8 / SPLIT ranges each.  Their range sums meet in LDS (where
+// the table was: it is gone afterwards) and are added in range order.
+template <int VPL, int SPLIT, class Put>
+__device__ __forceinline__ void direct_block_cell(Cell* T, int64_t row0, int64_t limit,
+                                                  const double* __restrict__ u,
+                                                  const double* __restrict__ v,
+                                                  const double* __restrict__ w,
+                                                  const CompCell* __restrict__ comp, int n_comp,
+                                                  double sgn, Put&& put,
+                                                  int* __restrict__ status) {
+    constexpr int kLanes = kTabBlock / SPLIT;   // lanes that own rows
+    constexpr int kRows = kLanes * VPL;         // rows per workgroup
+    static_assert(8 * kRows <= kTabCells, "range sums fit where the table was");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int part = wave % SPLIT, local = wave / SPLIT * 64 + lane;
+    int64_t j[VPL];
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) j[i] = row0 + i * kLanes + local;
+    double U[VPL], V[VPL], W[VPL];
+    const bool wide = load_rows<VPL>(j, limit, u, v, w, U, V, W);
+    const CompRanges R(n_comp);
+    constexpr int kOwn = 8 / SPLIT;   // ranges per wave
+    double pr[kOwn][VPL], pi[kOwn][VPL];
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+        const auto keep = [&](int, const double(&re)[VPL], const double(&im)[VPL]) {
+#pragma unroll
+            for (int i = 0; i < VPL; ++i) {
+                pr[q][i] = re[i];
+                pi[q][i] = im[i];
+            }
+        };
+        const int a = part * kOwn + q;
+        if (__builtin_expect(wide, 0))
+            range_sums<VPL, true>((CellPtr)T, uniform_ptr(comp), R, a, a + 1, U, V, W, keep);
+        else
+            range_sums<VPL, false>((CellPtr)T, uniform_ptr(comp), R, a, a + 1, U, V, W, keep);
+    }
+    __syncthreads();   // every wave is done with the table
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q)
+#pragma unroll
+        for (int i = 0; i < VPL; ++i)
+            T[(part * kOwn + q) * kRows + i * kLanes + local] = Cell{pr[q][i], pi[q][i]};
+    __syncthreads();
+    for (int r = threadIdx.x; r < kRows && row0 + r < limit; r += kTabBlock) {
+        double re = 0.0, im = 0.0;
+#pragma unroll
+        for (int a = 0; a < 8; ++a) {
+            const Cell p = T[a * kRows + r];
+            re += p.x;
+            im += p.y;
+        }
+        const int64_t jr = row0 + r;
+        if (!isfinite(u[jr] + v[jr] + w[jr])) atomicOr(status, kStatusNonFinite);
+        put(jr, re, sgn * im);
     }
 }
 
@@ -285,11 +345,12 @@ __device__ __forceinline__ void direct_rows_f64(const int64_t (&j)[VPL], int64_t
 // total in FP64.
 constexpr int kF32cSub = 128;
 
-template <int VPL, bool FAST, class CompPtr>
-__device__ __forceinline__ void add_components_f32c(CompPtr cp, double magic, int k0, int k1,
+template <int VPL, int FORM, class CompPtr>
+__device__ __forceinline__ void add_components_f32c(CompPtr cp, int k0, int k1,
                                                     const double (&U)[VPL], const double (&V)[VPL],
-                                                    const double (&W)[VPL], double (&re)[VPL],
-                                                    double (&im)[VPL]) {
+                                                    const double (&W)[VPL],
+                                                    const TurnRow (&row)[VPL],
+                                                    double (&re)[VPL], double (&im)[VPL]) {
     float sr[VPL], si[VPL], cr[VPL], ci[VPL];
 #pragma unroll
     for (int i = 0; i < VPL; ++i) sr[i] = cr[i] = si[i] = ci[i] = 0.0f;
@@ -305,7 +366,7 @@ __device__ __forceinline__ void add_components_f32c(CompPtr cp, double magic, in
 #pragma unroll
             for (int b = N - 1; b >= 0; --b) {
                 float co, sn;
-                cis2pi_f32(turns_f32<FAST>(U[i], V[i], W[i], c[b].l, c[b].m, c[b].nm1, magic), co,
+                cis2pi_f32(turns_f32<FORM>(U[i], V[i], W[i], c[b].l, c[b].m, c[b].nm1, row[i]), co,
                            sn);
                 yr = fmaf(c[b].I, co, yr);
                 yi = fmaf(c[b].I, sn, yi);
@@ -330,11 +391,11 @@ __device__ __forceinline__ void add_components_f32c(CompPtr cp, double magic, in
 }
 
 // The sums of ranges [a0, a1), handed to put(a, re, im) as each is complete.
-template <int VPL, bool FAST, class CompPtr, class Put>
+template <int VPL, int FORM, class CompPtr, class Put>
 __device__ __forceinline__ void range_sums_f32c(CompPtr cp, const CompRanges& R, int a0, int a1,
                                                 const double (&U)[VPL], const double (&V)[VPL],
-                                                const double (&W)[VPL], Put&& put) {
-    const double magic = vector_const(kTurnMagic);
+                                                const double (&W)[VPL],
+                                                const TurnRow (&row)[VPL], Put&& put) {
 #pragma unroll 1
     for (int a = a0; a < a1; ++a) {
         double rr[VPL], ri[VPL];
@@ -343,10 +404,49 @@ __device__ __forceinline__ void range_sums_f32c(CompPtr cp, const CompRanges& R,
         const int last = (int)R.end_of(a);
 #pragma unroll 1
         for (int k0 = a * R.A; k0 < last; k0 += R.B)
-            add_components_f32c<VPL, FAST>(cp, magic, k0, k0 + R.B < last ? k0 + R.B : last, U, V,
-                                           W, rr, ri);
+            add_components_f32c<VPL, FORM>(cp, k0, k0 + R.B < last ? k0 + R.B : last, U, V, W, row,
+                                           rr, ri);
         put(a, rr, ri);
     }
+}
+
+// Rows j[0 .. VPL) of a lane, clamped to the last one; the loop's form.
+template <int VPL>
+__device__ __forceinline__ int load_rows_f32c(const int64_t (&j)[VPL], int64_t limit,
+                                              const double* __restrict__ u,
+                                              const double* __restrict__ v,
+                                              const double* __restrict__ w, double (&U)[VPL],
+                                              double (&V)[VPL], double (&W)[VPL],
+                                              TurnRow (&row)[VPL]) {
+    bool far = false, shifted = false;
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) {
+        const int64_t jj = j[i] < limit ? j[i] : limit - 1;
+        U[i] = u[jj];
+        V[i] = v[jj];
+        W[i] = w[jj];
+        row[i] = turn_row(U[i], V[i], W[i]);
+        far = far || row[i].far;
+        shifted = shifted || row[i].shift != 0;
+    }
+    const int form = __any(far) ? 2 : (__any(shifted) ? 1 : 0);
+    if (form == 0) {   // one magic number for all, in a register of its own
+        const double magic = vector_const(1.5 * 0x1p20);
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) row[i].magic = magic;
+    }
+    return form;
+}
+
+// f(form) for the loop's form as a constant.
+template <class F>
+__device__ __forceinline__ void with_form(int form, F&& f) {
+    if (__builtin_expect(form == 0, 1))
+        f(std::integral_constant<int, 0>());
+    else if (form == 1)
+        f(std::integral_constant<int, 1>());
+    else
+        f(std::integral_constant<int, 2>());
 }
 
 template <int VPL>
@@ -358,7 +458,8 @@ __device__ __forceinline__ void direct_rows_f32c(const int64_t (&j)[VPL], int64_
                                                  double sgn, float2* __restrict__ out,
                                                  int* __restrict__ status) {
     double U[VPL], V[VPL], W[VPL], sr[VPL], si[VPL];
-    const bool far = load_rows<VPL>(j, limit, u, v, w, kTurnMaxBaseline, U, V, W);
+    TurnRow row[VPL];
+    const int form = load_rows_f32c<VPL>(j, limit, u, v, w, U, V, W, row);
 #pragma unroll
     for (int i = 0; i < VPL; ++i) sr[i] = si[i] = 0.0;
     const CompRanges R(n_comp, kF32cSub);
@@ -369,10 +470,9 @@ __device__ __forceinline__ void direct_rows_f32c(const int64_t (&j)[VPL], int64_
             si[i] += ri[i];
         }
     };
-    if (__builtin_expect(far, 0))
-        range_sums_f32c<VPL, false>(uniform_ptr(comp), R, 0, 8, U, V, W, add);
-    else
-        range_sums_f32c<VPL, true>(uniform_ptr(comp), R, 0, 8, U, V, W, add);
+    with_form(form, [&](auto f) {
+        range_sums_f32c<VPL, decltype(f)::value>(uniform_ptr(comp), R, 0, 8, U, V, W, row, add);
+    });
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
         if (j[i] < limit) {

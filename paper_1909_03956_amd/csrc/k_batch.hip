@@ -1,12 +1,13 @@
-// Persistent batched prediction: many instances (channels x pointings) of
-// uneven size in one launch per route.
+// Batched prediction: many instances (channels x pointings) of uneven size in
+// one launch for the FP64 ones (direct sums and trees' leaf sums) and one for the
+// FP32-compensated.
 //
-// The host splits every instance into row tiles and orders the (instance,
-// tile) work items by decreasing cost, largest first.  Each wave of a
-// grid sized to stay resident takes the next item from a device counter
-// (one atomic per item, on lane 0), so long and short instances balance
-// across the chip without a second launch; a wave leaves when the counter
-// passes the item count, so every wave exits.  The row arithmetic is the
+// The host splits every instance into row tiles and orders the (instance, tile)
+// work items by decreasing cost, largest first, so long and short instances
+// balance across the chip.  FP64: a workgroup per item, dealt by the hardware.
+// FP32-compensated: each wave of a grid sized to stay resident takes the next
+// item from a device counter (one atomic per item, on lane 0) and leaves when the
+// counter passes the item count, so every wave exits.  The row arithmetic is the
 // single-instance kernels' (direct_rows.h).
 #include "direct_rows.h"
 
@@ -51,51 +52,51 @@ __device__ __forceinline__ unsigned next_item(unsigned* counter) {
     return __builtin_amdgcn_readfirstlane(it);
 }
 
-// FP64 items: one workgroup fills the phasor table once, then its waves take
-// items on their own.  Lists too short for the table kernels go through the
+// FP64 items.  An item is either whole rows per wave, kBatchRows at a time, or
+// kBatchSplitRows rows whose components all eight waves share (short work for the
+// chip, long lists).  Lists too short for the table kernels go through the
 // polynomial phasor, as in the single-instance call, so the bits are the same.
-template <int VPL>
 __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) void
-k_batch_direct(const BatchInst* __restrict__ inst, const WorkItem* __restrict__ items, unsigned n_items,
-               unsigned* __restrict__ counter, int* __restrict__ status) {
+k_batch_direct(const BatchInst* __restrict__ inst, const WorkItem* __restrict__ items,
+               int* __restrict__ status) {
     __shared__ Cell T[kTabCells];
-    fill_cells(T);
-    const int lane = threadIdx.x & 63;
-    const auto* IT = uniform_ptr(items);
-    const auto* IN = uniform_ptr(inst);
-    for (;;) {
-        const unsigned it = next_item(counter);
-        if (it >= n_items) break;
-        const int64_t row0 = IT[it].row0;
-        const int nrows = IT[it].nrows;
-        const int ii = IT[it].inst;
-        const int64_t n_vis = IN[ii].n_vis;
-        const int64_t limit = row0 + nrows < n_vis ? row0 + nrows : n_vis;
-        const double* u = IN[ii].u;
-        const double* v = IN[ii].v;
-        const double* w = IN[ii].w;
-        void* out = IN[ii].out;
-        const CompCell* comp = IN[ii].comp;
-        const int n_comp = IN[ii].n_comp;
-        const double sgn = IN[ii].sgn;
-        const bool single = IN[ii].prec == SWV_F32C;   // a tree with complex64 output
-        const auto put = [out, single](int64_t j, double re, double im) {
-            if (single)
-                store_vis((float2*)out, j, re, im);
-            else
-                store_vis((double2*)out, j, re, im);
-        };
-        for (int sub = 0; sub < nrows; sub += 64 * VPL) {
-            int64_t j[VPL];
-#pragma unroll
-            for (int i = 0; i < VPL; ++i) j[i] = row0 + sub + i * 64 + lane;
-            if (n_comp >= kTableMinComp)
-                direct_rows_cell<VPL>((CellPtr)T, j, limit, u, v, w, comp, n_comp, sgn, put,
-                                      status);
-            else
-                direct_rows_f64<VPL>(j, limit, u, v, w, uniform_ptr((const CompCell*)comp), n_comp,
-                                     sgn, put, status);
+    const auto* it = uniform_ptr(items) + blockIdx.x;
+    const auto* I = uniform_ptr(inst) + it->inst;
+    const int64_t row0 = it->row0, n_vis = I->n_vis;
+    const int64_t limit = row0 + it->nrows < n_vis ? row0 + it->nrows : n_vis;
+    const double* u = I->u;
+    const double* v = I->v;
+    const double* w = I->w;
+    void* out = I->out;
+    const CompCell* comp = I->comp;
+    const int n_comp = I->n_comp;
+    const double sgn = I->sgn;
+    const bool single = I->prec == SWV_F32C;   // a tree with complex64 output
+    const auto put = [out, single](int64_t j, double re, double im) {
+        if (single)
+            store_vis((float2*)out, j, re, im);
+        else
+            store_vis((double2*)out, j, re, im);
+    };
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (n_comp < kTableMinComp) {
+        for (int64_t r = row0 + threadIdx.x; r < limit; r += kTabBlock) {
+            const int64_t j[1] = {r};
+            direct_rows_f64<1>(j, limit, u, v, w, uniform_ptr((const CompCell*)comp), n_comp, sgn,
+                               put, status);
         }
+        return;
+    }
+    fill_cells(T);
+    if (it->split) {
+        direct_block_cell<4, 8>(T, row0, limit, u, v, w, comp, n_comp, sgn, put, status);
+        return;
+    }
+    for (int64_t r = row0 + wave * 256; r < limit; r += kBatchRows) {
+        int64_t j[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) j[i] = r + i * 64 + lane;
+        direct_rows_cell<4>((CellPtr)T, j, limit, u, v, w, comp, n_comp, sgn, put, status);
     }
 }
 
@@ -140,33 +141,22 @@ static int resident(K kernel, int block) {
     return nb > 0 ? nb : 1;
 }
 
-int batch_direct_blocks_per_cu(int vpl) {
-    return vpl == 1   ? resident(k_batch_direct<1>, kTabBlock)
-           : vpl == 2 ? resident(k_batch_direct<2>, kTabBlock)
-                      : resident(k_batch_direct<4>, kTabBlock);
+bool batch_split(int64_t total_rows, int64_t n_comp, int n_cu) {
+    return n_comp >= 500 || total_rows < 4 * (int64_t)kBatchRows * 2 * n_cu;
 }
 
-int batch_direct_vpl(int64_t rows, int vpl_max, int n_cu) {
-    int vpl = vpl_max;
-    while (vpl > 1 && rows < 4 * 64 * (int64_t)vpl * n_cu * batch_direct_blocks_per_cu(vpl) *
-                                 (kTabBlock / 64))
-        vpl /= 2;
-    return vpl;
+int batch_item_rows(int64_t total_rows, int64_t n_comp, int n_cu) {
+    if (batch_split(total_rows, n_comp, n_cu)) return kBatchSplitRows;
+    const int64_t rounds = total_rows / ((int64_t)kBatchRows * 2 * n_cu);
+    return kBatchRows * (int)(rounds >= 32 ? (rounds >= 512 ? 16 : rounds / 32) : 1);
 }
 
 int batch_direct_f32c_blocks_per_cu() { return resident(k_batch_direct_f32c, kBatchF32Block); }
 
-hipError_t launch_batch_direct(hipStream_t s, int vpl, int grid, const BatchInst* inst,
-                               const WorkItem* items, unsigned n_items, unsigned* counter,
-                               int* status) {
+hipError_t launch_batch_direct(hipStream_t s, const BatchInst* inst, const WorkItem* items,
+                               unsigned n_items, int* status) {
     if (n_items == 0) return hipSuccess;
-    const dim3 g(grid), b(kTabBlock);
-    switch (vpl) {
-        case 1: k_batch_direct<1><<<g, b, 0, s>>>(inst, items, n_items, counter, status); break;
-        case 2: k_batch_direct<2><<<g, b, 0, s>>>(inst, items, n_items, counter, status); break;
-        case 4: k_batch_direct<4><<<g, b, 0, s>>>(inst, items, n_items, counter, status); break;
-        default: return hipErrorInvalidValue;
-    }
+    k_batch_direct<<<dim3(n_items), dim3(kTabBlock), 0, s>>>(inst, items, status);
     return hipGetLastError();
 }
 

@@ -152,56 +152,11 @@ k_direct_cell_split(const double* __restrict__ u, const double* __restrict__ v,
                     const double* __restrict__ w, int64_t n_vis,
                     const CompCell* __restrict__ comp, int n_comp, double sgn,
                     OUT* __restrict__ out, int* __restrict__ status) {
-    constexpr int kLanes = kTabBlock / SPLIT;   // lanes that own rows
-    constexpr int kRows = kLanes * VPL;         // rows per workgroup
     __shared__ Cell T[kTabCells];
-    static_assert(8 * kRows <= kTabCells, "range sums fit where the table was");
     fill_cells(T);
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int part = wave % SPLIT, local = wave / SPLIT * 64 + lane;
-    const int64_t row0 = (int64_t)blockIdx.x * kRows;
-    int64_t j[VPL];
-#pragma unroll
-    for (int i = 0; i < VPL; ++i) j[i] = row0 + i * kLanes + local;
-    double U[VPL], V[VPL], W[VPL];
-    const bool wide = load_rows<VPL>(j, n_vis, u, v, w, kTabMaxBaseline, U, V, W);
-    const CompRanges R(n_comp);
-    constexpr int kOwn = 8 / SPLIT;   // ranges per wave
-    double pr[kOwn][VPL], pi[kOwn][VPL];
-#pragma unroll
-    for (int q = 0; q < kOwn; ++q) {
-        const auto keep = [&](int, const double(&re)[VPL], const double(&im)[VPL]) {
-#pragma unroll
-            for (int i = 0; i < VPL; ++i) {
-                pr[q][i] = re[i];
-                pi[q][i] = im[i];
-            }
-        };
-        const int a = part * kOwn + q;
-        if (__builtin_expect(wide, 0))
-            range_sums<VPL, true>((CellPtr)T, uniform_ptr(comp), R, a, a + 1, U, V, W, keep);
-        else
-            range_sums<VPL, false>((CellPtr)T, uniform_ptr(comp), R, a, a + 1, U, V, W, keep);
-    }
-    __syncthreads();   // every wave is done with the table
-#pragma unroll
-    for (int q = 0; q < kOwn; ++q)
-#pragma unroll
-        for (int i = 0; i < VPL; ++i)
-            T[(part * kOwn + q) * kRows + i * kLanes + local] = Cell{pr[q][i], pi[q][i]};
-    __syncthreads();
-    for (int r = threadIdx.x; r < kRows && row0 + r < n_vis; r += kTabBlock) {
-        double re = 0.0, im = 0.0;
-#pragma unroll
-        for (int a = 0; a < 8; ++a) {
-            const Cell p = T[a * kRows + r];
-            re += p.x;
-            im += p.y;
-        }
-        const int64_t jr = row0 + r;
-        if (!isfinite(u[jr] + v[jr] + w[jr])) atomicOr(status, kStatusNonFinite);
-        store_vis(out, jr, re, sgn * im);
-    }
+    const auto put = [out](int64_t row, double re, double im) { store_vis(out, row, re, im); };
+    direct_block_cell<VPL, SPLIT>(T, (int64_t)blockIdx.x * (kTabBlock / SPLIT * VPL), n_vis, u, v,
+                                  w, comp, n_comp, sgn, put, status);
 }
 
 // The smallest row counts: workgroup (x, b) takes 64 rows and sub-range b of
@@ -217,7 +172,7 @@ k_direct_cell_part(const double* __restrict__ u, const double* __restrict__ v,
     const int b = blockIdx.y;
     const int64_t j[1] = {(int64_t)blockIdx.x * 64 + lane};
     double U[1], V[1], W[1], re[1] = {0.0}, im[1] = {0.0};
-    const bool wide = load_rows<1>(j, n_vis, u, v, w, kTabMaxBaseline, U, V, W);
+    const bool wide = load_rows<1>(j, n_vis, u, v, w, U, V, W);
     const CompRanges R(n_comp);
     const int k0 = R.begin(a, b), k1 = R.end(a, b);
     if (__builtin_expect(wide, 0))
@@ -383,15 +338,16 @@ __global__ __launch_bounds__(kF32cBlock) void k_direct_f32c_split(
     const int64_t row0 = (int64_t)blockIdx.x * kRows;
     const int64_t j[1] = {row0 + local};
     double U[1], V[1], W[1];
-    const bool far = load_rows<1>(j, n_vis, u, v, w, kTurnMaxBaseline, U, V, W);
+    TurnRow row[1];
+    const int form = load_rows_f32c<1>(j, n_vis, u, v, w, U, V, W, row);
     const CompRanges R(n_comp, kF32cSub);
     const auto keep = [&](int a, const double(&re)[1], const double(&im)[1]) {
         part[a][local] = make_double2(re[0], im[0]);
     };
-    if (__builtin_expect(far, 0))
-        range_sums_f32c<1, false>(uniform_ptr(comp), R, own * kOwn, (own + 1) * kOwn, U, V, W, keep);
-    else
-        range_sums_f32c<1, true>(uniform_ptr(comp), R, own * kOwn, (own + 1) * kOwn, U, V, W, keep);
+    with_form(form, [&](auto f) {
+        range_sums_f32c<1, decltype(f)::value>(uniform_ptr(comp), R, own * kOwn, (own + 1) * kOwn,
+                                               U, V, W, row, keep);
+    });
     __syncthreads();
     for (int r = threadIdx.x; r < kRows && row0 + r < n_vis; r += kF32cBlock) {
         double re = 0.0, im = 0.0;
@@ -416,14 +372,13 @@ __global__ __launch_bounds__(kF32cBlock) void k_direct_f32c_part(
     const int b = blockIdx.y;
     const int64_t j[1] = {(int64_t)blockIdx.x * 64 + lane};
     double U[1], V[1], W[1], re[1] = {0.0}, im[1] = {0.0};
-    const bool far = load_rows<1>(j, n_vis, u, v, w, kTurnMaxBaseline, U, V, W);
+    TurnRow row[1];
+    const int form = load_rows_f32c<1>(j, n_vis, u, v, w, U, V, W, row);
     const CompRanges R(n_comp, kF32cSub);
     const int k0 = R.begin(a, b), k1 = R.end(a, b);
-    const double magic = vector_const(kTurnMagic);
-    if (__builtin_expect(far, 0))
-        add_components_f32c<1, false>(uniform_ptr(comp), magic, k0, k1, U, V, W, re, im);
-    else
-        add_components_f32c<1, true>(uniform_ptr(comp), magic, k0, k1, U, V, W, re, im);
+    with_form(form, [&](auto f) {
+        add_components_f32c<1, decltype(f)::value>(uniform_ptr(comp), k0, k1, U, V, W, row, re, im);
+    });
     if (j[0] < n_vis) {
         if (a == 0 && b == 0 && !isfinite(U[0] + V[0] + W[0])) atomicOr(status, kStatusNonFinite);
         partial[((int64_t)a * 8 + b) * n_vis + j[0]] = make_double2(re[0], im[0]);

@@ -69,8 +69,7 @@ __device__ __forceinline__ bool chunk_is_wide(const WaveJob& job, const double* 
     bool big = false;
     if (job.active)
         for (int j = threadIdx.x & 63; j < job.nrow; j += 64)
-            big = big || !(fabs(u[job.j0 + j]) + fabs(v[job.j0 + j]) + fabs(w[job.j0 + j]) <
-                           kTabMaxBaseline);
+            big = big || !cells_reach(u[job.j0 + j], v[job.j0 + j], w[job.j0 + j]);
     return __any(big);
 }
 

@@ -163,29 +163,35 @@ struct BatchInst {
     double sgn;
 };
 
-// A tile of rows [row0, row0 + nrows) of one instance.
+// A tile of rows [row0, row0 + nrows) of one instance; split: the FP64 kernel's
+// waves share its rows' components.
 struct WorkItem {
     int64_t row0;
     int inst;
     int nrows;
+    int split;
+    int unused;
 };
 
 hipError_t launch_batch_ingest(hipStream_t s, const BatchInst* inst, int n_inst, int max_comp,
                                int* status);
 hipError_t launch_reset_counters(hipStream_t s, unsigned* counters, int n);
-// Blocks per CU that stay resident for the persistent kernels: FP64 (blocks of
-// kTabBlock threads) and F32C (blocks of kBatchF32Block).
-int batch_direct_blocks_per_cu(int vpl);
-// Rows per lane of a persistent FP64 launch over `rows` rows: fewer when the
-// widest would leave a resident wave less than four row tiles to balance with.
-int batch_direct_vpl(int64_t rows, int vpl_max, int n_cu);
+// Items of FP64 direct instances and of trees of either precision go through the
+// first launch (a workgroup each), those of F32C direct instances through the
+// second (persistent, batch_direct_f32c_blocks_per_cu() blocks of kBatchF32Block
+// threads on each CU).
+constexpr int kBatchRows = 2048, kBatchSplitRows = 256;
+// Whether an instance's items share their rows' components: long lists (as
+// direct_shape finds), and any list where whole rows would make less than four
+// rounds of workgroups in all.
+bool batch_split(int64_t total_rows, int64_t n_comp, int n_cu);
+// Rows of its items: more than kBatchRows, and so fewer table fills, where that
+// leaves 32 rounds of workgroups.
+int batch_item_rows(int64_t total_rows, int64_t n_comp, int n_cu);
 int batch_direct_f32c_blocks_per_cu();
 constexpr int kBatchF32Vpl = 2, kBatchF32Block = 64;
-// Items of FP64 direct instances and of trees of either precision go through the
-// first launch, those of F32C direct instances through the second.
-hipError_t launch_batch_direct(hipStream_t s, int vpl, int grid, const BatchInst* inst,
-                               const WorkItem* items, unsigned n_items, unsigned* counter,
-                               int* status);
+hipError_t launch_batch_direct(hipStream_t s, const BatchInst* inst, const WorkItem* items,
+                               unsigned n_items, int* status);
 hipError_t launch_batch_direct_f32c(hipStream_t s, int grid, const BatchInst* inst,
                                     const WorkItem* items, unsigned n_items, unsigned* counter,
                                     int* status);

@@ -40,6 +40,9 @@ constexpr double kTabMagic = 1.5 * 0x1p40;
 // Rows whose |u| + |v| + |w| stays below this have |phase| < 2^39 for every
 // direction with |l|, |m|, |n - 1| <= 2.
 constexpr double kTabMaxBaseline = 0x1p38;
+__device__ __forceinline__ bool cells_reach(double u, double v, double w) {
+    return fabs(u) + fabs(v) + fabs(w) < kTabMaxBaseline;
+}
 
 typedef double Cell __attribute__((ext_vector_type(2)));
 using CellPtr = const __attribute__((address_space(3))) Cell*;

@@ -64,3 +64,16 @@ def test_rows_beyond_the_magic_number(env):
         swv.synchronize()
     keep = ~np.isin(np.arange(n), (70, 300))
     assert np.isnan(x[~keep]).all() and np.abs(x[keep] - ref[keep]).max() <= PER_TERM * k
+
+
+def test_a_row_keeps_its_bits_beside_far_rows(env):
+    torch, swv = env
+    rng = np.random.default_rng(6)
+    u, v, w = (rng.uniform(-5e4, 5e4, 300) for _ in range(3))
+    l, m, f = rng.uniform(-0.03, 0.03, 50), rng.uniform(-0.03, 0.03, 50), rng.lognormal(-3, 1, 50)
+    run = lambda a: host(swv.predict_direct(*(dev(x, torch) for x in (a, v, w, l, m, f)), prec="f32c"))
+    alone = run(u)
+    u2 = u.copy()
+    u2[[0, 130, 299]] = 4e5, 3e7, -2e6
+    keep = ~np.isin(np.arange(300), (0, 130, 299))
+    assert np.array_equal(run(u2)[keep], alone[keep])
