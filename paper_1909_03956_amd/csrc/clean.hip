@@ -419,12 +419,7 @@ int grid_image(swv_ctx ctx, const GridGeom& g, const GridPlan& p, int64_t n_vis,
     const int64_t cap = std::max<int64_t>(1, (int64_t)(kGridSlabBytes / grid_row_bytes(g)));
     const int64_t n_slabs = (n_vis + cap - 1) / cap;
     const int64_t rows = (n_vis + n_slabs - 1) / n_slabs;
-    int64_t chunk = choose_chunk(rows, p.tiles, ctx->n_cu, grid_blocks_per_cu());
-    // the dies' clocks differ, and with a single round of workgroups the faster
-    // ones wait: four shorter rounds take 2.95 instead of 3.22 ms (256^2 pixels,
-    // 176,904 rows) and 5.2 instead of 5.8 ms (511^2, 88,904 rows)
-    if ((rows + chunk - 1) / chunk * p.tiles < 4 * (int64_t)ctx->n_cu * grid_blocks_per_cu())
-        chunk = std::max<int64_t>(64, (chunk + 3) / 4);
+    const int64_t chunk = grid_chunk(g, p, rows, ctx->n_cu);
     const int64_t n_chunks = (rows + chunk - 1) / chunk;
     int rc = ensure(ctx, ctx->grid, grid_slab_bytes(g, rows));
     if (!rc) rc = ensure(ctx, ctx->partial, grid_partial_bytes(g, n_chunks));

@@ -10,11 +10,11 @@
 // The kernel accumulates P, Q, R, S per quad (|l|, |m|): 25 FP64 instructions
 // per row and quad (4 for the w phase and its cell, 5 for the rest of the
 // angle, 8 to turn y, 8 for the products), 6.25 a pixel where the general
-// adjoint takes 20 (table phasor) and throws its imaginary half away.  Bound by
-// FP64 issue: 176,904 rows x 256^2 pixels 19.6 -> 2.95 ms, the same of a 511^2
-// beam (y = 1, 21 instructions) 60 -> 10.4 ms, about 70 % of the issue rate at
-// 2.4 GHz.  With every table read from one row instead: 2.81 and 9.6 ms, so the
-// loads are nearly hidden.
+// adjoint takes 20 (table phasor) and throws its imaginary half away.  n - 1 is
+// also the same for (|l|, |m|) and (|m|, |l|): such a pair of quads, an octet,
+// shares z and takes 33.  Bound by FP64 issue: 176,904 rows x 256^2 pixels
+// 2.64 ms (19.6 by the adjoint with the polynomial phasor, 2.90 by quads alone),
+// 88,904 rows of a 511^2 beam (y = 1, four instructions less) 4.60 ms (30; 5.10).
 //
 // Accuracy: the phases u l, v m are reduced with their products' rounding
 // errors, w (n - 1) enters the cell search and the rest by FMAs, so no phase is
@@ -23,11 +23,14 @@
 // Layout.  A prep kernel writes, for a slab of rows, {w, y} records and the
 // tables E_x, E_y (16 (Kx + Ky) + 32 bytes a row; slabs bound the workspace).
 // A wave takes 64 neighbouring |k| of one axis (the lane axis, E by coalesced
-// vector loads) and up to four of the other (E by scalar loads, an SGPR operand
-// of every lane's products).  Kx is rarely a multiple of 64 (129 for a 256-pixel
-// side), so what is left over beyond whole waves of one axis is covered by a
-// strip with the axes exchanged.
-#include "chunking.h"
+// vector loads) and a few of the other (E by scalar loads, an SGPR operand of
+// every lane's products).  The square of whole 64 x 64 blocks goes by octets below
+// its diagonal and by quads on it.  Kx is rarely a multiple of 64 (129 for a
+// 256-pixel side): what is left over beyond whole waves is covered by strips with
+// the axes exchanged.
+//
+// Jobs (wave, chunk of rows) are numbered chunk-major and dealt in runs, one run
+// of workgroups per XCD, as in the adjoint.
 #include "device_math.h"
 #include "launch.h"
 #include "phasor_table.h"
@@ -36,7 +39,8 @@ namespace swv {
 
 namespace {
 
-constexpr int kStep = 4;   // scalar-axis positions per wave
+constexpr int kStep = 4;   // scalar-axis positions per wave of quads
+constexpr int kOct = 2;    // of octets
 
 // One row of a slab as the kernel reads it (scalar loads); wide: |w| asks for
 // the WIDE form of the cell search.
@@ -85,12 +89,11 @@ namespace {
 using RowPtr = const __attribute__((address_space(4))) GridRow*;
 using ScalarCells = const __attribute__((address_space(4))) Cell*;
 
-// acc[i] += (P, lane-sine products Q and R, step-sine product S) of row
-// (w, z = y): UNIT for y = 1.
+// (zr, zi) of G phases w nm1[i]: E_w y, UNIT for y = 1.
 template <int G, bool UNIT, bool WIDE>
-__device__ __forceinline__ void add_row(CellPtr T, const CellCoefs& K, double w, double yr, double yi, Cell a,
-                                        ScalarCells b, const double (&nm1)[G],
-                                        double (&acc)[G][4]) {
+__device__ __forceinline__ void turn_row_value(CellPtr T, const CellCoefs& K, double w, double yr,
+                                               double yi, const double (&nm1)[G], double (&zr)[G],
+                                               double (&zi)[G]) {
     Cell e[G];
     double d[G];
 #pragma unroll
@@ -104,99 +107,119 @@ __device__ __forceinline__ void add_row(CellPtr T, const CellCoefs& K, double w,
             tr = fma(cr, yr, -(sr * yi));
             ti = fma(cr, yi, sr * yr);
         }
-        const double zr = fma(e[i].x, tr, -(e[i].y * ti));
-        const double zi = fma(e[i].x, ti, e[i].y * tr);
-        const double cb = b[i].x, sb = b[i].y;
-        acc[i][0] = fma(zr * a.x, cb, acc[i][0]);
-        acc[i][1] = fma(zr * a.y, sb, acc[i][1]);
-        acc[i][2] = fma(zi * a.y, cb, acc[i][2]);
-        acc[i][3] = fma(zi * a.x, sb, acc[i][3]);
+        zr[i] = fma(e[i].x, tr, -(e[i].y * ti));
+        zi[i] = fma(e[i].x, ti, e[i].y * tr);
     }
 }
 
-template <int G, bool UNIT, bool WIDE>
-__device__ __forceinline__ void add_rows(CellPtr T, const CellCoefs& K, RowPtr R, int nrow,
+// acc += (P, Q, R, S) of one quad: a the lane axis' phasor, b the step axis' (R
+// has the lane axis' sine).
+__device__ __forceinline__ void add_quad(double zr, double zi, Cell a, double cb, double sb,
+                                         double (&acc)[4]) {
+    acc[0] = fma(zr * a.x, cb, acc[0]);
+    acc[1] = fma(zr * a.y, sb, acc[1]);
+    acc[2] = fma(zi * a.y, cb, acc[2]);
+    acc[3] = fma(zi * a.x, sb, acc[3]);
+}
+
+// Rows of a chunk into Q quads per lane and step position: Q = 1, or 2 for octets,
+// whose second quad has the other axis' tables at the same positions.
+template <int G, int Q, bool UNIT, bool WIDE>
+__device__ __forceinline__ void add_rows(CellPtr T, RowPtr R, int nrow,
                                          const Cell* __restrict__ A, int KA, ScalarCells B, int KB,
-                                         const double (&nm1)[G], double (&acc)[G][4]) {
-    Cell next = A[0];
+                                         const Cell* __restrict__ A2, ScalarCells B2,
+                                         const double (&nm1)[G], double (&acc)[Q][G][4]) {
+    const CellCoefs K = cell_coefs();
+    Cell next = A[0], next2 = Q == 2 ? A2[0] : Cell{0.0, 0.0};
 #pragma unroll 1
     for (int j = 0; j < nrow; ++j) {
-        const Cell a = next;
-        next = A[(int64_t)(j + 1 < nrow ? j + 1 : j) * KA];   // ahead of this row's arithmetic
-        add_row<G, UNIT, WIDE>(T, K, R[j].w, R[j].yr, R[j].yi, a, B + (int64_t)j * KB, nm1, acc);
+        const Cell a = next, a2 = next2;
+        const int64_t jn = j + 1 < nrow ? j + 1 : j;   // ahead of this row's arithmetic
+        next = A[jn * KA];
+        if constexpr (Q == 2) next2 = A2[jn * KB];
+        double zr[G], zi[G];
+        turn_row_value<G, UNIT, WIDE>(T, K, R[j].w, R[j].yr, R[j].yi, nm1, zr, zi);
+        const ScalarCells b = B + (int64_t)j * KB;
+#pragma unroll
+        for (int i = 0; i < G; ++i) add_quad(zr[i], zi[i], a, b[i].x, b[i].y, acc[0][i]);
+        if constexpr (Q == 2) {
+            const ScalarCells b2 = B2 + (int64_t)j * KA;
+#pragma unroll
+            for (int i = 0; i < G; ++i) add_quad(zr[i], zi[i], a2, b2[i].x, b2[i].y, acc[1][i]);
+        }
     }
 }
 
-// One wave's quads (lane position `lane`, step positions step0 .. step0 + G) over
-// the rows of a chunk.
-template <int G, bool UNIT>
+struct GridData {
+    const GridRow* rec;
+    const Cell *ex, *ey;
+    double* partial;
+    bool resume;
+};
+
+// One wave's quads or octets (lane position `lane`, step positions step ..
+// step + G) over the rows of a chunk.
+template <int G, int Q, bool UNIT>
 __device__ __forceinline__ void grid_wave(CellPtr T, const GridGeom& g, bool swapped, int lane,
                                           int lane_end, int step, int step_end, int64_t j0,
-                                          int nrow, const GridRow* rec, const Cell* ex,
-                                          const Cell* ey, bool wide, bool resume, int64_t quad_base,
-                                          double* partial) {
+                                          int nrow, bool wide, const GridData& data,
+                                          int64_t quad_base) {
     const int la = lane < lane_end ? lane : lane_end - 1;   // idle lanes repeat the last
     const int KA = swapped ? g.Ky : g.Kx, KB = swapped ? g.Kx : g.Ky;
-    const Cell* __restrict__ A = (swapped ? ey : ex) + j0 * KA + la;
-    ScalarCells B = uniform_ptr((swapped ? ex : ey) + j0 * KB + step);
-    RowPtr R = uniform_ptr(rec + j0);
-    double nm1[G], acc[G][4];
-    int64_t quad[G];
+    const Cell* __restrict__ A = (swapped ? data.ey : data.ex) + j0 * KA + la;
+    const ScalarCells B = uniform_ptr((swapped ? data.ex : data.ey) + j0 * KB + step);
+    // octets (lanes along x): the other quad's lane axis is y, its step axis x
+    const Cell* __restrict__ A2 = data.ey + j0 * KB + la;
+    const ScalarCells B2 = uniform_ptr(data.ex + j0 * KA + step);
+    const RowPtr R = uniform_ptr(data.rec + j0);
+    double nm1[G], acc[Q][G][4];
+    int64_t quad[Q][G];
 #pragma unroll
     for (int i = 0; i < G; ++i) {
         const int st = step + i < step_end ? step + i : step_end - 1;
         const int kx = swapped ? st : la, ky = swapped ? la : st;
         nm1[i] = g.nm1(kx, ky);
-        quad[i] = quad_base + (int64_t)ky * g.Kx + kx;
+        quad[0][i] = quad_base + (int64_t)ky * g.Kx + kx;
+        if constexpr (Q == 2) quad[1][i] = quad_base + (int64_t)kx * g.Kx + ky;
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-            acc[i][t] = resume ? partial[4 * quad[i] + (swapped && t >= 2 ? 5 - t : t)] : 0.0;
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                // lanes along y: R and S change places
+                const int at = (swapped || q == 1) && t >= 2 ? 5 - t : t;
+                acc[q][i][t] = data.resume ? data.partial[4 * quad[q][i] + at] : 0.0;
+            }
     }
-    const CellCoefs K = cell_coefs();
     if (__builtin_expect(wide, 0))
-        add_rows<G, UNIT, true>(T, K, R, nrow, A, KA, B, KB, nm1, acc);
+        add_rows<G, Q, UNIT, true>(T, R, nrow, A, KA, B, KB, A2, B2, nm1, acc);
     else
-        add_rows<G, UNIT, false>(T, K, R, nrow, A, KA, B, KB, nm1, acc);
+        add_rows<G, Q, UNIT, false>(T, R, nrow, A, KA, B, KB, A2, B2, nm1, acc);
 #pragma unroll
-    for (int i = 0; i < G; ++i) {
-        if (lane < lane_end && step + i < step_end) {
-            // exchanged axes: R and S change places
-            double2* o = (double2*)(partial + 4 * quad[i]);
-            o[0] = make_double2(acc[i][0], acc[i][1]);
-            o[1] = swapped ? make_double2(acc[i][3], acc[i][2]) : make_double2(acc[i][2], acc[i][3]);
-        }
-    }
+    for (int i = 0; i < G; ++i)
+        if (lane < lane_end && step + i < step_end)
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                double2* o = (double2*)(data.partial + 4 * quad[q][i]);
+                const double(&x)[4] = acc[q][i];
+                o[0] = make_double2(x[0], x[1]);
+                o[1] = swapped || q == 1 ? make_double2(x[3], x[2]) : make_double2(x[2], x[3]);
+            }
 }
 
 }  // namespace
 
-// Block (chunk, tile): the tile's waves take consecutive jobs, first those of
-// the main region, then the strip's.
 template <bool UNIT>
 __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_grid_sums(
-    GridGeom g, GridPlan p, int64_t n_rows, int64_t chunk, int64_t n_chunks, int64_t bid0,
-    const GridRow* __restrict__ rec, const Cell* __restrict__ ex, const Cell* __restrict__ ey,
-    bool resume, double* __restrict__ partial) {
+    GridGeom g, GridPlan p, int64_t n_rows, int64_t chunk, int64_t jobs, int64_t run,
+    GridData data) {
     __shared__ Cell T[kTabCells];
-    int64_t chunk_id, tile;
-    chunk_tile(bid0 + blockIdx.x, p.tiles, chunk_id, tile);
-    if (chunk_id >= n_chunks) return;   // padding of the last XCD group (whole block)
-    fill_cells(T);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int64_t job = tile * (kTabBlock / 64) + wave;
-    const bool strip = job >= p.jobs[0];
-    if (strip) job -= p.jobs[0];
-    if (job >= p.jobs[strip]) return;
-    // (region, exchanged) of a job; lane tiles run fastest, so neighbouring waves
-    // share their scalar-axis positions
-    const int region = __builtin_amdgcn_readfirstlane(strip ? 1 : 0);
-    const int lane0 = p.lane0[region], lane_end = lane0 + p.lane_n[region];
-    const int step0 = p.step0[region], step_end = step0 + p.step_n[region];
-    const bool swapped = p.swapped != (region == 1);
-    const int lt = (p.lane_n[region] + 63) / 64;
-    const int la = lane0 + (int)(job % lt) * 64 + lane;
-    const int step = __builtin_amdgcn_readfirstlane(step0 + (int)(job / lt) * kStep);
-    const int left = step_end - step;
+    const int64_t bid = blockIdx.x;
+    const int64_t all = ((bid & 7) * run + (bid >> 3)) * (kTabBlock / 64) + wave;
+    fill_cells(T);
+    if (all >= jobs) return;
+    const int64_t chunk_id = all / p.jobs;
+    int64_t job = all - chunk_id * p.jobs;
     const int64_t j0 = chunk_id * chunk;
     const int nrow = __builtin_amdgcn_readfirstlane(
         (int)(j0 + chunk < n_rows ? chunk : n_rows - j0));
@@ -204,17 +227,51 @@ __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) 
     const CellPtr TP = (CellPtr)T;
     // a row that needs the WIDE form puts the whole chunk through it
     bool any = false;
-    for (int j = lane; j < nrow; j += 64) any = any || rec[j0 + j].wide != 0;
+    for (int j = lane; j < nrow; j += 64) any = any || data.rec[j0 + j].wide != 0;
     const bool wide = __any(any);
+    if (job < p.oct_jobs) {
+        // block row b of the square has 64 b / kOct jobs, the ones above it 16 b (b - 1)
+        static_assert(kOct == 2, "numbering of the octets");
+        int b = (int)((1.0f + sqrtf(1.0f + 0.25f * (float)job)) * 0.5f);
+        while (16 * (int64_t)b * (b - 1) > job) --b;
+        while (16 * (int64_t)(b + 1) * b <= job) ++b;
+        b = __builtin_amdgcn_readfirstlane(b);
+        const int step =
+            __builtin_amdgcn_readfirstlane((int)(job - 16 * (int64_t)b * (b - 1)) * kOct);
+        grid_wave<kOct, 2, UNIT>(TP, g, false, 64 * b + lane, 64 * b + 64, step, 64 * b, j0, nrow,
+                                 wide, data, base);
+        return;
+    }
+    job -= p.oct_jobs;
+    GridRegion r;
+    int la, step;
+    if (job < p.diag_jobs) {
+        const int b = (int)(job / (64 / kStep));
+        r = GridRegion{64 * b, 64, 64 * b, 64, false};
+        la = 64 * b + lane;
+        step = 64 * b + (int)(job % (64 / kStep)) * kStep;
+    } else {
+        job -= p.diag_jobs;
+        int q = 0;
+        while (q < 2 && job >= p.region_jobs[q]) job -= p.region_jobs[q++];
+        r = p.region[q];
+        // lane tiles run fastest, so neighbouring waves share their step positions
+        const int lt = (r.lane_n + 63) / 64;
+        la = r.lane0 + (int)(job % lt) * 64 + lane;
+        step = r.step0 + (int)(job / lt) * kStep;
+    }
+    step = __builtin_amdgcn_readfirstlane(step);
+    const int lane_end = r.lane0 + r.lane_n, step_end = r.step0 + r.step_n;
+    const int left = __builtin_amdgcn_readfirstlane(step_end - step);
     if (left > 2)
-        grid_wave<4, UNIT>(TP, g, swapped, la, lane_end, step, step_end, j0, nrow, rec, ex, ey,
-                           wide, resume, base, partial);
+        grid_wave<4, 1, UNIT>(TP, g, r.swapped, la, lane_end, step, step_end, j0, nrow, wide, data,
+                              base);
     else if (left == 2)
-        grid_wave<2, UNIT>(TP, g, swapped, la, lane_end, step, step_end, j0, nrow, rec, ex, ey,
-                           wide, resume, base, partial);
+        grid_wave<2, 1, UNIT>(TP, g, r.swapped, la, lane_end, step, step_end, j0, nrow, wide, data,
+                              base);
     else
-        grid_wave<1, UNIT>(TP, g, swapped, la, lane_end, step, step_end, j0, nrow, rec, ex, ey,
-                           wide, resume, base, partial);
+        grid_wave<1, 1, UNIT>(TP, g, r.swapped, la, lane_end, step, step_end, j0, nrow, wide, data,
+                              base);
 }
 
 // Adds the chunks of each quad (16 threads take every 16th chunk in order, their
@@ -260,11 +317,32 @@ static void axis_offsets(int n, int64_t c, int64_t* first, int64_t* count) {
     *count = (a > b ? a : b) - *first + 1;
 }
 
-// Waves of a cover: the whole lane tiles, and the rest either as one more,
-// partly idle lane tile or as a strip with the axes exchanged.
-static int64_t cover(int64_t lane_n, int64_t step_n, bool strip) {
-    if (!strip) return (lane_n + 63) / 64 * step_n;
-    return lane_n / 64 * step_n + lane_n % 64 * ((step_n + 63) / 64);
+// Instructions per row of a wave of `n` step positions.
+static int64_t quads_cost(int64_t n) { return 25 * n; }
+
+// Covers x in [x0, x0 + nX), y in [y0, y0 + nY) by at most two regions: lanes along
+// the axis that wastes less, and its rest beyond whole waves either as one more,
+// partly idle lane tile or as a strip with the axes exchanged.  Returns the cost.
+static int64_t cover(int x0, int nX, int y0, int nY, GridRegion out[2]) {
+    int64_t best = INT64_MAX;
+    out[0] = out[1] = GridRegion{0, 0, 0, 0, false};
+    if (nX <= 0 || nY <= 0) return 0;
+    for (int swapped = 0; swapped < 2; ++swapped)
+        for (int strip = 0; strip < 2; ++strip) {
+            const int l0 = swapped ? y0 : x0, ln = swapped ? nY : nX;
+            const int s0 = swapped ? x0 : y0, sn = swapped ? nX : nY;
+            const int rest = ln % 64;
+            if (strip && rest == 0) continue;
+            const int main_n = strip ? ln - rest : ln;
+            const int64_t cost = (int64_t)((main_n + 63) / 64) * quads_cost(sn) +
+                                 (strip ? (int64_t)((sn + 63) / 64) * quads_cost(rest) : 0);
+            if (cost >= best) continue;
+            best = cost;
+            out[0] = GridRegion{l0, main_n, s0, main_n ? sn : 0, swapped != 0};
+            out[1] = strip ? GridRegion{s0, sn, l0 + main_n, rest, swapped == 0}
+                           : GridRegion{0, 0, 0, 0, false};
+        }
+    return best;
 }
 
 bool grid_plan(int nx, int ny, int cx, int cy, double cell, GridGeom* g, GridPlan* p) {
@@ -274,34 +352,42 @@ bool grid_plan(int nx, int ny, int cx, int cy, double cell, GridGeom* g, GridPla
     // offsets are used as ints; a centre that far away shares nothing anyway
     if (x0 + nX > (int64_t(1) << 30) || y0 + nY > (int64_t(1) << 30)) return false;
     *g = GridGeom{(int)x0, (int)nX, (int)y0, (int)nY, cell};
-    int64_t best = INT64_MAX;
-    for (int swapped = 0; swapped < 2; ++swapped)
-        for (int strip = 0; strip < 2; ++strip) {
-            const int64_t ln = swapped ? nY : nX, sn = swapped ? nX : nY;
-            if (strip && (ln % 64 == 0)) continue;
-            const int64_t waves = cover(ln, sn, strip != 0);
-            if (waves >= best) continue;
-            best = waves;
-            *p = GridPlan{};
-            p->swapped = swapped != 0;
-            const int main_n = (int)(strip ? ln / 64 * 64 : ln);
-            p->lane_n[0] = main_n;
-            p->step_n[0] = main_n ? (int)sn : 0;
-            if (strip) {   // axes exchanged: lanes along the other axis
-                p->lane_n[1] = (int)sn;
-                p->step0[1] = main_n;
-                p->step_n[1] = (int)(ln - main_n);
-            }
-        }
-    for (int r = 0; r < 2; ++r)
-        p->jobs[r] = (int64_t)((p->lane_n[r] + 63) / 64) * ((p->step_n[r] + kStep - 1) / kStep);
-    const int per_block = kTabBlock / 64;
-    p->tiles = (p->jobs[0] + p->jobs[1] + per_block - 1) / per_block;
-    // 25 instructions per quad and row against 20 per pixel of the general
-    // adjoint (its idle lanes are few): 256^2 about its centre 264 waves of quads
-    // against 1,024 of pixels
-    const int64_t pixel_waves = ((int64_t)nx * ny + 63) / 64;
-    return 25 * best <= 20 * pixel_waves;
+    *p = GridPlan{};
+    const int Kx = (int)nX, Ky = (int)nY;
+    // whole 64 x 64 blocks of the square in which (i, k) and (k, i) have one n
+    int nb = x0 == y0 ? (Kx < Ky ? Kx : Ky) / 64 : 0;
+    if (nb < 2) nb = 0;
+    const int64_t b = nb;
+    const int sq = 64 * nb;
+    p->oct_jobs = 16 * b * (b - 1);
+    p->diag_jobs = b * (64 / kStep);
+    int64_t cost = p->oct_jobs * 33 * kOct + p->diag_jobs * quads_cost(kStep);
+    // beside the square: x from sq on, then, over the square, y from sq on
+    cost += cover(sq, Kx - sq, 0, Ky, p->region);
+    if (sq > 0 && Ky > sq) {
+        cost += b * quads_cost(Ky - sq);   // whole lane tiles along x
+        p->region[2] = GridRegion{0, sq, sq, Ky - sq, false};
+    }
+    p->jobs = p->oct_jobs + p->diag_jobs;
+    for (int r = 0; r < 3; ++r) {
+        const GridRegion& R = p->region[r];
+        p->region_jobs[r] = (int64_t)((R.lane_n + 63) / 64) * ((R.step_n + kStep - 1) / kStep);
+        p->jobs += p->region_jobs[r];
+    }
+    // against 20 instructions per pixel of the general adjoint, whose idle lanes
+    // are few: 256^2 about its centre 5,400 for quads and octets, 20,480 for pixels
+    return cost <= 20 * (((int64_t)nx * ny + 63) / 64);
+}
+
+// Rows per chunk: four rounds of workgroups (two per CU) rather than one, since
+// the dies' clocks differ, while the partial sums stay within 256 MiB (8 chunks at
+// least); 64 rows at least, so that filling the table stays small beside them.
+int64_t grid_chunk(const GridGeom& g, const GridPlan& p, int64_t rows, int n_cu) {
+    const int64_t fill = 4 * (int64_t)n_cu * 2 * (kTabBlock / 64) / p.jobs;
+    const int64_t cap = (int64_t(256) << 20) / (32 * (int64_t)g.Kx * g.Ky);
+    const int64_t chunks = fill < cap ? (fill < 8 ? 8 : fill) : (cap < 8 ? 8 : cap);
+    const int64_t chunk = (rows + chunks - 1) / chunks;
+    return chunk < 64 ? 64 : (chunk < (int64_t(1) << 30) ? chunk : int64_t(1) << 30);
 }
 
 size_t grid_row_bytes(const GridGeom& g) {
@@ -317,8 +403,6 @@ size_t grid_partial_bytes(const GridGeom& g, int64_t n_chunks) {
     return 32 * (size_t)g.Kx * (size_t)g.Ky * (size_t)n_chunks;
 }
 
-int grid_blocks_per_cu() { return 2; }
-
 hipError_t launch_grid_slab(hipStream_t s, const GridGeom& g, const GridPlan& p, int64_t rows,
                             int64_t chunk, const double* u, const double* v, const double* w,
                             const void* y, int sign, bool resume, void* slab, double* partial) {
@@ -332,15 +416,15 @@ hipError_t launch_grid_slab(hipStream_t s, const GridGeom& g, const GridPlan& p,
         u, v, w, (const double2*)y, rows, g, sign > 0 ? -1.0 : 1.0, rec, ex, ey);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int64_t n_chunks = (rows + chunk - 1) / chunk;
-    launch_slabs(xcd_padded(n_chunks) * p.tiles, [&](int64_t b0, unsigned b) {
-        if (y)
-            k_grid_sums<false><<<dim3(b), dim3(kTabBlock), 0, s>>>(g, p, rows, chunk, n_chunks, b0,
-                                                                   rec, ex, ey, resume, partial);
-        else
-            k_grid_sums<true><<<dim3(b), dim3(kTabBlock), 0, s>>>(g, p, rows, chunk, n_chunks, b0,
-                                                                  rec, ex, ey, resume, partial);
-    });
+    const int64_t jobs = (rows + chunk - 1) / chunk * p.jobs;
+    const int64_t per = kTabBlock / 64, run = ((jobs + per - 1) / per + 7) / 8;
+    if (run > (int64_t(1) << 27)) return hipErrorInvalidConfiguration;
+    const GridData data{rec, ex, ey, partial, resume};
+    const dim3 grid((unsigned)(8 * run)), blk(kTabBlock);
+    if (y)
+        k_grid_sums<false><<<grid, blk, 0, s>>>(g, p, rows, chunk, jobs, run, data);
+    else
+        k_grid_sums<true><<<grid, blk, 0, s>>>(g, p, rows, chunk, jobs, run, data);
     return hipGetLastError();
 }
 

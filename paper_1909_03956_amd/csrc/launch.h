@@ -99,13 +99,16 @@ struct GridGeom {
         return t < 1.0 ? -t / (1.0 + sqrt(1.0 - t)) : 0.0;
     }
 };
-// How waves cover the quads: region 0 with lanes along x (along y if swapped),
-// region 1, the rest of the lane axis, with the axes exchanged.
+// Quads with lanes along x (along y if swapped).
+struct GridRegion {
+    int lane0, lane_n, step0, step_n;
+    bool swapped;
+};
+// How waves cover the quads: octets and diagonal blocks of the square of whole 64
+// x 64 blocks, then up to three regions beside it.
 struct GridPlan {
-    int lane0[2] = {0, 0}, lane_n[2] = {0, 0}, step0[2] = {0, 0}, step_n[2] = {0, 0};
-    int64_t jobs[2] = {0, 0};
-    int64_t tiles = 0;   // workgroups per chunk of rows
-    bool swapped = false;
+    int64_t oct_jobs = 0, diag_jobs = 0, region_jobs[3] = {0, 0, 0}, jobs = 0;
+    GridRegion region[3] = {};
 };
 // Geometry and cover of an image; whether this form takes fewer instructions
 // than the general adjoint on the image's pixels.
@@ -113,7 +116,7 @@ bool grid_plan(int nx, int ny, int cx, int cy, double cell, GridGeom* g, GridPla
 size_t grid_row_bytes(const GridGeom& g);
 size_t grid_slab_bytes(const GridGeom& g, int64_t rows);
 size_t grid_partial_bytes(const GridGeom& g, int64_t n_chunks);
-int grid_blocks_per_cu();
+int64_t grid_chunk(const GridGeom& g, const GridPlan& p, int64_t rows, int n_cu);
 // Adds `rows` rows in chunks of `chunk` to the partial sums (resume) or starts
 // them.  y null: unit visibilities.
 hipError_t launch_grid_slab(hipStream_t s, const GridGeom& g, const GridPlan& p, int64_t rows,

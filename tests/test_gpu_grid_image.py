@@ -82,3 +82,19 @@ def test_non_finite_rows_reach_every_pixel(env):
         r[k][5] = np.nan if k != 2 else np.inf
         args = [dev(a, torch) for a in r[:3]] + [dev_c(r[3], torch)]
         assert not np.isfinite(host(swv.dirty_image(*args, 70, 66, 0.001))).any()
+
+
+@pytest.mark.parametrize("nx,ny,cx,cy,sign", [(255, 255, None, None, -1), (256, 383, None, None, 1),
+                                              (391, 259, 195, 129, -1), (300, 300, 128, 170, -1)])
+def test_octets_against_oracle(env, nx, ny, cx, cy, sign):
+    """Images with two and three whole 64-position blocks to the square, beside
+    longer axes and centres off the middle: pixels from every region."""
+    torch, swv = env
+    u, v, w, y = _rows(90, nx + ny)
+    cell = 0.5 / max(nx, ny)
+    got = host(swv.dirty_image(dev(u, torch), dev(v, torch), dev(w, torch), dev_c(y, torch), nx, ny,
+                               cell, cx, cy, sign))
+    c = (nx // 2 if cx is None else cx, ny // 2 if cy is None else cy)
+    l, m, nm1, _ = oc.image_grid(nx, ny, cell, *c)
+    ref = oc.dirty_image(u, v, w, y, l, m, nm1, sign)
+    assert np.all(np.abs(got.ravel() - ref) <= _bound(u, v, w, y, l, m, nm1))
