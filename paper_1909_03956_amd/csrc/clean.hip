@@ -432,7 +432,7 @@ int grid_image(swv_ctx ctx, const GridGeom& g, const GridPlan& p, int64_t n_vis,
                              y ? (const double2*)y + j : nullptr, sign, j > 0, ctx->grid.p, part);
         if (e != hipSuccess) return hip_fail(e, "swv_dirty_image");
     }
-    const hipError_t e = launch_grid_finish(ctx->stream, g, part, n_chunks, nx, ny, cx, cy, n_vis, img);
+    const hipError_t e = launch_grid_finish(ctx->stream, g, SWV_FP64, part, n_chunks, nx, ny, cx, cy, n_vis, img);
     return e == hipSuccess ? SWV_OK : hip_fail(e, "swv_dirty_image");
 }
 
@@ -483,8 +483,18 @@ extern "C" int swv_dirty_image(swv_ctx ctx, int64_t n_vis, const double* u, cons
     CLEAN_GUARD(ctx);
     GridGeom geom;
     GridPlan plan;
-    if (prec == SWV_FP64 && grid_plan(nx, ny, cx, cy, cell, &geom, &plan))
-        return grid_image(ctx, geom, plan, n_vis, u, v, w, y, nx, ny, cx, cy, sign, img_out);
+    if (grid_plan(nx, ny, cx, cy, cell, prec, &geom, &plan)) {
+        if (prec == SWV_FP64)
+            return grid_image(ctx, geom, plan, n_vis, u, v, w, y, nx, ny, cx, cy, sign, img_out);
+        // in the adjoint's chunks of rows, whose Kahan sums these are
+        const AdjointShape sh = adjoint_shape(ctx, n_vis, (int64_t)nx * ny, prec);
+        CLEAN_RC(ensure(ctx, ctx->partial, grid_partial_bytes(geom, sh.n_chunks)));
+        double* part = (double*)ctx->partial.p;
+        CLEAN_HIP(launch_image_f32c(ctx->stream, geom, plan, n_vis, sh.chunk, u, v, w, y, sign, part));
+        CLEAN_HIP(launch_grid_finish(ctx->stream, geom, prec, part, sh.n_chunks, nx, ny, cx, cy, n_vis,
+                                     img_out));
+        return SWV_OK;
+    }
     const int64_t n = (int64_t)nx * ny;
     CLEAN_RC(ensure(ctx, ctx->grid, 40 * (size_t)n));
     // the complex adjoint output first, so that it is 16-byte aligned for any n

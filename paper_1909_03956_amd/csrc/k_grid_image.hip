@@ -31,6 +31,8 @@
 //
 // Jobs (wave, chunk of rows) are numbered chunk-major and dealt in runs, one run
 // of workgroups per XCD, as in the adjoint.
+#include <type_traits>
+
 #include "device_math.h"
 #include "launch.h"
 #include "phasor_table.h"
@@ -208,6 +210,23 @@ __device__ __forceinline__ void grid_wave(CellPtr T, const GridGeom& g, bool swa
 
 }  // namespace
 
+namespace {
+
+// Region, lane position and first step of a job of the regions, `step` positions
+// to a job; lane tiles run fastest, so neighbouring waves share their positions.
+__device__ __forceinline__ GridRegion region_job(const GridPlan& p, int64_t job, int per, int lane,
+                                                 int& la, int& step) {
+    int q = 0;
+    while (q < 2 && job >= p.region_jobs[q]) job -= p.region_jobs[q++];
+    const GridRegion r = p.region[q];
+    const int lt = (r.lane_n + 63) / 64;
+    la = r.lane0 + (int)(job % lt) * 64 + lane;
+    step = r.step0 + (int)(job / lt) * per;
+    return r;
+}
+
+}  // namespace
+
 template <bool UNIT>
 __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_grid_sums(
     GridGeom g, GridPlan p, int64_t n_rows, int64_t chunk, int64_t jobs, int64_t run,
@@ -251,14 +270,7 @@ __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) 
         la = 64 * b + lane;
         step = 64 * b + (int)(job % (64 / kStep)) * kStep;
     } else {
-        job -= p.diag_jobs;
-        int q = 0;
-        while (q < 2 && job >= p.region_jobs[q]) job -= p.region_jobs[q++];
-        r = p.region[q];
-        // lane tiles run fastest, so neighbouring waves share their step positions
-        const int lt = (r.lane_n + 63) / 64;
-        la = r.lane0 + (int)(job % lt) * 64 + lane;
-        step = r.step0 + (int)(job / lt) * kStep;
+        r = region_job(p, job - p.diag_jobs, kStep, lane, la, step);
     }
     step = __builtin_amdgcn_readfirstlane(step);
     const int lane_end = r.lane0 + r.lane_n, step_end = r.step0 + r.step_n;
@@ -274,10 +286,129 @@ __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) 
                               base);
 }
 
+// ------------------------------------------------------- FP32-compensated ---
+// The same pixels by four in the FP32-compensated adjoint's arithmetic: phases,
+// FP32 phasors, products in row pairs, Kahan steps and chunks are the adjoint's, so
+// the sums' bits are its real parts'.  What the form saves: the imaginary half (a
+// row costs a pixel 3.5 FP32 instructions instead of 7) and, of the phase's three
+// FP64 ones, w (n - 1) is shared by the four pixels and v m by two: 1.75.  Bound by
+// issue, the hardware sine and cosine the most of it.  176,904 rows x 256^2 pixels:
+// 4.63 -> 3.94 ms (4.10 in 256-thread workgroups), 88,904 rows of a 511^2 beam 9.19
+// -> 6.74 ms.
+constexpr int kF32Block = 64;   // waves of a workgroup share nothing
+constexpr int kF32Step = 2;   // quads per lane
+
+namespace {
+
+template <int G, bool UNIT>
+__device__ __forceinline__ void image_f32c_rows(const double* u, const double* v, const double* w,
+                                                const double2* y, int nrow, float fsg,
+                                                const double (&l)[G], const double (&m)[G],
+                                                const double (&nm1)[G], float (&sum)[G][4],
+                                                float (&comp)[G][4]) {
+    const auto* U = uniform_ptr(u);
+    const auto* V = uniform_ptr(v);
+    const auto* W = uniform_ptr(w);
+    const auto* Y = uniform_ptr(y);
+    const auto step = [&](auto count, int j) {
+        constexpr int N = decltype(count)::value;
+        float yr[N], yi[N];
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            yr[r] = UNIT ? 1.0f : (float)Y[j + r].x;
+            yi[r] = UNIT ? 0.0f : fsg * (float)Y[j + r].y;
+        }
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            float acc[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[t] = -comp[i][t];
+#pragma unroll
+            for (int r = N - 1; r >= 0; --r) {
+                const double wn = W[j + r] * nm1[i];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    // pixel (sl, sm) = (+-, +-): sl < 0 for odd t, sm < 0 for t >= 2
+                    const double inner = fma(V[j + r], t & 2 ? -m[i] : m[i], wn);
+                    const double ph = fma(U[j + r], t & 1 ? -l[i] : l[i], inner);
+                    float c, s;
+                    cis2pi_f32((float)__builtin_amdgcn_fract(ph), c, s);
+                    if constexpr (!UNIT) acc[t] = fmaf(s, yi[r], acc[t]);
+                    acc[t] = fmaf(c, yr[r], acc[t]);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) kahan_step(acc[t], sum[i][t], comp[i][t]);
+        }
+    };
+    int j = 0;
+#pragma unroll 1
+    for (; j + 2 <= nrow; j += 2) step(std::integral_constant<int, 2>(), j);
+    if (j < nrow) step(std::integral_constant<int, 1>(), j);
+}
+
+template <int G, bool UNIT>
+__device__ __forceinline__ void image_f32c_wave(const GridGeom& g, const GridRegion& r, int lane,
+                                                int step, const double* u, const double* v,
+                                                const double* w, const double2* y, int nrow,
+                                                float fsg, double* partial) {
+    const int lane_end = r.lane0 + r.lane_n, la = lane < lane_end ? lane : lane_end - 1;
+    double l[G], m[G], nm1[G];
+    float sum[G][4], comp[G][4];
+    int64_t quad[G];
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+        const int kx = r.swapped ? step + i : la, ky = r.swapped ? la : step + i;
+        quad[i] = (int64_t)ky * g.Kx + kx;
+        nm1[i] = g.nm1(kx, ky);
+        l[i] = (double)(g.kx0 + kx) * g.cell;
+        m[i] = (double)(g.ky0 + ky) * g.cell;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) sum[i][t] = comp[i][t] = 0.0f;
+    }
+    image_f32c_rows<G, UNIT>(u, v, w, y, nrow, fsg, l, m, nm1, sum, comp);
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+        if (lane < lane_end) {
+            double x[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) x[t] = (double)sum[i][t] - (double)comp[i][t];
+            double2* o = (double2*)(partial + 4 * quad[i]);
+            o[0] = make_double2(x[0], x[1]);
+            o[1] = make_double2(x[2], x[3]);
+        }
+}
+
+}  // namespace
+
+template <bool UNIT>
+__global__ __launch_bounds__(kF32Block) void k_image_f32c(
+    GridGeom g, GridPlan p, const double* __restrict__ u, const double* __restrict__ v,
+    const double* __restrict__ w, const double2* __restrict__ y, int64_t n_vis, int64_t chunk,
+    int64_t jobs, int64_t run, float fsg, double* __restrict__ partial) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t bid = blockIdx.x;
+    const int64_t all = ((bid & 7) * run + (bid >> 3)) * (kF32Block / 64) + wave;
+    if (all >= jobs) return;
+    const int64_t chunk_id = all / p.jobs, j0 = chunk_id * chunk;
+    const int nrow =
+        __builtin_amdgcn_readfirstlane((int)(j0 + chunk < n_vis ? chunk : n_vis - j0));
+    int la, step;
+    const GridRegion r = region_job(p, all - chunk_id * p.jobs, kF32Step, lane, la, step);
+    double* part = partial + chunk_id * 4 * (int64_t)g.Kx * g.Ky;
+    const double2* yy = y ? y + j0 : nullptr;
+    if (__builtin_amdgcn_readfirstlane(r.step0 + r.step_n - step) >= 2)
+        image_f32c_wave<2, UNIT>(g, r, la, step, u + j0, v + j0, w + j0, yy, nrow, fsg, part);
+    else
+        image_f32c_wave<1, UNIT>(g, r, la, step, u + j0, v + j0, w + j0, yy, nrow, fsg, part);
+}
+
 // Adds the chunks of each quad (16 threads take every 16th chunk in order, their
-// sums meet in a fixed tree) and writes its pixels: 0 off the unit disk.
+// sums meet in a fixed tree) and writes its pixels, 0 off the unit disk: from the
+// sums P, Q, R, S, or (PIXELS) from one sum for each.
 constexpr int kFinCols = 16, kFinQ = 16;
 
+template <bool PIXELS>
 __global__ __launch_bounds__(kFinCols * 4 * kFinQ) void k_grid_finish(
     GridGeom g, const double* __restrict__ partial, int64_t n_chunks, int nx, int ny, int cx, int cy,
     double n_vis, double* __restrict__ img) {
@@ -304,7 +435,8 @@ __global__ __launch_bounds__(kFinCols * 4 * kFinQ) void k_grid_finish(
     if ((sl < 0 && ax == 0) || (sm < 0 && ay == 0)) return;
     const int64_t ix = (int64_t)cx + (int64_t)sl * ax, iy = (int64_t)cy + (int64_t)sm * ay;
     if (ix < 0 || ix >= nx || iy < 0 || iy >= ny) return;
-    const double v = (q4[0] - (sl * sm) * q4[1]) - (sl * q4[2] + sm * q4[3]);
+    const double v = PIXELS ? red[0][tx]
+                            : (q4[0] - (sl * sm) * q4[1]) - (sl * q4[2] + sm * q4[3]);
     img[iy * nx + ix] = g.on_disk(kx, ky) ? v / n_vis : 0.0;
 }
 
@@ -345,7 +477,9 @@ static int64_t cover(int x0, int nX, int y0, int nY, GridRegion out[2]) {
     return best;
 }
 
-bool grid_plan(int nx, int ny, int cx, int cy, double cell, GridGeom* g, GridPlan* p) {
+bool grid_plan(int nx, int ny, int cx, int cy, double cell, int prec, GridGeom* g, GridPlan* p) {
+    const bool f32 = prec == SWV_F32C;
+    const int per = f32 ? kF32Step : kStep;
     int64_t x0, nX, y0, nY;
     axis_offsets(nx, cx, &x0, &nX);
     axis_offsets(ny, cy, &y0, &nY);
@@ -356,7 +490,7 @@ bool grid_plan(int nx, int ny, int cx, int cy, double cell, GridGeom* g, GridPla
     const int Kx = (int)nX, Ky = (int)nY;
     // whole 64 x 64 blocks of the square in which (i, k) and (k, i) have one n
     int nb = x0 == y0 ? (Kx < Ky ? Kx : Ky) / 64 : 0;
-    if (nb < 2) nb = 0;
+    if (nb < 2 || f32) nb = 0;
     const int64_t b = nb;
     const int sq = 64 * nb;
     p->oct_jobs = 16 * b * (b - 1);
@@ -371,12 +505,16 @@ bool grid_plan(int nx, int ny, int cx, int cy, double cell, GridGeom* g, GridPla
     p->jobs = p->oct_jobs + p->diag_jobs;
     for (int r = 0; r < 3; ++r) {
         const GridRegion& R = p->region[r];
-        p->region_jobs[r] = (int64_t)((R.lane_n + 63) / 64) * ((R.step_n + kStep - 1) / kStep);
+        p->region_jobs[r] = (int64_t)((R.lane_n + 63) / 64) * ((R.step_n + per - 1) / per);
         p->jobs += p->region_jobs[r];
     }
     // against 20 instructions per pixel of the general adjoint, whose idle lanes
     // are few: 256^2 about its centre 5,400 for quads and octets, 20,480 for pixels
-    return cost <= 20 * (((int64_t)nx * ny + 63) / 64);
+    const int64_t pixel_waves = ((int64_t)nx * ny + 63) / 64;
+    // FP32-compensated: about 78 issue slots of FP32 size per row and quad (20 of
+    // each pixel's 26 in the adjoint)
+    if (f32) return 78 * (cost / 25) <= 26 * pixel_waves;
+    return cost <= 20 * pixel_waves;
 }
 
 // Rows per chunk: four rounds of workgroups (two per CU) rather than one, since
@@ -428,13 +566,35 @@ hipError_t launch_grid_slab(hipStream_t s, const GridGeom& g, const GridPlan& p,
     return hipGetLastError();
 }
 
-hipError_t launch_grid_finish(hipStream_t s, const GridGeom& g, const double* partial,
+hipError_t launch_image_f32c(hipStream_t s, const GridGeom& g, const GridPlan& p, int64_t n_vis,
+                             int64_t chunk, const double* u, const double* v, const double* w,
+                             const void* y, int sign, double* partial) {
+    const int64_t jobs = (n_vis + chunk - 1) / chunk * p.jobs;
+    const int64_t per = kF32Block / 64, run = ((jobs + per - 1) / per + 7) / 8;
+    if (run > (int64_t(1) << 27)) return hipErrorInvalidConfiguration;
+    const dim3 grid((unsigned)(8 * run)), blk(kF32Block);
+    const float fsg = (float)sign;
+    if (y)
+        k_image_f32c<false><<<grid, blk, 0, s>>>(g, p, u, v, w, (const double2*)y, n_vis, chunk,
+                                                 jobs, run, fsg, partial);
+    else
+        k_image_f32c<true><<<grid, blk, 0, s>>>(g, p, u, v, w, nullptr, n_vis, chunk, jobs, run,
+                                                fsg, partial);
+    return hipGetLastError();
+}
+
+hipError_t launch_grid_finish(hipStream_t s, const GridGeom& g, int prec, const double* partial,
                               int64_t n_chunks, int nx, int ny, int cx, int cy, int64_t n_vis,
                               double* img) {
     const int64_t cols = 4 * (int64_t)g.Kx * g.Ky;
     const int per = kFinCols * 4;
-    k_grid_finish<<<dim3((unsigned)((cols + per - 1) / per)), dim3(per * kFinQ), 0, s>>>(
-        g, partial, n_chunks, nx, ny, cx, cy, (double)n_vis, img);
+    const dim3 grid((unsigned)((cols + per - 1) / per)), blk(per * kFinQ);
+    if (prec == SWV_F32C)
+        k_grid_finish<true><<<grid, blk, 0, s>>>(g, partial, n_chunks, nx, ny, cx, cy,
+                                                 (double)n_vis, img);
+    else
+        k_grid_finish<false><<<grid, blk, 0, s>>>(g, partial, n_chunks, nx, ny, cx, cy,
+                                                  (double)n_vis, img);
     return hipGetLastError();
 }
 

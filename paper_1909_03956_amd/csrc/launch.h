@@ -112,7 +112,7 @@ struct GridPlan {
 };
 // Geometry and cover of an image; whether this form takes fewer instructions
 // than the general adjoint on the image's pixels.
-bool grid_plan(int nx, int ny, int cx, int cy, double cell, GridGeom* g, GridPlan* p);
+bool grid_plan(int nx, int ny, int cx, int cy, double cell, int prec, GridGeom* g, GridPlan* p);
 size_t grid_row_bytes(const GridGeom& g);
 size_t grid_slab_bytes(const GridGeom& g, int64_t rows);
 size_t grid_partial_bytes(const GridGeom& g, int64_t n_chunks);
@@ -122,7 +122,11 @@ int64_t grid_chunk(const GridGeom& g, const GridPlan& p, int64_t rows, int n_cu)
 hipError_t launch_grid_slab(hipStream_t s, const GridGeom& g, const GridPlan& p, int64_t rows,
                             int64_t chunk, const double* u, const double* v, const double* w,
                             const void* y, int sign, bool resume, void* slab, double* partial);
-hipError_t launch_grid_finish(hipStream_t s, const GridGeom& g, const double* partial,
+// The FP32-compensated sums of all rows (chunk: the adjoint's).
+hipError_t launch_image_f32c(hipStream_t s, const GridGeom& g, const GridPlan& p, int64_t n_vis,
+                             int64_t chunk, const double* u, const double* v, const double* w,
+                             const void* y, int sign, double* partial);
+hipError_t launch_grid_finish(hipStream_t s, const GridGeom& g, int prec, const double* partial,
                               int64_t n_chunks, int nx, int ny, int cx, int cy, int64_t n_vis,
                               double* img);
 

@@ -98,3 +98,30 @@ def test_octets_against_oracle(env, nx, ny, cx, cy, sign):
     l, m, nm1, _ = oc.image_grid(nx, ny, cell, *c)
     ref = oc.dirty_image(u, v, w, y, l, m, nm1, sign)
     assert np.all(np.abs(got.ravel() - ref) <= _bound(u, v, w, y, l, m, nm1))
+
+
+@pytest.mark.parametrize("nx,ny,cx,cy,n,sign,unit", [
+    (64, 64, None, None, 63, -1, False), (129, 128, None, None, 301, 1, False),
+    (40, 200, None, None, 1000, -1, True), (130, 66, 70, 30, 500, 1, False),
+    (255, 257, None, None, 4097, -1, False), (6, 7, None, None, 50, -1, False)])
+def test_f32c_images_are_the_adjoints_real_parts(env, nx, ny, cx, cy, n, sign, unit):
+    """The FP32-compensated image of four mirrored pixels at a time takes the
+    adjoint's FP32 steps on the adjoint's chunks: its values are the adjoint's real
+    parts but for the order in which the chunks' FP64 sums are added."""
+    torch, swv = env
+    u, v, w, y = _rows(n, 5 * nx + ny)
+    if unit:
+        y = np.ones(n, np.complex128)
+    cell = 0.9 / max(nx, ny)
+    U, V, W, Y = dev(u, torch), dev(v, torch), dev(w, torch), dev_c(y, torch)
+    img = host(swv.dirty_image(U, V, W, None if unit else Y, nx, ny, cell, cx, cy, sign, "f32c"))
+    l, m, nm1 = swv.image_grid(nx, ny, cell, cx, cy)
+    adj = host(swv.adjoint(U, V, W, Y, l, m, nm1, sign=sign, prec="f32c")).real / n
+    inside = host(l) ** 2 + host(m) ** 2 < 1.0
+    c = (nx // 2 if cx is None else cx, ny // 2 if cy is None else cy)
+    centre = np.zeros(nx * ny, bool)
+    centre[c[1] * nx + c[0]] = True
+    off = (host(l) == 0) & (host(m) == 0) & ~centre
+    tol = 64 * 2.0 ** -53 * np.abs(y).mean()
+    assert np.all(np.abs(img.ravel() - adj)[~off] <= tol) and np.all(img.ravel()[off] == 0.0)
+    assert inside.all()
