@@ -25,40 +25,119 @@ namespace swv {
 // and y is turned by the rest, then by the node straight into the sums: 20 FP64
 // instructions per row and pixel (phase 3, cell 4, rest 5, 4 + 4), against 29
 // with the polynomial phasor; bound by their issue.  8,355,840 rows x 955
-// pixels: 7.48 -> 5.52 ms (77 % of the issue rate at 2.4 GHz).
+// pixels: 7.48 -> 5.14 ms (83 % of the issue rate at 2.4 GHz; the clock under this
+// load is about 1.9).
 //
-// Jobs are numbered chunk-major and dealt to the waves of 512-thread workgroups
-// (two share a CU, a 64 KB table each) in runs, one run of workgroups per XCD
-// (workgroup ids go to the XCDs round-robin), so a chunk's rows come into one
-// L2 and no workgroup is partly idle but the last.
+// Workgroups of 512 threads (two share a CU, a 64 KB table each).  Up to 32 groups
+// make 1, 2, 4 or 8 columns, and a workgroup takes a chunk: its waves the columns
+// and, by parts, the chunk's rows; the parts' sums meet in LDS where the table
+// was, so there is one set of partial sums per workgroup and four rounds of them stay
+// small: 955 pixels 5.58 -> 5.14 ms against a chunk per wave and two rounds, 40
+// pixels x 5,000,000 rows 0.322 -> 0.291.  More columns are numbered chunk-major and dealt to the
+// waves in order.  Workgroups go to the XCDs in runs (their ids go round-robin), so
+// a chunk's rows come into one L2 and no workgroup is partly idle but the last.
 constexpr int kAdjWaves = kTabBlock / 64;
 // rows per step: 1, 2 and 4 take 0.708, 0.485 and 0.394 ms on 5,000,000 rows x 40
-// pixels, where the rows' loads show, and 5.57, 5.53 and 5.52 ms on 955 pixels
+// pixels, where the rows' loads show (and 5.57, 5.53 and 5.52 ms on 955 pixels), with a
+// chunk per wave
 constexpr int kAdjRows = 4;
 constexpr int64_t kAdjMinRows = 32;
+
+// How n outputs go to waves: `groups` of 64 in `cols` columns; `parts` waves of a
+// workgroup share a column's rows (1: columns past eight, dealt wave by wave).
+struct Columns {
+    int64_t groups, cols;
+    int parts;
+};
+
+static Columns columns_of(int64_t n, int per_lane) {
+    Columns c;
+    c.groups = (n + 63) / 64;
+    c.cols = (c.groups + per_lane - 1) / per_lane;
+    c.parts = 1;
+    if (c.cols <= kAdjWaves) {
+        int64_t p = 1;
+        while (p < c.cols) p *= 2;
+        c.cols = p;
+        c.parts = kAdjWaves / (int)p;
+    }
+    return c;
+}
 
 // What a wave does: rows j0 .. j0 + nrow of chunk `chunk`, the G groups of 64
 // outputs from group g0 (the groups spread evenly over the columns).  active is
 // false past the last job.
 struct WaveJob {
     int64_t chunk, j0, g0;
-    int nrow, G;
+    int nrow, G, part, slot;   // slot: of the wave's sums in LDS (part > 0)
     bool active;
 };
-__device__ __forceinline__ WaveJob wave_job(int64_t n_vis, int64_t chunk, int64_t groups,
-                                            int64_t cols, int64_t jobs, int64_t run) {
+__device__ __forceinline__ WaveJob wave_job(int64_t n_vis, int64_t chunk, const Columns& C,
+                                            int64_t n_chunks, int64_t run) {
     const int64_t bid = blockIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t job = ((bid & 7) * run + (bid >> 3)) * kAdjWaves + wave;
+    const int64_t blk = (bid & 7) * run + (bid >> 3);
     WaveJob w;
-    w.active = job < jobs;
-    w.chunk = w.active ? job / cols : 0;
-    const int64_t c = w.active ? job - w.chunk * cols : 0;
-    w.j0 = w.chunk * chunk;
-    w.nrow = __builtin_amdgcn_readfirstlane((int)(w.j0 + chunk < n_vis ? chunk : n_vis - w.j0));
-    w.g0 = c * groups / cols;
-    w.G = __builtin_amdgcn_readfirstlane((int)((c + 1) * groups / cols - w.g0));
+    int64_t c, end;
+    if (C.parts > 1 || C.cols == kAdjWaves) {
+        c = wave % (int)C.cols;
+        w.part = wave / (int)C.cols;
+        w.chunk = blk;
+        const int64_t sub = (chunk + C.parts - 1) / C.parts;
+        w.j0 = blk * chunk + w.part * sub;
+        end = w.part + 1 < C.parts ? w.j0 + sub : (blk + 1) * chunk;
+        end = end < (blk + 1) * chunk ? end : (blk + 1) * chunk;
+        w.slot = (w.part - 1) * (int)C.cols + (int)c;
+    } else {
+        const int64_t job = blk * kAdjWaves + wave;
+        w.chunk = job / C.cols;
+        c = job - w.chunk * C.cols;
+        w.part = w.slot = 0;
+        w.j0 = w.chunk * chunk;
+        end = w.j0 + chunk;
+    }
+    w.active = w.chunk < n_chunks;
+    end = end < n_vis ? end : n_vis;
+    if (!w.active) w.chunk = w.j0 = c = end = 0;
+    w.nrow = __builtin_amdgcn_readfirstlane(end > w.j0 ? (int)(end - w.j0) : 0);
+    w.g0 = c * C.groups / C.cols;
+    w.G = __builtin_amdgcn_readfirstlane((int)((c + 1) * C.groups / C.cols - w.g0));
     return w;
+}
+
+// Adds the sums of a column's parts in order: x[t][i] for the group i < G.  All
+// waves of the workgroup call it (it takes the table's place); true in the waves
+// that hold the result.
+template <int N>
+__device__ __forceinline__ bool join_parts(Cell* T, const WaveJob& job, const Columns& C,
+                                           double (&x)[N][4]) {
+    static_assert(N % 2 == 0 && (kAdjWaves - 1) * 4 * 64 * (N / 2) <= kTabCells, "fits the table");
+    if (C.parts == 1) return job.active;
+    const int lane = threadIdx.x & 63;
+    const auto at = [&](int slot, int i, int h) {
+        return ((slot * 4 + i) * (N / 2) + h) * 64 + lane;
+    };
+    __syncthreads();   // every wave is done with the table
+    if (job.part > 0)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i < job.G)
+#pragma unroll
+                for (int h = 0; h < N / 2; ++h)
+                    T[at(job.slot, i, h)] = Cell{x[2 * h][i], x[2 * h + 1][i]};
+    __syncthreads();
+    if (job.part > 0) return false;
+    for (int k = 1; k < C.parts; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i < job.G)
+#pragma unroll
+                for (int h = 0; h < N / 2; ++h) {
+                    const Cell p = T[at(job.slot + k * (int)C.cols, i, h)];
+                    x[2 * h][i] += p.x;
+                    x[2 * h + 1][i] += p.y;
+                }
+    return job.active;
 }
 
 // Whether a row of the wave's chunk has phases that need the WIDE form (or are
@@ -67,9 +146,8 @@ __device__ __forceinline__ bool chunk_is_wide(const WaveJob& job, const double* 
                                               const double* __restrict__ v,
                                               const double* __restrict__ w) {
     bool big = false;
-    if (job.active)
-        for (int j = threadIdx.x & 63; j < job.nrow; j += 64)
-            big = big || !cells_reach(u[job.j0 + j], v[job.j0 + j], w[job.j0 + j]);
+    for (int j = threadIdx.x & 63; j < job.nrow; j += 64)
+        big = big || !cells_reach(u[job.j0 + j], v[job.j0 + j], w[job.j0 + j]);
     return __any(big);
 }
 
@@ -123,12 +201,13 @@ __device__ __forceinline__ void adjoint_rows(
     for (; j < nrow; ++j) step(std::integral_constant<int, 1>(), j);
 }
 
+// x[0], x[1]: the sums' real and imaginary parts.
 template <int G>
 __device__ __forceinline__ void adjoint_wave(
     CellPtr T, const double* __restrict__ u, const double* __restrict__ v,
     const double* __restrict__ w, const double2* __restrict__ y, int nrow, bool wide,
     const double* __restrict__ pl, const double* __restrict__ pm, const double* __restrict__ pn,
-    int64_t q0, int64_t n_pix, double sgn, double2* __restrict__ partial) {
+    int64_t q0, int64_t n_pix, double sgn, double (&x)[2][4]) {
     double L[G], M[G], N[G], ar[G], ai[G];
     bool far = false;
 #pragma unroll
@@ -147,8 +226,8 @@ __device__ __forceinline__ void adjoint_wave(
         adjoint_rows<G, false>(T, u, v, w, y, nrow, L, M, N, ar, ai);
 #pragma unroll
     for (int i = 0; i < G; ++i) {
-        const int64_t p = q0 + (int64_t)i * 64;
-        if (p < n_pix) partial[p] = make_double2(ar[i], ai[i]);
+        x[0][i] = ar[i];
+        x[1][i] = ai[i];
     }
 }
 
@@ -156,25 +235,32 @@ __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) 
     const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
     const double2* __restrict__ y, int64_t n_vis, int64_t chunk, const double* __restrict__ pl,
     const double* __restrict__ pm, const double* __restrict__ pn, int64_t n_pix, double sgn,
-    int64_t groups, int64_t cols, int64_t jobs, int64_t run, double2* __restrict__ partial) {
+    Columns C, int64_t n_chunks, int64_t run, double2* __restrict__ partial) {
     __shared__ Cell T[kTabCells];
-    const WaveJob job = wave_job(n_vis, chunk, groups, cols, jobs, run);
+    const WaveJob job = wave_job(n_vis, chunk, C, n_chunks, run);
     const bool wide = chunk_is_wide(job, u, v, w);
     fill_cells(T);
-    if (!job.active) return;
     const int64_t j0 = job.j0, q0 = job.g0 * 64 + (threadIdx.x & 63);
-    const int nrow = job.nrow;
-    double2* part = partial + job.chunk * n_pix;
     const CellPtr TP = (CellPtr)T;
-#define SWV_WAVE(N)                                                                               \
-    adjoint_wave<N>(TP, u + j0, v + j0, w + j0, y + j0, nrow, wide, pl, pm, pn, q0, n_pix, sgn, part)
-    switch (job.G) {
+    double x[2][4] = {};
+#define SWV_WAVE(N)                                                                          \
+    adjoint_wave<N>(TP, u + j0, v + j0, w + j0, y + j0, job.nrow, wide, pl, pm, pn, q0, n_pix, \
+                    sgn, x)
+    switch (job.nrow > 0 ? job.G : 0) {
+        case 0: break;
         case 1: SWV_WAVE(1); break;
         case 2: SWV_WAVE(2); break;
         case 3: SWV_WAVE(3); break;
         default: SWV_WAVE(4); break;
     }
 #undef SWV_WAVE
+    if (!join_parts<2>(T, job, C, x)) return;
+    double2* part = partial + job.chunk * n_pix;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t p = q0 + (int64_t)i * 64;
+        if (i < job.G && p < n_pix) part[p] = make_double2(x[0][i], x[1][i]);
+    }
 }
 
 // FP32-compensated: FP64 phase reduced exactly; FP32 phasor, products and Kahan
@@ -387,50 +473,55 @@ int adjoint_f32c_blocks_per_cu(int ppl, int block) {
     return 1;
 }
 
-// Rows per chunk of the FP64 adjoint and gradients.  Workgroups of kAdjWaves
-// jobs run in rounds of two per CU; up to four rounds rather than one, since the
-// dies' clocks differ, but fewer while the partial sums (one set of `bytes` per
-// chunk) exceed 32 MiB, and whole rounds: the chunk count is the most that fits
-// r of them.  At least kAdjMinRows rows, so that filling the table stays small
-// beside them, and at least 8 chunks from 512 rows on.
-static int64_t cell_chunk(int64_t n_vis, int64_t cols, int64_t bytes, int n_cu) {
+// Rows per chunk of the FP64 adjoint and gradients.  Workgroups run in rounds of
+// two per CU; up to four rounds rather than one, since the dies' clocks differ, but
+// fewer while the partial sums (one set of `bytes` per chunk) exceed 32 MiB, and
+// whole rounds: the chunk count is the most that fits r of them.  At least
+// kAdjMinRows rows for a wave, so that filling the table stays small beside them,
+// and at least 8 chunks of 64 rows and more.
+static int64_t cell_chunk(int64_t n_vis, const Columns& C, int64_t bytes, int n_cu) {
     if (n_vis <= 0) return 1;
-    const int64_t round = (int64_t)n_cu * 2 * kAdjWaves;
+    const int64_t per_block = C.parts > 1 ? 1 : kAdjWaves;   // (chunk, column) jobs
+    const int64_t cols = C.parts > 1 ? 1 : std::max<int64_t>(C.cols, 1);
     const int64_t cap = (int64_t(32) << 20) / std::max<int64_t>(bytes, 1);
     int64_t chunks = 0;
     for (int64_t r = 4; r >= 1; --r) {
-        chunks = r * round / std::max<int64_t>(cols, 1);
+        chunks = r * n_cu * 2 * per_block / cols;
         if (chunks <= cap) break;
     }
     chunks = std::max<int64_t>(8, std::min(chunks, cap));
-    const int64_t least = n_vis < 512 ? 64 : kAdjMinRows;
-    const int64_t chunk = std::max(least, (n_vis + chunks - 1) / chunks);
+    const int64_t least = (n_vis + chunks - 1) / chunks;
+    const int64_t eight = std::max<int64_t>(64, std::max(least, (n_vis + 7) / 8));
+    const int64_t chunk = std::min(eight, std::max<int64_t>({64, C.parts * kAdjMinRows, least}));
     return std::min<int64_t>(chunk, int64_t(1) << 30);   // rows per chunk fit an int
 }
 
-static int64_t columns(int64_t n, int per_lane) {
-    return ((n + 63) / 64 + per_lane - 1) / per_lane;
-}
-
 int64_t adjoint_cell_chunk(int64_t n_vis, int64_t n_pix, int ppl, int n_cu) {
-    return cell_chunk(n_vis, columns(n_pix, ppl), 16 * n_pix, n_cu);
+    return cell_chunk(n_vis, columns_of(n_pix, ppl), 16 * n_pix, n_cu);
 }
 
 int64_t grad_chunk(int64_t n_vis, int64_t n_comp, int cpl, int n_cu) {
-    return cell_chunk(n_vis, columns(n_comp, cpl), 32 * n_comp, n_cu);
+    return cell_chunk(n_vis, columns_of(n_comp, cpl), 32 * n_comp, n_cu);
+}
+
+// Workgroups per XCD.
+static int64_t cell_run(const Columns& C, int64_t n_chunks) {
+    const int64_t blocks = C.parts > 1 || C.cols == kAdjWaves
+                               ? n_chunks
+                               : (n_chunks * C.cols + kAdjWaves - 1) / kAdjWaves;
+    return (blocks + 7) / 8;
 }
 
 static hipError_t run_adjoint_cell(hipStream_t s, int ppl, int64_t chunk, int64_t n_vis,
                                    const double* u, const double* v, const double* w,
                                    const void* y, int64_t n_pix, const double* l, const double* m,
                                    const double* nm1, int sign, void* partial) {
-    const int64_t groups = (n_pix + 63) / 64, cols = columns(n_pix, ppl);
-    const int64_t jobs = (n_vis + chunk - 1) / chunk * cols;
-    const int64_t run = ((jobs + kAdjWaves - 1) / kAdjWaves + 7) / 8;   // workgroups per XCD
+    const Columns C = columns_of(n_pix, ppl);
+    const int64_t n_chunks = (n_vis + chunk - 1) / chunk, run = cell_run(C, n_chunks);
     if (run > (int64_t(1) << 27)) return hipErrorInvalidConfiguration;
     k_adjoint_cell<<<dim3((unsigned)(8 * run)), dim3(kTabBlock), 0, s>>>(
-        u, v, w, (const double2*)y, n_vis, chunk, l, m, nm1, n_pix, (double)sign, groups, cols,
-        jobs, run, (double2*)partial);
+        u, v, w, (const double2*)y, n_vis, chunk, l, m, nm1, n_pix, (double)sign, C, n_chunks, run,
+        (double2*)partial);
     return hipGetLastError();
 }
 
@@ -477,7 +568,7 @@ hipError_t launch_adjoint(hipStream_t s, int prec, int ppl, int block, int64_t c
 // against 32 with the polynomial phasor, bound by their issue.  Rows come by
 // scalar loads: staged in LDS as broadcasts they would take as long there as the
 // arithmetic does, beside the table's gathers.  261,120 rows x 1,000 components:
-// 0.23 ms (67 % of the issue rate at 2.4 GHz); with its prediction 0.53 -> 0.37 ms.
+// with its prediction and the sums over chunks, 0.53 -> 0.36 ms.
 template <int G, bool WIDE>
 __device__ __forceinline__ void grad_rows(CellPtr T, const double* u, const double* v,
                                           const double* w, const double2* y, int nrow,
@@ -536,7 +627,7 @@ __device__ __forceinline__ void grad_wave(CellPtr T, const double* __restrict__ 
                                           const double2* __restrict__ y, int nrow, bool wide,
                                           const double* __restrict__ comp, int comp_stride,
                                           int64_t k0, int64_t n_comp, double sgn,
-                                          double* __restrict__ partial) {
+                                          double (&x)[4][4]) {
     double L[G], M[G], N[G], z[4][G];
 #pragma unroll
     for (int i = 0; i < G; ++i) {
@@ -552,42 +643,48 @@ __device__ __forceinline__ void grad_wave(CellPtr T, const double* __restrict__ 
     else
         grad_rows<G, false>(T, u, v, w, y, nrow, L, M, N, z);
 #pragma unroll
-    for (int i = 0; i < G; ++i) {
-        const int64_t k = k0 + (int64_t)i * 64;
-        if (k < n_comp)
+    for (int i = 0; i < G; ++i)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) partial[t * n_comp + k] = z[t][i];
-    }
+        for (int t = 0; t < 4; ++t) x[t][i] = z[t][i];
 }
 
 // n_comp_dev, if not null, holds the number of components on the device (a
 // captured major cycle whose model changes between replays): the jobs are then
-// those of n_comp, the capacity, and waves past the actual count leave.
+// those of n_comp, the capacity, and waves past the actual count do nothing.
 __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) void k_grad_cell(
     const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
     const double2* __restrict__ y, int64_t n_vis, int64_t chunk, const double* __restrict__ comp,
-    int comp_stride, int64_t n_comp, const int* __restrict__ n_comp_dev, double sgn,
-    int64_t groups, int64_t cols, int64_t jobs, int64_t run, double* __restrict__ partial) {
+    int comp_stride, int64_t n_comp, const int* __restrict__ n_comp_dev, double sgn, Columns C,
+    int64_t n_chunks, int64_t run, double* __restrict__ partial) {
     __shared__ Cell T[kTabCells];
     if (n_comp_dev) n_comp = *n_comp_dev;
-    WaveJob job = wave_job(n_vis, chunk, groups, cols, jobs, run);
-    job.active = job.active && job.g0 * 64 < n_comp;
+    WaveJob job = wave_job(n_vis, chunk, C, n_chunks, run);
+    if (job.g0 * 64 >= n_comp) job.nrow = 0;
     const bool wide = chunk_is_wide(job, u, v, w);
     fill_cells(T);
-    if (!job.active) return;
     const int64_t j0 = job.j0, k0 = job.g0 * 64 + (threadIdx.x & 63);
-    double* part = partial + job.chunk * 4 * n_comp;
     const CellPtr TP = (CellPtr)T;
+    double x[4][4] = {};
 #define SWV_WAVE(N)                                                                              \
     grad_wave<N>(TP, u + j0, v + j0, w + j0, y + j0, job.nrow, wide, comp, comp_stride, k0, n_comp, \
-                 sgn, part)
-    switch (job.G) {
+                 sgn, x)
+    switch (job.nrow > 0 ? job.G : 0) {
+        case 0: break;
         case 1: SWV_WAVE(1); break;
         case 2: SWV_WAVE(2); break;
         case 3: SWV_WAVE(3); break;
         default: SWV_WAVE(4); break;
     }
 #undef SWV_WAVE
+    if (!join_parts<4>(T, job, C, x)) return;
+    double* part = partial + job.chunk * 4 * n_comp;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t k = k0 + (int64_t)i * 64;
+        if (i < job.G && k < n_comp)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) part[t * n_comp + k] = x[t][i];
+    }
 }
 
 // A block owns kGradCols components; thread (q, t, x) adds sum t of component x
@@ -642,13 +739,12 @@ hipError_t launch_grad(hipStream_t s, int cpl, int64_t chunk, int64_t n_vis, con
     if (cpl != 1 && cpl != 2 && cpl != 4) return hipErrorInvalidValue;
     const int64_t n_chunks = n_vis > 0 ? (n_vis + chunk - 1) / chunk : 0;
     if (n_chunks > 0) {
-        const int64_t groups = (n_comp + 63) / 64, cols = columns(n_comp, cpl);
-        const int64_t jobs = n_chunks * cols;
-        const int64_t run = ((jobs + kAdjWaves - 1) / kAdjWaves + 7) / 8;   // workgroups per XCD
+        const Columns C = columns_of(n_comp, cpl);
+        const int64_t run = cell_run(C, n_chunks);
         if (run > (int64_t(1) << 27)) return hipErrorInvalidConfiguration;
         k_grad_cell<<<dim3((unsigned)(8 * run)), dim3(kTabBlock), 0, s>>>(
             u, v, w, (const double2*)y, n_vis, chunk, comp, comp_stride, n_comp, n_comp_dev,
-            (double)sign, groups, cols, jobs, run, partial);
+            (double)sign, C, n_chunks, run, partial);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -26,7 +26,8 @@ def _run(env, u, v, w, y, l, m, f, sign=-1):
 
 @pytest.mark.parametrize("n,k,sign", [
     (1, 1, -1), (33, 64, 1), (64, 65, -1), (511, 128, 1), (513, 193, -1), (2047, 257, 1),
-    (100003, 3, -1), (30001, 321, 1), (1027, 2049, -1)])
+    (100003, 3, -1), (30001, 321, 1), (1027, 2049, -1),
+    (1501, 577, 1), (2300, 1100, -1), (1027, 2048, 1)])   # 4, 8 and 8 columns of a workgroup
 def test_edges_against_oracle(env, n, k, sign):
     rng = np.random.default_rng(n + 3 * k)
     u, v, w = (rng.uniform(-5e4, 5e4, n) for _ in range(3))
