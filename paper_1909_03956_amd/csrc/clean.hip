@@ -71,13 +71,80 @@ __global__ __launch_bounds__(kGridBlock) void k_real_image(int64_t n, const doub
 // peak (largest key, lowest pixel id on ties: a total order, so the result
 // does not depend on the reduction's shape), and one pass over the pixels
 // subtracts the shifted beam and finds the next running peaks.  One barrier
-// per iteration: the per-wave results alternate between two LDS slots.
+// per iteration: the per-wave results alternate between two LDS slots.  Latency
+// bound: 40 x 40 pixels 3.3 -> 2.3 us per iteration (DPP reductions).
 constexpr int kHogBlock = 1024;
 constexpr int kHogWaves = kHogBlock / 64;
 constexpr int kHogBatch = 8;
 
 __device__ __forceinline__ bool ahead(double k1, int i1, double k2, int i2) {
     return k1 > k2 || (k1 == k2 && i1 < i2);
+}
+
+// x of the lane that `CTRL` names (DPP, within rows of 16 lanes).
+template <int CTRL>
+__device__ __forceinline__ int dpp(int x) {
+    return __builtin_amdgcn_mov_dpp(x, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+    return __hiloint2double(dpp<CTRL>(__double2hiint(x)), dpp<CTRL>(__double2loint(x)));
+}
+__device__ __forceinline__ int lane_value(int x, int lane) {
+    return __builtin_amdgcn_readlane(x, lane);
+}
+__device__ __forceinline__ double lane_value(double x, int lane) {
+    return __hiloint2double(lane_value(__double2hiint(x), lane),
+                            lane_value(__double2loint(x), lane));
+}
+
+// op over groups of W lanes, W = 4, 16 or 64; the result is in every lane.
+constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+template <int W, class T, class Op>
+__device__ __forceinline__ T over_lanes(T x, Op op) {
+    x = op(x, dpp<kDppXor1>(x));
+    x = op(x, dpp<kDppXor2>(x));
+    if constexpr (W >= 16) {
+        x = op(x, dpp<kDppHalfMirror>(x));
+        x = op(x, dpp<kDppMirror>(x));
+    }
+    if constexpr (W == 64)
+        x = op(op(lane_value(x, 0), lane_value(x, 16)), op(lane_value(x, 32), lane_value(x, 48)));
+    return x;
+}
+
+// The best (key, val, idx) of W lanes, for all of them (W < 64: the groups hold
+// the same): the largest key, then the lowest index that has it, then that lane's
+// value, each by itself.  A third of the dependent steps of a butterfly of all three.
+template <int W>
+__device__ __forceinline__ void lanes_best(double& key, double& val, int& idx) {
+    const double k = over_lanes<W>(key, [](double a, double b) { return a > b ? a : b; });
+    const int i = over_lanes<W>(key == k ? idx : INT_MAX,
+                                [](int a, int b) { return a < b ? a : b; });
+    const unsigned long long who = __ballot(key == k && idx == i);
+    const int lane = __builtin_amdgcn_readfirstlane(__ffsll(who) - 1);
+    key = lane_value(key, lane);
+    val = lane_value(val, lane);
+    idx = i;
+}
+
+// The workgroup's best for every thread: waves, then their results by way of LDS.
+// One barrier: a call may use the arrays again once another call lies between.
+template <int WAVES>
+__device__ __forceinline__ void block_best(double& key, double& val, int& idx, double* sk,
+                                           double* sv, int* si) {
+    lanes_best<64>(key, val, idx);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane == 0) {
+        sk[wave] = key;
+        sv[wave] = val;
+        si[wave] = idx;
+    }
+    __syncthreads();
+    key = sk[lane & (WAVES - 1)];
+    val = sv[lane & (WAVES - 1)];
+    idx = si[lane & (WAVES - 1)];
+    lanes_best<WAVES>(key, val, idx);
 }
 
 template <bool ABS>
@@ -87,7 +154,7 @@ __global__ __launch_bounds__(kHogBlock) void k_hogbom(
     double* __restrict__ comp_val, int64_t* __restrict__ n_found) {
     __shared__ double s_key[2][kHogWaves], s_val[2][kHogWaves];
     __shared__ int s_idx[2][kHogWaves];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x;
     const int n = nx * ny;
     const int64_t bw = 2 * (int64_t)nx - 1;
     // the thread's first pixel and the stride as (rows, columns)
@@ -107,33 +174,7 @@ __global__ __launch_bounds__(kHogBlock) void k_hogbom(
     }
     int64_t it = 0;
     for (int buf = 0;; buf ^= 1) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            const double k2 = __shfl_xor(key, off, 64);
-            const double v2 = __shfl_xor(val, off, 64);
-            const int i2 = __shfl_xor(idx, off, 64);
-            if (ahead(k2, i2, key, idx)) {
-                key = k2;
-                val = v2;
-                idx = i2;
-            }
-        }
-        if (lane == 0) {
-            s_key[buf][wave] = key;
-            s_val[buf][wave] = val;
-            s_idx[buf][wave] = idx;
-        }
-        __syncthreads();
-        key = s_key[buf][0];
-        val = s_val[buf][0];
-        idx = s_idx[buf][0];
-        for (int q = 1; q < kHogWaves; ++q) {
-            if (ahead(s_key[buf][q], s_idx[buf][q], key, idx)) {
-                key = s_key[buf][q];
-                val = s_val[buf][q];
-                idx = s_idx[buf][q];
-            }
-        }
+        block_best<kHogWaves>(key, val, idx, s_key[buf], s_val[buf], s_idx[buf]);
         // the same decision in every thread
         if (it >= max_iter || !(key > threshold)) break;
         const double gc = gain * val;
@@ -188,64 +229,56 @@ __global__ __launch_bounds__(kHogBlock) void k_hogbom(
 // The same minor cycle spread over G workgroups, all resident at once (a
 // cooperative launch: the runtime refuses a grid that could not be).  Global
 // thread g owns pixels g, g + G B, ...  Each iteration a workgroup publishes
-// its peak in its slot (key, value, index, then the iteration number with
-// release order) and gathers every workgroup's slot of that iteration
-// (acquire loads of the iteration number, then the data): the gather is the
-// barrier, with no shared counter.  Every workgroup reduces the G peaks in
-// the same total order, so all take the same decision.  Slots alternate
-// between two buffers: a workgroup can only reuse a buffer after every other
-// one has published the next iteration, i.e. finished reading it.  Every wait
-// is bounded: after kHogSpinLimit polls the workgroup gives up, the cycle
+// its peak in its slot and gathers every workgroup's slot of that iteration:
+// the gather is the barrier, with no shared counter.  Every workgroup reduces
+// the G peaks in the same total order, so all take the same decision.  Slots
+// alternate between two buffers: a workgroup can only reuse a buffer after every
+// other one has published the next iteration, i.e. finished reading it.  Every
+// wait is bounded: after kHogSpinLimit polls the workgroup gives up, the cycle
 // ends and *n_found is set to -1.
+//
+// A slot is three 64-bit words, each with 32 bits of the peak (value high, value
+// low, index) beside the iteration's low 32 bits: a word with the right number is
+// of that iteration whatever the others are, so the words need no order among
+// themselves, and nothing else passes between workgroups (a pixel belongs to one
+// thread).  Ordered by release and acquire instead, each exchange would write
+// back and drop the caches that hold image and beam.  Bound by the exchange's and
+// the loads' latency: 256 x 256 pixels 5.45 -> 4.12 us per iteration, 1024 x 1024
+// 26 -> 11.1.
 constexpr int kHogGridBlock = 256;
 constexpr int kHogGridWaves = kHogGridBlock / 64;
-constexpr int kHogSpinLimit = 1 << 22;
+constexpr int kHogGridBatch = 2;
+constexpr int kHogSpinLimit = 1 << 23;
 
-// Block-wide best (key, val, idx): wave butterflies, then every thread
-// reduces the per-wave results in wave order.
-__device__ __forceinline__ void block_best(double& key, double& val, int& idx, double* sk,
-                                           double* sv, int* si) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const double k2 = __shfl_xor(key, off, 64);
-        const double v2 = __shfl_xor(val, off, 64);
-        const int i2 = __shfl_xor(idx, off, 64);
-        if (ahead(k2, i2, key, idx)) {
-            key = k2;
-            val = v2;
-            idx = i2;
-        }
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    __syncthreads();   // the previous reader of these slots is done
-    if (lane == 0) {
-        sk[wave] = key;
-        sv[wave] = val;
-        si[wave] = idx;
-    }
-    __syncthreads();
-    key = sk[0];
-    val = sv[0];
-    idx = si[0];
-    for (int q = 1; q < kHogGridWaves; ++q)
-        if (ahead(sk[q], si[q], key, idx)) {
-            key = sk[q];
-            val = sv[q];
-            idx = si[q];
-        }
+// slot layout: [buffer][workgroup][value high, value low, index, unused], the
+// iteration's number + 1 in the upper half of each 64-bit word
+__device__ __forceinline__ void publish(unsigned long long* slot, double val, int idx,
+                                        unsigned tag) {
+    const unsigned long long t = (unsigned long long)tag << 32;
+    const unsigned long long x = (unsigned long long)__double_as_longlong(val);
+    __hip_atomic_store(slot + 0, t | (x >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(slot + 1, t | (x & 0xffffffffull), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(slot + 2, t | (unsigned)idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// slot layout: [buffer][workgroup][key, val, idx, iteration + 1] as 64-bit words
-__device__ __forceinline__ void publish(unsigned long long* slot, double key, double val,
-                                        int idx, int64_t it) {
-    __hip_atomic_store(slot + 0, (unsigned long long)__double_as_longlong(key), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(slot + 1, (unsigned long long)__double_as_longlong(val), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(slot + 2, (unsigned long long)(unsigned)idx, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(slot + 3, (unsigned long long)(it + 1), __ATOMIC_RELEASE,
-                       __HIP_MEMORY_SCOPE_AGENT);
+// Waits for the slot's words of iteration `tag`; false if they do not come.
+__device__ __forceinline__ bool await(const unsigned long long* slot, unsigned tag, double& val,
+                                      int& idx) {
+    for (int spins = 0; spins <= kHogSpinLimit; ++spins) {
+        unsigned long long a[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            a[i] = __hip_atomic_load(slot + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((unsigned)(a[0] >> 32) == tag && (unsigned)(a[1] >> 32) == tag &&
+            (unsigned)(a[2] >> 32) == tag) {
+            val = __longlong_as_double((long long)(a[0] << 32 | (a[1] & 0xffffffffull)));
+            idx = (int)(unsigned)a[2];
+            return true;
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+    return false;
 }
 
 template <bool ABS>
@@ -254,8 +287,8 @@ __global__ __launch_bounds__(kHogGridBlock) void k_hogbom_grid(
     double threshold, int64_t max_iter, int64_t* __restrict__ comp_pix,
     double* __restrict__ comp_val, int64_t* __restrict__ n_found,
     unsigned long long* __restrict__ slots) {
-    __shared__ double sk[kHogGridWaves], sv[kHogGridWaves];
-    __shared__ int si[kHogGridWaves];
+    __shared__ double sk[2][kHogGridWaves], sv[2][kHogGridWaves];
+    __shared__ int si[2][kHogGridWaves];
     __shared__ int s_timeout;
     const int G = (int)gridDim.x;
     const int n = nx * ny;
@@ -279,37 +312,30 @@ __global__ __launch_bounds__(kHogGridBlock) void k_hogbom_grid(
     }
     int64_t it = 0;   // the peaks being exchanged belong to the image after `it` components
     for (;;) {
-        block_best(key, val, idx, sk, sv, si);
+        block_best<kHogGridWaves>(key, val, idx, sk[0], sv[0], si[0]);
         unsigned long long* buf = slots + (size_t)(it & 1) * 4 * G;
-        if (threadIdx.x == 0) publish(buf + 4 * (size_t)blockIdx.x, key, val, idx, it);
+        const unsigned tag = (unsigned)(it + 1);
+        if (threadIdx.x == 0) publish(buf + 4 * (size_t)blockIdx.x, val, idx, tag);
         // gather: thread b waits for workgroup b's slot of this iteration
         key = -HUGE_VAL;
         val = 0.0;
         idx = INT_MAX;
         for (int b = threadIdx.x; b < G; b += kHogGridBlock) {
-            const unsigned long long* sl = buf + 4 * (size_t)b;
-            int spins = 0;
-            while (__hip_atomic_load(sl + 3, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) !=
-                   (unsigned long long)(it + 1)) {
-                if (++spins > kHogSpinLimit) {
-                    s_timeout = 1;
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
+            double v2;
+            int i2;
+            if (!await(buf + 4 * (size_t)b, tag, v2, i2)) {
+                s_timeout = 1;
+                continue;
             }
-            const double k2 = __longlong_as_double(
-                (long long)__hip_atomic_load(sl + 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-            const double v2 = __longlong_as_double(
-                (long long)__hip_atomic_load(sl + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-            const int i2 = (int)(unsigned)__hip_atomic_load(sl + 2, __ATOMIC_RELAXED,
-                                                             __HIP_MEMORY_SCOPE_AGENT);
+            const double k2 = i2 == INT_MAX ? -HUGE_VAL : (ABS ? fabs(v2) : v2);
             if (ahead(k2, i2, key, idx)) {
                 key = k2;
                 val = v2;
                 idx = i2;
             }
         }
-        block_best(key, val, idx, sk, sv, si);   // its barriers also publish s_timeout
+        // its barrier also publishes s_timeout
+        block_best<kHogGridWaves>(key, val, idx, sk[1], sv[1], si[1]);
         if (s_timeout) {
             if (threadIdx.x == 0) *n_found = -1;
             return;
@@ -327,22 +353,36 @@ __global__ __launch_bounds__(kHogGridBlock) void k_hogbom_grid(
         val = 0.0;
         idx = INT_MAX;
         int y = y0, x = x0;
-        for (int p = g0; p < n; p += stride) {
-            const double t = gc * B[(int64_t)y * bw + x];
-            const double r = img[p] - t;
-            img[p] = r;
-            const double k = ABS ? fabs(r) : r;
-            if (k > key) {
-                key = k;
-                val = r;
-                idx = p;
+        // kHogGridBatch pixels per step: their loads are all in flight together
+        for (int p0 = g0; p0 < n; p0 += kHogGridBatch * stride) {
+            double iv[kHogGridBatch], bv[kHogGridBatch];
+#pragma unroll
+            for (int b = 0; b < kHogGridBatch; ++b) {
+                if (b * stride < n - p0) {
+                    iv[b] = img[p0 + b * stride];
+                    bv[b] = B[(int64_t)y * bw + x];
+                }
+                x += sx;
+                y += sy;
+                if (x >= nx) {
+                    x -= nx;
+                    ++y;
+                }
             }
-            x += sx;
-            y += sy;
-            while (x >= nx) {
-                x -= nx;
-                ++y;
-            }
+#pragma unroll
+            for (int b = 0; b < kHogGridBatch; ++b)
+                if (b * stride < n - p0) {
+                    const int p = p0 + b * stride;
+                    const double t = gc * bv[b];
+                    const double r = iv[b] - t;
+                    img[p] = r;
+                    const double k = ABS ? fabs(r) : r;
+                    if (k > key) {
+                        key = k;
+                        val = r;
+                        idx = p;
+                    }
+                }
         }
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) *n_found = it;
@@ -389,14 +429,32 @@ __global__ void k_zero_u64(int64_t n, unsigned long long* p) {
     if (i < n) p[i] = 0ull;
 }
 
-// Below this many pixels one workgroup is as fast as an exchange per iteration.
-constexpr int kHogGridMinPixels = 16384;
-constexpr int kHogGridMaxBlocks = 64;
+// From how many pixels the cycle runs grid-wide: one workgroup takes 2.6, 3.2 and
+// 4.7 us per iteration at 64^2, 80^2 and 100^2 pixels, the grid 2.8, 2.9 and 3.2.
+// A capture records one workgroup up to 16,383 pixels: a cooperative launch may not
+// be capturable.
+constexpr int kHogGridMinPixels = 5120, kHogGridMinCaptured = 16384;
+// Two pixels per thread (one: 4.7 us at 256^2 against 4.1, four: 3.8 at 160^2
+// against 3.5) and up to 256 workgroups of 256 (64 and 128 take 31 and 17 us at
+// 1024^2 against 11); each waits for every other, one slot per thread.
+constexpr int kHogGridPerThread = 2, kHogGridMaxBlocks = 256;
 
 bool coop_supported(int device) {
     int v = 0;
     return hipDeviceGetAttribute(&v, hipDeviceAttributeCooperativeLaunch, device) == hipSuccess &&
            v != 0;
+}
+
+bool hogbom_grid_wide(swv_ctx ctx, int n, int flags) {
+    if (n < kHogGridMinPixels || (flags & SWV_HOGBOM_SINGLE) || !coop_supported(ctx->device))
+        return false;
+    if (n >= kHogGridMinCaptured) return true;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return st == hipStreamCaptureStatusNone;
 }
 
 int check_grid(int nx, int ny, double cell) {
@@ -537,10 +595,9 @@ extern "C" int swv_hogbom(swv_ctx ctx, int nx, int ny, double* image, const doub
         return fail(SWV_EINVAL, "swv_hogbom: unknown flags %d", flags);
     CLEAN_GUARD(ctx);
     const int n = nx * ny;
-    if (n >= kHogGridMinPixels && !(flags & SWV_HOGBOM_SINGLE) && coop_supported(ctx->device)) {
-        // about four pixels per thread, at most kHogGridMaxBlocks workgroups: the
-        // exchange (every workgroup polls every slot) grows with their square
-        int G = (n + 4 * kHogGridBlock - 1) / (4 * kHogGridBlock);
+    if (hogbom_grid_wide(ctx, n, flags)) {
+        constexpr int per = kHogGridPerThread * kHogGridBlock;
+        int G = (n + per - 1) / per;
         G = G < kHogGridMaxBlocks ? G : kHogGridMaxBlocks;
         G = G < ctx->n_cu ? G : ctx->n_cu;
         CLEAN_RC(ensure(ctx, ctx->hog, 64 * (size_t)G));
