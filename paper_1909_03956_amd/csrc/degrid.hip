@@ -150,9 +150,13 @@ __global__ __launch_bounds__(kDgBlock) void k_fill_planes(
 // contiguous read of the group, and the 3 W kernel weights are one exponential
 // per lane and direction.  With a visibility per lane every 16-byte cell was a
 // cache line of its own, and each lane computed all 3 W weights.  707,616 rows,
-// W = 10: 3.5 -> 0.9 ms, 12 TB/s of cells; half of the lines come from L1, the
-// rest at about 20 TB/s from L2, which bounds it.  Handing each XCD a contiguous
-// run of rows took 1.16 ms.
+// W = 10: 3.5 -> 0.93 ms, half of the lines from L1 and the rest at about 20 TB/s
+// from L2, which bound it; rows sorted by tile, 0.60 ms, 19 TB/s of cells (L1
+// gives a line per clock and CU: 0.46 ms).  Handing each XCD a contiguous run of
+// unsorted rows took 1.16 ms.
+//
+// Rows in records (rows != null) are read from there and say where their
+// visibility goes; otherwise row j is the j-th of u, v, w.
 //
 // Cell W of a direction lies outside the support unless x - W/2 is an integer,
 // and then takes weight phi(+-1) like the first; it is a rare extra step.
@@ -165,18 +169,36 @@ __device__ __forceinline__ int wrap_index(int64_t k, int n) {
     return r < 0 ? r + n : r;
 }
 
+// One row and its place.
+struct alignas(32) DgRow {
+    double u, v, w;
+    long long j;
+};
+
 template <int W>
 __global__ __launch_bounds__(kDgBlock) void k_degrid(
-    int64_t n_vis, const double* __restrict__ u, const double* __restrict__ v,
+    int64_t n_vis, const DgRow* __restrict__ rows, const double* __restrict__ u, const double* __restrict__ v,
     const double* __restrict__ w, int Nx, int Ny, int64_t n_planes, double cell, double w0,
     double dw, double c, double beta, int sign, const double2* __restrict__ G,
     double2* __restrict__ out) {
     constexpr int LV = W <= 4 ? 4 : (W <= 8 ? 8 : 16);
     const int a = threadIdx.x & (LV - 1);
-    const int64_t j = (int64_t)blockIdx.x * (kDgBlock / LV) + threadIdx.x / LV;
+    int64_t j = (int64_t)blockIdx.x * (kDgBlock / LV) + threadIdx.x / LV;
     if (j >= n_vis) return;   // whole groups
+    double uj, vj, wj;
+    if (rows) {
+        const DgRow r = rows[j];
+        uj = r.u;
+        vj = r.v;
+        wj = r.w;
+        j = r.j;
+    } else {
+        uj = u[j];
+        vj = v[j];
+        wj = w[j];
+    }
     const double h = 0.5 * W;
-    const double xi = u[j] * Nx * cell, zeta = v[j] * Ny * cell, eta = (w[j] - w0) / dw;
+    const double xi = uj * Nx * cell, zeta = vj * Ny * cell, eta = (wj - w0) / dw;
     // non-finite or absurd coordinates give NaN, never an index
     if (!(fabs(xi) < 0x1p50 && fabs(zeta) < 0x1p50 && eta >= 0.0 && eta <= (double)n_planes)) {
         if (a == 0) out[j] = make_double2(NAN, NAN);
@@ -245,30 +267,151 @@ __global__ __launch_bounds__(kDgBlock) void k_degrid(
         vr += __shfl_xor(vr, o, LV);
         vi += __shfl_xor(vi, o, LV);
     }
-    const double t = w[j] * c;
+    const double t = wj * c;
     double cs, q4;
     cis2pi_q(t - rint(t), cs, q4);
     const double sn = sign * 4.0 * q4;
     if (a == 0) out[j] = make_double2(vr * cs - vi * sn, vr * sn + vi * cs);
 }
 
+// Rows put in the order of their tile, so that what is in flight on a CU shares
+// cells in L1 (any order within a tile: a row's result depends on itself alone).
+// A counting sort: a histogram, its prefix sums, then every workgroup reserves a
+// run in each tile that its rows lie in, 0.04 ms for 707,616 rows.  Tiles are 2^shift cells square, the
+// least that keeps to kTiles of them.
+constexpr int kTiles = 1024;
+constexpr int kSortBlock = 512, kSortPer = 4;
+
+struct Tiles {
+    int Nx, Ny, shift, across;
+    double cell;
+};
+
+__device__ __forceinline__ int tile_of(const Tiles& t, double u, double v) {
+    const double xi = u * t.Nx * t.cell, zeta = v * t.Ny * t.cell;
+    if (!(fabs(xi) < 0x1p50 && fabs(zeta) < 0x1p50)) return 0;
+    const int x = wrap_index((int64_t)floor(xi), t.Nx), y = wrap_index((int64_t)floor(zeta), t.Ny);
+    return (y >> t.shift) * t.across + (x >> t.shift);
+}
+
+__global__ void k_zero_tiles(int* __restrict__ count) {
+    count[blockIdx.x * blockDim.x + threadIdx.x] = 0;
+}
+
+__global__ __launch_bounds__(kSortBlock) void k_count_tiles(int n, const double* __restrict__ u,
+                                                            const double* __restrict__ v, Tiles t,
+                                                            int* __restrict__ count) {
+    __shared__ int h[kTiles];
+    for (int i = threadIdx.x; i < kTiles; i += kSortBlock) h[i] = 0;
+    __syncthreads();
+    const int i0 = blockIdx.x * (kSortBlock * kSortPer) + threadIdx.x;
+#pragma unroll
+    for (int r = 0; r < kSortPer; ++r) {
+        const int i = i0 + r * kSortBlock;
+        if (i < n) atomicAdd(&h[tile_of(t, u[i], v[i])], 1);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kTiles; i += kSortBlock)
+        if (h[i]) atomicAdd(&count[i], h[i]);
+}
+
+// Counts to the tiles' first places (exclusive sums), one workgroup.
+__global__ __launch_bounds__(kTiles) void k_tile_starts(int* __restrict__ count) {
+    __shared__ int s[kTiles / 64];
+    const int own = count[threadIdx.x], lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int x = own;
+    for (int o = 1; o < 64; o *= 2) {
+        const int y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    if (lane == 63) s[wave] = x;
+    __syncthreads();
+    for (int k = 0; k < wave; ++k) x += s[k];
+    count[threadIdx.x] = x - own;
+}
+
+__global__ __launch_bounds__(kSortBlock) void k_place_rows(
+    int n, const double* __restrict__ u, const double* __restrict__ v,
+    const double* __restrict__ w, Tiles t, int* __restrict__ next, DgRow* __restrict__ rows) {
+    __shared__ int h[kTiles];
+    for (int i = threadIdx.x; i < kTiles; i += kSortBlock) h[i] = 0;
+    __syncthreads();
+    const int i0 = blockIdx.x * (kSortBlock * kSortPer) + threadIdx.x;
+    int tile[kSortPer], rank[kSortPer];
+    double ur[kSortPer], vr[kSortPer], wr[kSortPer];
+#pragma unroll
+    for (int r = 0; r < kSortPer; ++r) {
+        const int i = i0 + r * kSortBlock;
+        if (i >= n) continue;
+        ur[r] = u[i];
+        vr[r] = v[i];
+        wr[r] = w[i];
+        tile[r] = tile_of(t, ur[r], vr[r]);
+        rank[r] = atomicAdd(&h[tile[r]], 1);
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < kTiles; i += kSortBlock)
+        if (h[i]) h[i] = atomicAdd(&next[i], h[i]);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSortPer; ++r) {
+        const int i = i0 + r * kSortBlock;
+        if (i < n) rows[h[tile[r]] + rank[r]] = DgRow{ur[r], vr[r], wr[r], (long long)i};
+    }
+}
+
+// Rows are sorted in slabs of this many (64 MB of records).
+constexpr int64_t kSortSlab = int64_t(1) << 21;
+constexpr size_t kTileBytes = sizeof(int) * kTiles;
+
+// Whether sorting pays, whole calls unsorted and sorted: 707,616 rows, 256 x 256
+// pixels, support 10 (96 MB of planes): 1.08 and 0.75 ms; 100,000 of them 0.299 and
+// 0.273, 50,000 0.235 and 0.232; 300,000 rows, support 8, 6.4 MB: 0.220 and 0.193.
+// Planes that an XCD's 4 MB of L2 hold: 0.327 and 0.350 (support 10, 70 x 70
+// pixels); support 6: 0.265 either way.
+bool sort_rows(int support, int64_t n_vis, size_t plane_bytes) {
+    return support > 6 && n_vis >= 65536 && plane_bytes > (size_t(4) << 20);
+}
+
+size_t sort_bytes(int64_t n_vis) {
+    return kTileBytes + sizeof(DgRow) * (size_t)std::min(n_vis, kSortSlab);
+}
+
+Tiles tiles_of(int Nx, int Ny, double cell) {
+    int shift = 0;
+    while ((int64_t)(((Nx - 1) >> shift) + 1) * (((Ny - 1) >> shift) + 1) > kTiles) ++shift;
+    return Tiles{Nx, Ny, shift, ((Nx - 1) >> shift) + 1, cell};
+}
+
 template <int W>
 void launch_degrid_w(hipStream_t s, int64_t n_vis, const double* u, const double* v,
                      const double* w, int Nx, int Ny, int64_t nq, double cell, double w0,
-                     double dw, double c, double beta, int sign, const double2* G, double2* out) {
+                     double dw, double c, double beta, int sign, const double2* G, double2* out,
+                     void* sorted) {
     constexpr int LV = W <= 4 ? 4 : (W <= 8 ? 8 : 16);
-    // rows in slabs that stay within a launch's grid
-    constexpr int64_t kSlab = int64_t(1) << 28;
-    for (int64_t j = 0; j < n_vis; j += kSlab) {
-        const int64_t n = std::min<int64_t>(kSlab, n_vis - j);
+    const Tiles t = tiles_of(Nx, Ny, cell);
+    int* next = (int*)sorted;
+    DgRow* rows = sorted ? (DgRow*)((char*)sorted + kTileBytes) : nullptr;
+    // rows in slabs that stay within a launch's grid, or the records
+    const int64_t slab = sorted ? kSortSlab : int64_t(1) << 28;
+    for (int64_t j = 0; j < n_vis; j += slab) {
+        const int64_t n = std::min<int64_t>(slab, n_vis - j);
+        if (sorted) {
+            constexpr int per = kSortBlock * kSortPer;
+            const unsigned nb = (unsigned)((n + per - 1) / per);
+            k_zero_tiles<<<kTiles / 256, 256, 0, s>>>(next);
+            k_count_tiles<<<nb, kSortBlock, 0, s>>>((int)n, u + j, v + j, t, next);
+            k_tile_starts<<<1, kTiles, 0, s>>>(next);
+            k_place_rows<<<nb, kSortBlock, 0, s>>>((int)n, u + j, v + j, w + j, t, next, rows);
+        }
         k_degrid<W><<<(unsigned)((n * LV + kDgBlock - 1) / kDgBlock), kDgBlock, 0, s>>>(
-            n, u + j, v + j, w + j, Nx, Ny, nq, cell, w0, dw, c, beta, sign, G, out + j);
+            n, rows, u + j, v + j, w + j, Nx, Ny, nq, cell, w0, dw, c, beta, sign, G, out + j);
     }
 }
 
 using DegridFn = void (*)(hipStream_t, int64_t, const double*, const double*, const double*, int,
                           int, int64_t, double, double, double, double, double, int,
-                          const double2*, double2*);
+                          const double2*, double2*, void*);
 constexpr DegridFn kDegrid[] = {
     nullptr, nullptr, launch_degrid_w<2>, launch_degrid_w<3>, launch_degrid_w<4>,
     launch_degrid_w<5>, launch_degrid_w<6>, launch_degrid_w<7>, launch_degrid_w<8>,
@@ -420,12 +563,15 @@ extern "C" int swv_predict_degrid(swv_ctx ctx, int nx, int ny, double cell, cons
     // planes as keep a transform busy; the last batch may run over the end.
     const int64_t batch = cells >= (1 << 21) ? 1 : cells >= (1 << 20) ? 2 : cells >= (1 << 19) ? 4 : 8;
     const int64_t nq_pad = (nq + batch - 1) / batch * batch;
-    // scratch: planes, then base, sn, hx, hy
+    // scratch: planes, then base, sn, hx, hy, then the sorted rows
     const int64_t n_pix = (int64_t)nx * ny;
     const size_t plane_bytes = 16 * (size_t)(nq * cells);
     const size_t padded = 16 * (size_t)(nq_pad * cells);
-    const size_t extra = 8 * (size_t)(2 * n_pix + nx + ny) + 256;
-    rc = ensure(ctx, ctx->degrid, padded + extra);
+    const size_t extra = (8 * (size_t)(2 * n_pix + nx + ny) + 31) / 32 * 32;
+    bool sort = sort_rows(support, n_vis, plane_bytes);
+    if (sort && ensure(ctx, ctx->degrid, padded + extra + sort_bytes(n_vis)) != SWV_OK)
+        sort = false;   // no room for the records: rows as they come
+    rc = sort ? SWV_OK : ensure(ctx, ctx->degrid, padded + extra);
     if (rc) return rc;
     double2* G = (double2*)ctx->degrid.p;
     double* base = (double*)((char*)ctx->degrid.p + padded);
@@ -461,7 +607,8 @@ extern "C" int swv_predict_degrid(swv_ctx ctx, int nx, int ny, double cell, cons
     }
     if (!ok) return fail(SWV_EHIP, "swv_predict_degrid: hipfftExecZ2Z failed");
     kDegrid[support](s, n_vis, u, v, w, Nx, Ny, nq, cell, w0, dw, c, beta, sign, G,
-                     (double2*)vis_out);
+                     (double2*)vis_out,
+                     sort ? (char*)ctx->degrid.p + padded + extra : nullptr);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "swv_predict_degrid: degrid");
     if (stats) {
