@@ -493,7 +493,8 @@ typedef struct {
  * [n_vis] DEVICE; vis_out [n_vis] DEVICE complex128 (NaN for a row with
  * non-finite coordinates); support W in 2 .. 16; stats HOST or NULL.
  * Synchronises once (for the w range); uses a context workspace of
- * 16 n_planes (4 nx ny) bytes plus the image, and a cached FFT plan.
+ * 16 n_planes (4 nx ny) bytes plus the image (many rows: and up to 64 MB in
+ * which they are sorted, left out where it cannot be had), and a cached FFT plan.
  * SWV_ENOMEM if the planes would exceed 64 GiB. */
 int swv_predict_degrid(swv_ctx ctx, int nx, int ny, double cell, const double* image,
                        int64_t n_vis, const double* u, const double* v, const double* w,

@@ -664,7 +664,8 @@ class Graph:
 
 
 class BatchPlan:
-    """One persistent launch per route over many prediction instances.
+    """Many prediction instances in one launch for FP64 and tree instances and one
+    for FP32-compensated direct ones.
 
     instances: dicts with keys route ("direct" | "tree"), u, v, w (float64 GPU
     tensors), out (complex128, or complex64 for a "f32c" instance),

@@ -1,4 +1,4 @@
-// Batched persistent prediction (plans), HIP-graph capture of a planned
+// Batched prediction (plans), HIP-graph capture of a planned
 // prediction, and the tile-shape autotuner.
 #include <algorithm>
 #include <chrono>
@@ -170,7 +170,8 @@ int swv_batch_plan(swv_ctx ctx, int n, const swv_instance* inst, swv_plan* out) 
             p->inst.push_back(b);
         }
 
-        // persistent grid: as many blocks as stay resident, about 16 items for each
+        // F32C direct instances, a persistent grid: as many blocks as stay resident,
+        // about 16 items for each
         p->grid32 = ctx->n_cu * batch_direct_f32c_blocks_per_cu();
         const int64_t unit = 64LL * kBatchF32Vpl;
         int64_t tile32 = rows32 / std::max<int64_t>(1, 16 * (int64_t)p->grid32);

@@ -35,9 +35,6 @@ struct alignas(64) CompCell {
 // meta of nodes and leaves:
 //   bits 0-3   child mask (bit c set if child 4k + c exists; 0 for a leaf)
 //   bits 8-12  level j
-//   bits 32-63 for a node with exactly one child: the number of consecutive
-//              one-child nodes that start here (this one, its child, ...);
-//              they are contiguous in the stream.  0 otherwise.
 struct alignas(32) TRec {
     double a, b, c;
     unsigned long long meta;
@@ -45,10 +42,8 @@ struct alignas(32) TRec {
 
 constexpr unsigned meta_mask(unsigned long long meta) { return (unsigned)(meta & 0xFu); }
 constexpr int meta_level(unsigned long long meta) { return (int)((meta >> 8) & 31u); }
-constexpr int meta_chain(unsigned long long meta) { return (int)(meta >> 32); }
-constexpr unsigned long long make_meta(unsigned mask, int level, int chain) {
-    return (unsigned long long)(mask & 0xFu) | ((unsigned long long)level << 8) |
-           ((unsigned long long)(unsigned)chain << 32);
+constexpr unsigned long long make_meta(unsigned mask, int level) {
+    return (unsigned long long)(mask & 0xFu) | ((unsigned long long)level << 8);
 }
 
 // Deferred-error bits the kernels raise in the context's status word.

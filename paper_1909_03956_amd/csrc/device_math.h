@@ -100,46 +100,27 @@ __device__ __forceinline__ double vector_const(double x) {
     return v;
 }
 
-template <bool VOP3>
-__host__ __device__ __forceinline__ double fma_sel(double a, double b, double c) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    if constexpr (VOP3) return fma_v(a, b, c);
-#endif
-    return fma(a, b, c);
-}
-
-template <bool VOP3>
-__host__ __device__ __forceinline__ void cis2pi_q_impl(double r, double& c, double& q) {
+__host__ __device__ __forceinline__ void cis2pi_q(double r, double& c, double& q) {
     const double t = r * r;
     double ps = kS64[6];
-    ps = fma_sel<VOP3>(ps, t, kS64[5]);
-    ps = fma_sel<VOP3>(ps, t, kS64[4]);
-    ps = fma_sel<VOP3>(ps, t, kS64[3]);
-    ps = fma_sel<VOP3>(ps, t, kS64[2]);
-    ps = fma_sel<VOP3>(ps, t, kS64[1]);
-    ps = fma_sel<VOP3>(ps, t, kS64[0]);
+    ps = fma(ps, t, kS64[5]);
+    ps = fma(ps, t, kS64[4]);
+    ps = fma(ps, t, kS64[3]);
+    ps = fma(ps, t, kS64[2]);
+    ps = fma(ps, t, kS64[1]);
+    ps = fma(ps, t, kS64[0]);
     double pc = kC64[5];
-    pc = fma_sel<VOP3>(pc, t, kC64[4]);
-    pc = fma_sel<VOP3>(pc, t, kC64[3]);
-    pc = fma_sel<VOP3>(pc, t, kC64[2]);
-    pc = fma_sel<VOP3>(pc, t, kC64[1]);
-    pc = fma_sel<VOP3>(pc, t, kC64[0]);
+    pc = fma(pc, t, kC64[4]);
+    pc = fma(pc, t, kC64[3]);
+    pc = fma(pc, t, kC64[2]);
+    pc = fma(pc, t, kC64[1]);
+    pc = fma(pc, t, kC64[0]);
     const double s1 = r * ps;
     const double c1 = fma(pc, t, 1.0);
     const double p = s1 * c1;
     const double d = fma(c1, c1, -(s1 * s1));
     c = fma(-8.0 * p, p, 1.0);
     q = p * d;
-}
-
-__host__ __device__ __forceinline__ void cis2pi_q(double r, double& c, double& q) {
-    cis2pi_q_impl<false>(r, c, q);
-}
-
-// The same phasor with every polynomial step a 3-operand FMA (for kernels
-// whose coefficients live in VGPRs; bitwise equal to cis2pi_q).
-__host__ __device__ __forceinline__ void cis2pi_q_vop3(double r, double& c, double& q) {
-    cis2pi_q_impl<true>(r, c, q);
 }
 
 // FP32 phasor of a reduced phase r in cycles (the callers pass |r| <= 1):
@@ -157,13 +138,6 @@ __host__ __device__ __forceinline__ void kahan_step(float y, float& sum, float& 
     const float t = sum + y;
     comp = (t - sum) - y;
     sum = t;
-}
-
-// Kahan-compensated accumulation of the product a b into (sum, comp); the
-// product is rounded once, inside the FMA that removes the compensation.
-__host__ __device__ __forceinline__ void kahan_add_prod(float a, float b, float& sum,
-                                                        float& comp) {
-    kahan_step(fmaf(a, b, -comp), sum, comp);
 }
 
 }  // namespace swv

@@ -1,5 +1,5 @@
 // Per-row device code of the direct component sum (section 3.3, Eq. 12),
-// shared by the single-instance kernels and the persistent batched kernel.
+// shared by the single-instance kernels and the batched ones.
 //
 // A lane owns VPL visibility rows j[0..VPL) (rows >= limit are computed on a
 // clamped index and not stored); every lane of a wave walks the same

@@ -153,7 +153,7 @@ hipError_t launch_residual(hipStream_t s, int64_t n_vis, const void* obs, const 
 int residual_blocks(int64_t n_vis);
 
 // ------------------------------------------------------------ batched --
-// One prediction instance as the persistent kernels read it.
+// One prediction instance as the batched kernels read it.
 struct BatchInst {
     const double* u;
     const double* v;

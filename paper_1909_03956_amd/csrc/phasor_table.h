@@ -135,16 +135,4 @@ __host__ __device__ __forceinline__ CompCell comp_cell(double l, double m, doubl
                     I * kCellC[0], I * kCellC[1], I * kCellS[0], I * kCellS[1]};
 }
 
-// exp(2 pi i phase) = c + i s.
-template <bool WIDE>
-__device__ __forceinline__ void cis_cell(CellPtr T, double phase, double& c, double& s) {
-    double d;
-    const Cell e = find_cell<WIDE>(T, phase, d);
-    const double q = d * d;
-    const double sd = d * fma(kCellS[1], q, kCellS[0]);
-    const double cd = q * fma(kCellC[1], q, kCellC[0]);   // cos - 1
-    c = fma(e.x, cd, fma(-e.y, sd, e.x));
-    s = fma(e.y, cd, fma(e.x, sd, e.y));
-}
-
 }  // namespace swv

@@ -43,14 +43,14 @@ static void record_coefficients(double a, unsigned mask, const double* gamma, co
 
 static void emit(const swv_tree_s& t, int j, int64_t idx, std::vector<TRec>& out) {
     if (j == t.J) {
-        out.push_back(TRec{t.leaf_l[idx], t.leaf_m[idx], t.leaf_nm1[idx], make_meta(0, j, 0)});
+        out.push_back(TRec{t.leaf_l[idx], t.leaf_m[idx], t.leaf_nm1[idx], make_meta(0, j)});
         return;
     }
     const TreeLevel& L = t.levels[j - 1];
     const bool all[3] = {true, true, true};
     double h[3];
     record_coefficients(record_factor(j, t.J), (unsigned)L.mask[idx], &L.gamma[3 * idx], all, h);
-    out.push_back(TRec{h[0], h[1], h[2], make_meta((unsigned)L.mask[idx], j, L.chain[idx])});
+    out.push_back(TRec{h[0], h[1], h[2], make_meta((unsigned)L.mask[idx], j)});
     int64_t child = L.first_child[idx];
     for (int c = 0; c < 4; ++c)
         if (L.mask[idx] & (1 << c)) emit(t, j + 1, child++, out);
@@ -96,15 +96,11 @@ void build_coefficients(swv_tree_s* t) {
         }
     }
 
-    // one-child runs and branching depth, bottom-up
+    // branching depth, bottom-up
     std::vector<int> depth_below(nl, 0);   // branching nodes strictly below, per node
-    top.chain.assign(nl, 0);
-    t->n_one_child = 0;
     for (int j = J - 1; j >= 1; --j) {
-        TreeLevel& L = t->levels[j - 1];
-        const TreeLevel& below = t->levels[j];
+        const TreeLevel& L = t->levels[j - 1];
         const int64_t n = (int64_t)L.pix.size();
-        L.chain.assign(n, 0);
         std::vector<int> depth(n, 0);
         for (int64_t k = 0; k < n; ++k) {
             const int nch = __builtin_popcount((unsigned)L.mask[k]);
@@ -112,10 +108,6 @@ void build_coefficients(swv_tree_s* t) {
             int d = 0;
             for (int i = 0; i < nch; ++i) d = std::max(d, depth_below[c0 + i]);
             depth[k] = d + (nch >= 2 ? 1 : 0);
-            if (nch == 1) {
-                L.chain[k] = 1 + (j + 1 < J ? below.chain[c0] : 0);
-                ++t->n_one_child;
-            }
         }
         depth_below.swap(depth);
     }
@@ -212,7 +204,6 @@ struct Pruner {
     std::vector<int64_t> off;                    // flat offset of level j's coefficients
     std::vector<uint8_t> keep;                   // per flat index
     std::vector<std::vector<uint8_t>> alive;     // [j - 1][k], levels < J
-    std::vector<std::vector<int32_t>> chain;     // one-child runs of the pruned tree
     std::vector<std::vector<int32_t>> depth;     // branching nodes at and below
     swv_tree_s* out;
 
@@ -221,7 +212,7 @@ struct Pruner {
     void emit(int j, int64_t idx) {
         if (j == t.J) {
             out->records.push_back(
-                TRec{t.leaf_l[idx], t.leaf_m[idx], t.leaf_nm1[idx], make_meta(0, j, 0)});
+                TRec{t.leaf_l[idx], t.leaf_m[idx], t.leaf_nm1[idx], make_meta(0, j)});
             out->levels[j - 1].pix.push_back(t.leaf_pix[idx]);
             out->leaf_pix.push_back(t.leaf_pix[idx]);
             return;
@@ -234,7 +225,7 @@ struct Pruner {
             double l, m, nm1;
             pix2xyz(j, L.pix[idx], xyz);
             xyz_to_lmn(F, xyz, &l, &m, &nm1);
-            out->records.push_back(TRec{l, m, nm1, make_meta(0, j, 0)});
+            out->records.push_back(TRec{l, m, nm1, make_meta(0, j)});
             out->levels[j - 1].pix.push_back(L.pix[idx]);
             out->leaf_pix.push_back(L.pix[idx]);
             return;
@@ -244,11 +235,9 @@ struct Pruner {
         double h[3];
         record_coefficients(record_factor(j, t.J), (unsigned)L.mask[idx], &L.gamma[3 * idx], kept3,
                             h);
-        out->records.push_back(
-            TRec{h[0], h[1], h[2], make_meta((unsigned)L.mask[idx], j, chain[j - 1][idx])});
+        out->records.push_back(TRec{h[0], h[1], h[2], make_meta((unsigned)L.mask[idx], j)});
         out->levels[j - 1].pix.push_back(L.pix[idx]);
         ++out->n_alive;
-        if (__builtin_popcount((unsigned)L.mask[idx]) == 1) ++out->n_one_child;
         int64_t child = L.first_child[idx];
         for (int c = 0; c < 4; ++c)
             if (L.mask[idx] & (1 << c)) emit(j + 1, child++);
@@ -271,16 +260,14 @@ int prune_tree(const swv_tree_s& t, const std::vector<int64_t>& kept, swv_tree_s
                         (long long)n_coeffs);
         P.keep[(size_t)f] = 1;
     }
-    // bottom-up: whether a node keeps a coefficient at or below it, its
-    // one-child run and its branching depth in the pruned tree
+    // bottom-up: whether a node keeps a coefficient at or below it, and its
+    // branching depth in the pruned tree
     P.alive.assign(J, {});
-    P.chain.assign(J, {});
     P.depth.assign(J, {});
     for (int j = J - 1; j >= 1; --j) {
         const TreeLevel& L = t.levels[j - 1];
         const int64_t n = (int64_t)L.pix.size();
         P.alive[j - 1].assign(n, 0);
-        P.chain[j - 1].assign(n, 0);
         P.depth[j - 1].assign(n, 0);
         for (int64_t k = 0; k < n; ++k) {
             const int64_t f = P.off[j - 1] + 3 * k;
@@ -296,9 +283,6 @@ int prune_tree(const swv_tree_s& t, const std::vector<int64_t>& kept, swv_tree_s
                     }
             P.alive[j - 1][k] = a;
             P.depth[j - 1][k] = d + (nch >= 2 ? 1 : 0);
-            if (nch == 1)
-                P.chain[j - 1][k] =
-                    1 + ((j + 1 < J && P.alive[j][c0]) ? P.chain[j][c0] : 0);
         }
     }
     out->J = J;
@@ -312,7 +296,6 @@ int prune_tree(const swv_tree_s& t, const std::vector<int64_t>& kept, swv_tree_s
     out->records.clear();
     out->leaf_pix.clear();
     out->n_alive = 0;
-    out->n_one_child = 0;
     out->max_branching = 0;
     const TreeLevel& L1 = t.levels[0];
     const double A1 = pixel_area(1);

@@ -16,7 +16,6 @@ struct TreeLevel {
     std::vector<int64_t> first_child; // index of the first child in the next level
     std::vector<double> lambda;       // lambda_{j,k}
     std::vector<double> gamma;        // gamma^m_{j,k} at [3 k + m] (level < J)
-    std::vector<int32_t> chain;       // one-child run starting here (see TRec)
 };
 
 }  // namespace swv
@@ -50,7 +49,6 @@ struct swv_tree_s {
     // `leaf_pix` the leaves of every level
     bool thresholded = false;
     int64_t n_alive = 0;                 // internal nodes of the pruned tree
-    int64_t n_one_child = 0;             // internal nodes with a single child
     int64_t n_coeffs = 0;                // wavelet coefficients of the source tree
     std::vector<int64_t> kept;           // retained ones, flat indices, increasing
 };
