@@ -383,37 +383,41 @@ __global__ __launch_bounds__(BLOCK) void k_adjoint_f32c(
 }
 
 // out[p] = sum over chunks c of partial[c][p].
-// Chunk reductions: a block owns kSumCols consecutive outputs (coalesced along
-// x); its kSumQ rows of threads each add the chunks q, q + kSumQ, ... in order,
-// kAhead loads in flight, and the kSumQ subtotals are then added by a fixed
-// binary tree in LDS.  The order depends only on the chunk count, so results are
-// run-to-run identical.  Bound by the latency of a thread's chain and by the few
-// blocks: 16 columns and 64 rows rather than 64 and 16 quarter the chain and
-// quadruple the blocks (300,000 rows x 300 pixels in
-// the F32C form: 120 -> 67 us the whole call).
-constexpr int kSumCols = 16;
-constexpr int kSumQ = 64;
+// Chunk reductions: a block owns COLS consecutive outputs (coalesced along x); its
+// Q rows of threads each add the chunks q, q + Q, ... in order, kAhead loads in
+// flight, and the Q subtotals are then added by a fixed binary tree in LDS.  The
+// order depends only on the counts of chunks and outputs, so results are run-to-run
+// identical.  Bound by the latency of a thread's chain and by the few blocks: 16
+// columns and 64 rows rather than 64 and 16 quarter the chain and quadruple the
+// blocks (300,000 rows x 300 pixels in the F32C form: 120 -> 69 us the whole call),
+// 8 and 128 do so again (65 us; 300,000 x 40, FP64: 26.9 -> 25.4) but halve the
+// segments read, which costs where 16 fill the chip (100,000 x 60,000: 3.74 -> 3.78
+// ms).
+constexpr int kSumBlock = 1024;
+constexpr int64_t kSumNarrow = 4096;   // outputs below which a block takes 8
 constexpr int kAhead = 8;
 
-__global__ __launch_bounds__(kSumCols * kSumQ) void k_sum_chunks_c128(
+template <int COLS>
+__global__ __launch_bounds__(kSumBlock) void k_sum_chunks_c128(
     const double2* __restrict__ partial, int64_t n_chunks, int64_t n, double2* __restrict__ out) {
-    __shared__ double red_r[kSumQ][kSumCols], red_i[kSumQ][kSumCols];
-    const int tx = threadIdx.x % kSumCols, q = threadIdx.x / kSumCols;
-    const int64_t p = (int64_t)blockIdx.x * kSumCols + tx;
+    constexpr int Q = kSumBlock / COLS;
+    __shared__ double red_r[Q][COLS], red_i[Q][COLS];
+    const int tx = threadIdx.x % COLS, q = threadIdx.x / COLS;
+    const int64_t p = (int64_t)blockIdx.x * COLS + tx;
     double re = 0.0, im = 0.0;
     if (p < n) {
         int64_t c = q;
-        for (; c + (kAhead - 1) * kSumQ < n_chunks; c += kAhead * kSumQ) {
+        for (; c + (kAhead - 1) * Q < n_chunks; c += kAhead * Q) {
             double2 x[kAhead];
 #pragma unroll
-            for (int t = 0; t < kAhead; ++t) x[t] = partial[(c + t * kSumQ) * n + p];
+            for (int t = 0; t < kAhead; ++t) x[t] = partial[(c + t * Q) * n + p];
 #pragma unroll
             for (int t = 0; t < kAhead; ++t) {
                 re += x[t].x;
                 im += x[t].y;
             }
         }
-        for (; c < n_chunks; c += kSumQ) {
+        for (; c < n_chunks; c += Q) {
             const double2 x = partial[c * n + p];
             re += x.x;
             im += x.y;
@@ -422,7 +426,7 @@ __global__ __launch_bounds__(kSumCols * kSumQ) void k_sum_chunks_c128(
     red_r[q][tx] = re;
     red_i[q][tx] = im;
     __syncthreads();
-    for (int h = kSumQ / 2; h > 0; h >>= 1) {
+    for (int h = Q / 2; h > 0; h >>= 1) {
         if (q < h) {
             red_r[q][tx] += red_r[q + h][tx];
             red_i[q][tx] += red_i[q + h][tx];
@@ -550,9 +554,12 @@ hipError_t launch_adjoint(hipStream_t s, int prec, int ppl, int block, int64_t c
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    k_sum_chunks_c128<<<dim3((unsigned)((n_pix + kSumCols - 1) / kSumCols)),
-                        dim3(kSumCols * kSumQ), 0, s>>>((const double2*)partial, n_chunks, n_pix,
-                                                       (double2*)out);
+    if (n_pix < kSumNarrow)
+        k_sum_chunks_c128<8><<<dim3((unsigned)((n_pix + 7) / 8)), dim3(kSumBlock), 0, s>>>(
+            (const double2*)partial, n_chunks, n_pix, (double2*)out);
+    else
+        k_sum_chunks_c128<16><<<dim3((unsigned)((n_pix + 15) / 16)), dim3(kSumBlock), 0, s>>>(
+            (const double2*)partial, n_chunks, n_pix, (double2*)out);
     return hipGetLastError();
 }
 
@@ -689,8 +696,10 @@ __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) 
 
 // A block owns kGradCols components; thread (q, t, x) adds sum t of component x
 // over the chunks q, q + kGradQ, ... in order, then as in the chunk reduction.
-constexpr int kGradCols = 16;
-constexpr int kGradQ = 16;
+// 8 components rather than 16: twice the blocks (1,536 chunks x 600 components in a
+// cycle: 18.6 -> 15 us; 4 are no better).
+constexpr int kGradCols = 8;
+constexpr int kGradQ = 32;
 
 __global__ __launch_bounds__(4 * kGradCols * kGradQ) void k_grad_finish(
     const double* __restrict__ partial, int64_t n_chunks, const double* __restrict__ comp,

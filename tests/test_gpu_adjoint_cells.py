@@ -32,7 +32,8 @@ def _run(env, u, v, w, y, l, m, nm1, sign=-1):
 @pytest.mark.parametrize("n,p,sign", [
     (1, 1, -1), (31, 64, 1), (33, 65, -1), (64, 129, 1), (511, 193, -1), (512, 255, 1),
     (513, 257, -1), (2047, 321, 1), (70001, 5, -1), (300003, 130, 1), (1027, 2049, -1),
-    (1501, 577, 1), (2300, 1100, -1), (1027, 2048, 1)])   # 4, 8 and 8 columns of a workgroup
+    (1501, 577, 1), (2300, 1100, -1), (1027, 2048, 1),   # 4, 8 and 8 columns of a workgroup
+    (9000, 4095, 1), (9000, 4097, -1)])                  # the chunk sums' two widths
 def test_edges_against_oracle(env, n, p, sign):
     u, v, w, y, l, m, nm1 = _case(n, p, n + 5 * p)
     got = _run(env, u, v, w, y, l, m, nm1, sign)
