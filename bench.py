@@ -52,14 +52,14 @@ FLOPS = {
 PHASOR_FLOPS = 3 + 8
 
 # Operations per term of the FP32-compensated forms, by the unit that executes
-# them.  Direct: the FP64 phase summed onto a magic number (3 FMA), its low word
-# converted and scaled, the hardware sine and cosine, and per re/im an FMA per
-# term and the 3 additions of a Kahan step per four.  Adjoint: the FP64 phase and
+# them.  Direct: the FP64 phase and its exact reduction to [-1/2, 1/2] (1 mul, 2
+# FMA, rint, subtraction), the conversion, the hardware sine and cosine, and per
+# re/im an FMA per term and the 3 additions of a Kahan step per four.  Adjoint: the FP64 phase and
 # its exact reduction to [0, 1) (1 mul, 2 FMA, fract), the conversion, sine and
 # cosine, and per re/im a pair's four FMAs (conj(e) y of both rows, less the
 # compensation) and 3 additions, 7 per pair.
 F32C_OPS = {
-    "direct_f32c": {"f64": 3, "cvt": 1, "trans": 2, "f32": 4.5},
+    "direct_f32c": {"f64": 5, "cvt": 1, "trans": 2, "f32": 3.5},
     "adjoint_f32c": {"f64": 4, "cvt": 1, "trans": 2, "f32": 7},
 }
 

@@ -39,49 +39,6 @@ __device__ __forceinline__ double fract_phase(double u, double v, double w, doub
     return __builtin_amdgcn_fract(fma(u, l, fma(v, m, w * nm1)));
 }
 
-// The phase reduced to [-1/2, 1/2) turns in FP32.  The three products enter a sum
-// that starts at a magic number, 1.5 2^(20 + shift): it rounds to 2^(shift - 32)
-// turns and its low word, shifted back up, is the phase modulo one turn as a
-// signed 32-bit fraction.  So the reduction costs nothing and the conversion to
-// FP32 is that of an integer: 3 FP64 and 2 FP32 instructions, against 4 FP64 ones
-// and a conversion from FP64.  At shift 0 the roundings (three of at most 2^-33
-// turns) are far below that of the FP32 result, at most 2^-26 turns; fract's
-// [0, 1) rounds by up to 2^-25.
-//
-// A row's shift follows from its baseline alone.  For a direction on the near
-// hemisphere l^2 + m^2 + (n - 1)^2 = 2 (1 - n) <= 2, so |phase| <= sqrt(2)
-// |(u, v, w)|, which has to stay below 2^(19 + shift): 370,000 wavelengths at
-// shift 0, 5.9 million at shift 4; rows beyond that, or not finite, take fract.
-// The forms of a wave's loop: 0 every lane at shift 0, 1 shifts by lane, 2 fract
-// by lane besides; a row has the same bits in each that serves it.
-struct TurnRow {
-    double magic;
-    unsigned shift;
-    bool far;
-};
-__device__ __forceinline__ TurnRow turn_row(double u, double v, double w) {
-    const double b2 = 1.0001 * fma(u, u, fma(v, v, w * w));
-    TurnRow r;
-    r.far = !(b2 < 0x1p45);
-    // b2 < 2^e: 2 b2 < 2^(38 + 2 shift)
-    const int e = r.far ? 0 : __builtin_amdgcn_frexp_exp(b2);
-    r.shift = e > 37 ? (unsigned)(e - 36) >> 1 : 0u;
-    r.magic = 1.5 * (double)(1u << (20 + r.shift));
-    return r;
-}
-
-template <int FORM>
-__device__ __forceinline__ float turns_f32(double u, double v, double w, double l, double m,
-                                           double nm1, const TurnRow& row) {
-    const double t = fma(u, l, fma(v, m, fma(w, nm1, row.magic)));
-    unsigned low = (unsigned)__double_as_longlong(t);
-    if constexpr (FORM > 0) low <<= row.shift;
-    const float r = (float)(int)low * 0x1p-32f;
-    if constexpr (FORM < 2) return r;
-    const float far = (float)fract_phase(u, v, w, l, m, nm1);
-    return row.far ? far : r;
-}
-
 // Fused multiply-add as one 3-operand v_fma_f64 on VGPRs: the same rounding
 // as fma(), but never the two-address form (a copy of the addend into the
 // destination, then v_fmac_f64) that the compiler picks when the addend is a

@@ -331,25 +331,32 @@ __device__ __forceinline__ void direct_rows_f64(const int64_t (&j)[VPL], int64_t
     }
 }
 
-// FP32-compensated form: FP64 phase; FP32 phasor, products and Kahan sums.
-// Components come in fours: their products and the running compensation meet in a
-// chain of FMAs, then one Kahan step, so a component costs a quarter of a step
-// (the chain's roundings stay within a few 2^-24 of the four terms); then a pair
-// and a single one.  Per row and component 3 FP64 instructions, 2 FP32 for the
-// phase, the hardware sine and cosine, 3.5 FP32 for the sums.  1,263,601 rows x
-// 1,999 components: 0.92 -> 0.79 ms (from 4 FP64, a conversion from FP64 and 5
-// FP32, in pairs).
+// FP32-compensated form: FP64 phase, reduced to [-1/2, 1/2] turns exactly; FP32
+// phasor, products and Kahan sums.  Components come in fours: their products and
+// the running compensation meet in a chain of FMAs, then one Kahan step, so a
+// component costs a quarter of a step (the chain's roundings stay within a few
+// 2^-24 of the four terms); then a pair and a single one.  Per row and component 5
+// FP64 instructions and the conversion for the phase, the hardware sine and cosine,
+// 3.5 FP32 for the sums.  1,263,601 rows x 1,999 components: 0.90 ms.
+//
+// The reduction is exact for every baseline and direction, those behind the phase
+// centre's horizon too, and a phase near zero, of either sign, keeps FP32's relative
+// accuracy.  Reduced to [0, 1) by the hardware fract, one instruction less, it takes
+// 0.83 ms, but rounds by up to 2^-25 turns instead of 2^-26 (4.2e-9 of the flux
+// against 3.4e-9 rms, 2,000 components, 1e5 wavelengths) and negative phases near
+// zero not relatively at all; summed onto a magic number whose last place is a
+// fixed fraction of a turn, 0.80 ms, but right only as far as that number's range
+// goes.
 //
 // The list is summed in the FP64 kernels' two-level order with sub-ranges of at
 // least kF32cSub components; their compensated sums enter the ranges' and the
 // total in FP64.
 constexpr int kF32cSub = 128;
 
-template <int VPL, int FORM, class CompPtr>
+template <int VPL, class CompPtr>
 __device__ __forceinline__ void add_components_f32c(CompPtr cp, int k0, int k1,
                                                     const double (&U)[VPL], const double (&V)[VPL],
                                                     const double (&W)[VPL],
-                                                    const TurnRow (&row)[VPL],
                                                     double (&re)[VPL], double (&im)[VPL]) {
     float sr[VPL], si[VPL], cr[VPL], ci[VPL];
 #pragma unroll
@@ -366,8 +373,7 @@ __device__ __forceinline__ void add_components_f32c(CompPtr cp, int k0, int k1,
 #pragma unroll
             for (int b = N - 1; b >= 0; --b) {
                 float co, sn;
-                cis2pi_f32(turns_f32<FORM>(U[i], V[i], W[i], c[b].l, c[b].m, c[b].nm1, row[i]), co,
-                           sn);
+                cis2pi_f32((float)reduced_phase(U[i], V[i], W[i], c[b].l, c[b].m, c[b].nm1), co, sn);
                 yr = fmaf(c[b].I, co, yr);
                 yi = fmaf(c[b].I, sn, yi);
             }
@@ -391,11 +397,10 @@ __device__ __forceinline__ void add_components_f32c(CompPtr cp, int k0, int k1,
 }
 
 // The sums of ranges [a0, a1), handed to put(a, re, im) as each is complete.
-template <int VPL, int FORM, class CompPtr, class Put>
+template <int VPL, class CompPtr, class Put>
 __device__ __forceinline__ void range_sums_f32c(CompPtr cp, const CompRanges& R, int a0, int a1,
                                                 const double (&U)[VPL], const double (&V)[VPL],
-                                                const double (&W)[VPL],
-                                                const TurnRow (&row)[VPL], Put&& put) {
+                                                const double (&W)[VPL], Put&& put) {
 #pragma unroll 1
     for (int a = a0; a < a1; ++a) {
         double rr[VPL], ri[VPL];
@@ -404,49 +409,25 @@ __device__ __forceinline__ void range_sums_f32c(CompPtr cp, const CompRanges& R,
         const int last = (int)R.end_of(a);
 #pragma unroll 1
         for (int k0 = a * R.A; k0 < last; k0 += R.B)
-            add_components_f32c<VPL, FORM>(cp, k0, k0 + R.B < last ? k0 + R.B : last, U, V, W, row,
-                                           rr, ri);
+            add_components_f32c<VPL>(cp, k0, k0 + R.B < last ? k0 + R.B : last, U, V, W, rr, ri);
         put(a, rr, ri);
     }
 }
 
-// Rows j[0 .. VPL) of a lane, clamped to the last one; the loop's form.
+// Rows j[0 .. VPL) of a lane, clamped to the last one.
 template <int VPL>
-__device__ __forceinline__ int load_rows_f32c(const int64_t (&j)[VPL], int64_t limit,
-                                              const double* __restrict__ u,
-                                              const double* __restrict__ v,
-                                              const double* __restrict__ w, double (&U)[VPL],
-                                              double (&V)[VPL], double (&W)[VPL],
-                                              TurnRow (&row)[VPL]) {
-    bool far = false, shifted = false;
+__device__ __forceinline__ void load_rows_f32c(const int64_t (&j)[VPL], int64_t limit,
+                                               const double* __restrict__ u,
+                                               const double* __restrict__ v,
+                                               const double* __restrict__ w, double (&U)[VPL],
+                                               double (&V)[VPL], double (&W)[VPL]) {
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
         const int64_t jj = j[i] < limit ? j[i] : limit - 1;
         U[i] = u[jj];
         V[i] = v[jj];
         W[i] = w[jj];
-        row[i] = turn_row(U[i], V[i], W[i]);
-        far = far || row[i].far;
-        shifted = shifted || row[i].shift != 0;
     }
-    const int form = __any(far) ? 2 : (__any(shifted) ? 1 : 0);
-    if (form == 0) {   // one magic number for all, in a register of its own
-        const double magic = vector_const(1.5 * 0x1p20);
-#pragma unroll
-        for (int i = 0; i < VPL; ++i) row[i].magic = magic;
-    }
-    return form;
-}
-
-// f(form) for the loop's form as a constant.
-template <class F>
-__device__ __forceinline__ void with_form(int form, F&& f) {
-    if (__builtin_expect(form == 0, 1))
-        f(std::integral_constant<int, 0>());
-    else if (form == 1)
-        f(std::integral_constant<int, 1>());
-    else
-        f(std::integral_constant<int, 2>());
 }
 
 template <int VPL>
@@ -458,8 +439,7 @@ __device__ __forceinline__ void direct_rows_f32c(const int64_t (&j)[VPL], int64_
                                                  double sgn, float2* __restrict__ out,
                                                  int* __restrict__ status) {
     double U[VPL], V[VPL], W[VPL], sr[VPL], si[VPL];
-    TurnRow row[VPL];
-    const int form = load_rows_f32c<VPL>(j, limit, u, v, w, U, V, W, row);
+    load_rows_f32c<VPL>(j, limit, u, v, w, U, V, W);
 #pragma unroll
     for (int i = 0; i < VPL; ++i) sr[i] = si[i] = 0.0;
     const CompRanges R(n_comp, kF32cSub);
@@ -470,9 +450,7 @@ __device__ __forceinline__ void direct_rows_f32c(const int64_t (&j)[VPL], int64_
             si[i] += ri[i];
         }
     };
-    with_form(form, [&](auto f) {
-        range_sums_f32c<VPL, decltype(f)::value>(uniform_ptr(comp), R, 0, 8, U, V, W, row, add);
-    });
+    range_sums_f32c<VPL>(uniform_ptr(comp), R, 0, 8, U, V, W, add);
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
         if (j[i] < limit) {

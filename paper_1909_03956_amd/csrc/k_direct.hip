@@ -338,16 +338,12 @@ __global__ __launch_bounds__(kF32cBlock) void k_direct_f32c_split(
     const int64_t row0 = (int64_t)blockIdx.x * kRows;
     const int64_t j[1] = {row0 + local};
     double U[1], V[1], W[1];
-    TurnRow row[1];
-    const int form = load_rows_f32c<1>(j, n_vis, u, v, w, U, V, W, row);
+    load_rows_f32c<1>(j, n_vis, u, v, w, U, V, W);
     const CompRanges R(n_comp, kF32cSub);
     const auto keep = [&](int a, const double(&re)[1], const double(&im)[1]) {
         part[a][local] = make_double2(re[0], im[0]);
     };
-    with_form(form, [&](auto f) {
-        range_sums_f32c<1, decltype(f)::value>(uniform_ptr(comp), R, own * kOwn, (own + 1) * kOwn,
-                                               U, V, W, row, keep);
-    });
+    range_sums_f32c<1>(uniform_ptr(comp), R, own * kOwn, (own + 1) * kOwn, U, V, W, keep);
     __syncthreads();
     for (int r = threadIdx.x; r < kRows && row0 + r < n_vis; r += kF32cBlock) {
         double re = 0.0, im = 0.0;
@@ -372,13 +368,10 @@ __global__ __launch_bounds__(kF32cBlock) void k_direct_f32c_part(
     const int b = blockIdx.y;
     const int64_t j[1] = {(int64_t)blockIdx.x * 64 + lane};
     double U[1], V[1], W[1], re[1] = {0.0}, im[1] = {0.0};
-    TurnRow row[1];
-    const int form = load_rows_f32c<1>(j, n_vis, u, v, w, U, V, W, row);
+    load_rows_f32c<1>(j, n_vis, u, v, w, U, V, W);
     const CompRanges R(n_comp, kF32cSub);
     const int k0 = R.begin(a, b), k1 = R.end(a, b);
-    with_form(form, [&](auto f) {
-        add_components_f32c<1, decltype(f)::value>(uniform_ptr(comp), k0, k1, U, V, W, row, re, im);
-    });
+    add_components_f32c<1>(uniform_ptr(comp), k0, k1, U, V, W, re, im);
     if (j[0] < n_vis) {
         if (a == 0 && b == 0 && !isfinite(U[0] + V[0] + W[0])) atomicOr(status, kStatusNonFinite);
         partial[((int64_t)a * 8 + b) * n_vis + j[0]] = make_double2(re[0], im[0]);
