@@ -25,13 +25,29 @@ __device__ __forceinline__ void chunk_tile(int64_t bid, int64_t tiles, int64_t& 
     chunk = g * 8 + (r & 7);
 }
 
-// Launches `total` blocks as 1-D grids of at most 2^30 blocks, passing the
-// first linear id of each.
+// HIP takes no launch of 2^32 threads or more in a dimension; kernels that would
+// need more go out in slabs of half that.
+constexpr int64_t kMaxLaunchThreads = int64_t(1) << 31;
+
+// Launches `total` blocks of `block` threads as 1-D grids of one slab each, passing
+// the first linear id of each.
 template <class F>
-static void launch_slabs(int64_t total, F&& launch) {
-    constexpr int64_t kSlab = int64_t(1) << 30;
-    for (int64_t b0 = 0; b0 < total; b0 += kSlab)
-        launch(b0, (unsigned)(total - b0 < kSlab ? total - b0 : kSlab));
+static void launch_slabs(int64_t total, int block, F&& launch) {
+    const int64_t slab = kMaxLaunchThreads / block;
+    for (int64_t b0 = 0; b0 < total; b0 += slab)
+        launch(b0, (unsigned)(total - b0 < slab ? total - b0 : slab));
+}
+
+// Rows of one launch of the kernels that give a row up to eight threads.
+constexpr int64_t kRowSlab = kMaxLaunchThreads / 8;
+
+// Calls launch(first row, rows) for slabs of that many rows; the first error.
+template <class F>
+static hipError_t launch_row_slabs(int64_t n, F&& launch) {
+    hipError_t e = hipSuccess;
+    for (int64_t j = 0; j < n && e == hipSuccess; j += kRowSlab)
+        e = launch(j, n - j < kRowSlab ? n - j : kRowSlab);
+    return e;
 }
 
 }  // namespace swv

@@ -3,6 +3,7 @@
 // the block size so each of a lane's VPL loads is coalesced.
 #include <cmath>
 
+#include "chunking.h"
 #include "direct_rows.h"
 
 namespace swv {
@@ -114,16 +115,17 @@ static dim3 few_grid(int64_t n_vis) {
 hipError_t launch_direct_few(hipStream_t s, int64_t n_vis, const double* u, const double* v,
                              const double* w, int n_comp, const double* l, const double* m,
                              const double* flux, int sign, double2* out, int* status) {
-    if (n_vis <= 0) return hipSuccess;
     if (n_comp >= kTableMinComp) return hipErrorInvalidValue;
-    const dim3 grid = few_grid(n_vis), blk(kFewBlock);
-    if (few_vpl(n_vis) == 1)
-        k_direct_few<1><<<grid, blk, 0, s>>>(u, v, w, n_vis, l, m, flux, n_comp, (double)sign, out,
-                                             status);
-    else
-        k_direct_few<4><<<grid, blk, 0, s>>>(u, v, w, n_vis, l, m, flux, n_comp, (double)sign, out,
-                                             status);
-    return hipGetLastError();
+    return launch_row_slabs(n_vis, [&](int64_t j, int64_t n) {
+        const dim3 grid = few_grid(n), blk(kFewBlock);
+        if (few_vpl(n) == 1)
+            k_direct_few<1><<<grid, blk, 0, s>>>(u + j, v + j, w + j, n, l, m, flux, n_comp,
+                                                 (double)sign, out + j, status);
+        else
+            k_direct_few<4><<<grid, blk, 0, s>>>(u + j, v + j, w + j, n, l, m, flux, n_comp,
+                                                 (double)sign, out + j, status);
+        return hipGetLastError();
+    });
 }
 
 // -------------------------------------------------- FP64, table phasor ----
@@ -255,7 +257,6 @@ static hipError_t run_direct_cell(hipStream_t s, const DirectShape& sh, int64_t 
                                   const double* u, const double* v, const double* w,
                                   const CompCell* comp, int64_t n_comp, int sign, OUT* out,
                                   double2* partial, int* status) {
-    if (n_vis <= 0) return hipSuccess;
     const double sg = (double)sign;
     const int nc = (int)n_comp;
     if (n_comp < kTableMinComp) {
@@ -299,11 +300,13 @@ hipError_t launch_direct_cell(hipStream_t s, const DirectShape& sh, int64_t n_vi
                               const double* v, const double* w, const CompCell* comp,
                               int64_t n_comp, int sign, int prec, void* out, double2* partial,
                               int* status) {
-    if (prec == SWV_FP64)
-        return run_direct_cell(s, sh, n_vis, u, v, w, comp, n_comp, sign, (double2*)out, partial,
-                               status);
-    return run_direct_cell(s, sh, n_vis, u, v, w, comp, n_comp, sign, (float2*)out, partial,
-                           status);
+    return launch_row_slabs(n_vis, [&](int64_t j, int64_t n) {
+        if (prec == SWV_FP64)
+            return run_direct_cell(s, sh, n, u + j, v + j, w + j, comp, n_comp, sign,
+                                   (double2*)out + j, partial, status);
+        return run_direct_cell(s, sh, n, u + j, v + j, w + j, comp, n_comp, sign,
+                               (float2*)out + j, partial, status);
+    });
 }
 
 // ------------------------------------------------------------------ F32C ---
@@ -412,11 +415,10 @@ static hipError_t run_direct_b(hipStream_t s, int block, int64_t n_vis, const do
     }
 }
 
-hipError_t launch_direct_f32c(hipStream_t s, const DirectShape& sh, int vpl, int block,
-                              int64_t n_vis, const double* u, const double* v, const double* w,
-                              const CompF* comp, int64_t n_comp, int sign, void* out,
-                              double2* partial, int* status) {
-    if (n_vis <= 0) return hipSuccess;
+static hipError_t run_direct_f32c(hipStream_t s, const DirectShape& sh, int vpl, int block,
+                                  int64_t n_vis, const double* u, const double* v,
+                                  const double* w, const CompF* comp, int64_t n_comp, int sign,
+                                  float2* out, double2* partial, int* status) {
     const int nc = (int)n_comp;
     const double sg = (double)sign;
     if (sh.parts > 1) {
@@ -426,16 +428,16 @@ hipError_t launch_direct_f32c(hipStream_t s, const DirectShape& sh, int vpl, int
                                                                     partial, status);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        k_direct_join<float2><<<dim3(nb), dim3(64), 0, s>>>(partial, n_vis, sg, (float2*)out);
+        k_direct_join<float2><<<dim3(nb), dim3(64), 0, s>>>(partial, n_vis, sg, out);
         return hipGetLastError();
     }
     if (sh.split > 1) {
         const int64_t rows = kF32cBlock / sh.split;
         const dim3 grid((unsigned)((n_vis + rows - 1) / rows)), blk(kF32cBlock);
         switch (sh.split) {
-            case 2: k_direct_f32c_split<2><<<grid, blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, (float2*)out, status); break;
-            case 4: k_direct_f32c_split<4><<<grid, blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, (float2*)out, status); break;
-            case 8: k_direct_f32c_split<8><<<grid, blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, (float2*)out, status); break;
+            case 2: k_direct_f32c_split<2><<<grid, blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status); break;
+            case 4: k_direct_f32c_split<4><<<grid, blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status); break;
+            case 8: k_direct_f32c_split<8><<<grid, blk, 0, s>>>(u, v, w, n_vis, comp, nc, sg, out, status); break;
             default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
@@ -446,6 +448,16 @@ hipError_t launch_direct_f32c(hipStream_t s, const DirectShape& sh, int vpl, int
         case 4: return run_direct_b<4>(s, block, n_vis, u, v, w, comp, n_comp, sign, out, status);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_direct_f32c(hipStream_t s, const DirectShape& sh, int vpl, int block,
+                              int64_t n_vis, const double* u, const double* v, const double* w,
+                              const CompF* comp, int64_t n_comp, int sign, void* out,
+                              double2* partial, int* status) {
+    return launch_row_slabs(n_vis, [&](int64_t j, int64_t n) {
+        return run_direct_f32c(s, sh, vpl, block, n, u + j, v + j, w + j, comp, n_comp, sign,
+                               (float2*)out + j, partial, status);
+    });
 }
 
 }  // namespace swv

@@ -442,7 +442,7 @@ static void run_adjoint_f32c(hipStream_t s, int64_t tiles, int64_t chunk, int64_
                              int64_t n_pix, const double* l, const double* m, const double* nm1,
                              int sign, void* partial) {
     const int64_t n_chunks = (n_vis + chunk - 1) / chunk;
-    launch_slabs(xcd_padded(n_chunks) * tiles, [&](int64_t b0, unsigned nb) {
+    launch_slabs(xcd_padded(n_chunks) * tiles, BLOCK, [&](int64_t b0, unsigned nb) {
         k_adjoint_f32c<PPL, BLOCK><<<dim3(nb), dim3(BLOCK), 0, s>>>(
             u, v, w, (const double2*)y, n_vis, chunk, l, m, nm1, n_pix, (double)sign, n_chunks,
             tiles, b0, (double2*)partial);

@@ -1,0 +1,57 @@
+"""Calls whose kernels need 2^32 threads or more in all, which no single launch
+takes: layouts that give a row several threads, at row counts past that border."""
+import numpy as np
+import pytest
+
+from oracle import visibility as ov
+
+from .gpu_util import fp64_row_bound, host, note, require_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    torch, swv = require_gpu()
+    yield torch, swv
+    torch.cuda.empty_cache()
+
+
+def _room(torch, need):
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free, _ = torch.cuda.mem_get_info()
+    if free < need + (8 << 30):
+        pytest.skip(f"needs {need / 2**30:.0f} GiB of free device memory")
+
+
+def _rows(rng, n, border):
+    """Sampled rows, those around the border and the last ones among them."""
+    return np.unique(np.concatenate([rng.integers(0, n, 300), np.arange(n - 300, n),
+                                     np.arange(border - 20, min(border + 20, n))]))
+
+
+def _track(torch, n):
+    """One coordinate for all three axes (8 bytes a row), from the row index."""
+    return torch.arange(n, dtype=torch.float64, device="cuda").mul_(3.7e-7).add_(0.1).sin_().mul_(2e4)
+
+
+def test_direct_sum_of_long_lists_past_2_31_rows(env):
+    """600 components: four rows a lane over eight waves, two threads a row."""
+    torch, swv = env
+    n, k = (1 << 31) + 300, 600
+    _room(torch, 24 * n)
+    note(f"direct sum, {n} rows x {k} components")
+    rng = np.random.default_rng(3)
+    l, m, f = rng.uniform(-0.02, 0.02, k), rng.uniform(-0.02, 0.02, k), rng.lognormal(-3, 1, k)
+    L, M, F = (torch.as_tensor(a, device="cuda") for a in (l, m, f))
+    x = _track(torch, n)
+    out = torch.empty(n, dtype=torch.complex128, device="cuda")
+    swv.predict_direct(x, x, x, L, M, F, out=out)
+    swv.synchronize()
+    rows = _rows(rng, n, 1 << 31)
+    idx = torch.as_tensor(rows, device="cuda")
+    xs = host(x[idx])
+    ref = ov.predict_direct(xs, xs, xs, l, m, f)
+    bound = fp64_row_bound(xs, xs, xs, l, m, ov.n_minus_1(l, m), f)
+    assert np.all(np.abs(host(out[idx]) - ref) <= bound)
