@@ -9,6 +9,7 @@
 // item from a device counter (one atomic per item, on lane 0) and leaves when the
 // counter passes the item count, so every wave exits.  The row arithmetic is the
 // single-instance kernels' (direct_rows.h).
+#include "chunking.h"
 #include "direct_rows.h"
 
 namespace swv {
@@ -155,8 +156,9 @@ int batch_direct_f32c_blocks_per_cu() { return resident(k_batch_direct_f32c, kBa
 
 hipError_t launch_batch_direct(hipStream_t s, const BatchInst* inst, const WorkItem* items,
                                unsigned n_items, int* status) {
-    if (n_items == 0) return hipSuccess;
-    k_batch_direct<<<dim3(n_items), dim3(kTabBlock), 0, s>>>(inst, items, status);
+    launch_slabs(n_items, kTabBlock, [&](int64_t i0, unsigned n) {
+        k_batch_direct<<<dim3(n), dim3(kTabBlock), 0, s>>>(inst, items + i0, status);
+    });
     return hipGetLastError();
 }
 

@@ -55,3 +55,23 @@ def test_direct_sum_of_long_lists_past_2_31_rows(env):
     ref = ov.predict_direct(xs, xs, xs, l, m, f)
     bound = fp64_row_bound(xs, xs, xs, l, m, ov.n_minus_1(l, m), f)
     assert np.all(np.abs(host(out[idx]) - ref) <= bound)
+
+
+def test_batched_plan_past_2_31_rows(env):
+    """512 threads to every 256 rows; the same bits as the single call."""
+    torch, swv = env
+    n, k = (1 << 31) + 300, 500
+    _room(torch, (8 + 16 + 24) * n)
+    note(f"batched plan, {n} rows x {k} components")
+    rng = np.random.default_rng(4)
+    l, m, f = rng.uniform(-0.02, 0.02, k), rng.uniform(-0.02, 0.02, k), rng.lognormal(-3, 1, k)
+    L, M, F = (torch.as_tensor(a, device="cuda") for a in (l, m, f))
+    x = _track(torch, n)
+    out = torch.empty(n, dtype=torch.complex128, device="cuda")
+    plan = swv.BatchPlan([dict(route="direct", u=x, v=x, w=x, l=L, m=M, flux=F, out=out)])
+    plan.run()
+    swv.synchronize()
+    plan.close()
+    idx = torch.as_tensor(_rows(rng, n, 1 << 31), device="cuda")
+    xs = x[idx]
+    assert torch.equal(out[idx], swv.predict_direct(xs, xs, xs, L, M, F))
