@@ -21,6 +21,7 @@
 #include <cmath>
 
 #include "api_internal.h"
+#include "chunking.h"
 #include "device_math.h"
 
 namespace swv {
@@ -392,8 +393,8 @@ void launch_degrid_w(hipStream_t s, int64_t n_vis, const double* u, const double
     const Tiles t = tiles_of(Nx, Ny, cell);
     int* next = (int*)sorted;
     DgRow* rows = sorted ? (DgRow*)((char*)sorted + kTileBytes) : nullptr;
-    // rows in slabs that stay within a launch's grid, or the records
-    const int64_t slab = sorted ? kSortSlab : int64_t(1) << 28;
+    // rows in slabs that stay within a launch's threads, or the records
+    const int64_t slab = sorted ? kSortSlab : kMaxLaunchThreads / LV;
     for (int64_t j = 0; j < n_vis; j += slab) {
         const int64_t n = std::min<int64_t>(slab, n_vis - j);
         if (sorted) {

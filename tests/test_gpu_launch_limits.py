@@ -75,3 +75,22 @@ def test_batched_plan_past_2_31_rows(env):
     idx = torch.as_tensor(_rows(rng, n, 1 << 31), device="cuda")
     xs = x[idx]
     assert torch.equal(out[idx], swv.predict_direct(xs, xs, xs, L, M, F))
+
+
+def test_degridding_of_2_28_rows(env):
+    """16 lanes a row at support 9; planes small enough that rows stay unsorted."""
+    torch, swv = env
+    n, nx = (1 << 28) + 40, 12
+    _room(torch, 40 * n)
+    note(f"degridding, {n} rows, support 9")
+    rng = np.random.default_rng(5)
+    img = torch.as_tensor(rng.lognormal(-1, 1, (nx, nx)), device="cuda")
+    x = _track(torch, n).mul_(0.01)
+    out, st = swv.predict_degrid(img, x, x, x, 0.003, support=9)
+    assert st["plane_bytes"] <= 4 << 20
+    rows = torch.as_tensor(_rows(rng, n, 1 << 28), device="cuda")
+    # the same w range, so the same planes, by way of its ends
+    ends = torch.stack([x.argmin(), x.argmax()])
+    rows = torch.cat([rows, ends])
+    xs = x[rows]
+    assert torch.equal(out[rows], swv.predict_degrid(img, xs, xs, xs, 0.003, support=9)[0])
