@@ -33,6 +33,7 @@
 // of workgroups per XCD, as in the adjoint.
 #include <type_traits>
 
+#include "chunking.h"
 #include "device_math.h"
 #include "launch.h"
 #include "phasor_table.h"
@@ -410,12 +411,12 @@ constexpr int kFinCols = 16, kFinQ = 16;
 
 template <bool PIXELS>
 __global__ __launch_bounds__(kFinCols * 4 * kFinQ) void k_grid_finish(
-    GridGeom g, const double* __restrict__ partial, int64_t n_chunks, int nx, int ny, int cx, int cy,
-    double n_vis, double* __restrict__ img) {
+    GridGeom g, const double* __restrict__ partial, int64_t n_chunks, int64_t bid0, int nx, int ny,
+    int cx, int cy, double n_vis, double* __restrict__ img) {
     __shared__ double red[kFinQ][kFinCols * 4];
     const int64_t quads = (int64_t)g.Kx * g.Ky;
     const int tx = threadIdx.x % (kFinCols * 4), r = threadIdx.x / (kFinCols * 4);
-    const int64_t at = (int64_t)blockIdx.x * (kFinCols * 4) + tx;   // 4 quad + component
+    const int64_t at = (bid0 + blockIdx.x) * (kFinCols * 4) + tx;   // 4 quad + component
     double s = 0.0;
     if (at < 4 * quads)
         for (int64_t c = r; c < n_chunks; c += kFinQ) s += partial[c * 4 * quads + at];
@@ -556,7 +557,7 @@ hipError_t launch_grid_slab(hipStream_t s, const GridGeom& g, const GridPlan& p,
     if (e != hipSuccess) return e;
     const int64_t jobs = (rows + chunk - 1) / chunk * p.jobs;
     const int64_t per = kTabBlock / 64, run = ((jobs + per - 1) / per + 7) / 8;
-    if (run > (int64_t(1) << 27)) return hipErrorInvalidConfiguration;
+    if (8 * run > kMaxLaunchThreads / kTabBlock) return hipErrorInvalidConfiguration;
     const GridData data{rec, ex, ey, partial, resume};
     const dim3 grid((unsigned)(8 * run)), blk(kTabBlock);
     if (y)
@@ -571,7 +572,7 @@ hipError_t launch_image_f32c(hipStream_t s, const GridGeom& g, const GridPlan& p
                              const void* y, int sign, double* partial) {
     const int64_t jobs = (n_vis + chunk - 1) / chunk * p.jobs;
     const int64_t per = kF32Block / 64, run = ((jobs + per - 1) / per + 7) / 8;
-    if (run > (int64_t(1) << 27)) return hipErrorInvalidConfiguration;
+    if (8 * run > kMaxLaunchThreads / kF32Block) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)(8 * run)), blk(kF32Block);
     const float fsg = (float)sign;
     if (y)
@@ -587,14 +588,15 @@ hipError_t launch_grid_finish(hipStream_t s, const GridGeom& g, int prec, const 
                               int64_t n_chunks, int nx, int ny, int cx, int cy, int64_t n_vis,
                               double* img) {
     const int64_t cols = 4 * (int64_t)g.Kx * g.Ky;
-    const int per = kFinCols * 4;
-    const dim3 grid((unsigned)((cols + per - 1) / per)), blk(per * kFinQ);
-    if (prec == SWV_F32C)
-        k_grid_finish<true><<<grid, blk, 0, s>>>(g, partial, n_chunks, nx, ny, cx, cy,
-                                                 (double)n_vis, img);
-    else
-        k_grid_finish<false><<<grid, blk, 0, s>>>(g, partial, n_chunks, nx, ny, cx, cy,
-                                                  (double)n_vis, img);
+    const int per = kFinCols * 4, block = per * kFinQ;
+    launch_slabs((cols + per - 1) / per, block, [&](int64_t b0, unsigned nb) {
+        if (prec == SWV_F32C)
+            k_grid_finish<true><<<dim3(nb), dim3(block), 0, s>>>(
+                g, partial, n_chunks, b0, nx, ny, cx, cy, (double)n_vis, img);
+        else
+            k_grid_finish<false><<<dim3(nb), dim3(block), 0, s>>>(
+                g, partial, n_chunks, b0, nx, ny, cx, cy, (double)n_vis, img);
+    });
     return hipGetLastError();
 }
 

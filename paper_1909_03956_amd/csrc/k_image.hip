@@ -399,11 +399,12 @@ constexpr int kAhead = 8;
 
 template <int COLS>
 __global__ __launch_bounds__(kSumBlock) void k_sum_chunks_c128(
-    const double2* __restrict__ partial, int64_t n_chunks, int64_t n, double2* __restrict__ out) {
+    const double2* __restrict__ partial, int64_t n_chunks, int64_t n, int64_t bid0,
+    double2* __restrict__ out) {
     constexpr int Q = kSumBlock / COLS;
     __shared__ double red_r[Q][COLS], red_i[Q][COLS];
     const int tx = threadIdx.x % COLS, q = threadIdx.x / COLS;
-    const int64_t p = (int64_t)blockIdx.x * COLS + tx;
+    const int64_t p = (bid0 + blockIdx.x) * COLS + tx;
     double re = 0.0, im = 0.0;
     if (p < n) {
         int64_t c = q;
@@ -522,7 +523,7 @@ static hipError_t run_adjoint_cell(hipStream_t s, int ppl, int64_t chunk, int64_
                                    const double* nm1, int sign, void* partial) {
     const Columns C = columns_of(n_pix, ppl);
     const int64_t n_chunks = (n_vis + chunk - 1) / chunk, run = cell_run(C, n_chunks);
-    if (run > (int64_t(1) << 27)) return hipErrorInvalidConfiguration;
+    if (8 * run > kMaxLaunchThreads / kTabBlock) return hipErrorInvalidConfiguration;
     k_adjoint_cell<<<dim3((unsigned)(8 * run)), dim3(kTabBlock), 0, s>>>(
         u, v, w, (const double2*)y, n_vis, chunk, l, m, nm1, n_pix, (double)sign, C, n_chunks, run,
         (double2*)partial);
@@ -554,12 +555,15 @@ hipError_t launch_adjoint(hipStream_t s, int prec, int ppl, int block, int64_t c
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (n_pix < kSumNarrow)
-        k_sum_chunks_c128<8><<<dim3((unsigned)((n_pix + 7) / 8)), dim3(kSumBlock), 0, s>>>(
-            (const double2*)partial, n_chunks, n_pix, (double2*)out);
-    else
-        k_sum_chunks_c128<16><<<dim3((unsigned)((n_pix + 15) / 16)), dim3(kSumBlock), 0, s>>>(
-            (const double2*)partial, n_chunks, n_pix, (double2*)out);
+    const int cols = n_pix < kSumNarrow ? 8 : 16;
+    launch_slabs((n_pix + cols - 1) / cols, kSumBlock, [&](int64_t b0, unsigned nb) {
+        if (cols == 8)
+            k_sum_chunks_c128<8><<<dim3(nb), dim3(kSumBlock), 0, s>>>(
+                (const double2*)partial, n_chunks, n_pix, b0, (double2*)out);
+        else
+            k_sum_chunks_c128<16><<<dim3(nb), dim3(kSumBlock), 0, s>>>(
+                (const double2*)partial, n_chunks, n_pix, b0, (double2*)out);
+    });
     return hipGetLastError();
 }
 
@@ -703,14 +707,14 @@ constexpr int kGradQ = 32;
 
 __global__ __launch_bounds__(4 * kGradCols * kGradQ) void k_grad_finish(
     const double* __restrict__ partial, int64_t n_chunks, const double* __restrict__ comp,
-    int comp_stride, int64_t n_comp, const int* __restrict__ n_comp_dev, double sgn, double alpha,
-    double* __restrict__ d_flux, double* __restrict__ d_l, double* __restrict__ d_m) {
+    int comp_stride, int64_t n_comp, const int* __restrict__ n_comp_dev, int64_t bid0, double sgn,
+    double alpha, double* __restrict__ d_flux, double* __restrict__ d_l, double* __restrict__ d_m) {
     __shared__ double red[kGradQ][4][kGradCols];
     if (n_comp_dev) n_comp = *n_comp_dev;
-    if ((int64_t)blockIdx.x * kGradCols >= n_comp) return;   // whole block past the count
+    if ((bid0 + blockIdx.x) * kGradCols >= n_comp) return;   // whole block past the count
     const int tx = threadIdx.x % kGradCols, t = threadIdx.x / kGradCols % 4,
               q = threadIdx.x / (4 * kGradCols);
-    const int64_t k = (int64_t)blockIdx.x * kGradCols + tx;
+    const int64_t k = (bid0 + blockIdx.x) * kGradCols + tx;
     double z = 0.0;
     if (k < n_comp) {
         const double* p = partial + t * n_comp + k;
@@ -750,17 +754,19 @@ hipError_t launch_grad(hipStream_t s, int cpl, int64_t chunk, int64_t n_vis, con
     if (n_chunks > 0) {
         const Columns C = columns_of(n_comp, cpl);
         const int64_t run = cell_run(C, n_chunks);
-        if (run > (int64_t(1) << 27)) return hipErrorInvalidConfiguration;
+        if (8 * run > kMaxLaunchThreads / kTabBlock) return hipErrorInvalidConfiguration;
         k_grad_cell<<<dim3((unsigned)(8 * run)), dim3(kTabBlock), 0, s>>>(
             u, v, w, (const double2*)y, n_vis, chunk, comp, comp_stride, n_comp, n_comp_dev,
             (double)sign, C, n_chunks, run, partial);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    k_grad_finish<<<dim3((unsigned)((n_comp + kGradCols - 1) / kGradCols)),
-                    dim3(4 * kGradCols * kGradQ), 0, s>>>(partial, n_chunks, comp, comp_stride,
-                                                          n_comp, n_comp_dev, (double)sign, alpha,
-                                                          d_flux, d_l, d_m);
+    constexpr int kFinish = 4 * kGradCols * kGradQ;
+    launch_slabs((n_comp + kGradCols - 1) / kGradCols, kFinish, [&](int64_t b0, unsigned nb) {
+        k_grad_finish<<<dim3(nb), dim3(kFinish), 0, s>>>(partial, n_chunks, comp, comp_stride,
+                                                         n_comp, n_comp_dev, b0, (double)sign,
+                                                         alpha, d_flux, d_l, d_m);
+    });
     return hipGetLastError();
 }
 

@@ -1,5 +1,6 @@
 """Calls whose kernels need 2^32 threads or more in all, which no single launch
-takes: layouts that give a row several threads, at row counts past that border."""
+takes: layouts that give a row, a pixel or a component several threads, past that
+border."""
 import numpy as np
 import pytest
 
@@ -94,3 +95,55 @@ def test_degridding_of_2_28_rows(env):
     rows = torch.cat([rows, ends])
     xs = x[rows]
     assert torch.equal(out[rows], swv.predict_degrid(img, xs, xs, xs, 0.003, support=9)[0])
+
+
+def test_image_sums_past_2_26_pixels_and_gradients_past_2_25_components(env):
+    """64 threads a pixel and 128 a component add the chunks' sums."""
+    torch, swv = env
+    rng = np.random.default_rng(6)
+    u, v, w = (rng.uniform(-3e3, 3e3, 2) for _ in range(3))
+    y = rng.normal(size=2) + 1j * rng.normal(size=2)
+    rows = [torch.as_tensor(a, device="cuda") for a in (u, v, w, y)]
+    n = (1 << 26) + 5
+    note(f"adjoint, {n} pixels")
+    l = torch.arange(n, dtype=torch.float64, device="cuda").mul_(1.3 / n).sub_(0.65)
+    m = l.flip(0).mul_(0.3)
+    nm1 = -(l * l + m * m) / (1 + torch.sqrt(1 - l * l - m * m))
+    img = swv.adjoint(*rows, l, m, nm1)
+    idx = torch.as_tensor(_rows(rng, n, 1 << 26), device="cuda")
+    lp, mp, np_ = (host(a[idx]) for a in (l, m, nm1))
+    ref = ov.adjoint(u, v, w, y, lp, mp, np_)
+    # the same bound as a direct sum's, rows and pixels exchanged
+    bound = fp64_row_bound(lp, mp, np_, u, v, w, np.abs(y))
+    assert np.all(np.abs(host(img[idx]) - ref) <= bound)
+    del img, nm1
+    k = (1 << 25) + 3
+    note(f"gradients, {k} components")
+    f = torch.ones(k, dtype=torch.float64, device="cuda")
+    g = swv.grad_direct(*rows, l[:k], m[:k], f)
+    idx = torch.as_tensor(_rows(rng, k, 1 << 25), device="cuda")
+    lp, mp = host(l[idx]), host(m[idx])
+    gr = ov.grad_direct(u, v, w, y, lp, mp, np.ones(lp.size))
+    nm1 = ov.n_minus_1(lp, mp)
+    err = fp64_row_bound(lp, mp, nm1, u, v, w, np.abs(y))
+    wide = 4 * np.pi * np.abs([u, v, w]).max(axis=1).sum() / (1 + nm1)   # |d phi / dl|, |d phi / dm|
+    for a, b, s in zip(g, gr, (1.0, wide, wide)):
+        assert np.all(np.abs(host(a[idx]) - b) <= s * err)
+    swv.synchronize()
+
+
+def test_dirty_image_of_2_26_pixels_about_its_corner(env):
+    torch, swv = env
+    rng = np.random.default_rng(7)
+    u, v, w = (rng.uniform(-300, 300, 3) for _ in range(3))
+    y = rng.normal(size=3) + 1j * rng.normal(size=3)
+    n, cell = 8192, 0.7 / 8192
+    note(f"dirty image, {n} x {n} pixels about the corner")
+    img = swv.dirty_image(*(torch.as_tensor(a, device="cuda") for a in (u, v, w, y)), n, n, cell, 0, 0)
+    p = np.unique(np.concatenate([rng.integers(0, n * n, 500), np.arange(n * n - 300, n * n)]))
+    got = host(img.reshape(-1)[torch.as_tensor(p, device="cuda")])
+    l, m = (p % n) * cell, (p // n) * cell
+    nm1 = ov.n_minus_1(l, m)
+    ref = ov.adjoint(u, v, w, y, l, m, nm1).real / 3
+    bound = fp64_row_bound(l, m, nm1, u, v, w, np.abs(y)) / 3
+    assert np.all(np.abs(got - ref) <= bound)
