@@ -48,6 +48,15 @@ int ensure(swv_ctx ctx, DevBuf& b, size_t bytes) {
     return SWV_OK;
 }
 
+bool stream_captured(swv_ctx ctx) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
 void tune_defaults(swv_ctx ctx) {
     // (per_lane, block) per family, both size classes; see swv_tune_get.  The
     // fastest shapes measured on MI355X for a few thousand components, a
@@ -223,8 +232,8 @@ void ctx_release(swv_ctx ctx) {
     {
         DeviceGuard g(ctx->device);
         (void)hipStreamSynchronize(ctx->stream);
-        for (DevBuf* b : {&ctx->comp, &ctx->partial, &ctx->partial2, &ctx->grid, &ctx->ones,
-                          &ctx->degrid, &ctx->hog})
+        for (DevBuf* b : {&ctx->comp, &ctx->partial, &ctx->direct_partial, &ctx->partial2,
+                          &ctx->grid, &ctx->ones, &ctx->degrid, &ctx->hog})
             if (b->p) (void)hipFree(b->p);
         destroy_fft_plan(ctx->fft_plan);
         if (ctx->d_status) (void)hipFree(ctx->d_status);
@@ -336,19 +345,30 @@ int swv_ctx_destroy(swv_ctx ctx) {
 }
 
 // ------------------------------------------------------- direct route ---
+// Whether the context has its partial sums of small direct sums.  They have a
+// buffer of their own, as large as any such call needs: it is not freed before the
+// context, so a call in a caller's graph keeps its address.  Where it cannot be had
+// (no memory, or the stream is being captured), the call takes the best layout
+// without partial sums; every layout gives the same bits.
+static bool have_direct_partials(swv_ctx ctx) {
+    const size_t bytes = direct_partial_bytes(ctx->n_cu);
+    if (ctx->direct_partial.n >= bytes) return true;
+    if (stream_captured(ctx)) return false;
+    if (ensure(ctx, ctx->direct_partial, bytes) == SWV_OK) return true;
+    clear_error();
+    return false;
+}
+
 // The FP64 direct sum over packed components; prec of the output alone.
 static int run_direct_cell(swv_ctx ctx, int64_t n_vis, const double* u, const double* v,
                            const double* w, const CompCell* comp, int64_t n_comp, int sign,
                            int prec, void* vis_out) {
-    const DirectShape sh =
-        direct_shape(n_vis, n_comp, ctx->per_lane[kFamDirect64][size_class(n_vis)], ctx->n_cu);
-    const size_t bytes = direct_partial_bytes(sh, n_vis);
-    if (bytes) {
-        const int rc = ensure(ctx, ctx->partial, bytes);
-        if (rc) return rc;
-    }
+    const int vpl = ctx->per_lane[kFamDirect64][size_class(n_vis)];
+    DirectShape sh = direct_shape(n_vis, n_comp, vpl, ctx->n_cu, true);
+    if (sh.parts > 1 && !have_direct_partials(ctx))
+        sh = direct_shape(n_vis, n_comp, vpl, ctx->n_cu, false);
     HIPCALL(launch_direct_cell(ctx->stream, sh, n_vis, u, v, w, comp, n_comp, sign, prec, vis_out,
-                               (double2*)ctx->partial.p, ctx->d_status));
+                               (double2*)ctx->direct_partial.p, ctx->d_status));
     return SWV_OK;
 }
 
@@ -356,16 +376,13 @@ static int run_direct_cell(swv_ctx ctx, int64_t n_vis, const double* u, const do
 static int run_direct_f32c(swv_ctx ctx, int64_t n_vis, const double* u, const double* v,
                            const double* w, const CompF* comp, int64_t n_comp, int sign,
                            void* vis_out) {
-    const DirectShape sh = direct_shape_f32c(n_vis, n_comp, ctx->n_cu);
-    const size_t bytes = direct_partial_bytes(sh, n_vis);
-    if (bytes) {
-        const int rc = ensure(ctx, ctx->partial, bytes);
-        if (rc) return rc;
-    }
+    DirectShape sh = direct_shape_f32c(n_vis, n_comp, ctx->n_cu, true);
+    if (sh.parts > 1 && !have_direct_partials(ctx))
+        sh = direct_shape_f32c(n_vis, n_comp, ctx->n_cu, false);
     const int sc = size_class(n_vis);
     HIPCALL(launch_direct_f32c(ctx->stream, sh, ctx->per_lane[kFamDirect32][sc],
                                ctx->block[kFamDirect32][sc], n_vis, u, v, w, comp, n_comp, sign,
-                               vis_out, (double2*)ctx->partial.p, ctx->d_status));
+                               vis_out, (double2*)ctx->direct_partial.p, ctx->d_status));
     return SWV_OK;
 }
 

@@ -29,7 +29,8 @@ struct swv_ctx_s {
     int device = 0;
     hipStream_t stream = nullptr;
     swv::DevBuf comp;       // packed components
-    swv::DevBuf partial;    // per-chunk partial sums (adjoint, gradients)
+    swv::DevBuf partial;    // per-chunk partial sums (adjoint, gradients, images)
+    swv::DevBuf direct_partial;   // partial sums of small direct sums, of one size
     swv::DevBuf partial2;   // per-block chi^2 partials
     swv::DevBuf grid;       // image-grid directions and adjoint output (dirty images)
     swv::DevBuf ones;       // unit visibilities (dirty beam)
@@ -56,6 +57,9 @@ namespace swv {
 
 int hip_fail(hipError_t e, const char* what);
 int ensure(swv_ctx ctx, DevBuf& b, size_t bytes);
+// Whether the context's stream is being captured (or cannot say): nothing may be
+// allocated then.
+bool stream_captured(swv_ctx ctx);
 void tune_defaults(swv_ctx ctx);
 int size_class(int64_t rows);
 // Rows per chunk of the adjoint (image) and gradient reductions: enough

@@ -448,13 +448,7 @@ bool coop_supported(int device) {
 bool hogbom_grid_wide(swv_ctx ctx, int n, int flags) {
     if (n < kHogGridMinPixels || (flags & SWV_HOGBOM_SINGLE) || !coop_supported(ctx->device))
         return false;
-    if (n >= kHogGridMinCaptured) return true;
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return st == hipStreamCaptureStatusNone;
+    return n >= kHogGridMinCaptured || !stream_captured(ctx);
 }
 
 int check_grid(int nx, int ny, double cell) {

@@ -221,7 +221,7 @@ __global__ __launch_bounds__(64) void k_direct_join(const double2* __restrict__ 
 // gets no credit for that, since nothing keeps two of them off the same CU
 // (261,120 rows x 1,000 components in 255 workgroups: 180 us at best, 336 us
 // behind the ingest kernel).
-DirectShape direct_shape(int64_t n_vis, int64_t n_comp, int vpl_max, int n_cu) {
+DirectShape direct_shape(int64_t n_vis, int64_t n_comp, int vpl_max, int n_cu, bool partials) {
     const struct {
         int vpl, split, parts;
         double per_comp;
@@ -234,7 +234,7 @@ DirectShape direct_shape(int64_t n_vis, int64_t n_comp, int vpl_max, int n_cu) {
         const int64_t rows = (int64_t)kTabBlock / c.split * c.vpl;
         const int64_t blocks = (n_vis + rows - 1) / rows * c.parts;
         // the partial sums of a call cost a second launch and 2 x 1 KB a row
-        if (c.parts > 1 && (blocks > 4 * (int64_t)n_cu || n_comp < 256)) continue;
+        if (c.parts > 1 && (!partials || blocks > 4 * (int64_t)n_cu || n_comp < 256)) continue;
         const int64_t rounds = (blocks + 2 * (int64_t)n_cu - 1) / (2 * (int64_t)n_cu);
         double t = (double)rounds * (c.per_comp * (double)n_comp / (c.split * c.parts) + 14.0);
         if (c.parts > 1) t += 45.0;   // the second launch
@@ -246,10 +246,6 @@ DirectShape direct_shape(int64_t n_vis, int64_t n_comp, int vpl_max, int n_cu) {
         }
     }
     return best;
-}
-
-size_t direct_partial_bytes(const DirectShape& sh, int64_t n_vis) {
-    return sh.parts > 1 ? 64 * sizeof(double2) * (size_t)n_vis : 0;
 }
 
 template <class OUT>
@@ -384,11 +380,11 @@ __global__ __launch_bounds__(kF32cBlock) void k_direct_f32c_part(
 // A wave alone on its SIMD runs at its latencies: components are shared until
 // there are 4 waves for each of them, by the workgroups too where the ranges have
 // sub-ranges enough to pay for the second launch.
-DirectShape direct_shape_f32c(int64_t n_vis, int64_t n_comp, int n_cu) {
+DirectShape direct_shape_f32c(int64_t n_vis, int64_t n_comp, int n_cu, bool partials) {
     const int64_t waves = (n_vis + 63) / 64, want = 16 * (int64_t)n_cu;
     DirectShape sh;
     while (sh.split < 8 && waves * sh.split < want && n_comp >= 16 * sh.split) sh.split *= 2;
-    if (sh.split == 8 && waves * 8 * 2 <= want && n_comp >= 32 * kF32cSub) sh.parts = 8;
+    if (partials && sh.split == 8 && waves * 8 * 2 <= want && n_comp >= 32 * kF32cSub) sh.parts = 8;
     return sh;
 }
 

@@ -51,16 +51,18 @@ struct DirectShape {
     int vpl = 1, split = 1, parts = 1;
 };
 // FP32-compensated direct sum; (vpl, block) where no components are shared.
-DirectShape direct_shape_f32c(int64_t n_vis, int64_t n_comp, int n_cu);
+// partials: whether workgroups may share components too.
+DirectShape direct_shape_f32c(int64_t n_vis, int64_t n_comp, int n_cu, bool partials);
 hipError_t launch_direct_f32c(hipStream_t s, const DirectShape& sh, int vpl, int block,
                               int64_t n_vis, const double* u, const double* v, const double* w,
                               const CompF* comp, int64_t n_comp, int sign, void* out,
                               double2* partial, int* status);
 
 // vpl_max: most rows per lane (1, 2, 4).
-DirectShape direct_shape(int64_t n_vis, int64_t n_comp, int vpl_max, int n_cu);
-// Bytes of partial sums a launch needs (0 if parts is 1).
-size_t direct_partial_bytes(const DirectShape& sh, int64_t n_vis);
+DirectShape direct_shape(int64_t n_vis, int64_t n_comp, int vpl_max, int n_cu, bool partials);
+// Bytes of partial sums that hold any launch of these shapes: the most rows whose
+// components workgroups share are 64 per compute unit (FP64: half of that).
+inline size_t direct_partial_bytes(int n_cu) { return 64 * sizeof(double2) * 64 * (size_t)n_cu; }
 // FP64 direct sum of packed components (fewer than kTableMinComp: polynomial
 // phasor, whatever the layout); prec is that of the output alone (SWV_F32C:
 // complex64).
