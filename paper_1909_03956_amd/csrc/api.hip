@@ -306,6 +306,9 @@ int swv_ctx_create(int device, void* stream, swv_ctx* out) {
     // the fixed scratch of swv_adjoint_noalloc on this device (the device is
     // current here); a failure is reported by that entry point instead
     if (noalloc_scratch(device, &c->scratch) != SWV_OK) c->scratch = nullptr;
+    // short lists are packed in the kernel in FP64, but not in the other calls
+    // that may be captured after one; a failure is reported by those
+    (void)ensure(c, c->comp, kTableMinComp * sizeof(CompCell));
     tune_defaults(c);
     if (const char* path = getenv("SWV_TUNE_CACHE")) {
         if (path[0] && swv_tune_load(c, path) != SWV_OK) tune_defaults(c);
@@ -386,6 +389,16 @@ static int run_direct_f32c(swv_ctx ctx, int64_t n_vis, const double* u, const do
     return SWV_OK;
 }
 
+// The buffer of packed components, of `rec` bytes each: as large as the largest
+// records' list of that length where it can be had, so that a call of one kind
+// serves as the warm-up of a captured call of another.
+static int ensure_components(swv_ctx ctx, int64_t n_comp, size_t rec) {
+    const size_t n = (size_t)(n_comp > 0 ? n_comp : 1);
+    if (ctx->comp.n >= n * rec) return SWV_OK;
+    const int rc = ensure(ctx, ctx->comp, n * sizeof(CompCell));
+    return rc != SWV_ENOMEM || rec == sizeof(CompCell) ? rc : ensure(ctx, ctx->comp, n * rec);
+}
+
 int swv_predict_direct(swv_ctx ctx, int64_t n_vis, const double* u, const double* v,
                        const double* w, int64_t n_comp, const double* l, const double* m,
                        const double* flux, int sign, int prec, void* vis_out) {
@@ -405,7 +418,7 @@ int swv_predict_direct(swv_ctx ctx, int64_t n_vis, const double* u, const double
         return SWV_OK;
     }
     const size_t rec = prec == SWV_FP64 ? sizeof(CompCell) : sizeof(CompF);
-    rc = ensure(ctx, ctx->comp, rec * (size_t)(n_comp > 0 ? n_comp : 1));
+    rc = ensure_components(ctx, n_comp, rec);
     if (rc) return rc;
     if (prec == SWV_FP64) {
         CompCell* comp = (CompCell*)ctx->comp.p;
@@ -794,7 +807,7 @@ int swv_grad_direct(swv_ctx ctx, int64_t n_vis, const double* u, const double* v
     if (n_comp == 0) return SWV_OK;
     TRY_BEGIN
     GUARD(ctx);
-    rc = ensure(ctx, ctx->comp, sizeof(Comp) * (size_t)n_comp);
+    rc = ensure_components(ctx, n_comp, sizeof(Comp));
     if (rc) return rc;
     Comp* comp = (Comp*)ctx->comp.p;
     HIPCALL(launch_ingest(ctx->stream, n_comp, l, m, flux, comp, ctx->d_status));

@@ -61,3 +61,43 @@ def test_captured_small_call(env, route, prec, warm):
         ctx.synchronize()
     assert np.isfinite(host(out)).all()
     t.close()
+
+
+@pytest.mark.parametrize("k", [7, 16, 4000])
+@pytest.mark.parametrize("warm,captured", [("f32c", "fp64"), ("fp64", "f32c"), ("grad", "fp64"),
+                                           ("fp64", "grad")])
+def test_a_call_of_another_kind_is_warm_up_enough(env, k, warm, captured):
+    """Calls that pack the same list: the captured one finds its buffer made."""
+    torch, swv = env
+    rng = np.random.default_rng(k)
+    u, v, w = (rng.uniform(-1e4, 1e4, 20000) for _ in range(3))
+    l, m, f = rng.uniform(-0.4, 0.4, k), rng.uniform(-0.4, 0.4, k), rng.lognormal(-3, 1, k)
+    rows, comps = [dev(a, torch) for a in (u, v, w)], [dev(a, torch) for a in (l, m, f)]
+    y = dev_c(np.ones(u.size), torch)
+
+    def call(kind):
+        if kind == "grad":
+            return torch.stack(swv.grad_direct(*rows, y, *comps))
+        return swv.predict_direct(*rows, *comps, prec=kind)
+
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    note(f"captured {captured} after {warm}, {k} components")
+    with torch.cuda.stream(s):
+        swv.api._CONTEXTS.pop((0, s.cuda_stream), None)   # a context of its own
+        call(warm)
+        # the adjoint of the components' directions has the gradients' other workspace
+        z = torch.zeros(3 * k, dtype=torch.float64, device="cuda")
+        swv.adjoint(*rows, y, z, z, z)
+        s.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        out = call(captured)
+    with torch.cuda.stream(s):
+        ref = call(captured)
+        for _ in range(3):
+            out.zero_()
+            g.replay()
+            s.synchronize()
+            assert torch.equal(out, ref)
+        swv.context(rows[0].device).synchronize()
