@@ -437,15 +437,18 @@ int swv_autotune(swv_ctx ctx, const char* cache_path, int flags) {
             for (int pl : kPerLaneOptions) {
                 for (int bl : kBlockOptions) {
                     if (!tune_valid(fam, pl, bl)) continue;
+                    // the FP64 direct sum's workgroups have a size of their own
+                    if (fam == kFamDirect64 && bl != kBlockOptions[0]) continue;
                     float tmin = 1e30f;
                     for (int r = 0; r <= reps; ++r) {
                         hipEventRecord(e0, s);
                         hipError_t e = hipSuccess;
                         if (fam == kFamDirect64) {
-                            // rows enough for whole rows per wave: no partial sums
-                            e = launch_direct_cell(s, DirectShape{pl, 1, 1}, rows, u, v, w, comp,
-                                                   n_comp, -1, SWV_FP64, out, nullptr,
-                                                   ctx->d_status);
+                            // the layout that a call takes under this limit (too many
+                            // rows for partial sums)
+                            e = launch_direct_cell(
+                                s, direct_shape(rows, n_comp, pl, ctx->n_cu, false), rows, u, v, w,
+                                comp, n_comp, -1, SWV_FP64, out, nullptr, ctx->d_status);
                         } else if (fam == kFamDirect32) {
                             e = launch_direct_f32c(s, DirectShape(), pl, bl, rows, u, v, w, comp32,
                                                    n_comp, -1, out, nullptr, ctx->d_status);
