@@ -111,7 +111,7 @@ __device__ __forceinline__ void component_step(CellPtr T, CompCellPtr cp, int k,
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int i = 0; i < VPL; ++i)
-            e[b][i] = find_cell<WIDE>(
+            e[b][i] = find_cell_by_cells<WIDE>(
                 T, fma(U[i], c[b].l, fma(V[i], c[b].m, W[i] * c[b].nm1)), d[b][i]);
 #pragma unroll
     for (int b = 0; b < NB; ++b)
@@ -170,8 +170,9 @@ __device__ __forceinline__ void range_sums(CellPtr T, CompCellPtr cp, const Comp
     }
 }
 
-// Rows j[0 .. VPL) of a lane, clamped to the last one.  Returns whether some row
-// of the wave is beyond the cells' direct reach (or not finite).
+// Rows j[0 .. VPL) of a lane, clamped to the last one, times the cells of a turn.
+// Returns whether some row of the wave is beyond the cells' direct reach (or not
+// finite); the wave's rows are then as they came.
 template <int VPL>
 __device__ __forceinline__ bool load_rows(const int64_t (&j)[VPL], int64_t limit,
                                           const double* __restrict__ u,
@@ -187,7 +188,15 @@ __device__ __forceinline__ bool load_rows(const int64_t (&j)[VPL], int64_t limit
         W[i] = w[jj];
         small = small && cells_reach(U[i], V[i], W[i]);
     }
-    return __any(!small);
+    const bool wide = __any(!small);
+    const double scale = wide ? 1.0 : (double)kTabCells;
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) {
+        U[i] *= scale;
+        V[i] *= scale;
+        W[i] *= scale;
+    }
+    return wide;
 }
 
 // A visibility in the output's type (the sums are FP64 for either).

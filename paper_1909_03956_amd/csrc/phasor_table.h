@@ -129,10 +129,33 @@ __device__ __forceinline__ Cell find_cell_product(CellPtr T, double a, double b,
     return *(CellPtr)((const __attribute__((address_space(3))) char*)T + off);
 }
 
-// A component with the cell polynomials' coefficients times its flux.
+// The direct sums' form: phases and rests in cells instead of turns (rows times
+// 4,096, exactly, so every bit is the other form's), which keeps the coefficients
+// below 1 in magnitude: their products with a flux stay finite up to the largest
+// one.  WIDE takes the phase in turns.
+constexpr double kCellTurns = 1.0 / kTabCells;
+constexpr double kCellMagic = kTabMagic * kTabCells;
+template <bool WIDE>
+__device__ __forceinline__ Cell find_cell_by_cells(CellPtr T, double phase, double& d) {
+    const double r = WIDE ? (phase - rint(phase)) * kTabCells : phase;
+    const double t = r + kCellMagic;
+    d = r - (t - kCellMagic);
+    unsigned off;
+    asm("v_lshlrev_b16_e32 %0, 4, %1" : "=v"(off) : "v"((unsigned)__double_as_longlong(t)));
+    return *(CellPtr)((const __attribute__((address_space(3))) char*)T + off);
+}
+
+// A component with its flux times the polynomials' coefficients of rests in cells.
 __host__ __device__ __forceinline__ CompCell comp_cell(double l, double m, double nm1, double I) {
-    return CompCell{l,           m,           nm1,         I,
-                    I * kCellC[0], I * kCellC[1], I * kCellS[0], I * kCellS[1]};
+    constexpr double c = kCellTurns, c2 = c * c;
+    return CompCell{l,
+                    m,
+                    nm1,
+                    I,
+                    I * (kCellC[0] * c2),
+                    I * (kCellC[1] * c2 * c2),
+                    I * (kCellS[0] * c),
+                    I * (kCellS[1] * c * c2)};
 }
 
 }  // namespace swv
