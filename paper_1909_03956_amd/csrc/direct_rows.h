@@ -74,6 +74,11 @@ struct CompRanges {
         const int64_t e = (int64_t)(a + 1) * A;
         return e < n ? e : n;
     }
+    // where the sub-range from k0 ends in a range up to `last`; the borders of lists
+    // of up to 2^31 - 1 components may not be passed in 32 bits
+    __host__ __device__ int next(int k0, int last) const {
+        return last - k0 > B ? k0 + B : last;
+    }
 };
 
 // Copy of a wave-uniform double into a vector register: an FP64 FMA can read
@@ -135,7 +140,7 @@ __device__ __forceinline__ void add_components(CellPtr T, CompCellPtr cp, int k0
     constexpr int NB = VPL >= 4 ? 1 : 4 / VPL;
     int k = k0;
 #pragma unroll 1
-    for (; k + NB <= k1; k += NB) component_step<VPL, WIDE, NB>(T, cp, k, U, V, W, re, im);
+    for (; k1 - k >= NB; k += NB) component_step<VPL, WIDE, NB>(T, cp, k, U, V, W, re, im);
     if constexpr (NB > 1) {
 #pragma unroll 1
         for (; k < k1; ++k) component_step<VPL, WIDE, 1>(T, cp, k, U, V, W, re, im);
@@ -154,12 +159,12 @@ __device__ __forceinline__ void range_sums(CellPtr T, CompCellPtr cp, const Comp
         for (int i = 0; i < VPL; ++i) rr[i] = ri[i] = 0.0;
         const int last = (int)R.end_of(a);
 #pragma unroll 1
-        for (int k0 = a * R.A; k0 < last; k0 += R.B) {
+        for (int k0 = a * R.A, k1; k0 < last; k0 = k1) {
+            k1 = R.next(k0, last);
             double re[VPL], im[VPL];
 #pragma unroll
             for (int i = 0; i < VPL; ++i) re[i] = im[i] = 0.0;
-            add_components<VPL, WIDE>(T, cp, k0, k0 + R.B < last ? k0 + R.B : last, U, V, W, re,
-                                      im);
+            add_components<VPL, WIDE>(T, cp, k0, k1, U, V, W, re, im);
 #pragma unroll
             for (int i = 0; i < VPL; ++i) {
                 rr[i] += re[i];
@@ -392,8 +397,8 @@ __device__ __forceinline__ void add_components_f32c(CompPtr cp, int k0, int k1,
     };
     int k = k0;
 #pragma unroll 1
-    for (; k + 4 <= k1; k += 4) step(std::integral_constant<int, 4>(), k);
-    if (k + 2 <= k1) {
+    for (; k1 - k >= 4; k += 4) step(std::integral_constant<int, 4>(), k);
+    if (k1 - k >= 2) {
         step(std::integral_constant<int, 2>(), k);
         k += 2;
     }
@@ -417,8 +422,10 @@ __device__ __forceinline__ void range_sums_f32c(CompPtr cp, const CompRanges& R,
         for (int i = 0; i < VPL; ++i) rr[i] = ri[i] = 0.0;
         const int last = (int)R.end_of(a);
 #pragma unroll 1
-        for (int k0 = a * R.A; k0 < last; k0 += R.B)
-            add_components_f32c<VPL>(cp, k0, k0 + R.B < last ? k0 + R.B : last, U, V, W, rr, ri);
+        for (int k0 = a * R.A, k1; k0 < last; k0 = k1) {
+            k1 = R.next(k0, last);
+            add_components_f32c<VPL>(cp, k0, k1, U, V, W, rr, ri);
+        }
         put(a, rr, ri);
     }
 }
