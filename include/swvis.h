@@ -63,7 +63,8 @@ extern "C" {
 #define SWV_FP64  0  /* phase, sincos and sums in FP64; output complex128 */
 #define SWV_F32C  1  /* phase and its reduction mod 1 in FP64; sincos (the hardware
                         v_sin_f32 / v_cos_f32, which take revolutions), products and
-                        Kahan-compensated sums in FP32; output complex64 */
+                        Kahan-compensated sums in FP32 (the direct sum adds those of
+                        its sub-ranges in FP64); output complex64 */
 
 /* Routes of a batched instance. */
 #define SWV_ROUTE_DIRECT 0
@@ -108,7 +109,12 @@ int swv_ctx_destroy(swv_ctx ctx);
  * u, v, w [n_vis] DEVICE; l, m, flux [n_comp] DEVICE (l^2 + m^2 < 1);
  * vis_out [n_vis] DEVICE complex128 (SWV_FP64) or complex64 (SWV_F32C).
  * n - 1 is formed as -(l^2 + m^2) / (1 + n).  Work: n_vis * n_comp terms.
- * Uses a context workspace of 32 * n_comp bytes (the packed components). */
+ * Context workspaces: 64 * n_comp bytes (the packed components; half of that in
+ * SWV_F32C where more cannot be had, and none in SWV_FP64 below 16 components),
+ * and 64 KB per compute unit of partial sums from the first call of few rows (at
+ * most 64 per compute unit) with a long list, which is kept until the context is
+ * destroyed.  Where those cannot be had, or the stream is being captured before
+ * they are there, such a call runs without them, with the same bits. */
 int swv_predict_direct(swv_ctx ctx, int64_t n_vis, const double* u, const double* v,
                        const double* w, int64_t n_comp, const double* l, const double* m,
                        const double* flux, int sign, int prec, void* vis_out);
@@ -180,7 +186,9 @@ int swv_tree_set_flux(swv_tree tree, const double* leaf_flux);
  * device on first use with this context's device (64 bytes per leaf).
  * SWV_ENOTSUP for a tree deeper than J = 16 with more than 15 nodes of two or
  * more children on one root-to-leaf path (swv_tree_stats_t.max_branching), or
- * whose record stream (32 bytes per record) exceeds 4 GiB - 32. */
+ * whose record stream (32 bytes per record) exceeds 4 GiB - 32: limits of the
+ * interface that the leaf sum itself does not have (swv_predict_tree_leaves takes
+ * such trees). */
 int swv_predict_tree(swv_ctx ctx, swv_tree tree, int64_t n_vis, const double* u,
                      const double* v, const double* w, int sign, int prec, void* vis_out);
 
@@ -208,8 +216,8 @@ int swv_predict_tree_leaves(swv_ctx ctx, swv_tree tree, int64_t n_vis, const dou
  *  - a node with nothing retained at or below it becomes a leaf at its own
  *    level: the plane wave is sampled at its pixel centre, as at the level-J
  *    leaves, and nothing below it is visited.
- * swv_predict_tree then evaluates Eq. 17 over the thresholded tree (FP64 or
- * F32C); fraction 1 gives the exact tree route.  The thresholded tree works
+ * swv_predict_tree then evaluates Eq. 17 over the thresholded tree (in FP64, for
+ * either output); fraction 1 gives the exact tree route.  The thresholded tree works
  * with swv_predict_tree, swv_tree_stats (n_leaves counts the leaves of every
  * level, n_internal the remaining internal nodes) and batched plans;
  * swv_tree_leaves, swv_tree_level, swv_tree_set_flux, swv_predict_tree_leaves
@@ -272,11 +280,12 @@ int swv_residual_chi2(swv_ctx ctx, int64_t n_vis, const void* vis_obs, const voi
  * centres, n - 1 given explicitly); img_out [n_pix] DEVICE complex128 for
  * both precisions (SWV_F32C: FP32 sincos and products, Kahan sums per
  * visibility chunk).  Deterministic: fixed chunking and summation order.
- * Uses a workspace of 16 * n_pix * ceil(n_vis / chunk) bytes; the chunk
- * count is a multiple of 8 (a chunk of every group of 8 per XCD) chosen for
- * whole rounds of resident blocks on each XCD, at most about 8 rounds, which
- * keeps the workspace under 128 * (pixels per block) * (resident blocks)
- * bytes (about 240 MB at the default tiling). */
+ * Uses a workspace of 16 * n_pix * ceil(n_vis / chunk) bytes.  SWV_FP64: up to
+ * four rounds of workgroups, fewer where that exceeds 32 MiB (8 chunks at least
+ * from 512 rows on).  SWV_F32C: the chunk count is a multiple of 8 (a chunk of
+ * every group of 8 per XCD) chosen for whole rounds of resident blocks on each
+ * XCD, at most about 8 rounds, which keeps the workspace under 128 * (pixels per
+ * block) * (resident blocks) bytes (about 240 MB at the default tiling). */
 int swv_adjoint(swv_ctx ctx, int64_t n_vis, const double* u, const double* v, const double* w,
                 const void* y, int64_t n_pix, const double* l, const double* m,
                 const double* nm1, int sign, int prec, void* img_out);
@@ -308,7 +317,8 @@ int swv_adjoint_noalloc(swv_ctx ctx, int64_t n_vis, const double* u, const doubl
  * give the backward of a real loss.  All arrays DEVICE; FP64.  Deterministic.
  * Per component only four real sums over the rows are formed:
  * Re sum conj(y) e and Im sum {u, v, w} conj(y) e.  Uses a workspace of
- * 32 * n_comp * ceil(n_vis / chunk) bytes plus the packed components. */
+ * 32 * n_comp * ceil(n_vis / chunk) bytes, with chunks as in the FP64 adjoint, plus
+ * the packed components (as swv_predict_direct). */
 int swv_grad_direct(swv_ctx ctx, int64_t n_vis, const double* u, const double* v,
                     const double* w, const void* y, int64_t n_comp, const double* l,
                     const double* m, const double* flux, int sign, double alpha,
@@ -342,9 +352,16 @@ int swv_image_grid(swv_ctx ctx, int nx, int ny, int cx, int cy, double cell, dou
  * complex128; img_out [nx * ny] DEVICE FP64.  With y = NULL the visibilities
  * are all 1: on the beam grid (cx = nx' - 1 of an nx' image) that is the
  * dirty beam B_D, the image of a unit source at the phase centre.  prec is
- * the adjoint's: SWV_FP64, or SWV_F32C (FP32 phasors and Kahan sums, about
- * twice as fast, relative error up to ~1e-6).  Uses 40 * nx * ny bytes of
- * device scratch plus the adjoint's workspace. */
+ * the adjoint's: SWV_FP64, or SWV_F32C (FP32 phasors and Kahan sums, relative
+ * error up to ~1e-6).  SWV_FP64 is the faster of the two wherever the grid lets it
+ * split the phasors over the axes, which it does unless few pixels mirror each
+ * other about the phase centre: 256 x 256 pixels of 176,904 rows take 2.7 ms, in
+ * SWV_F32C 3.9.
+ * Device scratch, with Q distinct pairs (|ix - cx|, |iy - cy|) of which Kx and Ky
+ * distinct first and second: split SWV_FP64 images up to 256 MB of tables (16 (Kx +
+ * Ky) + 32 bytes a row) and 32 Q bytes per chunk of rows, up to 256 MiB or 8
+ * chunks; SWV_F32C images 32 Q bytes per chunk of the adjoint; others 40 * nx * ny
+ * bytes plus the adjoint's workspace. */
 int swv_dirty_image(swv_ctx ctx, int64_t n_vis, const double* u, const double* v,
                     const double* w, const void* y, int nx, int ny, int cx, int cy,
                     double cell, int sign, int prec, double* img_out);
@@ -654,9 +671,9 @@ int swv_measure_peaks(swv_ctx ctx, swv_peaks_t* out);
 
 /* ------------------------------------------------------------- tuning --- */
 
-/* Times every compiled tile shape of each kernel family (direct FP64,
- * direct F32C, adjoint, gradients) on synthetic inputs of the two size
- * classes (2^18 and 2^22 rows), keeps
+/* Times every compiled tile shape of each kernel family (direct FP64: the layout
+ * that a call takes under each limit; direct F32C; adjoint, in F32C; gradients) on
+ * synthetic inputs of the two size classes (2^18 and 2^22 rows), keeps
  * the fastest per (family, size class) in the context's tuning table and, if
  * `cache_path` is not NULL, writes the table there as JSON.  flags: 0 =
  * full sweep, 1 = quick sweep (fewer repetitions). */
@@ -673,9 +690,8 @@ int swv_tune_load(swv_ctx ctx, const char* cache_path);
  * {64, 128, 256} (the FP64 direct sum and adjoint have their own).  The tree's
  * entries are kept and checked but decide nothing: it runs the FP64 direct sum's
  * kernels with their shapes.  The
- * gradients' entries hold 128 (swv_tune_set rejects any other value for them):
- * their launches take the narrowest block of 128 .. 1024 threads that holds
- * every component at per_lane (else 1024).  Results do not depend on the
+ * gradients' entries hold 128 (swv_tune_set rejects any other value for them; their
+ * workgroups have a size of their own too).  Results do not depend on the
  * shape except for the summation order of the adjoint and gradients. */
 int swv_tune_get(swv_ctx ctx, int family, int size_class, int* per_lane, int* block);
 

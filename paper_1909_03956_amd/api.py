@@ -290,7 +290,7 @@ class Tree:
 
     def predict(self, u, v, w, sign: int = -1, prec="fp64", out=None):
         """Model visibilities by the wavelet route (Eqs. 14-17): complex128
-        (prec "fp64") or complex64 ("f32c", FP32 phasors at the leaves)."""
+        (prec "fp64") or complex64 ("f32c": the same FP64 sums, rounded)."""
         u = _dev_f64(u, "u")
         dev = u.device
         v, w = _dev_f64(v, "v", dev), _dev_f64(w, "w", dev)

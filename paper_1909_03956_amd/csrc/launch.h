@@ -73,7 +73,8 @@ hipError_t launch_direct_cell(hipStream_t s, const DirectShape& sh, int64_t n_vi
 
 // Limits of the trees the entry points predict: levels up to kTreeMaxJ, or at
 // any level fewer than kTreeMaxSeg branching nodes on a root-to-leaf path; a
-// record stream that 32-bit byte offsets address.
+// record stream that 32-bit byte offsets address.  The leaf sum has none of them:
+// they are the interface's, which refuses what it always has.
 constexpr int kTreeMaxJ = 16;
 constexpr int kTreeMaxSeg = 16;
 constexpr size_t kMaxRecordBytes = 0xFFFFFFE0u;
