@@ -387,14 +387,14 @@ __global__ __launch_bounds__(BLOCK) void k_adjoint_f32c(
 // Q rows of threads each add the chunks q, q + Q, ... in order, kAhead loads in
 // flight, and the Q subtotals are then added by a fixed binary tree in LDS.  The
 // order depends only on the counts of chunks and outputs, so results are run-to-run
-// identical.  Bound by the latency of a thread's chain and by the few blocks: 16
-// columns and 64 rows rather than 64 and 16 quarter the chain and quadruple the
-// blocks (300,000 rows x 300 pixels in the F32C form: 120 -> 69 us the whole call),
-// 8 and 128 do so again (65 us; 300,000 x 40, FP64: 26.9 -> 25.4) but halve the
-// segments read, which costs where 16 fill the chip (100,000 x 60,000: 3.74 -> 3.78
-// ms).
+// identical.  Few outputs are bound by the latency of a thread's chain and by the few
+// blocks: 8 columns and 128 rows (955 outputs x 512 chunks: 3.0 us, 5.6 with 64 and
+// 16).  Many are bound by their bytes, and by the blocks themselves where the chunks
+// are few: 64 columns (10,000 x 152: 3.9 us, 5.1 with 16, 6.4 with 8), and 256 and 4
+// rows for up to 24 chunks (1,000,000 x 2: 11 us, 36 with 64, 153 with 16).
 constexpr int kSumBlock = 1024;
 constexpr int64_t kSumNarrow = 4096;   // outputs below which a block takes 8
+constexpr int64_t kSumFew = 24;        // chunks up to which it takes 256
 constexpr int kAhead = 8;
 
 template <int COLS>
@@ -555,15 +555,19 @@ hipError_t launch_adjoint(hipStream_t s, int prec, int ppl, int block, int64_t c
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    const int cols = n_pix < kSumNarrow ? 8 : 16;
-    launch_slabs((n_pix + cols - 1) / cols, kSumBlock, [&](int64_t b0, unsigned nb) {
-        if (cols == 8)
-            k_sum_chunks_c128<8><<<dim3(nb), dim3(kSumBlock), 0, s>>>(
+    const auto sum = [&](auto columns) {
+        constexpr int COLS = decltype(columns)::value;
+        launch_slabs((n_pix + COLS - 1) / COLS, kSumBlock, [&](int64_t b0, unsigned nb) {
+            k_sum_chunks_c128<COLS><<<dim3(nb), dim3(kSumBlock), 0, s>>>(
                 (const double2*)partial, n_chunks, n_pix, b0, (double2*)out);
-        else
-            k_sum_chunks_c128<16><<<dim3(nb), dim3(kSumBlock), 0, s>>>(
-                (const double2*)partial, n_chunks, n_pix, b0, (double2*)out);
-    });
+        });
+    };
+    if (n_pix < kSumNarrow)
+        sum(std::integral_constant<int, 8>());
+    else if (n_chunks <= kSumFew)
+        sum(std::integral_constant<int, 256>());
+    else
+        sum(std::integral_constant<int, 64>());
     return hipGetLastError();
 }
 
@@ -698,39 +702,42 @@ __global__ __launch_bounds__(kTabBlock) __attribute__((amdgpu_waves_per_eu(4))) 
     }
 }
 
-// A block owns kGradCols components; thread (q, t, x) adds sum t of component x
-// over the chunks q, q + kGradQ, ... in order, then as in the chunk reduction.
-// 8 components rather than 16: twice the blocks (1,536 chunks x 600 components in a
-// cycle: 18.6 -> 15 us; 4 are no better).
-constexpr int kGradCols = 8;
-constexpr int kGradQ = 32;
+// A block owns COLS components; thread (q, t, x) adds sum t of component x over
+// the chunks q, q + Q, ... in order, then as in the chunk reduction.  8 columns for
+// short lists (600 components x 1,536 chunks: 11.3 us, 15.0 with 16), 16 for longer
+// ones, whose 64-byte segments cost (2,000 x 1,536: 16.9 us, 30.4 with 8), 64 for the
+// longest (100,000 x 64: 30 us, 36 with 16) and for few chunks (1,000,000 x 2: 34 us,
+// 270 with 8).
+constexpr int kFinishBlock = 1024;
 
-__global__ __launch_bounds__(4 * kGradCols * kGradQ) void k_grad_finish(
+template <int COLS>
+__global__ __launch_bounds__(kFinishBlock) void k_grad_finish(
     const double* __restrict__ partial, int64_t n_chunks, const double* __restrict__ comp,
     int comp_stride, int64_t n_comp, const int* __restrict__ n_comp_dev, int64_t bid0, double sgn,
     double alpha, double* __restrict__ d_flux, double* __restrict__ d_l, double* __restrict__ d_m) {
-    __shared__ double red[kGradQ][4][kGradCols];
+    constexpr int Q = kFinishBlock / (4 * COLS);
+    __shared__ double red[Q][4][COLS];
     if (n_comp_dev) n_comp = *n_comp_dev;
-    if ((bid0 + blockIdx.x) * kGradCols >= n_comp) return;   // whole block past the count
-    const int tx = threadIdx.x % kGradCols, t = threadIdx.x / kGradCols % 4,
-              q = threadIdx.x / (4 * kGradCols);
-    const int64_t k = (bid0 + blockIdx.x) * kGradCols + tx;
+    if ((bid0 + blockIdx.x) * COLS >= n_comp) return;   // whole block past the count
+    const int tx = threadIdx.x % COLS, t = threadIdx.x / COLS % 4,
+              q = threadIdx.x / (4 * COLS);
+    const int64_t k = (bid0 + blockIdx.x) * COLS + tx;
     double z = 0.0;
     if (k < n_comp) {
         const double* p = partial + t * n_comp + k;
         int64_t c = q;
-        for (; c + (kAhead - 1) * kGradQ < n_chunks; c += kAhead * kGradQ) {
+        for (; c + (kAhead - 1) * Q < n_chunks; c += kAhead * Q) {
             double x[kAhead];
 #pragma unroll
-            for (int i = 0; i < kAhead; ++i) x[i] = p[(c + i * kGradQ) * 4 * n_comp];
+            for (int i = 0; i < kAhead; ++i) x[i] = p[(c + i * Q) * 4 * n_comp];
 #pragma unroll
             for (int i = 0; i < kAhead; ++i) z += x[i];
         }
-        for (; c < n_chunks; c += kGradQ) z += p[c * 4 * n_comp];
+        for (; c < n_chunks; c += Q) z += p[c * 4 * n_comp];
     }
     red[q][t][tx] = z;
     __syncthreads();
-    for (int h = kGradQ / 2; h > 0; h >>= 1) {
+    for (int h = Q / 2; h > 0; h >>= 1) {
         if (q < h) red[q][t][tx] += red[q + h][t][tx];
         __syncthreads();
     }
@@ -761,12 +768,20 @@ hipError_t launch_grad(hipStream_t s, int cpl, int64_t chunk, int64_t n_vis, con
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    constexpr int kFinish = 4 * kGradCols * kGradQ;
-    launch_slabs((n_comp + kGradCols - 1) / kGradCols, kFinish, [&](int64_t b0, unsigned nb) {
-        k_grad_finish<<<dim3(nb), dim3(kFinish), 0, s>>>(partial, n_chunks, comp, comp_stride,
-                                                         n_comp, n_comp_dev, b0, (double)sign,
-                                                         alpha, d_flux, d_l, d_m);
-    });
+    const auto finish = [&](auto columns) {
+        constexpr int COLS = decltype(columns)::value;
+        launch_slabs((n_comp + COLS - 1) / COLS, kFinishBlock, [&](int64_t b0, unsigned nb) {
+            k_grad_finish<COLS><<<dim3(nb), dim3(kFinishBlock), 0, s>>>(
+                partial, n_chunks, comp, comp_stride, n_comp, n_comp_dev, b0, (double)sign, alpha,
+                d_flux, d_l, d_m);
+        });
+    };
+    if (n_comp >= 8192 || n_chunks <= kSumFew)
+        finish(std::integral_constant<int, 64>());
+    else if (n_comp >= 1024)
+        finish(std::integral_constant<int, 16>());
+    else
+        finish(std::integral_constant<int, 8>());
     return hipGetLastError();
 }
 

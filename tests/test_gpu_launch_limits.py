@@ -98,7 +98,7 @@ def test_degridding_of_2_28_rows(env):
 
 
 def test_image_sums_past_2_26_pixels_and_gradients_past_2_25_components(env):
-    """64 threads a pixel and 128 a component add the chunks' sums."""
+    """Adding up chunks at 64 threads a pixel and 128 a component would take 2^32."""
     torch, swv = env
     rng = np.random.default_rng(6)
     u, v, w = (rng.uniform(-3e3, 3e3, 2) for _ in range(3))

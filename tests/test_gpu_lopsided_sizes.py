@@ -1,0 +1,62 @@
+"""Calls with one dimension tiny and the other large take about the time of their
+bytes: within five times a copy of what their kernels read and write."""
+import numpy as np
+import pytest
+
+from .gpu_util import dev, note, require_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    return require_gpu()
+
+
+def best_us(torch, call, least_ms=30.0, runs=20):
+    """Least time of a call, in runs of four after least_ms of them (the clock settles)."""
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best, spent, done = float("inf"), 0.0, 0
+    while done < runs:
+        a.record()
+        for _ in range(4):
+            call()
+        b.record()
+        b.synchronize()
+        t = a.elapsed_time(b)
+        spent += t
+        if spent > least_ms:
+            best, done = min(best, 250.0 * t), done + 1
+    return best
+
+
+def copy_us(torch, n_bytes):
+    x = torch.zeros(n_bytes // 16, dtype=torch.float64, device="cuda")   # read and written
+    y = torch.empty_like(x)
+    return best_us(torch, lambda: y.copy_(x))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "f32c"])
+def test_adjoint_of_one_row(env, prec):
+    torch, swv = env
+    n = 6_000_000
+    r = [dev(np.array([x]), torch) for x in (10.0, -20.0, 3.0)]
+    y = torch.ones(1, dtype=torch.complex128, device="cuda")
+    l = torch.linspace(-0.3, 0.3, n, dtype=torch.float64, device="cuda")
+    t = best_us(torch, lambda: swv.adjoint(*r, y, l, l, l, prec=prec))
+    least = copy_us(torch, (24 + 16 + 32) * n)   # directions, image, one set of partial sums
+    note(f"adjoint {prec}, 1 row x {n} pixels: {t:.0f} us, a copy of its bytes {least:.0f}")
+    assert t <= 5 * least
+
+
+def test_gradients_of_one_row(env):
+    torch, swv = env
+    n = 1_000_000
+    r = [dev(np.array([x]), torch) for x in (10.0, -20.0, 3.0)]
+    y = torch.ones(1, dtype=torch.complex128, device="cuda")
+    l = torch.linspace(-0.3, 0.3, n, dtype=torch.float64, device="cuda")
+    t = best_us(torch, lambda: swv.grad_direct(*r, y, l, l, l))
+    # components, packed (read twice), sums written and read, gradients
+    least = copy_us(torch, (24 + 96 + 64 + 24) * n)
+    note(f"gradients, 1 row x {n} components: {t:.0f} us, a copy of its bytes {least:.0f}")
+    assert t <= 5 * least
