@@ -213,6 +213,7 @@ AdjointShape adjoint_shape(swv_ctx ctx, int64_t n_vis, int64_t n_pix, int prec) 
     sh.ppl = ctx->per_lane[kFamAdjoint][sc];
     sh.block = ctx->block[kFamAdjoint][sc];
     if (prec == SWV_FP64) {
+        sh.ppl = adjoint_cell_groups(n_vis, n_pix, sh.ppl, ctx->n_cu);
         sh.chunk = adjoint_cell_chunk(n_vis, n_pix, sh.ppl, ctx->n_cu);
     } else {
         const int64_t tile = (int64_t)sh.ppl * sh.block;

@@ -501,6 +501,20 @@ static int64_t cell_chunk(int64_t n_vis, const Columns& C, int64_t bytes, int n_
     return std::min<int64_t>(chunk, int64_t(1) << 30);   // rows per chunk fit an int
 }
 
+// Calls too small for four waves on every compute unit run at a wave's latencies,
+// which grow with its groups: fewer groups until there are as many waves (100 rows x
+// 10,000 pixels, the whole call: 26.8 us with four groups a wave, 17.2 with two, 16.2
+// with one, which is the host's time; 1,000 x 30,000, 1,888 waves of four: the same).
+int adjoint_cell_groups(int64_t n_vis, int64_t n_pix, int ppl, int n_cu) {
+    for (; ppl > 1; ppl /= 2) {
+        const Columns C = columns_of(n_pix, ppl);
+        const int64_t chunk = adjoint_cell_chunk(n_vis, n_pix, ppl, n_cu);
+        const int64_t waves = (n_vis + chunk - 1) / chunk * C.cols * C.parts;
+        if (waves >= 4 * (int64_t)n_cu) break;
+    }
+    return ppl;
+}
+
 int64_t adjoint_cell_chunk(int64_t n_vis, int64_t n_pix, int ppl, int n_cu) {
     return cell_chunk(n_vis, columns_of(n_pix, ppl), 16 * n_pix, n_cu);
 }

@@ -136,6 +136,8 @@ hipError_t launch_grid_finish(hipStream_t s, const GridGeom& g, int prec, const 
 // Rows per chunk of the FP64 adjoint and of the gradients (ppl, cpl: groups of 64
 // outputs per wave at most).
 int64_t adjoint_cell_chunk(int64_t n_vis, int64_t n_pix, int ppl, int n_cu);
+// Groups per wave of an adjoint, at most ppl.
+int adjoint_cell_groups(int64_t n_vis, int64_t n_pix, int ppl, int n_cu);
 int64_t grad_chunk(int64_t n_vis, int64_t n_comp, int cpl, int n_cu);
 // Resident blocks per compute unit of the F32C adjoint.
 int adjoint_f32c_blocks_per_cu(int ppl, int block);

@@ -60,3 +60,19 @@ def test_gradients_of_one_row(env):
     least = copy_us(torch, (24 + 96 + 64 + 24) * n)
     note(f"gradients, 1 row x {n} components: {t:.0f} us, a copy of its bytes {least:.0f}")
     assert t <= 5 * least
+
+
+@pytest.mark.parametrize("rows,pixels", [(100, 10_000), (64, 30_000), (300, 3_000)])
+def test_small_adjoint(env, rows, pixels):
+    """Little work for the chip: about the time of the same pixels' ten rows (the
+    call's own), not a few waves' chain of many pixels each."""
+    torch, swv = env
+    rng = np.random.default_rng(1)
+    r = [dev(rng.uniform(-1e4, 1e4, rows), torch) for _ in range(3)]
+    y = torch.ones(rows, dtype=torch.complex128, device="cuda")
+    l = dev(rng.uniform(-0.3, 0.3, pixels), torch)
+    n = -0.5 * l * l
+    t = best_us(torch, lambda: swv.adjoint(*r, y, l, l, n))
+    ten = best_us(torch, lambda: swv.adjoint(*(a[:10] for a in r), y[:10], l, l, n))
+    note(f"adjoint, {rows} rows x {pixels} pixels: {t:.1f} us, ten rows {ten:.1f}")
+    assert t <= 1.4 * ten
