@@ -59,11 +59,15 @@ using CompCellPtr = const __attribute__((address_space(4))) CompCell*;
 // Borders of the summation order.
 struct CompRanges {
     int n, A, B;
-    __host__ __device__ explicit CompRanges(int n_comp, int least = 32)
+    // least components of a sub-range, and of a range
+    __host__ __device__ explicit CompRanges(int n_comp, int least = 32, int least_range = 1)
         : n(n_comp), A((int)(((int64_t)n_comp + 7) / 8)), B(0) {
+        A = A < least_range ? least_range : A;
         B = (A + 7) / 8;
         B = B < least ? least : B;
     }
+    // ranges that hold components (the others are empty)
+    __host__ __device__ int count() const { return (int)(((int64_t)n + A - 1) / A); }
     // components [begin, end) of range a, sub-range b
     __host__ __device__ int begin(int a, int b) const {
         const int64_t k = (int64_t)a * A + (int64_t)b * B, e = end_of(a);
@@ -363,16 +367,21 @@ __device__ __forceinline__ void direct_rows_f64(const int64_t (&j)[VPL], int64_t
 // goes.
 //
 // The list is summed in the FP64 kernels' two-level order with sub-ranges of at
-// least kF32cSub components; their compensated sums enter the ranges' and the
-// total in FP64.
-constexpr int kF32cSub = 128;
+// least kF32cSub components and ranges of at least kF32cRange; their compensated
+// sums enter the ranges' and the total in FP64.  A range costs a row eight FP64
+// additions and conversions, so short lists are cut into few of them: 10,000,000 rows
+// x 32 components in 8, 2 and 1 ranges 161, 129 and 125 us, x 128 in 8, 4 and 2 450,
+// 437 and 429.  A list of one range keeps its sums in FP32 to the end (x 32: 119 us),
+// the same bits.
+constexpr int kF32cSub = 128, kF32cRange = 64;
 
+// Sums s and compensations c of components [k0, k1).
 template <int VPL, class CompPtr>
-__device__ __forceinline__ void add_components_f32c(CompPtr cp, int k0, int k1,
+__device__ __forceinline__ void sum_components_f32c(CompPtr cp, int k0, int k1,
                                                     const double (&U)[VPL], const double (&V)[VPL],
-                                                    const double (&W)[VPL],
-                                                    double (&re)[VPL], double (&im)[VPL]) {
-    float sr[VPL], si[VPL], cr[VPL], ci[VPL];
+                                                    const double (&W)[VPL], float (&sr)[VPL],
+                                                    float (&si)[VPL], float (&cr)[VPL],
+                                                    float (&ci)[VPL]) {
 #pragma unroll
     for (int i = 0; i < VPL; ++i) sr[i] = cr[i] = si[i] = ci[i] = 0.0f;
     const auto step = [&](auto count, int k) {
@@ -403,6 +412,16 @@ __device__ __forceinline__ void add_components_f32c(CompPtr cp, int k0, int k1,
         k += 2;
     }
     if (k < k1) step(std::integral_constant<int, 1>(), k);
+}
+
+// Their sums added to re + i im.
+template <int VPL, class CompPtr>
+__device__ __forceinline__ void add_components_f32c(CompPtr cp, int k0, int k1,
+                                                    const double (&U)[VPL], const double (&V)[VPL],
+                                                    const double (&W)[VPL],
+                                                    double (&re)[VPL], double (&im)[VPL]) {
+    float sr[VPL], si[VPL], cr[VPL], ci[VPL];
+    sum_components_f32c<VPL>(cp, k0, k1, U, V, W, sr, si, cr, ci);
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
         re[i] += (double)sr[i] - (double)cr[i];
@@ -456,9 +475,21 @@ __device__ __forceinline__ void direct_rows_f32c(const int64_t (&j)[VPL], int64_
                                                  int* __restrict__ status) {
     double U[VPL], V[VPL], W[VPL], sr[VPL], si[VPL];
     load_rows_f32c<VPL>(j, limit, u, v, w, U, V, W);
+    if (n_comp <= kF32cRange) {
+        float fr[VPL], fi[VPL], cr[VPL], ci[VPL];
+        sum_components_f32c<VPL>(uniform_ptr(comp), 0, n_comp, U, V, W, fr, fi, cr, ci);
+#pragma unroll
+        for (int i = 0; i < VPL; ++i) {
+            if (j[i] < limit) {
+                if (!isfinite(U[i] + V[i] + W[i])) atomicOr(status, kStatusNonFinite);
+                out[j[i]] = make_float2(fr[i] - cr[i], (float)sgn * (fi[i] - ci[i]));
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < VPL; ++i) sr[i] = si[i] = 0.0;
-    const CompRanges R(n_comp, kF32cSub);
+    const CompRanges R(n_comp, kF32cSub, kF32cRange);
     const auto add = [&](int, const double(&rr)[VPL], const double(&ri)[VPL]) {
 #pragma unroll
         for (int i = 0; i < VPL; ++i) {
@@ -466,7 +497,7 @@ __device__ __forceinline__ void direct_rows_f32c(const int64_t (&j)[VPL], int64_
             si[i] += ri[i];
         }
     };
-    range_sums_f32c<VPL>(uniform_ptr(comp), R, 0, 8, U, V, W, add);
+    range_sums_f32c<VPL>(uniform_ptr(comp), R, 0, R.count(), U, V, W, add);
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
         if (j[i] < limit) {

@@ -322,7 +322,7 @@ __global__ __launch_bounds__(BLOCK) void k_direct_f32c(const double* __restrict_
 }
 
 // Calls too small to fill the chip by rows alone: SPLIT waves of the workgroup
-// share a row's components, 8 / SPLIT ranges each; the range sums meet in LDS.
+// share a row's components, every SPLIT-th range each; the range sums meet in LDS.
 constexpr int kF32cBlock = 512;
 
 template <int SPLIT>
@@ -330,7 +330,7 @@ __global__ __launch_bounds__(kF32cBlock) void k_direct_f32c_split(
     const double* __restrict__ u, const double* __restrict__ v, const double* __restrict__ w,
     int64_t n_vis, const CompF* __restrict__ comp, int n_comp, double sgn,
     float2* __restrict__ out, int* __restrict__ status) {
-    constexpr int kRows = kF32cBlock / SPLIT, kOwn = 8 / SPLIT;
+    constexpr int kRows = kF32cBlock / SPLIT;
     __shared__ double2 part[8][kRows];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int own = wave % SPLIT, local = wave / SPLIT * 64 + lane;
@@ -338,11 +338,13 @@ __global__ __launch_bounds__(kF32cBlock) void k_direct_f32c_split(
     const int64_t j[1] = {row0 + local};
     double U[1], V[1], W[1];
     load_rows_f32c<1>(j, n_vis, u, v, w, U, V, W);
-    const CompRanges R(n_comp, kF32cSub);
+    const CompRanges R(n_comp, kF32cSub, kF32cRange);
     const auto keep = [&](int a, const double(&re)[1], const double(&im)[1]) {
         part[a][local] = make_double2(re[0], im[0]);
     };
-    range_sums_f32c<1>(uniform_ptr(comp), R, own * kOwn, (own + 1) * kOwn, U, V, W, keep);
+#pragma unroll 1
+    for (int a = own; a < 8; a += SPLIT)
+        range_sums_f32c<1>(uniform_ptr(comp), R, a, a + 1, U, V, W, keep);
     __syncthreads();
     for (int r = threadIdx.x; r < kRows && row0 + r < n_vis; r += kF32cBlock) {
         double re = 0.0, im = 0.0;
@@ -368,7 +370,7 @@ __global__ __launch_bounds__(kF32cBlock) void k_direct_f32c_part(
     const int64_t j[1] = {(int64_t)blockIdx.x * 64 + lane};
     double U[1], V[1], W[1], re[1] = {0.0}, im[1] = {0.0};
     load_rows_f32c<1>(j, n_vis, u, v, w, U, V, W);
-    const CompRanges R(n_comp, kF32cSub);
+    const CompRanges R(n_comp, kF32cSub, kF32cRange);
     const int k0 = R.begin(a, b), k1 = R.end(a, b);
     add_components_f32c<1>(uniform_ptr(comp), k0, k1, U, V, W, re, im);
     if (j[0] < n_vis) {
@@ -383,7 +385,7 @@ __global__ __launch_bounds__(kF32cBlock) void k_direct_f32c_part(
 DirectShape direct_shape_f32c(int64_t n_vis, int64_t n_comp, int n_cu, bool partials) {
     const int64_t waves = (n_vis + 63) / 64, want = 16 * (int64_t)n_cu;
     DirectShape sh;
-    while (sh.split < 8 && waves * sh.split < want && n_comp >= 16 * sh.split) sh.split *= 2;
+    while (sh.split < 8 && waves * sh.split < want && n_comp >= kF32cRange * sh.split) sh.split *= 2;
     if (partials && sh.split == 8 && waves * 8 * 2 <= want && n_comp >= 32 * kF32cSub) sh.parts = 8;
     return sh;
 }

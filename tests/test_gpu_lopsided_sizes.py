@@ -76,3 +76,18 @@ def test_small_adjoint(env, rows, pixels):
     ten = best_us(torch, lambda: swv.adjoint(*(a[:10] for a in r), y[:10], l, l, n))
     note(f"adjoint, {rows} rows x {pixels} pixels: {t:.1f} us, ten rows {ten:.1f}")
     assert t <= 1.4 * ten
+
+
+@pytest.mark.parametrize("rows,comps", [(10_000_000, 5), (10_000_000, 16), (1_000_000, 32)])
+def test_f32c_sum_of_a_short_list(env, rows, comps):
+    """A term costs about what it does in a long list, beside the rows' own bytes."""
+    torch, swv = env
+    rng = np.random.default_rng(2)
+    r = [dev(rng.uniform(-1e4, 1e4, rows), torch) for _ in range(3)]
+    c = [dev(rng.uniform(-0.3, 0.3, 1000), torch) for _ in range(3)]
+    out = torch.empty(rows, dtype=torch.complex64, device="cuda")
+    call = lambda k: swv.predict_direct(*r, *(a[:k] for a in c), prec="f32c", out=out)
+    t, full = best_us(torch, lambda: call(comps)), best_us(torch, lambda: call(1000))
+    least = max(full * comps / 1000, copy_us(torch, 32 * rows))
+    note(f"f32c, {rows} rows x {comps} components: {t:.1f} us; share of 1000 or bytes {least:.1f}")
+    assert t <= 1.4 * least + 5.0   # 5 us: the packing's launch and the rest of the call
