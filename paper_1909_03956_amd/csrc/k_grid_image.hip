@@ -520,13 +520,18 @@ bool grid_plan(int nx, int ny, int cx, int cy, double cell, int prec, GridGeom* 
 
 // Rows per chunk: four rounds of workgroups (two per CU) rather than one, since
 // the dies' clocks differ, while the partial sums stay within 256 MiB (8 chunks at
-// least); 64 rows at least, so that filling the table stays small beside them.
+// least); 64 rows at least, so that filling the table stays small beside them, and
+// fewer (8 at least) where that leaves less than four waves to a CU: they run at a
+// row's latency (100 rows of 64 x 64 pixels, the whole call: 45 us in chunks of 64, 18.6
+// in chunks of 8).
 int64_t grid_chunk(const GridGeom& g, const GridPlan& p, int64_t rows, int n_cu) {
     const int64_t fill = 4 * (int64_t)n_cu * 2 * (kTabBlock / 64) / p.jobs;
     const int64_t cap = (int64_t(256) << 20) / (32 * (int64_t)g.Kx * g.Ky);
     const int64_t chunks = fill < cap ? (fill < 8 ? 8 : fill) : (cap < 8 ? 8 : cap);
+    int64_t least = 64;
+    while (least > 8 && p.jobs * ((rows + least - 1) / least) < 4 * (int64_t)n_cu) least /= 2;
     const int64_t chunk = (rows + chunks - 1) / chunks;
-    return chunk < 64 ? 64 : (chunk < (int64_t(1) << 30) ? chunk : int64_t(1) << 30);
+    return chunk < least ? least : (chunk < (int64_t(1) << 30) ? chunk : int64_t(1) << 30);
 }
 
 size_t grid_row_bytes(const GridGeom& g) {

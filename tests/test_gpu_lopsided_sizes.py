@@ -91,3 +91,20 @@ def test_f32c_sum_of_a_short_list(env, rows, comps):
     least = max(full * comps / 1000, copy_us(torch, 32 * rows))
     note(f"f32c, {rows} rows x {comps} components: {t:.1f} us; share of 1000 or bytes {least:.1f}")
     assert t <= 1.4 * least + 5.0   # 5 us: the packing's launch and the rest of the call
+
+
+def _image_rows(torch, n):
+    rng = np.random.default_rng(3)
+    r = [dev(rng.uniform(-1e4, 1e4, n), torch) for _ in range(3)]
+    return r, torch.ones(n, dtype=torch.complex128, device="cuda")
+
+
+@pytest.mark.parametrize("nx,ny", [(64, 64), (100, 60)])
+def test_image_of_few_rows(env, nx, ny):
+    """About the time of ten rows, the call's own."""
+    torch, swv = env
+    r, y = _image_rows(torch, 100)
+    call = lambda n: swv.dirty_image(*(a[:n] for a in r), y[:n], nx, ny, 0.0005)
+    t, ten = best_us(torch, lambda: call(100)), best_us(torch, lambda: call(10))
+    note(f"image {nx} x {ny}, 100 rows: {t:.1f} us, ten rows {ten:.1f}")
+    assert t <= 1.5 * ten
