@@ -515,7 +515,10 @@ bool grid_plan(int nx, int ny, int cx, int cy, double cell, int prec, GridGeom* 
     // FP32-compensated: about 78 issue slots of FP32 size per row and quad (20 of
     // each pixel's 26 in the adjoint)
     if (f32) return 78 * (cost / 25) <= 26 * pixel_waves;
-    return cost <= 20 * pixel_waves;
+    // the tables' 16 bytes a position, written and read, take the time of about four
+    // more instructions each, which is what a thin image saves and more (1 x 300 pixels
+    // of 100,000 rows: 159 us through tables, 77 by pixels)
+    return cost + 4 * (nX + nY) <= 20 * pixel_waves;
 }
 
 // Rows per chunk: four rounds of workgroups (two per CU) rather than one, since

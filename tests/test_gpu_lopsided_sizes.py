@@ -108,3 +108,16 @@ def test_image_of_few_rows(env, nx, ny):
     t, ten = best_us(torch, lambda: call(100)), best_us(torch, lambda: call(10))
     note(f"image {nx} x {ny}, 100 rows: {t:.1f} us, ten rows {ten:.1f}")
     assert t <= 1.5 * ten
+
+
+@pytest.mark.parametrize("prec,rows,nx,ny", [("fp64", 100_000, 1, 300), ("fp64", 10_000, 300, 2)])
+def test_image_against_the_adjoint_of_its_pixels(env, prec, rows, nx, ny):
+    """No slower than the general route, whose half is thrown away."""
+    torch, swv = env
+    r, y = _image_rows(torch, rows)
+    lmn = swv.image_grid(nx, ny, 0.0005)
+    t = best_us(torch, lambda: swv.dirty_image(*r, y, nx, ny, 0.0005, prec=prec))
+    adj = best_us(torch, lambda: swv.adjoint(*r, y, *lmn, prec=prec))
+    note(f"image {prec} {nx} x {ny}, {rows} rows: {t:.1f} us, adjoint {adj:.1f}")
+    # 8 us: the general FP64 route has two more launches
+    assert t <= 1.1 * adj + (8.0 if prec == "fp64" else 0.0)
