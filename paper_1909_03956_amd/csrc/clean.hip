@@ -542,7 +542,8 @@ extern "C" int swv_dirty_image(swv_ctx ctx, int64_t n_vis, const double* u, cons
         const AdjointShape sh = adjoint_shape(ctx, n_vis, (int64_t)nx * ny, prec);
         CLEAN_RC(ensure(ctx, ctx->partial, grid_partial_bytes(geom, sh.n_chunks)));
         double* part = (double*)ctx->partial.p;
-        CLEAN_HIP(launch_image_f32c(ctx->stream, geom, plan, n_vis, sh.chunk, u, v, w, y, sign, part));
+        CLEAN_HIP(launch_image_f32c(ctx->stream, geom, plan, n_vis, sh.chunk, ctx->n_cu, u, v, w, y, sign,
+                                    part));
         CLEAN_HIP(launch_grid_finish(ctx->stream, geom, prec, part, sh.n_chunks, nx, ny, cx, cy, n_vis,
                                      img_out));
         return SWV_OK;

@@ -395,10 +395,10 @@ __global__ __launch_bounds__(kF32Block) void k_image_f32c(
     const int nrow =
         __builtin_amdgcn_readfirstlane((int)(j0 + chunk < n_vis ? chunk : n_vis - j0));
     int la, step;
-    const GridRegion r = region_job(p, all - chunk_id * p.jobs, kF32Step, lane, la, step);
+    const GridRegion r = region_job(p, all - chunk_id * p.jobs, p.step, lane, la, step);
     double* part = partial + chunk_id * 4 * (int64_t)g.Kx * g.Ky;
     const double2* yy = y ? y + j0 : nullptr;
-    if (__builtin_amdgcn_readfirstlane(r.step0 + r.step_n - step) >= 2)
+    if (p.step >= 2 && __builtin_amdgcn_readfirstlane(r.step0 + r.step_n - step) >= 2)
         image_f32c_wave<2, UNIT>(g, r, la, step, u + j0, v + j0, w + j0, yy, nrow, fsg, part);
     else
         image_f32c_wave<1, UNIT>(g, r, la, step, u + j0, v + j0, w + j0, yy, nrow, fsg, part);
@@ -478,9 +478,19 @@ static int64_t cover(int x0, int nX, int y0, int nY, GridRegion out[2]) {
     return best;
 }
 
+// Jobs of `step` step positions.
+static void count_jobs(GridPlan* p, int step) {
+    p->step = step;
+    p->jobs = p->oct_jobs + p->diag_jobs;
+    for (int r = 0; r < 3; ++r) {
+        const GridRegion& R = p->region[r];
+        p->region_jobs[r] = (int64_t)((R.lane_n + 63) / 64) * ((R.step_n + step - 1) / step);
+        p->jobs += p->region_jobs[r];
+    }
+}
+
 bool grid_plan(int nx, int ny, int cx, int cy, double cell, int prec, GridGeom* g, GridPlan* p) {
     const bool f32 = prec == SWV_F32C;
-    const int per = f32 ? kF32Step : kStep;
     int64_t x0, nX, y0, nY;
     axis_offsets(nx, cx, &x0, &nX);
     axis_offsets(ny, cy, &y0, &nY);
@@ -503,12 +513,7 @@ bool grid_plan(int nx, int ny, int cx, int cy, double cell, int prec, GridGeom* 
         cost += b * quads_cost(Ky - sq);   // whole lane tiles along x
         p->region[2] = GridRegion{0, sq, sq, Ky - sq, false};
     }
-    p->jobs = p->oct_jobs + p->diag_jobs;
-    for (int r = 0; r < 3; ++r) {
-        const GridRegion& R = p->region[r];
-        p->region_jobs[r] = (int64_t)((R.lane_n + 63) / 64) * ((R.step_n + per - 1) / per);
-        p->jobs += p->region_jobs[r];
-    }
+    count_jobs(p, f32 ? kF32Step : kStep);
     // against 20 instructions per pixel of the general adjoint, whose idle lanes
     // are few: 256^2 about its centre 5,400 for quads and octets, 20,480 for pixels
     const int64_t pixel_waves = ((int64_t)nx * ny + 63) / 64;
@@ -575,9 +580,13 @@ hipError_t launch_grid_slab(hipStream_t s, const GridGeom& g, const GridPlan& p,
     return hipGetLastError();
 }
 
-hipError_t launch_image_f32c(hipStream_t s, const GridGeom& g, const GridPlan& p, int64_t n_vis,
-                             int64_t chunk, const double* u, const double* v, const double* w,
-                             const void* y, int sign, double* partial) {
+hipError_t launch_image_f32c(hipStream_t s, const GridGeom& g, const GridPlan& plan, int64_t n_vis,
+                             int64_t chunk, int n_cu, const double* u, const double* v,
+                             const double* w, const void* y, int sign, double* partial) {
+    // one quad a lane where two leave less than eight waves to a CU (1,000 rows of 256 x
+    // 256 pixels, the whole call: 41 and 52 us)
+    GridPlan p = plan;
+    if (p.jobs * ((n_vis + chunk - 1) / chunk) < 8 * (int64_t)n_cu) count_jobs(&p, 1);
     const int64_t jobs = (n_vis + chunk - 1) / chunk * p.jobs;
     const int64_t per = kF32Block / 64, run = ((jobs + per - 1) / per + 7) / 8;
     if (8 * run > kMaxLaunchThreads / kF32Block) return hipErrorInvalidConfiguration;

@@ -111,6 +111,7 @@ struct GridRegion {
 // x 64 blocks, then up to three regions beside it.
 struct GridPlan {
     int64_t oct_jobs = 0, diag_jobs = 0, region_jobs[3] = {0, 0, 0}, jobs = 0;
+    int step = 0;   // step positions of a region's job
     GridRegion region[3] = {};
 };
 // Geometry and cover of an image; whether this form takes fewer instructions
@@ -126,9 +127,9 @@ hipError_t launch_grid_slab(hipStream_t s, const GridGeom& g, const GridPlan& p,
                             int64_t chunk, const double* u, const double* v, const double* w,
                             const void* y, int sign, bool resume, void* slab, double* partial);
 // The FP32-compensated sums of all rows (chunk: the adjoint's).
-hipError_t launch_image_f32c(hipStream_t s, const GridGeom& g, const GridPlan& p, int64_t n_vis,
-                             int64_t chunk, const double* u, const double* v, const double* w,
-                             const void* y, int sign, double* partial);
+hipError_t launch_image_f32c(hipStream_t s, const GridGeom& g, const GridPlan& plan, int64_t n_vis,
+                             int64_t chunk, int n_cu, const double* u, const double* v,
+                             const double* w, const void* y, int sign, double* partial);
 hipError_t launch_grid_finish(hipStream_t s, const GridGeom& g, int prec, const double* partial,
                               int64_t n_chunks, int nx, int ny, int cx, int cy, int64_t n_vis,
                               double* img);

@@ -110,7 +110,8 @@ def test_image_of_few_rows(env, nx, ny):
     assert t <= 1.5 * ten
 
 
-@pytest.mark.parametrize("prec,rows,nx,ny", [("fp64", 100_000, 1, 300), ("fp64", 10_000, 300, 2)])
+@pytest.mark.parametrize("prec,rows,nx,ny", [("fp64", 100_000, 1, 300), ("fp64", 10_000, 300, 2),
+                                             ("f32c", 1000, 256, 256), ("f32c", 1000, 128, 128)])
 def test_image_against_the_adjoint_of_its_pixels(env, prec, rows, nx, ny):
     """No slower than the general route, whose half is thrown away."""
     torch, swv = env
