@@ -147,8 +147,11 @@ static int upload_cells(swv_ctx ctx, std::map<int, void*>& copies, const std::ve
 }
 
 std::vector<CompCell> packed_sum(const swv_tree_s& t) {
+    const size_t n = t.leaf_pix.size();
     std::vector<CompCell> c;
-    for (const Comp& k : collapse_tree(t)) c.push_back(comp_cell(k.l, k.m, k.nm1, k.I));
+    c.reserve(n);
+    for (size_t k = 0; k < n; ++k)
+        c.push_back(comp_cell(t.leaf_l[k], t.leaf_m[k], t.leaf_nm1[k], t.weight[k]));
     return c;
 }
 

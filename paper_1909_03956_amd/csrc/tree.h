@@ -27,6 +27,8 @@ struct swv_tree_s {
     // leaves (level J), sorted by pixel id
     std::vector<int64_t> leaf_pix;
     std::vector<double> leaf_l, leaf_m, leaf_nm1, leaf_flux;
+    // the tree's visibility (Eq. 17) as a sum over its leaves: their weights
+    std::vector<double> weight;
     std::vector<swv::TreeLevel> levels;  // levels[j - 1] is level j
     // depth-first record stream
     std::vector<swv::TRec> records;
@@ -34,8 +36,7 @@ struct swv_tree_s {
     // most nodes with two or more children on one root-to-leaf path
     int max_branching = 0;
     double build_seconds = 0;
-    // device copies of the leaf sum (collapse_tree, packed as components of the
-    // direct kernels), one per HIP device id
+    // device copies of the leaf sum (packed as components of the direct kernels), one per HIP device id
     std::map<int, void*> device_sum;
     // device copies of the leaves packed as direct-sum components (l, m, n - 1,
     // flux), one per HIP device id (swv_predict_tree_leaves)
@@ -65,10 +66,6 @@ int build_tree(int J, double ra_p, double dec_p, int64_t n, const double* l, con
 // The same from the components' level-J pixel ids (the cross-referenced form).
 int build_tree_pixels(int J, double ra_p, double dec_p, int64_t n, const int64_t* kJ,
                       const double* flux, swv_tree_s* out);
-
-// The tree's visibility (Eq. 17) as a sum over its leaves in stream order:
-// {l, m, n - 1, weight}.
-std::vector<Comp> collapse_tree(const swv_tree_s& t);
 
 // Flat index of gamma^m_{j,k}: 3 x (nodes at levels < j) + 3 k + m.  The
 // retained coefficients of a proportion `fraction`: the round(fraction N)
