@@ -67,8 +67,10 @@ hipError_t launch_ingest(hipStream_t s, int64_t n, const double* l, const double
 // ------------------------------------------------- FP64, few components ---
 // Each block packs the components itself (one launch instead of two and no
 // workspace: the call is latency-bound); lanes read them as LDS broadcasts.
-// Four rows per lane from 2^20 rows on: fewer packings, and more row loads in
-// flight where the call is bound by them.
+// Two rows per lane from 3 x 2^20 rows on: fewer packings, and more row loads in
+// flight where the call is bound by them.  15 components, one, two and four rows
+// per lane: 2,000,000 rows 30.5, 31.9 and 32.9 us, 4,000,000 rows 60.5, 57.7 and
+// 59.4, 10,000,000 rows 158, 153 and 155.
 constexpr int kFewBlock = 256;
 
 template <int VPL>
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(kFewBlock) void k_direct_few_packed(
     direct_rows_f64<VPL>(j, n_vis, u, v, w, uniform_ptr(comp), n_comp, sgn, put, status);
 }
 
-static int few_vpl(int64_t n_vis) { return n_vis < (int64_t(1) << 20) ? 1 : 4; }
+static int few_vpl(int64_t n_vis) { return n_vis < (int64_t(3) << 20) ? 1 : 2; }
 static dim3 few_grid(int64_t n_vis) {
     const int64_t rows = kFewBlock * few_vpl(n_vis);
     return dim3((unsigned)((n_vis + rows - 1) / rows));
@@ -122,7 +124,7 @@ hipError_t launch_direct_few(hipStream_t s, int64_t n_vis, const double* u, cons
             k_direct_few<1><<<grid, blk, 0, s>>>(u + j, v + j, w + j, n, l, m, flux, n_comp,
                                                  (double)sign, out + j, status);
         else
-            k_direct_few<4><<<grid, blk, 0, s>>>(u + j, v + j, w + j, n, l, m, flux, n_comp,
+            k_direct_few<2><<<grid, blk, 0, s>>>(u + j, v + j, w + j, n, l, m, flux, n_comp,
                                                  (double)sign, out + j, status);
         return hipGetLastError();
     });
@@ -260,7 +262,7 @@ static hipError_t run_direct_cell(hipStream_t s, const DirectShape& sh, int64_t 
             k_direct_few_packed<1, OUT><<<few_grid(n_vis), dim3(kFewBlock), 0, s>>>(
                 u, v, w, n_vis, comp, nc, sg, out, status);
         else
-            k_direct_few_packed<4, OUT><<<few_grid(n_vis), dim3(kFewBlock), 0, s>>>(
+            k_direct_few_packed<2, OUT><<<few_grid(n_vis), dim3(kFewBlock), 0, s>>>(
                 u, v, w, n_vis, comp, nc, sg, out, status);
         return hipGetLastError();
     }
