@@ -355,7 +355,7 @@ int swv_image_grid(swv_ctx ctx, int nx, int ny, int cx, int cy, double cell, dou
  * the adjoint's: SWV_FP64, or SWV_F32C (FP32 phasors and Kahan sums, relative
  * error up to ~1e-6).  SWV_FP64 is the faster of the two wherever the grid lets it
  * split the phasors over the axes, which it does unless few pixels mirror each
- * other about the phase centre: 256 x 256 pixels of 176,904 rows take 2.7 ms, in
+ * other about the phase centre or the image is a few pixels wide: 256 x 256 pixels of 176,904 rows take 2.7 ms, in
  * SWV_F32C 3.9.
  * Device scratch, with Q distinct pairs (|ix - cx|, |iy - cy|) of which Kx and Ky
  * distinct first and second: split SWV_FP64 images up to 256 MB of tables (16 (Kx +
